@@ -11,6 +11,7 @@
 
 #include "sl1m_internal.h"
 #include "sl1m_trace.h"
+#include "sl1m_wgroup.h"
 
 namespace sl1m {
 
@@ -53,6 +54,11 @@ struct Analysis {
   int64_t grid_pairs = 0;      // pair records of all square segments
   int grid_vtiles = 0, grid_frows = 0;
   std::vector<Chunk> fd1, fg1, pd1, pg1;
+  // group evaluation of the delta grid segment (sl1m_wgroup.h)
+  bool wg = false;
+  int wg_seg = 0;
+  int64_t wg_cap = 0;          // visibility groups the workspace holds
+  WgPlan wgp;
 };
 
 sl1m_status d2h(void* dst, const void* src, size_t bytes, const char* what) {
@@ -157,7 +163,37 @@ bool analyze_grid(Analysis& a, int si, const std::vector<double>& L, const std::
   return true;
 }
 
-sl1m_status analyze(const sl1m_problem* pr, Analysis& a) {
+size_t layout_bytes(const Analysis& a);
+
+// Group evaluation of the delta grid segment (plans of one side: the grid
+// evaluation shares its phasors among several, and a side on its own then gives
+// the same bits as among others): its tiles, unless they hold more
+// than four times the segment's cells with padding.  A plan that fits the no-allocation
+// scratch without the group tables but not with them keeps the grid evaluation,
+// so that what sl1m_forward_noalloc takes does not shrink.
+void choose_groups(Analysis& a) {
+  for (size_t i = 0; i < a.gsegs.size(); ++i) {
+    const GridSeg& g = a.gsegs[i];
+    if (g.kind != SL1M_PIX_DELTA) continue;
+    WgPlan t;
+    wg_build_tiles(g, a.grid_la.data() + g.la_off, a.grid_mb.data() + g.mb_off,
+                   a.grid_c3.data() + g.cell_off, a.grid_slot.data() + 4 * g.cell_off, t);
+    if (t.padded > 4 * static_cast<int64_t>(g.na) * g.nb ||
+        t.nu.size() > static_cast<size_t>(INT32_MAX))
+      continue;
+    const size_t without = layout_bytes(a);
+    a.wgp = std::move(t);
+    a.wg_cap = wg_group_cap(a.n_vis);
+    a.wg_seg = static_cast<int>(i);
+    a.wg = true;
+    if (without <= SL1M_NOALLOC_SCRATCH_BYTES && layout_bytes(a) > SL1M_NOALLOC_SCRATCH_BYTES)
+      a.wg = false;
+  }
+}
+
+// `groups`: whether the plan may use the group evaluation (the server's plans run
+// kernels of their own and do not).
+sl1m_status analyze(const sl1m_problem* pr, Analysis& a, bool groups = true) {
   if (!pr) return set_error(SL1M_EINVAL, "problem is NULL");
   if (pr->n_pix < 0 || pr->n_vis < 0) return set_error(SL1M_EINVAL, "negative size");
   if (pr->n_pix > INT32_MAX || pr->n_vis > INT32_MAX)
@@ -506,6 +542,7 @@ sl1m_status analyze(const sl1m_problem* pr, Analysis& a) {
       a.n_achunks = static_cast<int>((nv32 + a.kchunk - 1) / a.kchunk);
     }
   }
+  if (groups && a.grid && a.max_rhs == 1) choose_groups(a);
   return SL1M_OK;
 }
 
@@ -514,7 +551,9 @@ struct Layout {
       rres, rpol, layerDs, chunks, fpart, apart, xperm, img, zbuf, res, red, red_out, flag, scal,
       grid_la,
       grid_mb, grid_c3, grid_c4, grid_slot, grid_rec, grid_fc, grid_pb, grid_segs, grid_gb,
-      grid_prec, grid_precm, mx, mr, mred, grid_mfma_b, grid_mfma_nu, phl, vhl, total;
+      grid_prec, grid_precm, mx, mr, mred, grid_mfma_b, grid_mfma_nu, phl, vhl,
+      wg_mac, wg_la, wg_mb, wg_nu, wg_eta, wg_slot, wg_order, wg_count, wg_su, wg_sv, wg_dw, wg_w0,
+      wg_h, wg_part, wg_res, total;
 };
 
 Layout layout(const Analysis& a) {
@@ -554,11 +593,24 @@ Layout layout(const Analysis& a) {
   L.chunks = take(sizeof(Chunk) * (nfc + npt + a.fd1.size() + a.fg1.size() + a.pd1.size() +
                                    a.pg1.size()));
   const size_t grid_rows = a.grid ? a.grid_fc.size() + a.fd1.size() + a.fg1.size() : 0;
+  // group evaluation: a row of slots per macro in place of the segment's rows
+  const size_t slots = a.wg ? static_cast<size_t>(a.wg_cap) * kWgVis : 0;
+  const size_t wg_rows = a.wg ? a.wgp.macros.size() * slots +
+                                    (grid_rows - static_cast<size_t>(a.gsegs[a.wg_seg].nfc)) * nv
+                              : 0;
   L.fpart = take(2 * rb *
-                 std::max({nfc * nr, grid_rows * std::max<size_t>(1, a.grid_multi),
-                           static_cast<size_t>(a.n_mfchunks) * nr}) *
-                 nv);
-  L.apart = take(rb * static_cast<size_t>(a.n_achunks) * np * nr);
+                 std::max(std::max({nfc * nr, grid_rows * std::max<size_t>(1, a.grid_multi),
+                                    static_cast<size_t>(a.n_mfchunks) * nr}) * nv,
+                          wg_rows));
+  // the group evaluation's chunk sums stand behind row 0 (which takes their
+  // total) where no other segment uses the rows, else in a region of their own
+  const size_t wg_part = a.wg ? 16 * a.wgp.nu.size() *
+                                    wg_chunk_cap(static_cast<int>(a.wgp.macros.size()))
+                              : 0;
+  const bool wg_alias = a.wg && a.segs.size() == 1;
+  L.apart = take(std::max(rb * static_cast<size_t>(a.n_achunks) * np * nr,
+                          wg_alias ? align_up(rb * np) + wg_part : 0));
+  if (wg_alias) L.wg_part = L.apart + align_up(rb * np);
   L.xperm = take(rb * np * nr);
   L.img = take(rb * np);
   L.zbuf = take(rb * np);
@@ -591,9 +643,30 @@ Layout layout(const Analysis& a) {
   L.grid_mfma_nu = take(a.grid_mfma ? 8 * pairs : 0);
   L.phl = take(hl ? sizeof(HLRec) * static_cast<size_t>(a.n_pix) : 0);
   L.vhl = take(hl ? sizeof(HLRec) * static_cast<size_t>(a.n_vis) : 0);
+  if (a.wg) {
+    const WgPlan& t = a.wgp;
+    const size_t wc = t.nu.size();
+    L.wg_mac = take(sizeof(WgMacro) * t.macros.size());
+    L.wg_la = take(8 * t.la.size());
+    L.wg_mb = take(8 * t.mb.size());
+    L.wg_nu = take(8 * wc);
+    L.wg_eta = take(4 * wc);
+    L.wg_slot = take(16 * wc);
+    L.wg_order = take(4 * slots);
+    L.wg_count = take(4 * static_cast<size_t>(a.wg_cap));
+    L.wg_su = take(8 * slots);
+    L.wg_sv = take(8 * slots);
+    L.wg_dw = take(4 * slots);
+    L.wg_w0 = take(8 * static_cast<size_t>(a.wg_cap));
+    L.wg_res = take(8 * slots);
+    if (!wg_alias) L.wg_part = take(wg_part);
+    L.wg_h = take(4 * static_cast<size_t>(a.wg_cap));
+  }
   L.total = off;
   return L;
 }
+
+size_t layout_bytes(const Analysis& a) { return layout(a).total; }
 
 inline hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
@@ -734,17 +807,13 @@ sl1m_status hip_error(hipError_t e, const char* what) {
 
 using namespace sl1m;
 
-extern "C" {
+namespace sl1m {
 
-const char* sl1m_last_error(void) { return g_last_error.c_str(); }
-
-const char* sl1m_version(void) { return "sl1m-mi355x 0.1 (gfx950)"; }
-
-sl1m_status sl1m_plan_workspace_bytes(const sl1m_problem* problem, size_t* bytes) {
+sl1m_status plan_bytes(const sl1m_problem* problem, bool groups, size_t* bytes) {
   try {
     if (!bytes) return set_error(SL1M_EINVAL, "bytes is NULL");
     Analysis a;
-    sl1m_status s = analyze(problem, a);
+    sl1m_status s = analyze(problem, a, groups);
     if (s) return s;
     *bytes = layout(a).total;
     return SL1M_OK;
@@ -755,14 +824,35 @@ sl1m_status sl1m_plan_workspace_bytes(const sl1m_problem* problem, size_t* bytes
   }
 }
 
+}  // namespace sl1m
+
+extern "C" {
+
+const char* sl1m_last_error(void) { return g_last_error.c_str(); }
+
+const char* sl1m_version(void) { return "sl1m-mi355x 0.1 (gfx950)"; }
+
+sl1m_status sl1m_plan_workspace_bytes(const sl1m_problem* problem, size_t* bytes) {
+  return plan_bytes(problem, true, bytes);
+}
+
 sl1m_status sl1m_plan_create(const sl1m_problem* pr, void* workspace, size_t workspace_bytes,
                              void* stream, sl1m_plan** out) {
+  return plan_build(pr, true, workspace, workspace_bytes, stream, out);
+}
+
+}  // extern "C"
+
+namespace sl1m {
+
+sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
+                       size_t workspace_bytes, void* stream, sl1m_plan** out) {
   const TraceRange range("sl1m_plan_create");
   try {
     if (!out) return set_error(SL1M_EINVAL, "out is NULL");
     *out = nullptr;
     Analysis a;
-    sl1m_status s = analyze(pr, a);
+    sl1m_status s = analyze(pr, a, groups);
     if (s) return s;
     const Layout L = layout(a);
     if (!workspace) return set_error(SL1M_EINVAL, "workspace is NULL");
@@ -773,6 +863,14 @@ sl1m_status sl1m_plan_create(const sl1m_problem* pr, void* workspace, size_t wor
     hipStream_t st = S(stream);
     int device = 0;
     SL1M_HIP(hipGetDevice(&device), "get device");
+    WgGroups wgg;
+    if (a.wg) {  // the visibilities by |w|; too many groups: the grid evaluation
+      std::vector<double> w(a.n_vis);
+      SL1M_HIP(hipMemcpyAsync(w.data(), pr->w, a.n_vis * sizeof(double), hipMemcpyDeviceToHost, st),
+               "read w");
+      SL1M_HIP(hipStreamSynchronize(st), "read w");
+      a.wg = wg_build_groups(w, a.wgp.eta_max, a.wg_cap, wgg);
+    }
     sl1m_plan* p = new sl1m_plan();
     p->device = device;
     p->n_pix = a.n_pix;
@@ -880,6 +978,30 @@ sl1m_status sl1m_plan_create(const sl1m_problem* pr, void* workspace, size_t wor
       p->grid_precm = a.grid_multi ? reinterpret_cast<float*>(w + L.grid_precm) : nullptr;
     }
 
+    if (a.wg) {
+      p->wg = true;
+      p->wg_seg = a.wg_seg;
+      p->wg_macros = static_cast<int>(a.wgp.macros.size());
+      p->wg_groups = static_cast<int>(wgg.w0.size());
+      p->wg_cells = static_cast<int64_t>(a.wgp.nu.size());
+      p->wg_chunks = wg_chunks(p->wg_macros, p->wg_groups);
+      p->wg_mac = reinterpret_cast<WgMacro*>(w + L.wg_mac);
+      p->wg_la = reinterpret_cast<double*>(w + L.wg_la);
+      p->wg_mb = reinterpret_cast<double*>(w + L.wg_mb);
+      p->wg_nu = reinterpret_cast<double*>(w + L.wg_nu);
+      p->wg_eta = reinterpret_cast<float*>(w + L.wg_eta);
+      p->wg_slot = reinterpret_cast<int32_t*>(w + L.wg_slot);
+      p->wg_count = reinterpret_cast<int32_t*>(w + L.wg_count);
+      p->wg_res = reinterpret_cast<float2*>(w + L.wg_res);
+      p->wg_part = reinterpret_cast<float4*>(w + L.wg_part);
+      p->wg_order = reinterpret_cast<int32_t*>(w + L.wg_order);
+      p->wg_su = reinterpret_cast<double*>(w + L.wg_su);
+      p->wg_sv = reinterpret_cast<double*>(w + L.wg_sv);
+      p->wg_dw = reinterpret_cast<float*>(w + L.wg_dw);
+      p->wg_w0 = reinterpret_cast<double*>(w + L.wg_w0);
+      p->wg_h = reinterpret_cast<float*>(w + L.wg_h);
+    }
+
     auto fail = [&](sl1m_status st_) {
       delete p;
       return st_;
@@ -908,11 +1030,23 @@ sl1m_status sl1m_plan_create(const sl1m_problem* pr, void* workspace, size_t wor
     if (e == hipSuccess && p->n_layers)
       e = hipMemcpyAsync(p->red, a.layer_sigma.data(), p->n_layers * sizeof(double),
                          hipMemcpyHostToDevice, st);
+    auto up = [&](void* dst, const void* src, size_t bytes) {
+      if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st);
+    };
+    if (a.wg) {
+      const WgPlan& t = a.wgp;
+      up(p->wg_mac, t.macros.data(), sizeof(WgMacro) * t.macros.size());
+      up(p->wg_la, t.la.data(), 8 * t.la.size());
+      up(p->wg_mb, t.mb.data(), 8 * t.mb.size());
+      up(p->wg_nu, t.nu.data(), 8 * t.nu.size());
+      up(p->wg_eta, t.eta.data(), 4 * t.eta.size());
+      up(p->wg_slot, t.slot.data(), 4 * t.slot.size());
+      up(p->wg_order, wgg.order.data(), 4 * wgg.order.size());
+      up(p->wg_count, wgg.count.data(), 4 * wgg.count.size());
+      up(p->wg_w0, wgg.w0.data(), 8 * wgg.w0.size());
+      up(p->wg_h, wgg.h.data(), 4 * wgg.h.size());
+    }
     if (a.grid) {
-      auto up = [&](void* dst, const void* src, size_t bytes) {
-        if (e == hipSuccess && bytes)
-          e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st);
-      };
       up(p->grid_la, a.grid_la.data(), 8 * a.grid_la.size());
       up(p->grid_mb, a.grid_mb.data(), 8 * a.grid_mb.size());
       up(p->grid_c3, a.grid_c3.data(), 8 * a.grid_c3.size());
@@ -931,6 +1065,7 @@ sl1m_status sl1m_plan_create(const sl1m_problem* pr, void* workspace, size_t wor
       e = launch_prep_vis(p, pr->u, pr->v, pr->w, pr->ant_p, pr->ant_q, pr->ant_gain,
                           a.beam_pair ? pr->ant_fwhm : nullptr, pr->n_ant, st);
     if (e == hipSuccess) e = launch_prep_hilo(p, st);
+    if (e == hipSuccess) e = launch_wg_setup(p, st);
     if (e == hipSuccess)
       e = launch_fill(p->apart, static_cast<size_t>(p->n_achunks) * p->n_pix * p->max_rhs, a.rb,
                       st);
@@ -961,6 +1096,10 @@ sl1m_status sl1m_plan_create(const sl1m_problem* pr, void* workspace, size_t wor
     return set_error(SL1M_EINVAL, "unexpected host error");
   }
 }
+
+}  // namespace sl1m
+
+extern "C" {
 
 static void timing_release(sl1m_plan* p) {
   for (auto& v : p->tev) {

@@ -153,6 +153,32 @@ __device__ __forceinline__ void strided_sum(const T* __restrict__ p, int n, int6
   for (; c < n; ++c) acc_add(acc, p[c * stride]);
 }
 
+// Power of two s with max * s in [2^13, 2^14) (1 for a zero or non-finite
+// maximum): operands stay inside float16's range with 2 bits of headroom for
+// the rounding of the largest one.
+__device__ __forceinline__ float op_scale(float mx) {
+  if (!(mx > 0.0f) || !isfinite(mx)) return 1.0f;
+  int ex;
+  frexpf(mx, &ex);  // mx = f 2^ex, f in [0.5, 1)
+  int e = 14 - ex;
+  e = e < -120 ? -120 : (e > 120 ? 120 : e);
+  return ldexpf(1.0f, e);
+}
+
+// Wavefront maximum through cross-lane shuffles, then the block's in LDS.
+__device__ __forceinline__ float block_max(float v) {
+  __shared__ float wm[kBlock / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float m = wm[0];
+#pragma unroll
+  for (int w = 1; w < kBlock / 64; ++w) m = fmaxf(m, wm[w]);
+  __syncthreads();
+  return m;
+}
+
 // ---------------------------------------------------------------------------
 // operator tiles
 // ---------------------------------------------------------------------------

@@ -4,6 +4,7 @@
 // launches (two each for a square delta grid: single cells and pairs); a plan
 // has at most 17 segments, the delta pixels and 16 Gaussian layers.
 #include "sl1m_grid.h"
+#include "sl1m_wgroup.h"
 
 namespace sl1m {
 
@@ -261,8 +262,13 @@ hipError_t launch_grid_forward(sl1m_plan* p, const void* xp, hipStream_t st) {
   if (p->n_vis == 0) return hipSuccess;
   const float* x = static_cast<const float*>(xp);
   const float* scale = static_cast<const float*>(p->pscale);
-  float2* part = static_cast<float2*>(p->fpart);
+  float2* part = static_cast<float2*>(fwd_rows1(p));
   for (const GridSeg& g : p->grid_segs) {
+    if (p->wg && &g == &p->grid_segs[p->wg_seg]) {
+      const hipError_t e = launch_wg_forward(p, xp, st);
+      if (e != hipSuccess) return e;
+      continue;
+    }
     const int64_t co = g.cell_off;
     const double* la = p->grid_la + g.la_off;
     const double* mb = p->grid_mb + g.mb_off;
@@ -338,6 +344,11 @@ hipError_t launch_grid_adjoint(sl1m_plan* p, hipStream_t st) {
   float* part = static_cast<float*>(p->apart);
   const float2* rres = static_cast<const float2*>(p->rres);
   for (const GridSeg& g : p->grid_segs) {
+    if (p->wg && &g == &p->grid_segs[p->wg_seg]) {
+      const hipError_t e = launch_wg_adjoint(p, st);
+      if (e != hipSuccess) return e;
+      continue;
+    }
     const int64_t co = g.cell_off;
     const double* la = p->grid_la + g.la_off;
     const double* mb = p->grid_mb + g.mb_off;

@@ -178,6 +178,7 @@ struct GridSeg {
 }  // namespace sl1m
 
 namespace sl1m {
+struct WgMacro;  // sl1m_wgroup.h
 // timing kinds (sl1m_timing): 0 forward, 1 adjoint, 2 FISTA update, then the
 // grid kernels by launch: 3 delta forward, 4 delta adjoint, 5 Gaussian
 // forward (one launch per layer), 6 Gaussian adjoint (all layers)
@@ -256,6 +257,22 @@ struct sl1m_plan {
   int grid_gblocks = 0;
   sl1m::Chunk* d_chunks1 = nullptr;         // fd1 | fg1 | pd1 | pg1
 
+  // group evaluation of the delta grid segment (sl1m_wgroup.h): its tables and
+  // the visibility groups
+  bool wg = false;
+  int wg_seg = 0;                 // index into grid_segs
+  int wg_macros = 0, wg_groups = 0, wg_chunks = 1;
+  int64_t wg_cells = 0;
+  sl1m::WgMacro* wg_mac = nullptr;
+  double *wg_la = nullptr, *wg_mb = nullptr, *wg_nu = nullptr;
+  float* wg_eta = nullptr;
+  int32_t* wg_slot = nullptr;
+  int32_t *wg_order = nullptr, *wg_count = nullptr;
+  double *wg_su = nullptr, *wg_sv = nullptr, *wg_w0 = nullptr;
+  float *wg_dw = nullptr, *wg_h = nullptr;
+  float4* wg_part = nullptr;      // adjoint partial sums [chunk][tile cell]
+  float2* wg_res = nullptr;       // residual records per slot (conjugated where w < 0)
+
   // device buffers (carved from the workspace)
   char* ws = nullptr;
   size_t ws_bytes = 0;
@@ -323,6 +340,11 @@ hipError_t timed(sl1m_plan* p, int kind, hipStream_t st, F&& launch) {
 sl1m_status set_error(sl1m_status s, const std::string& msg);
 sl1m_status hip_error(hipError_t e, const char* what);
 
+// plan creation with (`groups`) or without the group evaluation (sl1m_api.hip)
+sl1m_status plan_bytes(const sl1m_problem* problem, bool groups, size_t* bytes);
+sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
+                       size_t workspace_bytes, void* stream, sl1m_plan** out);
+
 // kernels and launchers (sl1m_kernels.hip)
 hipError_t launch_prep_pixels(sl1m_plan* p, const double* l, const double* m,
                               const double* ant_fwhm_dev_unused, double beam_coef,
@@ -366,7 +388,11 @@ hipError_t launch_objective_terms(sl1m_plan* p, const void* res, const void* img
                                   hipStream_t st);
 // grid evaluation (sl1m_grid.hip): the grid segments' forward partial rows
 // [0, grid_frows) and every pixel of the grid segments in the adjoint partials.
+// (`fwd_rows1`: base of the single-side partial rows that are indexed by
+// visibility; the group evaluation's rows stand before them in place of its
+// segment's).
 hipError_t launch_grid_forward(sl1m_plan* p, const void* xp, hipStream_t st);
+void* fwd_rows1(const sl1m_plan* p);
 hipError_t launch_grid_adjoint(sl1m_plan* p, hipStream_t st);
 // Several right-hand sides (nr = 2 or 4; plans whose grid segments are all
 // square delta grids): forward partial rows [r][forward_rows][n_vis] of the

@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "sl1m_device.h"
+#include "sl1m_wgroup.h"
 
 namespace sl1m {
 
@@ -151,13 +152,15 @@ __global__ void k_fwd_reduce(const C2<R>* __restrict__ part, int n_rows, int64_t
 // thread of the block must call it (it synchronises the block).
 constexpr int kRowPix = 64;
 static_assert(kBlock == 4 * kRowPix, "row_sum uses four wavefronts of kRowPix lanes");
+// Pixels [one.x, one.y) have their whole sum in row 0 (group evaluation).
 template <typename R>
 __device__ __forceinline__ R row_sum(const R* __restrict__ part, int n_rows, int64_t n_pix, int r,
-                                     int64_t j, R (*sh)[kRowPix]) {
+                                     int64_t j, int2 one, R (*sh)[kRowPix]) {
   const int wv = threadIdx.x / kRowPix, ln = threadIdx.x % kRowPix;
   R g = R(0);
-  if (j < n_pix && wv < n_rows)
-    strided_sum<R>(part + static_cast<int64_t>(r * n_rows + wv) * n_pix + j, (n_rows - wv + 3) / 4,
+  const int rows = j >= one.x && j < one.y ? 1 : n_rows;
+  if (j < n_pix && wv < rows)
+    strided_sum<R>(part + static_cast<int64_t>(r * n_rows + wv) * n_pix + j, (rows - wv + 3) / 4,
                    4 * n_pix, g);
   sh[wv][ln] = g;
   __syncthreads();
@@ -170,14 +173,14 @@ __device__ __forceinline__ R row_sum(const R* __restrict__ part, int n_rows, int
 // kBlock threads cover kRowPix pixels.
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_adj_reduce(const R* __restrict__ part, int n_rows,
-                                                       int64_t n_pix, int nr,
+                                                       int64_t n_pix, int nr, int2 one,
                                                        const R* __restrict__ scale,
                                                        const int32_t* __restrict__ perm,
                                                        R* __restrict__ out) {
   __shared__ R sh[4][kRowPix];
   const int64_t j = static_cast<int64_t>(blockIdx.x) * kRowPix + threadIdx.x % kRowPix;
   for (int r = 0; r < nr; ++r) {
-    const R g = row_sum<R>(part, n_rows, n_pix, r, j, sh);
+    const R g = row_sum<R>(part, n_rows, n_pix, r, j, one, sh);
     if (threadIdx.x < kRowPix && j < n_pix) out[r * n_pix + (perm ? perm[j] : j)] = g * scale[j];
   }
 }
@@ -192,13 +195,14 @@ __global__ __launch_bounds__(kBlock) void k_adj_reduce(const R* __restrict__ par
 // the threshold; it is recorded in *flag instead so the solve can report it.
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_fista(const R* __restrict__ part, int n_rows,
-                                                  int64_t n_pix, const R* __restrict__ scale,
+                                                  int64_t n_pix, int2 one,
+                                                  const R* __restrict__ scale,
                                                   R* __restrict__ y, R* __restrict__ img,
                                                   const double* __restrict__ scal,
                                                   int* __restrict__ flag) {
   __shared__ R sh[4][kRowPix];
   const int64_t j = static_cast<int64_t>(blockIdx.x) * kRowPix + threadIdx.x % kRowPix;
-  R g = row_sum<R>(part, n_rows, n_pix, 0, j, sh);
+  R g = row_sum<R>(part, n_rows, n_pix, 0, j, one, sh);
   if (threadIdx.x >= kRowPix || j >= n_pix) return;
   const double t = scal[0];
   const double tn = 0.5 * (1.0 + sqrt(1.0 + 4.0 * t * t));
@@ -217,13 +221,14 @@ __global__ __launch_bounds__(kBlock) void k_fista(const R* __restrict__ part, in
 // proximal step z_k = T^{lambda/L}(y_k - g / L) into z, g as for k_fista.
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_prox(const R* __restrict__ part, int n_rows,
-                                                 int64_t n_pix, const R* __restrict__ scale,
+                                                 int64_t n_pix, int2 one,
+                                                 const R* __restrict__ scale,
                                                  const R* __restrict__ y, R* __restrict__ z,
                                                  const double* __restrict__ scal,
                                                  int* __restrict__ flag) {
   __shared__ R sh[4][kRowPix];
   const int64_t j = static_cast<int64_t>(blockIdx.x) * kRowPix + threadIdx.x % kRowPix;
-  R g = row_sum<R>(part, n_rows, n_pix, 0, j, sh);
+  R g = row_sum<R>(part, n_rows, n_pix, 0, j, one, sh);
   if (threadIdx.x >= kRowPix || j >= n_pix) return;
   const R inv_L = static_cast<R>(scal[1]), thr = static_cast<R>(scal[2]);
   g *= scale[j];
@@ -570,7 +575,7 @@ inline unsigned grid1(int64_t n, int b = kBlock) { return static_cast<unsigned>(
 template <typename R, int VPL, bool BEAM, int NR, bool HL = false>
 hipError_t fwd_launch_t(sl1m_plan* p, const void* xp, hipStream_t st, bool grid = false) {
   const int64_t vt = (p->n_vis + kBlock * VPL - 1) / (kBlock * VPL);
-  C2<R>* part = static_cast<C2<R>*>(p->fpart);
+  C2<R>* part = static_cast<C2<R>*>(grid && NR == 1 ? fwd_rows1(p) : p->fpart);
   const Chunk* dch = grid ? p->d_chunks1 : p->d_fchunks;
   const int nd = static_cast<int>(grid ? p->fd1.size() : p->fchunks_delta.size());
   const int ng = static_cast<int>(grid ? p->fg1.size() : p->fchunks_gauss.size());
@@ -819,10 +824,19 @@ int forward_rows(const sl1m_plan* p, int nr) {
   return p->n_fchunks;
 }
 
+void* fwd_rows1(const sl1m_plan* p) {
+  if (!p->wg) return p->fpart;
+  const int64_t skip = static_cast<int64_t>(p->wg_macros) * p->wg_groups * kWgVis -
+                       static_cast<int64_t>(p->grid_segs[p->wg_seg].nfc) * p->n_vis;
+  return static_cast<float2*>(p->fpart) + skip;
+}
+
 template <typename R>
 static hipError_t fwd_reduce_t(sl1m_plan* p, const void* data, void* out, bool recs, int nr,
                                hipStream_t st) {
   if (p->n_vis == 0) return hipSuccess;
+  if (nr == 1 && p->wg && !mfma_forward_call(p, nr))
+    return launch_wg_forward_reduce(p, data, out, recs, st);
   hipLaunchKernelGGL((k_fwd_reduce<R>), dim3(grid1(p->n_vis)), dim3(kBlock), 0, st,
                      static_cast<const C2<R>*>(p->fpart), forward_rows(p, nr), p->n_vis, nr,
                      static_cast<const R*>(p->vgain), static_cast<const C2<R>*>(data),
@@ -839,6 +853,7 @@ hipError_t launch_forward_reduce(sl1m_plan* p, const void* data, void* out, bool
 template <typename R>
 static hipError_t adj_prep_t(sl1m_plan* p, const void* r, int nr, hipStream_t st) {
   if (p->n_vis == 0) return hipSuccess;
+  if (nr == 1 && p->wg && !mfma_adjoint_call(p, nr)) return launch_wg_adjoint_prep(p, r, st);
   hipLaunchKernelGGL((k_adj_prep<R>), dim3(grid1(p->n_vis)), dim3(kBlock), 0, st,
                      static_cast<const C2<R>*>(r), p->n_vis, nr, static_cast<const R*>(p->vgain),
                      static_cast<C2<R>*>(p->rres), static_cast<const R*>(p->layerDs),
@@ -893,11 +908,18 @@ hipError_t launch_adjoint(sl1m_plan* p, int nr, hipStream_t st) {
   return SL1M_DISPATCH_R(p, adjoint_t, p, nr, st);
 }
 
+// Pixels whose adjoint sum is whole in row 0 of the partials.
+static int2 wg_pixels(const sl1m_plan* p, int nr) {
+  if (!p->wg || nr != 1 || mfma_adjoint_call(p, nr)) return make_int2(0, 0);
+  const Segment& s = p->segs[p->grid_segs[p->wg_seg].seg];
+  return make_int2(static_cast<int>(s.start), static_cast<int>(s.start + s.count));
+}
+
 template <typename R>
 static hipError_t adj_reduce_t(sl1m_plan* p, void* g, bool unpermute, int nr, hipStream_t st) {
   if (p->n_pix == 0) return hipSuccess;
   hipLaunchKernelGGL((k_adj_reduce<R>), dim3(grid1(p->n_pix, kRowPix)), dim3(kBlock), 0, st,
-                     static_cast<const R*>(p->apart), p->n_achunks, p->n_pix, nr,
+                     static_cast<const R*>(p->apart), p->n_achunks, p->n_pix, nr, wg_pixels(p, nr),
                      static_cast<const R*>(p->pscale), unpermute ? p->perm : nullptr,
                      static_cast<R*>(g));
   return hipGetLastError();
@@ -910,7 +932,7 @@ template <typename R>
 static hipError_t fista_t(sl1m_plan* p, hipStream_t st) {
   if (p->n_pix > 0)
     hipLaunchKernelGGL((k_fista<R>), dim3(grid1(p->n_pix, kRowPix)), dim3(kBlock), 0, st,
-                       static_cast<const R*>(p->apart), p->n_achunks, p->n_pix,
+                       static_cast<const R*>(p->apart), p->n_achunks, p->n_pix, wg_pixels(p, 1),
                        static_cast<const R*>(p->pscale), static_cast<R*>(p->xperm),
                        static_cast<R*>(p->img), p->scal, p->flag);
   hipLaunchKernelGGL(k_tstep, dim3(1), dim3(64), 0, st, p->scal);
@@ -924,7 +946,7 @@ template <typename R>
 static hipError_t prox_t(sl1m_plan* p, hipStream_t st) {
   if (p->n_pix > 0)
     hipLaunchKernelGGL((k_prox<R>), dim3(grid1(p->n_pix, kRowPix)), dim3(kBlock), 0, st,
-                       static_cast<const R*>(p->apart), p->n_achunks, p->n_pix,
+                       static_cast<const R*>(p->apart), p->n_achunks, p->n_pix, wg_pixels(p, 1),
                        static_cast<const R*>(p->pscale), static_cast<const R*>(p->xperm),
                        static_cast<R*>(p->zbuf), p->scal, p->flag);
   return hipGetLastError();

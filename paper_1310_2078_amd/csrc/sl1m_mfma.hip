@@ -81,32 +81,6 @@ __device__ __forceinline__ typename MOp<PREC>::vec pack4(f4_t v) {
     return __builtin_bit_cast(s4_t, __builtin_convertvector(v, b4_t));
 }
 
-// Power of two s with max * s in [2^13, 2^14) (1 for a zero or non-finite
-// maximum): operands stay inside float16's range with 2 bits of headroom for
-// the rounding of the largest one.
-__device__ __forceinline__ float op_scale(float mx) {
-  if (!(mx > 0.0f) || !isfinite(mx)) return 1.0f;
-  int ex;
-  frexpf(mx, &ex);  // mx = f 2^ex, f in [0.5, 1)
-  int e = 14 - ex;
-  e = e < -120 ? -120 : (e > 120 ? 120 : e);
-  return ldexpf(1.0f, e);
-}
-
-// Wavefront maximum through cross-lane shuffles, then the block's in LDS.
-__device__ __forceinline__ float block_max(float v) {
-  __shared__ float wm[kBlock / 64];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float m = wm[0];
-#pragma unroll
-  for (int w = 1; w < kBlock / 64; ++w) m = fmaxf(m, wm[w]);
-  __syncthreads();
-  return m;
-}
-
 // Block maxima of |x[r][j] scale[j]| (scale may be null: |x[i]|) over n values.
 __global__ __launch_bounds__(kBlock) void k_mfma_absmax(const float* __restrict__ x, int64_t n,
                                                         const float* __restrict__ scale,

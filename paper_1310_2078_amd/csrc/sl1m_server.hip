@@ -707,7 +707,7 @@ sl1m_status admit(sl1m_server* s, Ticket& t) {
   if (t.grid_allowed) {
     sl1m_problem pg = pr;
     pg.grid_mode = SL1M_GRID_AUTO;
-    if (sl1m_status st = sl1m_plan_create(&pg, base, ws_al, s->admit_stream, &plan)) return st;
+    if (sl1m_status st = plan_build(&pg, false, base, ws_al, s->admit_stream, &plan)) return st;
     const bool pure = plan->grid_segs.size() == 1 && plan->fd1.empty() && plan->fg1.empty() &&
                       plan->pd1.empty() && plan->pg1.empty();
     if (pure) {
@@ -718,7 +718,7 @@ sl1m_status admit(sl1m_server* s, Ticket& t) {
     }
   }
   if (!plan) {
-    if (sl1m_status st = sl1m_plan_create(&pr, base, ws_al, s->admit_stream, &plan)) return st;
+    if (sl1m_status st = plan_build(&pr, false, base, ws_al, s->admit_stream, &plan)) return st;
   }
   t.plan = plan;
   char* extra = base + ws_al;
@@ -1145,10 +1145,10 @@ sl1m_status sl1m_server_submit(sl1m_server* s, const sl1m_problem* problem, cons
     // footprint covers either plan (decided at admission)
     size_t ws = 0, ws_off = 0;
     if (problem->grid_mode != SL1M_GRID_OFF) {
-      if (sl1m_status st = sl1m_plan_workspace_bytes(&t->problem, &ws)) return st;
+      if (sl1m_status st = plan_bytes(&t->problem, false, &ws)) return st;
     }
     t->problem.grid_mode = SL1M_GRID_OFF;
-    if (sl1m_status st = sl1m_plan_workspace_bytes(&t->problem, &ws_off)) return st;
+    if (sl1m_status st = plan_bytes(&t->problem, false, &ws_off)) return st;
     t->grid_allowed = problem->grid_mode != SL1M_GRID_OFF;
     t->footprint = sched::Arena::round_up(std::max(ws, ws_off)) + extra_bytes(t->problem);
     t->vis = vis;

@@ -1,0 +1,90 @@
+// Group evaluation of delta grid segments on the matrix cores (gfx950, float32
+// plans, one right-hand side): tables and launchers.
+//
+// The grid evaluation (sl1m_grid.h) factorises an entry into A_k(l) B_k(m) C_k(nu).
+// C, the only factor that is no product of an l and an m part, depends on the
+// visibility through w alone.  So the visibilities are ordered by |w| (w < 0
+// folded onto w > 0: a real image has V(-u,-v,-w) = conj V) and cut into groups
+// of at most 64 of nearly one w:
+//   C_k(a,b) = C_0(a,b) exp(-2 pi i dw_k nu(a,b)),  dw_k = w_k - w_0 small.
+// C_0 is formed once per (group, cell), and what is left of the sum over the
+// columns of a tile of cells (forward) or over the visibilities of the group
+// (adjoint) is a matrix product of real phasor components, which the matrix
+// cores take.  Inside a tile nu(a,b) = nuT + eta(a,b): the factor of nuT is
+// exact per visibility, that of eta a short series, whose argument 2 pi dw eta
+// the cut of the groups keeps below kWgX radians.
+//
+// The operands are float32 values split into two float16 (value = hi + lo to
+// 2^-22 of it), each product as hi hi + hi lo + lo hi with float32 sums.
+#pragma once
+
+#include "sl1m_internal.h"
+
+namespace sl1m {
+
+constexpr int kWgVis = 64;      // visibilities per group
+constexpr int kWgRows = 16;     // |l| values of a tile
+constexpr int kWgSteps = 2;     // steps of 16 |m| values of a tile
+constexpr int kWgCols = 16 * kWgSteps;
+constexpr int kWgCells = kWgRows * kWgCols;
+// series argument limits (radians), by the terms kept: up to kWgXN the first
+// order in one float16 product, up to kWgXM the second order too, up to kWgXW the
+// first order split like the zeroth, up to kWgX the third order too.  A unit pixel
+// at the phase centre (every entry 1; 32 x 32 x 2,000) comes out within 4.3e-7,
+// with limits of 1.5e-3, 3e-3, 2e-2 within 1.3e-6.
+constexpr float kWgXN = 1.2e-3f;
+constexpr float kWgXM = 2.5e-3f;
+constexpr float kWgXW = 1.5e-2f;
+constexpr float kWgX = 5.0e-2f;
+
+// Up to four tiles (one per wavefront) of neighbouring rows over the same columns.
+struct WgMacro {
+  int32_t a_off, b_off;        // first row / column position in wg_la / wg_mb
+  int32_t sets, steps;         // row sets (tiles) and column steps
+  int32_t cell_off;            // first cell of the first tile (kWgCells per tile)
+  float eta_max, nu_t[4];      // largest |eta|; each tile's nuT
+  float xs;                    // 2 pi s, s the power of two that the macro's eta are divided by
+};
+
+// Host-built tables of one delta grid segment.  Tile cells are numbered
+// column * kWgRows + row.
+struct WgPlan {
+  std::vector<WgMacro> macros;
+  std::vector<double> la, mb;      // row / column positions of the macros
+  std::vector<double> nu;          // per tile cell
+  std::vector<float> eta;          // per tile cell, divided by the macro's s (below 1)
+  std::vector<int32_t> slot;       // [4 per tile cell] permuted pixel or -1
+  float eta_max = 0.0f;
+  int64_t padded = 0;              // cells evaluated, padding included
+};
+
+// Visibility groups: `order` holds per slot (kWgVis per group) 2 k + (1 where
+// w_k < 0), -1 where padded (at a group's end).
+struct WgGroups {
+  std::vector<int32_t> order;
+  std::vector<double> w0;
+  std::vector<float> h;            // largest |dw| of the group
+  std::vector<int32_t> count;      // visibilities of the group
+};
+
+void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c3,
+                    const int32_t* slot, WgPlan& out);
+bool wg_build_groups(const std::vector<double>& w, float eta_max, int64_t max_groups,
+                     WgGroups& out);
+// groups a plan reserves room for
+int64_t wg_group_cap(int64_t n_vis);
+// group chunks (blocks per macro) of the operator kernels, at most wg_chunk_cap()
+int wg_chunks(int macros, int groups);
+int wg_chunk_cap(int macros);
+
+hipError_t launch_wg_setup(sl1m_plan* p, hipStream_t st);
+hipError_t launch_wg_forward(sl1m_plan* p, const void* xp, hipStream_t st);
+// the forward reduction (launch_forward_reduce) of a plan with groups, one side
+hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, bool adj_records,
+                                    hipStream_t st);
+// adjoint records of a plan with groups, one side (launch_adjoint_prep)
+hipError_t launch_wg_adjoint_prep(sl1m_plan* p, const void* r, hipStream_t st);
+// the segment's gradient sums into row 0 of the adjoint partials (its only row)
+hipError_t launch_wg_adjoint(sl1m_plan* p, hipStream_t st);
+
+}  // namespace sl1m

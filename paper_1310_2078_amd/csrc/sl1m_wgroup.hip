@@ -1,0 +1,1024 @@
+// Group evaluation of delta grid segments (sl1m_wgroup.h): host tables, kernels
+// and launchers.
+#include <algorithm>
+#include <cmath>
+
+#include "sl1m_device.h"
+#include "sl1m_wgroup.h"
+
+namespace sl1m {
+
+// ---------------------------------------------------------------------------
+// host tables
+// ---------------------------------------------------------------------------
+
+// Groups that hold few visibilities (sparse w, a wide field: the cut at kWgX ends
+// them early) still cost C_0 and the float16 splits of every cell.  Measured on
+// 256 x 256 pixels over +-0.3: 97,536 visibilities (1.19 times the full groups)
+// take 0.66 of the grid evaluation's time, 20,000 (2.28 times) 0.98 of it forward
+// and 1.17 adjoint; the line is drawn between.
+int64_t wg_group_cap(int64_t n_vis) {
+  const int64_t full = (n_vis + kWgVis - 1) / kWgVis;
+  return full + full * 3 / 4 + 2;
+}
+
+// Blocks: two of 256 threads stay resident per compute unit (512 in all).  Two
+// rounds of them for small grids (each block loads its tiles' cells first, and
+// the adjoint's chunk sums grow with the count), four for large ones, whose
+// macros differ more in work (256 x 256 x 97,536: 397 / 428 us at two rounds,
+// 395 / 424 at four, 402 / 442 at eight; 100,003 x 151 x 150 pixels 89 / 102 us
+// at two, 89 / 107 at three; 1024 x 1024 x 409,600: 28.4 / 31.5 ms at two, 27.3 /
+// 29.9 at four).
+int wg_chunk_cap(int macros) { return std::max(1, (macros <= 32 ? 1024 : 2048) / macros); }
+int wg_chunks(int macros, int groups) {
+  return std::max(1, std::min(groups, wg_chunk_cap(macros)));
+}
+
+// Row sets of kWgRows |l| values and column sets of up to kWgSteps steps of 16
+// |m| values, both spread evenly over the macros.
+void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c3,
+                    const int32_t* slot, WgPlan& out) {
+  const int na = g.na, nb = g.nb;
+  const int rsets = (na + kWgRows - 1) / kWgRows, rmac = (rsets + 3) / 4;
+  const int steps = (nb + 15) / 16, cmac = (steps + kWgSteps - 1) / kWgSteps;
+  for (int ri = 0; ri < rmac; ++ri)
+    for (int ci = 0; ci < cmac; ++ci) {
+      const int r0 = rsets * ri / rmac, r1 = rsets * (ri + 1) / rmac;
+      const int s0 = steps * ci / cmac, s1 = steps * (ci + 1) / cmac;
+      WgMacro m{};
+      m.sets = r1 - r0;
+      m.steps = s1 - s0;
+      m.a_off = static_cast<int32_t>(out.la.size());
+      m.b_off = static_cast<int32_t>(out.mb.size());
+      m.cell_off = static_cast<int32_t>(out.nu.size());
+      for (int i = 0; i < 4 * kWgRows; ++i) {
+        const int ia = kWgRows * r0 + i;
+        out.la.push_back(i < kWgRows * m.sets && ia < na ? la[ia] : 0.0);
+      }
+      for (int i = 0; i < kWgCols; ++i) {
+        const int ib = 16 * s0 + i;
+        out.mb.push_back(ib < 16 * s1 && ib < nb ? mb[ib] : 0.0);
+      }
+      double eta_max = 0.0;
+      const size_t first = out.nu.size();
+      for (int w = 0; w < m.sets; ++w) {
+        const int a0 = kWgRows * (r0 + w), a1 = std::min(a0 + kWgRows, na);
+        const int b0 = 16 * s0, b1 = std::min(16 * s1, nb);
+        auto cell = [&](int ia, int ib) {
+          return (static_cast<int64_t>(ib / kGridNB) * na + ia) * kGridNB + ib % kGridNB;
+        };
+        double lo = 1e300, hi = -1e300;
+        for (int ib = b0; ib < b1; ++ib)
+          for (int ia = a0; ia < a1; ++ia) {
+            const double v = c3[cell(ia, ib)];
+            lo = std::min(lo, v);
+            hi = std::max(hi, v);
+          }
+        // the tile's reference as the kernels hold it (float32)
+        m.nu_t[w] = static_cast<float>(0.5 * (lo + hi));
+        const double nt = static_cast<double>(m.nu_t[w]);
+        const size_t n0 = out.nu.size();
+        out.nu.resize(n0 + kWgCells, 0.0);
+        out.eta.resize(n0 + kWgCells, 0.0f);
+        out.slot.resize(4 * (n0 + kWgCells), -1);
+        for (int ib = b0; ib < b1; ++ib)
+          for (int ia = a0; ia < a1; ++ia) {
+            const int64_t q = cell(ia, ib);
+            const size_t o = n0 + static_cast<size_t>(ib - b0) * kWgRows + (ia - a0);
+            out.nu[o] = c3[q];
+            out.eta[o] = static_cast<float>(c3[q] - nt);
+            eta_max = std::max(eta_max, std::fabs(c3[q] - nt));
+            for (int s = 0; s < 4; ++s) out.slot[4 * o + s] = slot[4 * q + s];
+          }
+        out.padded += kWgRows * 16 * m.steps;
+      }
+      // eta / s in [-1, 1] and x s (at most 2 kWgX) both lie in float16's range
+      int ex = 0;
+      (void)std::frexp(eta_max, &ex);
+      const double s = eta_max > 0.0 ? std::ldexp(1.0, ex) : 1.0;
+      for (size_t o = first; o < out.eta.size(); ++o) out.eta[o] /= static_cast<float>(s);
+      m.xs = static_cast<float>(6.283185307179586 * s);
+      m.eta_max = static_cast<float>(eta_max);
+      out.eta_max = std::max(out.eta_max, m.eta_max);
+      out.macros.push_back(m);
+    }
+}
+
+bool wg_build_groups(const std::vector<double>& w, float eta_max, int64_t max_groups,
+                     WgGroups& out) {
+  const int64_t n = static_cast<int64_t>(w.size());
+  double wm = 0.0;
+  for (double x : w) {
+    if (!std::isfinite(x)) return false;
+    wm = std::max(wm, std::fabs(x));
+  }
+  if (wm >= 0x1.0p27) return false;  // phases below 2^27 turns (|nu| < 1): kMagicFine
+  // order by |w| in 2^20 bins (two stable counting passes of 10 bits); equal bins
+  // keep the caller's order
+  const double scale = wm > 0.0 ? 1048575.0 / wm : 0.0;
+  std::vector<uint32_t> key(n);
+  std::vector<int32_t> a(n), b(n);
+  for (int64_t k = 0; k < n; ++k) {
+    key[k] = static_cast<uint32_t>(std::fabs(w[k]) * scale);
+    a[k] = static_cast<int32_t>(k);
+  }
+  for (int pass = 0; pass < 2; ++pass) {
+    int64_t cnt[1025] = {};
+    const int sh = 10 * pass;
+    for (int64_t i = 0; i < n; ++i) ++cnt[((key[a[i]] >> sh) & 1023u) + 1];
+    for (int i = 0; i < 1024; ++i) cnt[i + 1] += cnt[i];
+    for (int64_t i = 0; i < n; ++i) b[cnt[(key[a[i]] >> sh) & 1023u]++] = a[i];
+    a.swap(b);
+  }
+  const double hmax = eta_max > 0.0f ? kWgX / (6.283185307179586 * eta_max) : 1e300;
+  for (int64_t i = 0; i < n;) {
+    double lo = std::fabs(w[a[i]]), hi = lo;
+    int64_t j = i + 1;
+    for (; j < n && j - i < kWgVis; ++j) {
+      const double x = std::fabs(w[a[j]]);
+      const double l2 = std::min(lo, x), h2 = std::max(hi, x);
+      if (h2 - l2 > 2.0 * hmax) break;
+      lo = l2;
+      hi = h2;
+    }
+    if (static_cast<int64_t>(out.w0.size()) >= max_groups) return false;
+    for (int s = 0; s < kWgVis; ++s)
+      out.order.push_back(i + s < j ? 2 * a[i + s] + (w[a[i + s]] < 0.0 ? 1 : 0) : -1);
+    out.w0.push_back(0.5 * (lo + hi));
+    out.h.push_back(static_cast<float>(0.5 * (hi - lo)));
+    out.count.push_back(static_cast<int32_t>(j - i));
+    i = j;
+  }
+  return true;
+}
+
+// ---------------------------------------------------------------------------
+// kernels
+// ---------------------------------------------------------------------------
+
+namespace {
+
+using namespace dev;
+
+typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
+typedef float f2_t __attribute__((ext_vector_type(2)));
+typedef float f4_t __attribute__((ext_vector_type(4)));
+
+constexpr float kTwoPi = 6.28318530717958648f;
+constexpr int kParts = 5;  // column operand: hi, lo, x hi, x lo, x^2 / 2 (x = 2 pi s dw)
+
+// exp(2 pi i a b) with the phase kept to 2^-24 turn (phasor: 2^-23) from FP64
+// kMagicFine = kMagic / 2 on: two more instructions, for C_0, whose phase every
+// entry of a group shares.
+constexpr double kMagicFine = 0.5 * kMagic;
+__device__ __forceinline__ void phasor_fine(double t, float& c, float& s) {
+  const int32_t f = static_cast<int32_t>(static_cast<uint32_t>(__double2loint(t)) << 8);
+  const float p = static_cast<float>(f) * 0x1.0p-32f;
+  s = __builtin_amdgcn_sinf(p);
+  c = __builtin_amdgcn_cosf(p);
+}
+
+// value = hi + lo in float16 (hi rounded to nearest, lo the rounded rest)
+__device__ __forceinline__ void split2(float p, float q, h2_t& hi, h2_t& lo) {
+  hi = __builtin_convertvector((f2_t{p, q}), h2_t);
+  lo = __builtin_convertvector(
+      (f2_t{p - static_cast<float>(hi[0]), q - static_cast<float>(hi[1])}), h2_t);
+}
+
+struct Op8 {
+  h2_t v[4];
+  __device__ __forceinline__ h8_t vec() const { return __builtin_bit_cast(h8_t, *this); }
+};
+
+__device__ __forceinline__ void split8(const float (&p)[8], Op8& hi, Op8& lo) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) split2(p[2 * j], p[2 * j + 1], hi.v[j], lo.v[j]);
+}
+
+__device__ __forceinline__ f4_t mma(h8_t a, h8_t b, f4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ h8_t as_h8(uint4 v) { return __builtin_bit_cast(h8_t, v); }
+__device__ __forceinline__ uint32_t as_u32(h2_t v) { return __builtin_bit_cast(uint32_t, v); }
+
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  return v;
+}
+
+// One step (16 columns) of one kind pair (re, im): the tile rows' values pr, pi
+// (float32, this lane's row and four columns) times the column operands of the
+// group's visibility tiles, with the series terms: D_re += x eta P_im,
+// D_im -= x eta P_re (first order), D -= (x eta)^2 / 2 P (second).
+template <int SER, bool FULL>
+__device__ __forceinline__ void kind_pair(const float (&pr)[8], const float (&pi)[8],
+                                          const float (&eta)[4], const uint4* __restrict__ col,
+                                          const float (&hx)[4], int nt, f4_t (&dre)[4],
+                                          f4_t (&dim)[4]) {
+  Op8 rh, rl, ih, il, erh, erl, eih, eil;
+  split8(pr, rh, rl);
+  split8(pi, ih, il);
+  if constexpr (SER >= 2) {
+    float er[8], ei[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      er[j] = -eta[j / 2] * pr[j];
+      ei[j] = eta[j / 2] * pi[j];
+    }
+    split8(er, erh, erl);
+    split8(ei, eih, eil);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const _Float16 e = static_cast<_Float16>(eta[j]);
+      erh.v[j] = rh.v[j] * -(h2_t{e, e});
+      eih.v[j] = ih.v[j] * h2_t{e, e};
+    }
+  }
+  Op8 srh, sih;  // -eta^2 P_re, -eta^2 P_im
+  if constexpr (SER >= 2) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float e = eta[j], e2 = -e * e;
+      srh.v[j] = __builtin_convertvector((f2_t{e2 * pr[2 * j], e2 * pr[2 * j + 1]}), h2_t);
+      sih.v[j] = __builtin_convertvector((f2_t{e2 * pi[2 * j], e2 * pi[2 * j + 1]}), h2_t);
+    }
+  } else if constexpr (SER == 1) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const _Float16 e = static_cast<_Float16>(eta[j]);
+      srh.v[j] = erh.v[j] * h2_t{e, e};
+      sih.v[j] = eih.v[j] * -(h2_t{e, e});
+    }
+  }
+  Op8 trh, tih;
+  if constexpr (SER == 3) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const _Float16 e = static_cast<_Float16>(eta[j]);
+      trh.v[j] = sih.v[j] * h2_t{e, e};     // -eta^3 P_im
+      tih.v[j] = srh.v[j] * -(h2_t{e, e});  // eta^3 P_re
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    if (!FULL && t >= nt) continue;
+    const h8_t bh = as_h8(col[16 * t]), bl = as_h8(col[64 + 16 * t]), ch = as_h8(col[128 + 16 * t]);
+    dre[t] = mma(rh.vec(), bh, dre[t]);
+    dim[t] = mma(ih.vec(), bh, dim[t]);
+    dre[t] = mma(rh.vec(), bl, dre[t]);
+    dim[t] = mma(ih.vec(), bl, dim[t]);
+    dre[t] = mma(rl.vec(), bh, dre[t]);
+    dim[t] = mma(il.vec(), bh, dim[t]);
+    dre[t] = mma(eih.vec(), ch, dre[t]);
+    dim[t] = mma(erh.vec(), ch, dim[t]);
+    if constexpr (SER >= 2) {
+      const h8_t cl = as_h8(col[192 + 16 * t]);
+      dre[t] = mma(eih.vec(), cl, dre[t]);
+      dim[t] = mma(erh.vec(), cl, dim[t]);
+      dre[t] = mma(eil.vec(), ch, dre[t]);
+      dim[t] = mma(erl.vec(), ch, dim[t]);
+    }
+    if constexpr (SER > 0) {
+      const h8_t sh = as_h8(col[256 + 16 * t]);
+      dre[t] = mma(srh.vec(), sh, dre[t]);
+      dim[t] = mma(sih.vec(), sh, dim[t]);
+      if constexpr (SER == 3) {
+        const h8_t th = sh * static_cast<_Float16>(hx[t]);  // x^3 / 6
+        dre[t] = mma(trh.vec(), th, dre[t]);
+        dim[t] = mma(tih.vec(), th, dim[t]);
+      }
+    }
+  }
+}
+
+struct FwdAcc {
+  f4_t cr[4], ci[4], sr[4], si[4];  // cos-row and sin-row sums (re, im) per visibility tile
+};
+
+// `e`: this lane's row and its four columns of every step.
+template <int SER, bool FULL>
+__device__ __forceinline__ void fwd_tile(int steps, double w0, const double* __restrict__ nu,
+                                         const float4 (&e)[kWgSteps][4],
+                                         const float (&eta)[kWgSteps][4],
+                                         const uint4* __restrict__ col, const float (&hx)[4], int nt,
+                                         FwdAcc& d) {
+#pragma unroll
+  for (int s = 0; s < kWgSteps; ++s) {
+    if (!FULL && s >= steps) continue;
+    float cc[4], cs[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) phasor_fine(fma(w0, nu[(s * 16 + j) * kWgRows], kMagicFine), cc[j], cs[j]);
+    float pr[8], pi[8];
+    const uint4* c = col + s * 4 * kParts * 64;
+    // C = cc - i cs; cos row: bc (C e1), bs (-i C e3); sin row: bc (-i C e4), bs (C e2)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      pr[2 * j] = cc[j] * e[s][j].x;
+      pr[2 * j + 1] = -cs[j] * e[s][j].z;
+      pi[2 * j] = -cs[j] * e[s][j].x;
+      pi[2 * j + 1] = -cc[j] * e[s][j].z;
+    }
+    kind_pair<SER, FULL>(pr, pi, eta[s], c, hx, nt, d.cr, d.ci);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      pr[2 * j] = -cs[j] * e[s][j].w;
+      pr[2 * j + 1] = cc[j] * e[s][j].y;
+      pi[2 * j] = -cc[j] * e[s][j].w;
+      pi[2 * j + 1] = -cs[j] * e[s][j].y;
+    }
+    kind_pair<SER, FULL>(pr, pi, eta[s], c, hx, nt, d.sr, d.si);
+  }
+}
+
+struct FwdLds {
+  uint4 col[kWgSteps * 4 * kParts * 64];  // [step, quarter][part][visibility]: 4 columns (cos, sin)
+  double nu[4][kWgCells];
+  double la[4 * kWgRows], mb[kWgCols], u[kWgVis];
+  float hx[kWgVis];                       // x / 3
+  float2 red[4][kWgVis];
+};
+
+// Forward: block (groups x, x + gridDim.x, ..; macro y); row y of the partial sums holds the
+// macro's sum per slot.
+__global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
+    const WgMacro* __restrict__ macros, const float* __restrict__ xp,
+    const float* __restrict__ pscale, const int4* __restrict__ slot, const double* __restrict__ nu,
+    const float* __restrict__ eta, const double* __restrict__ la, const double* __restrict__ mb,
+    const double* __restrict__ su, const double* __restrict__ sv, const float* __restrict__ sdw,
+    const double* __restrict__ w0s, const float* __restrict__ hs, const int32_t* __restrict__ cnt,
+    int n_groups, float2* __restrict__ rows) {
+  __shared__ FwdLds lds;
+  const int mac = blockIdx.y;
+  const ConstPtr<WgMacro> cm = as_const(macros) + mac;
+  const int sets = cm->sets, steps = cm->steps;
+  const float eta_max = cm->eta_max, xs = cm->xs;
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool active = wv < sets;
+  const float nu_t = cm->nu_t[wv];
+  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
+  if (tid < 4 * kWgRows) lds.la[tid] = la[cm->a_off + tid];
+  if (tid < kWgCols) lds.mb[tid] = mb[cm->b_off + tid];
+  const int64_t lane0 = cell0 + quad * 4 * kWgRows + r16;  // this lane's row, first column
+  // sign combinations of the cells' amplitudes, times the power of two that
+  // brings four times the tile's largest amplitude into [2^13, 2^14)
+  for (int i = lane; i < kWgCells; i += 64) lds.nu[wv][i] = nu[cell0 + i];
+  float4 e[kWgSteps][4];
+  float et[kWgSteps][4];
+  float mx = 0.0f;
+#pragma unroll
+  for (int s = 0; s < kWgSteps; ++s)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      et[s][j] = eta[lane0 + (s * 16 + j) * kWgRows];
+      const int4 q = slot[lane0 + (s * 16 + j) * kWgRows];
+      const float x0 = q.x >= 0 ? xp[q.x] * pscale[q.x] : 0.0f;
+      const float x1 = q.y >= 0 ? xp[q.y] * pscale[q.y] : 0.0f;
+      const float x2 = q.z >= 0 ? xp[q.z] * pscale[q.z] : 0.0f;
+      const float x3 = q.w >= 0 ? xp[q.w] * pscale[q.w] : 0.0f;
+      const float m = fmaxf(fmaxf(fabsf(x0), fabsf(x1)), fmaxf(fabsf(x2), fabsf(x3)));
+      const float sum = (x0 + x1) + (x2 + x3);
+      mx = fmaxf(mx, sum != sum ? __builtin_inff() : m);  // fmaxf drops a NaN
+      e[s][j] = make_float4(sum, (x1 + x2) - (x0 + x3), (x0 + x1) - (x2 + x3),
+                            (x0 - x1) + (x2 - x3));
+    }
+  const float c = op_scale(4.0f * wave_max(mx)), sc = 1.0f / c;
+#pragma unroll
+  for (int s = 0; s < kWgSteps; ++s)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      e[s][j].x *= c;
+      e[s][j].y *= c;
+      e[s][j].z *= c;
+      e[s][j].w *= c;
+    }
+  const int g0 = static_cast<int>(blockIdx.x), gs = static_cast<int>(gridDim.x);
+  const ConstPtr<double> cw0 = as_const(w0s);
+  const ConstPtr<float> chs = as_const(hs);
+  const ConstPtr<int32_t> ccnt = as_const(cnt);
+  // each group's coordinates are loaded during the group before it
+  double un_ = 0.0, vn = 0.0, w0n = 0.0;
+  float dwn = 0.0f, hn = 0.0f;
+  int cn = 0;
+  auto load = [&](int g) {
+    un_ = su[g * kWgVis + lane];
+    vn = sv[g * kWgVis + lane];
+    dwn = sdw[g * kWgVis + lane];
+    w0n = cw0[g];
+    hn = chs[g];
+    cn = ccnt[g];
+  };
+  if (g0 < n_groups) load(g0);
+  __syncthreads();
+  for (int g = g0; g < n_groups; g += gs) {
+    const float dw = dwn;
+    const double w0 = w0n;
+    const float xm = kTwoPi * hn * eta_max;
+    const int ser = xm <= kWgXN ? 0 : xm <= kWgXM ? 1 : xm <= kWgXW ? 2 : 3;
+    const bool wide = ser >= 2;
+    const int nt = (cn + 15) >> 4;
+    {
+      const double v = vn;
+      const float x = xs * dw;
+      if (wv == 0) {
+        lds.u[lane] = un_;
+        lds.hx[lane] = 0.33333334f * x;
+      }
+      load(g + gs < n_groups ? g + gs : g);
+      for (int un = wv; un < 4 * steps; un += 4) {
+        uint4 o[kParts];
+        uint32_t* const po = reinterpret_cast<uint32_t*>(o);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float cb, sb;
+          phasor(fma(v, lds.mb[un * 4 + j], kMagic), cb, sb);
+          h2_t hi, lo, fh, fl;
+          split2(cb, sb, hi, lo);
+          po[j] = as_u32(hi);
+          po[4 + j] = as_u32(lo);
+          const float xc = x * cb, xsn = x * sb;
+          if (ser > 0)
+            po[16 + j] = as_u32(__builtin_convertvector((f2_t{0.5f * x * xc, 0.5f * x * xsn}), h2_t));
+          if (wide) {
+            split2(xc, xsn, fh, fl);
+            po[12 + j] = as_u32(fl);
+          } else {
+            fh = __builtin_convertvector((f2_t{xc, xsn}), h2_t);
+          }
+          po[8 + j] = as_u32(fh);
+        }
+        uint4* dst = lds.col + un * kParts * 64 + lane;
+        dst[0] = o[0];
+        dst[64] = o[1];
+        dst[128] = o[2];
+        if (wide) dst[192] = o[3];
+        if (ser > 0) dst[256] = o[4];
+      }
+    }
+    __syncthreads();
+    float re = 0.0f, im = 0.0f;
+    if (active) {
+      FwdAcc d;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) d.cr[t] = d.ci[t] = d.sr[t] = d.si[t] = f4_t{0, 0, 0, 0};
+      float hx[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) hx[t] = lds.hx[16 * t + r16];
+      const uint4* col = lds.col + quad * kParts * 64 + r16;
+      const double* nuw = &lds.nu[wv][quad * 4 * kWgRows + r16];
+      const bool full = steps == kWgSteps && nt == 4;
+      if (full && ser == 0)
+        fwd_tile<0, true>(steps, w0, nuw, e, et, col, hx, nt, d);
+      else if (ser == 0)
+        fwd_tile<0, false>(steps, w0, nuw, e, et, col, hx, nt, d);
+      else if (ser == 1)
+        fwd_tile<1, false>(steps, w0, nuw, e, et, col, hx, nt, d);
+      else if (ser == 2)
+        fwd_tile<2, false>(steps, w0, nuw, e, et, col, hx, nt, d);
+      else
+        fwd_tile<3, false>(steps, w0, nuw, e, et, col, hx, nt, d);
+      // lane: visibility 16 t + r16, rows 4 quad + i
+      float vr[4], vi[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        vr[t] = vi[t] = 0.0f;
+        if (t >= nt) continue;
+        const double u = lds.u[16 * t + r16];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float ac, as;
+          phasor(fma(u, lds.la[wv * kWgRows + quad * 4 + i], kMagic), ac, as);
+          vr[t] = fmaf(ac, d.cr[t][i], vr[t]);
+          vi[t] = fmaf(ac, d.ci[t][i], vi[t]);
+          vr[t] = fmaf(as, d.sr[t][i], vr[t]);
+          vi[t] = fmaf(as, d.si[t][i], vi[t]);
+        }
+      }
+      // sum over the quads; lane L ends with visibility L
+      const bool hi = (lane & 32) != 0, md = (lane & 16) != 0;
+      float ar[2], ai[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const float kr = hi ? vr[t + 2] : vr[t], ki = hi ? vi[t + 2] : vi[t];
+        const float or_ = hi ? vr[t] : vr[t + 2], oi = hi ? vi[t] : vi[t + 2];
+        ar[t] = kr + __shfl_xor(or_, 32, 64);
+        ai[t] = ki + __shfl_xor(oi, 32, 64);
+      }
+      const float kr = md ? ar[1] : ar[0], ki = md ? ai[1] : ai[0];
+      const float or_ = md ? ar[0] : ar[1], oi = md ? ai[0] : ai[1];
+      const float sr = kr + __shfl_xor(or_, 16, 64), si = ki + __shfl_xor(oi, 16, 64);
+      const float th = dw * nu_t;
+      const float ct = __builtin_amdgcn_cosf(th), st = __builtin_amdgcn_sinf(th);
+      re = sc * fmaf(ct, sr, st * si);
+      im = sc * fmaf(ct, si, -st * sr);
+    }
+    lds.red[wv][lane] = make_float2(re, im);
+    __syncthreads();
+    if (tid < kWgVis) {
+      const float2 a = lds.red[0][tid], b = lds.red[1][tid], c2 = lds.red[2][tid],
+                   d = lds.red[3][tid];
+      rows[(static_cast<int64_t>(mac) * n_groups + g) * kWgVis + tid] =
+          make_float2((a.x + b.x) + (c2.x + d.x), (a.y + b.y) + (c2.y + d.y));
+    }
+  }
+}
+
+// Per-slot coordinates: the visibility's, negated where w < 0; w - w0.
+__global__ void k_wg_slots(const int32_t* __restrict__ order, const double* __restrict__ w0s,
+                           const double* __restrict__ vu, const double* __restrict__ vv,
+                           const double* __restrict__ vw, int64_t n, double* __restrict__ su,
+                           double* __restrict__ sv, float* __restrict__ sdw) {
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  const int32_t o = order[t];
+  if (o < 0) {
+    su[t] = sv[t] = 0.0;
+    sdw[t] = 0.0f;
+    return;
+  }
+  const int32_t k = o >> 1;
+  const double sg = o & 1 ? -1.0 : 1.0;
+  su[t] = sg * vu[k];
+  sv[t] = sg * vv[k];
+  sdw[t] = static_cast<float>(sg * vw[k] - w0s[t / kWgVis]);
+}
+
+// Slot t's visibility: the macros' rows, conjugated where w < 0, and the other
+// segments' rows (indexed by visibility); gain, data and adjoint records as
+// k_fwd_reduce.
+__global__ void k_wg_fwd_reduce(const float2* __restrict__ part, int n_macros, int64_t n_slots,
+                                const int32_t* __restrict__ order,
+                                const float2* __restrict__ rows, int n_rows, int64_t n_vis,
+                                const float* __restrict__ gain, const float2* __restrict__ data,
+                                float2* __restrict__ out, float2* __restrict__ rres,
+                                const float* __restrict__ layerDs, int n_layers,
+                                float2* __restrict__ res) {
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (t >= n_slots) return;
+  const int32_t o = order[t];
+  if (o < 0) {
+    if (rres) res[t] = make_float2(0.0f, 0.0f);
+    return;
+  }
+  const int64_t k = o >> 1;
+  float2 acc = make_float2(0.0f, 0.0f);
+  strided_sum<float2>(part + t, n_macros, n_slots, acc);
+  if (o & 1) acc.y = -acc.y;
+  strided_sum<float2>(rows + k, n_rows, n_vis, acc);
+  const float gr = gain ? gain[2 * k] : 1.0f, gi = gain ? gain[2 * k + 1] : 0.0f;
+  float re = acc.x, im = acc.y;
+  if (gain) {
+    re = gr * acc.x - gi * acc.y;
+    im = gr * acc.y + gi * acc.x;
+  }
+  if (data) {
+    re -= data[k].x;
+    im -= data[k].y;
+  }
+  if (out) out[k] = make_float2(re, im);
+  if (rres) {
+    write_res<float>(rres, layerDs, n_layers, n_vis, 1, k, 0, gr, gi, re, im);
+    const float ci = gr * im - gi * re;
+    res[t] = make_float2(gr * re + gi * im, o & 1 ? -ci : ci);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// adjoint: per group and tile the sums over its visibilities
+//   T_XY(a,b) = sum_k X_k(a) Y_k(b) rho_k, X, Y in {cos, sin}, rho the residual
+//   times exp(2 pi i dw nuT),
+// and the same with x_k, x_k^2 / 2, x_k^3 / 6 in front (T1, T2, T3; series in
+// eta), are matrix products over k; then conj(C_0) and the series are applied
+// once per cell:
+//   Z = conj(C_0) (T + i eta T1 - eta^2 T2 - i eta^3 T3),
+//   G1 += Re Z_cc, G2 += Re Z_ss, G3 += Im Z_cs, G4 += Im Z_sc  (sl1m_grid.h).
+// ---------------------------------------------------------------------------
+
+constexpr int kAdjPitch = 36;  // uint32 (visibility pairs) per column of an operand, padded
+
+struct alignas(16) AdjLds {
+  // [part][cos, sin][column][visibility pair]
+  uint32_t col[kParts][2][kWgCols][kAdjPitch];
+  uint32_t hx[kWgVis / 2];              // x / 3 of every pair
+  double nu[4][4 * kWgSteps][64];       // by lane: column 16 c + lane % 16, row 4 (lane / 16) + i
+  float eta[4][4 * kWgSteps][64];
+  double la[4 * kWgRows], mb[kWgCols], u[kWgVis];
+  float2 rho[4][kWgVis];
+};
+
+struct AdjOp {  // row operand of 32 visibilities: re and im, hi and lo
+  Op8 rh, rl, ih, il;
+};
+
+// One kind X Y over the group, t = T and T1 (re, im each): `b`: this lane's column
+// operand (part stride `ps`, column tile stride `cs`, in uint4).
+template <int SER, bool FULL>
+__device__ __forceinline__ void adj_low(const AdjOp (&a)[2], const uint4* __restrict__ b, int ps,
+                                        int cs, f4_t (&t)[4][kWgSteps], int steps) {
+#pragma unroll
+  for (int c = 0; c < kWgSteps; ++c) {
+#pragma unroll
+    for (int o = 0; o < 4; ++o) t[o][c] = f4_t{0, 0, 0, 0};
+    if (!FULL && c >= steps) continue;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const uint4* q = b + c * cs + 4 * kb;
+      const h8_t bh = as_h8(q[0]), bl = as_h8(q[ps]), ch = as_h8(q[2 * ps]);
+      t[0][c] = mma(a[kb].rh.vec(), bh, t[0][c]);
+      t[1][c] = mma(a[kb].ih.vec(), bh, t[1][c]);
+      t[2][c] = mma(a[kb].rh.vec(), ch, t[2][c]);
+      t[3][c] = mma(a[kb].ih.vec(), ch, t[3][c]);
+      t[0][c] = mma(a[kb].rh.vec(), bl, t[0][c]);
+      t[1][c] = mma(a[kb].ih.vec(), bl, t[1][c]);
+      if constexpr (SER >= 2) {
+        const h8_t cl = as_h8(q[3 * ps]);
+        t[2][c] = mma(a[kb].rh.vec(), cl, t[2][c]);
+        t[3][c] = mma(a[kb].ih.vec(), cl, t[3][c]);
+      }
+      t[0][c] = mma(a[kb].rl.vec(), bh, t[0][c]);
+      t[1][c] = mma(a[kb].il.vec(), bh, t[1][c]);
+      if constexpr (SER >= 2) {
+        t[2][c] = mma(a[kb].rl.vec(), ch, t[2][c]);
+        t[3][c] = mma(a[kb].il.vec(), ch, t[3][c]);
+      }
+    }
+  }
+}
+
+// The same, t = T2 and (SER 3) T3; `hx`: x / 3 of this lane's visibilities.
+template <int SER, bool FULL>
+__device__ __forceinline__ void adj_high(const AdjOp (&a)[2], const uint4* __restrict__ b, int ps,
+                                         int cs, const uint4* __restrict__ hx,
+                                         f4_t (&t)[4][kWgSteps], int steps) {
+#pragma unroll
+  for (int c = 0; c < kWgSteps; ++c) {
+#pragma unroll
+    for (int o = 0; o < 4; ++o) t[o][c] = f4_t{0, 0, 0, 0};
+    if (!FULL && c >= steps) continue;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const h8_t sh = as_h8(b[c * cs + 4 * kb + 4 * ps]);
+      t[0][c] = mma(a[kb].rh.vec(), sh, t[0][c]);
+      t[1][c] = mma(a[kb].ih.vec(), sh, t[1][c]);
+      if constexpr (SER == 3) {
+        const h8_t th = sh * as_h8(hx[4 * kb]);  // x^3 / 6
+        t[2][c] = mma(a[kb].rh.vec(), th, t[2][c]);
+        t[3][c] = mma(a[kb].ih.vec(), th, t[3][c]);
+      }
+    }
+  }
+}
+
+// G += Re (IM: Im) of conj(C) (T + i eta T1), or of conj(C) (-eta^2) (T2 + i eta T3)
+// (HIGH; T3 there with SER 3 only).
+template <int SER, bool IM, bool HIGH>
+__device__ __forceinline__ void adj_fold(const f4_t (&t)[4][kWgSteps],
+                                         const float (&cc)[kWgSteps][4],
+                                         const float (&cs)[kWgSteps][4],
+                                         const float* __restrict__ eta, float (&g)[kWgSteps][4]) {
+#pragma unroll
+  for (int c = 0; c < kWgSteps; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float e = eta[64 * (4 * c + i)];
+      float zr = t[0][c][i], zi = t[1][c][i];
+      if (!HIGH || SER == 3) {
+        zr = fmaf(-e, t[3][c][i], zr);
+        zi = fmaf(e, t[2][c][i], zi);
+      }
+      if constexpr (HIGH) {
+        const float e2 = -e * e;
+        zr *= e2;
+        zi *= e2;
+      }
+      if constexpr (IM) {
+        g[c][i] = fmaf(cc[c][i], zi, g[c][i]);
+        g[c][i] = fmaf(cs[c][i], zr, g[c][i]);
+      } else {
+        g[c][i] = fmaf(cc[c][i], zr, g[c][i]);
+        g[c][i] = fmaf(-cs[c][i], zi, g[c][i]);
+      }
+      // the sum is formed here: sunk below the next kinds it would keep their
+      // accumulators and this one's alive together (256 registers and spills)
+      asm volatile("" : "+v"(g[c][i]));
+    }
+}
+
+// Row operands of the group from this lane's row phasor components (cos or sin)
+// of its 16 visibilities.
+__device__ __forceinline__ void adj_rows(const float (&ph)[2][8], const float2* __restrict__ rho,
+                                         AdjOp (&a)[2]) {
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float2 r0 = rho[32 * kb + 2 * j], r1 = rho[32 * kb + 2 * j + 1];
+      const float p0 = ph[kb][2 * j], p1 = ph[kb][2 * j + 1];
+      split2(p0 * r0.x, p1 * r1.x, a[kb].rh.v[j], a[kb].rl.v[j]);
+      split2(p0 * r0.y, p1 * r1.y, a[kb].ih.v[j], a[kb].il.v[j]);
+    }
+}
+
+template <int SER, bool FULL, bool IM>
+__device__ __forceinline__ void adj_kind(const AdjOp (&a)[2], const uint4* __restrict__ b,
+                                         const uint4* __restrict__ hx,
+                                         const float (&cc)[kWgSteps][4],
+                                         const float (&cs)[kWgSteps][4],
+                                         const float* __restrict__ eta, int steps,
+                                         float (&g)[kWgSteps][4]) {
+  constexpr int kPart = 2 * kWgCols * kAdjPitch / 4, kTile = 16 * kAdjPitch / 4;
+  f4_t t[4][kWgSteps];
+  adj_low<SER, FULL>(a, b, kPart, kTile, t, steps);
+  adj_fold<SER, IM, false>(t, cc, cs, eta, g);
+  if constexpr (SER > 0) {
+    adj_high<SER, FULL>(a, b, kPart, kTile, hx, t, steps);
+    adj_fold<SER, IM, true>(t, cc, cs, eta, g);
+  }
+}
+
+template <int SER, bool FULL>
+__device__ __forceinline__ void adj_group(const float (&pc)[2][8], const float (&ps)[2][8],
+                                          const float2* __restrict__ rho,
+                                          const uint4* __restrict__ b, const uint4* __restrict__ hx,
+                                          const float (&cc)[kWgSteps][4],
+                                          const float (&cs)[kWgSteps][4],
+                                          const float* __restrict__ eta, int steps,
+                                          float (&g)[4][kWgSteps][4]) {
+  constexpr int kType = kWgCols * kAdjPitch / 4;
+  AdjOp a[2];
+  adj_rows(pc, rho, a);
+  adj_kind<SER, FULL, false>(a, b, hx, cc, cs, eta, steps, g[0]);
+  adj_kind<SER, FULL, true>(a, b + kType, hx, cc, cs, eta, steps, g[2]);
+  adj_rows(ps, rho, a);
+  adj_kind<SER, FULL, false>(a, b + kType, hx, cc, cs, eta, steps, g[1]);
+  adj_kind<SER, FULL, true>(a, b, hx, cc, cs, eta, steps, g[3]);
+}
+
+// Adjoint: block (groups x, x + gridDim.x, ..; macro y); part[x][cell] = (G1, G2,
+// G3, G4) of its groups.
+__global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
+    const WgMacro* __restrict__ macros, const float2* __restrict__ res,
+    const double* __restrict__ nu, const float* __restrict__ eta, const double* __restrict__ la,
+    const double* __restrict__ mb, const double* __restrict__ su, const double* __restrict__ sv,
+    const float* __restrict__ sdw, const double* __restrict__ w0s, const float* __restrict__ hs,
+    int n_groups, int64_t cells, float4* __restrict__ part) {
+  __shared__ AdjLds lds;
+  const ConstPtr<WgMacro> cm = as_const(macros) + blockIdx.y;
+  const int sets = cm->sets, steps = cm->steps;
+  const float eta_max = cm->eta_max, xs = cm->xs;
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool active = wv < sets;
+  const float nu_t = cm->nu_t[wv];
+  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
+  if (tid < 4 * kWgRows) lds.la[tid] = la[cm->a_off + tid];
+  if (tid < kWgCols) lds.mb[tid] = mb[cm->b_off + tid];
+  // this lane's cells: column 16 c + r16, rows 4 quad + i
+  float g[4][kWgSteps][4];
+#pragma unroll
+  for (int c = 0; c < kWgSteps; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t q = cell0 + (16 * c + r16) * kWgRows + quad * 4 + i;
+      lds.nu[wv][4 * c + i][lane] = nu[q];
+      lds.eta[wv][4 * c + i][lane] = eta[q];
+#pragma unroll
+      for (int o = 0; o < 4; ++o) g[o][c][i] = 0.0f;
+    }
+  const int g0 = static_cast<int>(blockIdx.x), gs = static_cast<int>(gridDim.x);
+  const ConstPtr<double> cw0 = as_const(w0s);
+  const ConstPtr<float> chs = as_const(hs);
+  const int vp = tid & 31, c8 = tid >> 5;  // column operands: visibility pair, column
+  // each group's coordinates and residuals are loaded during the group before it
+  double2 vn = make_double2(0.0, 0.0);
+  double un = 0.0, w0n = 0.0;
+  float2 dwp = make_float2(0.0f, 0.0f), rn = make_float2(0.0f, 0.0f);
+  float dwn = 0.0f, hn = 0.0f;
+  auto load = [&](int gi) {
+    vn = reinterpret_cast<const double2*>(sv)[gi * (kWgVis / 2) + vp];
+    dwp = reinterpret_cast<const float2*>(sdw)[gi * (kWgVis / 2) + vp];
+    un = su[gi * kWgVis + lane];
+    dwn = sdw[gi * kWgVis + lane];
+    rn = res[gi * kWgVis + lane];
+    w0n = cw0[gi];
+    hn = chs[gi];
+  };
+  if (g0 < n_groups) load(g0);
+  __syncthreads();
+  for (int gi = g0; gi < n_groups; gi += gs) {
+    const double w0 = w0n;
+    const float xm = kTwoPi * hn * eta_max;
+    const int ser = xm <= kWgXN ? 0 : xm <= kWgXM ? 1 : xm <= kWgXW ? 2 : 3;
+    // residuals times the tile's factor, scaled into float16's range
+    const float th = dwn * nu_t;
+    const float ct = __builtin_amdgcn_cosf(th), st = __builtin_amdgcn_sinf(th);
+    const float rr = fmaf(ct, rn.x, -st * rn.y), ri = fmaf(ct, rn.y, st * rn.x);
+    const float am = fmaxf(fabsf(rr), fabsf(ri));
+    const float sc = op_scale(wave_max(rr != rr || ri != ri ? __builtin_inff() : am));
+    lds.rho[wv][lane] = make_float2(rr * sc, ri * sc);
+    const float inv = 1.0f / sc;
+    if (wv == 0) lds.u[lane] = un;
+    const double2 v = vn;
+    const float x0 = xs * dwp.x, x1 = xs * dwp.y;
+    if (tid < 32) lds.hx[vp] = as_u32(__builtin_convertvector((f2_t{0.33333334f * x0, 0.33333334f * x1}), h2_t));
+    load(gi + gs < n_groups ? gi + gs : gi);
+    for (int c = c8; c < 16 * steps; c += 8) {
+      float a0, b0, a1, b1;
+      const double m = lds.mb[c];
+      phasor(fma(v.x, m, kMagic), a0, b0);
+      phasor(fma(v.y, m, kMagic), a1, b1);
+      h2_t hi, lo;
+      split2(a0, a1, hi, lo);
+      lds.col[0][0][c][vp] = as_u32(hi);
+      lds.col[1][0][c][vp] = as_u32(lo);
+      split2(b0, b1, hi, lo);
+      lds.col[0][1][c][vp] = as_u32(hi);
+      lds.col[1][1][c][vp] = as_u32(lo);
+      a0 *= x0;
+      a1 *= x1;
+      b0 *= x0;
+      b1 *= x1;
+      if (ser > 0) {
+        const float h0 = 0.5f * x0, h1 = 0.5f * x1;
+        lds.col[4][0][c][vp] = as_u32(__builtin_convertvector((f2_t{h0 * a0, h1 * a1}), h2_t));
+        lds.col[4][1][c][vp] = as_u32(__builtin_convertvector((f2_t{h0 * b0, h1 * b1}), h2_t));
+      }
+      if (ser >= 2) {
+        split2(a0, a1, hi, lo);
+        lds.col[2][0][c][vp] = as_u32(hi);
+        lds.col[3][0][c][vp] = as_u32(lo);
+        split2(b0, b1, hi, lo);
+        lds.col[2][1][c][vp] = as_u32(hi);
+        lds.col[3][1][c][vp] = as_u32(lo);
+      } else {
+        lds.col[2][0][c][vp] = as_u32(__builtin_convertvector((f2_t{a0, a1}), h2_t));
+        lds.col[2][1][c][vp] = as_u32(__builtin_convertvector((f2_t{b0, b1}), h2_t));
+      }
+    }
+    __syncthreads();
+    if (active) {
+      float pc[2][8], ps[2][8];
+      const double l = lds.la[wv * kWgRows + r16];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          phasor(fma(lds.u[32 * kb + 8 * quad + j], l, kMagic), pc[kb][j], ps[kb][j]);
+      float cc[kWgSteps][4], cs[kWgSteps][4];
+#pragma unroll
+      for (int c = 0; c < kWgSteps; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          phasor_fine(fma(w0, lds.nu[wv][4 * c + i][lane], kMagicFine), cc[c][i], cs[c][i]);
+          cc[c][i] *= inv;
+          cs[c][i] *= inv;
+        }
+      const uint4* b = reinterpret_cast<const uint4*>(&lds.col[0][0][r16][4 * quad]);
+      const uint4* hx = reinterpret_cast<const uint4*>(&lds.hx[4 * quad]);
+      const float2* rho = &lds.rho[wv][8 * quad];
+      if (ser == 0 && steps == kWgSteps)
+        adj_group<0, true>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+      else if (ser == 0)
+        adj_group<0, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+      else if (ser == 1)
+        adj_group<1, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+      else if (ser == 2)
+        adj_group<2, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+      else
+        adj_group<3, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+    }
+    __syncthreads();
+  }
+  if (!active) return;
+#pragma unroll
+  for (int c = 0; c < kWgSteps; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      part[blockIdx.x * cells + cell0 + (16 * c + r16) * kWgRows + quad * 4 + i] =
+          make_float4(g[0][c][i], g[1][c][i], g[2][c][i], g[3][c][i]);
+}
+
+// Chunk sums of every cell, combined into its sign slots (row 0 of the adjoint
+// partials).
+__global__ __launch_bounds__(kBlock) void k_wg_adj_reduce(const float4* __restrict__ part,
+                                                          int n_chunks, int64_t cells,
+                                                          const int4* __restrict__ slot,
+                                                          float* __restrict__ out) {
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+  if (q >= cells) return;
+  const int4 s = slot[q];
+  if (s.x < 0 && s.y < 0 && s.z < 0 && s.w < 0) return;
+  // four running sums: shorter chains of float32 roundings, four loads in flight
+  float4 a[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (int c = 0; c < n_chunks; c += 4)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (c + i < n_chunks) {
+        const float4 v = part[(c + i) * cells + q];
+        a[i].x += v.x;
+        a[i].y += v.y;
+        a[i].z += v.z;
+        a[i].w += v.w;
+      }
+  const float g1 = (a[0].x + a[1].x) + (a[2].x + a[3].x);
+  const float g2 = (a[0].y + a[1].y) + (a[2].y + a[3].y);
+  const float g3 = (a[0].z + a[1].z) + (a[2].z + a[3].z);
+  const float g4 = (a[0].w + a[1].w) + (a[2].w + a[3].w);
+  if (s.x >= 0) out[s.x] = g1 - g2 - g3 - g4;
+  if (s.y >= 0) out[s.y] = g1 + g2 - g3 + g4;
+  if (s.z >= 0) out[s.z] = g1 + g2 + g3 - g4;
+  if (s.w >= 0) out[s.w] = g1 - g2 + g3 + g4;
+}
+
+// Adjoint records per slot from the caller's residual (k_adj_prep by slot).
+__global__ void k_wg_adj_prep(const float2* __restrict__ r, const int32_t* __restrict__ order,
+                              int64_t n_slots, int64_t n_vis, const float* __restrict__ gain,
+                              float2* __restrict__ res, float2* __restrict__ rres,
+                              const float* __restrict__ layerDs, int n_layers) {
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (t >= n_slots) return;
+  const int32_t o = order[t];
+  float2 z = make_float2(0.0f, 0.0f);
+  if (o >= 0) {
+    const int64_t k = o >> 1;
+    const float gr = gain ? gain[2 * k] : 1.0f, gi = gain ? gain[2 * k + 1] : 0.0f;
+    const float2 v = r[k];
+    write_res<float>(rres, layerDs, n_layers, n_vis, 1, k, 0, gr, gi, v.x, v.y);
+    const float ci = gr * v.y - gi * v.x;
+    z = make_float2(gr * v.x + gi * v.y, o & 1 ? -ci : ci);
+  }
+  res[t] = z;
+}
+
+
+inline unsigned blocks1(int64_t n) { return static_cast<unsigned>((n + kBlock - 1) / kBlock); }
+
+}  // namespace
+
+hipError_t launch_wg_setup(sl1m_plan* p, hipStream_t st) {
+  const int64_t n = static_cast<int64_t>(p->wg_groups) * kWgVis;
+  if (!p->wg || n == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_wg_slots, dim3(blocks1(n)), dim3(kBlock), 0, st, p->wg_order, p->wg_w0,
+                     p->vu, p->vv, p->vw, n, p->wg_su, p->wg_sv, p->wg_dw);
+  return hipGetLastError();
+}
+
+hipError_t launch_wg_forward(sl1m_plan* p, const void* xp, hipStream_t st) {
+  return timed(p, T_GRID_FWD_DELTA, st, [&] {
+    hipLaunchKernelGGL(k_wg_fwd,
+                       dim3(static_cast<unsigned>(p->wg_chunks), static_cast<unsigned>(p->wg_macros)),
+                       dim3(kBlock), 0, st, p->wg_mac, static_cast<const float*>(xp),
+                       static_cast<const float*>(p->pscale),
+                       reinterpret_cast<const int4*>(p->wg_slot), p->wg_nu, p->wg_eta, p->wg_la,
+                       p->wg_mb, p->wg_su, p->wg_sv, p->wg_dw, p->wg_w0, p->wg_h, p->wg_count,
+                       p->wg_groups, static_cast<float2*>(p->fpart));
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, bool recs,
+                                    hipStream_t st) {
+  const int64_t slots = static_cast<int64_t>(p->wg_groups) * kWgVis;
+  const int nfc = p->grid_segs[p->wg_seg].nfc;
+  const float2* rows = static_cast<const float2*>(fwd_rows1(p)) + nfc * p->n_vis;
+  hipLaunchKernelGGL(k_wg_fwd_reduce, dim3(blocks1(slots)), dim3(kBlock), 0, st,
+                     static_cast<const float2*>(p->fpart), p->wg_macros, slots, p->wg_order, rows,
+                     forward_rows(p, 1) - nfc, p->n_vis, static_cast<const float*>(p->vgain),
+                     static_cast<const float2*>(data), static_cast<float2*>(out),
+                     recs ? static_cast<float2*>(p->rres) : nullptr,
+                     static_cast<const float*>(p->layerDs), p->n_layers, p->wg_res);
+  return hipGetLastError();
+}
+
+hipError_t launch_wg_adjoint_prep(sl1m_plan* p, const void* r, hipStream_t st) {
+  const int64_t slots = static_cast<int64_t>(p->wg_groups) * kWgVis;
+  hipLaunchKernelGGL(k_wg_adj_prep, dim3(blocks1(slots)), dim3(kBlock), 0, st,
+                     static_cast<const float2*>(r), p->wg_order, slots, p->n_vis,
+                     static_cast<const float*>(p->vgain), p->wg_res,
+                     static_cast<float2*>(p->rres), static_cast<const float*>(p->layerDs),
+                     p->n_layers);
+  return hipGetLastError();
+}
+
+hipError_t launch_wg_adjoint(sl1m_plan* p, hipStream_t st) {
+  hipError_t e = timed(p, T_GRID_ADJ_DELTA, st, [&] {
+    hipLaunchKernelGGL(k_wg_adj,
+                       dim3(static_cast<unsigned>(p->wg_chunks), static_cast<unsigned>(p->wg_macros)),
+                       dim3(kBlock), 0, st, p->wg_mac, p->wg_res, p->wg_nu, p->wg_eta, p->wg_la,
+                       p->wg_mb, p->wg_su, p->wg_sv, p->wg_dw, p->wg_w0, p->wg_h, p->wg_groups,
+                       p->wg_cells, p->wg_part);
+    return hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_wg_adj_reduce, dim3(blocks1(p->wg_cells)), dim3(kBlock), 0, st, p->wg_part,
+                     p->wg_chunks, p->wg_cells, reinterpret_cast<const int4*>(p->wg_slot),
+                     static_cast<float*>(p->apart));
+  return hipGetLastError();
+}
+
+}  // namespace sl1m

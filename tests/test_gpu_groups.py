@@ -1,0 +1,102 @@
+"""Group evaluation of delta grids (visibilities in groups of nearly one w, the sums on
+the matrix cores): operators against the FP64 oracle at the FP32 operator tolerance and
+the element-wise bound (tests/elementwise.py), at the sizes where its tiles (16 |l|
+values by 32 |m| values, four tiles to a block), its groups (64 visibilities, tiles of
+16) and its series (argument classes set by the spread of w in a group) end.
+
+A plan of one side takes it, a plan of two sides the grid evaluation for the same calls,
+so results that differ in their bits show that it ran.
+"""
+import numpy as np
+import pytest
+
+import elementwise as E
+import oracle as O
+from paper_1310_2078_amd import sl1m
+from paper_1310_2078_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5
+
+
+def rel(a, b):
+    return float(np.linalg.norm(np.asarray(a) - np.asarray(b)) / np.linalg.norm(np.asarray(b)))
+
+
+def _grid(nl, nm, d):
+    L, M = np.meshgrid((np.arange(nl) - nl // 2) * d, (np.arange(nm) - nm // 2) * d)
+    return L.ravel(), M.ravel()
+
+
+# name: |l| x |m| pixels, spacing, visibilities, w spread, gains, pixels kept (fraction)
+CASES = {
+    "one_group": (40, 40, 2e-3, 64, 1.0, False, 1.0),          # a full group, narrow
+    "one_more": (40, 40, 2e-3, 65, 1.0, False, 1.0),           # and a group of one
+    "odd_17_tiles": (33, 33, 2e-3, 1023, 2.0, False, 1.0),     # 17 x 17 cells: padded tiles
+    "exact_tiles": (63, 127, 1e-3, 3200, 5.0, True, 1.0),      # 32 x 64 cells: no padding
+    "columns_129": (40, 256, 1e-3, 2500, 10.0, False, 1.0),    # nine steps, a lone one
+    "rows_five_sets": (150, 34, 1.5e-3, 2111, 10.0, True, 1.0),
+    "wide_field": (48, 48, 6e-3, 6000, 30.0, True, 1.0),       # split first order, groups cut
+    "third_order": (40, 40, 6e-3, 3001, 40.0, False, 1.0),
+    "w_zero": (36, 36, 2e-3, 1500, 0.0, False, 1.0),           # one w: no series
+    "cut_off": (70, 70, 1e-3, 2700, 20.0, True, 0.55),         # truncated mid-row, shuffled
+}
+
+
+def _case(name):
+    nl, nm, d, nv, ws, gains, keep = CASES[name]
+    seed = 40 + sorted(CASES).index(name)
+    wl = W.small_random(seed, 10, nv, uv_radius=700.0, w_sigma=ws, with_gains=gains)
+    l, m = _grid(nl, nm, d)
+    rng = np.random.default_rng(seed)
+    if keep < 1.0:
+        n = int(keep * l.size)
+        sel = rng.permutation(n)
+        l, m = l[:n][sel], m[:n][sel]
+    wl.l, wl.m = l, m
+    wl.sigma, wl.kind = np.zeros(l.size), np.zeros(l.size, np.uint8)
+    wl.x_true = None
+    x = rng.standard_normal(l.size)
+    r = rng.standard_normal(nv) + 1j * rng.standard_normal(nv)
+    return wl, x, r
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_group_operators(name):
+    print(f"[case] groups {name}", flush=True)
+    wl, x, r = _case(name)
+    p = O.Problem.from_workload(wl)
+    Vo, go = O.forward(p, x), O.adjoint(p, r)
+    plan = sl1m.Plan.from_workload(wl)
+    other = sl1m.Plan.from_workload(wl, max_rhs=2, grid="require")
+    V, g = plan.forward(x).cpu().numpy(), plan.adjoint(r).cpu().numpy()
+    V2, g2 = other.forward(x).cpu().numpy(), other.adjoint(r).cpu().numpy()
+    wf = E.worst_ratio(V, Vo, E.abs_forward_rows(p, x), wl.n_pix)
+    wa = E.worst_ratio(g, go, E.abs_adjoint_cols(p, r), wl.n_vis)
+    print(f"    forward {rel(V, Vo):.3e} adjoint {rel(g, go):.3e} element-wise {wf:.3e} {wa:.3e} "
+          f"grid evaluation {rel(V2, Vo):.3e} {rel(g2, go):.3e}", flush=True)
+    assert not np.array_equal(V, V2) and not np.array_equal(g, g2), "the groups did not run"
+    assert rel(V, Vo) <= TOL and rel(g, go) <= TOL
+    assert wf <= 1.0 and wa <= 1.0
+    # the same bits again, whatever ran in between
+    plan.forward(2.0 * x), plan.adjoint(r.conj())
+    assert np.array_equal(plan.forward(x).cpu().numpy(), V)
+    assert np.array_equal(plan.adjoint(r).cpu().numpy(), g)
+
+
+def test_scales_zeros_and_non_finite():
+    """Operands far from 1 are scaled by powers of two, exactly; zero inputs give zero;
+    a NaN reaches every output."""
+    wl, x, r = _case("odd_17_tiles")
+    plan = sl1m.Plan.from_workload(wl)
+    V, g = plan.forward(x).cpu().numpy(), plan.adjoint(r).cpu().numpy()
+    for s in (2.0 ** -60, 2.0 ** 60):
+        assert np.array_equal(plan.forward(x * s).cpu().numpy(), V * np.float32(s))
+        assert np.array_equal(plan.adjoint(r * s).cpu().numpy(), g * np.float32(s))
+    assert not plan.forward(0 * x).cpu().numpy().any()
+    assert not plan.adjoint(0 * r).cpu().numpy().any()
+    x[5] = np.nan
+    r[7] = np.nan
+    assert not np.isfinite(plan.forward(x).cpu().numpy()).any()
+    assert not np.isfinite(plan.adjoint(r).cpu().numpy()).any()
