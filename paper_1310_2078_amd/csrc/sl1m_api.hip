@@ -54,9 +54,9 @@ struct Analysis {
   int64_t grid_pairs = 0;      // pair records of all square segments
   int grid_vtiles = 0, grid_frows = 0;
   std::vector<Chunk> fd1, fg1, pd1, pg1;
-  // group evaluation of the delta grid segment (sl1m_wgroup.h)
-  bool wg = false;
-  int wg_seg = 0;
+  // group evaluation of the first wg_n grid segments (sl1m_wgroup.h); their pixels
+  // follow one another
+  int wg_n = 0;
   int64_t wg_cap = 0;          // visibility groups the workspace holds
   WgPlan wgp;
 };
@@ -163,32 +163,31 @@ bool analyze_grid(Analysis& a, int si, const std::vector<double>& L, const std::
   return true;
 }
 
-size_t layout_bytes(const Analysis& a);
+size_t plan_total(const Analysis& a);
 
-// Group evaluation of the delta grid segment (plans of one side: the grid
+// Group evaluation of the grid segments (plans of one side: the grid
 // evaluation shares its phasors among several, and a side on its own then gives
-// the same bits as among others): its tiles, unless they hold more
-// than four times the segment's cells with padding.  A plan that fits the no-allocation
+// the same bits as among others): each segment's tiles, unless they hold more
+// than four times its cells with padding.  A plan that fits the no-allocation
 // scratch without the group tables but not with them keeps the grid evaluation,
 // so that what sl1m_forward_noalloc takes does not shrink.
 void choose_groups(Analysis& a) {
-  for (size_t i = 0; i < a.gsegs.size(); ++i) {
-    const GridSeg& g = a.gsegs[i];
-    if (g.kind != SL1M_PIX_DELTA) continue;
-    WgPlan t;
+  const size_t without = plan_total(a);
+  int n = 0;
+  for (const GridSeg& g : a.gsegs) {
+    const int64_t padded = wg_padded(g);
+    if (g.seg != a.gsegs[0].seg + n || padded > 4 * static_cast<int64_t>(g.na) * g.nb) break;
+    if (static_cast<int64_t>(a.wgp.nu.size()) + 2 * padded > INT32_MAX) break;
     wg_build_tiles(g, a.grid_la.data() + g.la_off, a.grid_mb.data() + g.mb_off,
-                   a.grid_c3.data() + g.cell_off, a.grid_slot.data() + 4 * g.cell_off, t);
-    if (t.padded > 4 * static_cast<int64_t>(g.na) * g.nb ||
-        t.nu.size() > static_cast<size_t>(INT32_MAX))
-      continue;
-    const size_t without = layout_bytes(a);
-    a.wgp = std::move(t);
-    a.wg_cap = wg_group_cap(a.n_vis);
-    a.wg_seg = static_cast<int>(i);
-    a.wg = true;
-    if (without <= SL1M_NOALLOC_SCRATCH_BYTES && layout_bytes(a) > SL1M_NOALLOC_SCRATCH_BYTES)
-      a.wg = false;
+                   (g.kind == SL1M_PIX_DELTA ? a.grid_c3 : a.grid_c4).data() + g.cell_off,
+                   a.grid_slot.data() + 4 * g.cell_off, a.wgp);
+    ++n;
   }
+  if (n == 0) return;
+  a.wg_cap = wg_group_cap(a.n_vis);
+  a.wg_n = n;
+  if (without <= SL1M_NOALLOC_SCRATCH_BYTES && plan_total(a) > SL1M_NOALLOC_SCRATCH_BYTES)
+    a.wg_n = 0;
 }
 
 // `groups`: whether the plan may use the group evaluation (the server's plans run
@@ -553,10 +552,11 @@ struct Layout {
       grid_mb, grid_c3, grid_c4, grid_slot, grid_rec, grid_fc, grid_pb, grid_segs, grid_gb,
       grid_prec, grid_precm, mx, mr, mred, grid_mfma_b, grid_mfma_nu, phl, vhl,
       wg_mac, wg_la, wg_mb, wg_nu, wg_eta, wg_slot, wg_order, wg_count, wg_su, wg_sv, wg_dw, wg_w0,
-      wg_h, wg_part, wg_res, total;
+      wg_h, wg_part, wg_res, wg_recg, total;
 };
 
-Layout layout(const Analysis& a) {
+// `wg_n`: grid segments in the group evaluation
+Layout layout(const Analysis& a, int wg_n) {
   Layout L{};
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -594,20 +594,22 @@ Layout layout(const Analysis& a) {
                                    a.pg1.size()));
   const size_t grid_rows = a.grid ? a.grid_fc.size() + a.fd1.size() + a.fg1.size() : 0;
   // group evaluation: a row of slots per macro in place of the segment's rows
-  const size_t slots = a.wg ? static_cast<size_t>(a.wg_cap) * kWgVis : 0;
-  const size_t wg_rows = a.wg ? a.wgp.macros.size() * slots +
-                                    (grid_rows - static_cast<size_t>(a.gsegs[a.wg_seg].nfc)) * nv
-                              : 0;
+  const size_t slots = wg_n ? static_cast<size_t>(a.wg_cap) * kWgVis : 0;
+  size_t wg_rows = grid_rows * nv, wg_macros = 0, wg_part = 0;
+  for (int i = 0; i < wg_n; ++i) {
+    const WgSeg& s = a.wgp.segs[i];
+    wg_rows -= static_cast<size_t>(a.gsegs[i].nfc) * nv;
+    wg_macros += static_cast<size_t>(s.macros);
+    wg_part = std::max(wg_part, 16 * static_cast<size_t>(s.cells) * wg_chunk_cap(s.macros));
+  }
+  wg_rows += wg_macros * slots;
   L.fpart = take(2 * rb *
                  std::max(std::max({nfc * nr, grid_rows * std::max<size_t>(1, a.grid_multi),
                                     static_cast<size_t>(a.n_mfchunks) * nr}) * nv,
-                          wg_rows));
+                          wg_n ? wg_rows : 0));
   // the group evaluation's chunk sums stand behind row 0 (which takes their
   // total) where no other segment uses the rows, else in a region of their own
-  const size_t wg_part = a.wg ? 16 * a.wgp.nu.size() *
-                                    wg_chunk_cap(static_cast<int>(a.wgp.macros.size()))
-                              : 0;
-  const bool wg_alias = a.wg && a.segs.size() == 1;
+  const bool wg_alias = wg_n > 0 && wg_n == static_cast<int>(a.segs.size());
   L.apart = take(std::max(rb * static_cast<size_t>(a.n_achunks) * np * nr,
                           wg_alias ? align_up(rb * np) + wg_part : 0));
   if (wg_alias) L.wg_part = L.apart + align_up(rb * np);
@@ -643,7 +645,7 @@ Layout layout(const Analysis& a) {
   L.grid_mfma_nu = take(a.grid_mfma ? 8 * pairs : 0);
   L.phl = take(hl ? sizeof(HLRec) * static_cast<size_t>(a.n_pix) : 0);
   L.vhl = take(hl ? sizeof(HLRec) * static_cast<size_t>(a.n_vis) : 0);
-  if (a.wg) {
+  if (wg_n) {
     const WgPlan& t = a.wgp;
     const size_t wc = t.nu.size();
     L.wg_mac = take(sizeof(WgMacro) * t.macros.size());
@@ -659,6 +661,7 @@ Layout layout(const Analysis& a) {
     L.wg_dw = take(4 * slots);
     L.wg_w0 = take(8 * static_cast<size_t>(a.wg_cap));
     L.wg_res = take(8 * slots);
+    L.wg_recg = take(sizeof(WgVisG) * slots * a.layer_sigma.size());
     if (!wg_alias) L.wg_part = take(wg_part);
     L.wg_h = take(4 * static_cast<size_t>(a.wg_cap));
   }
@@ -666,7 +669,20 @@ Layout layout(const Analysis& a) {
   return L;
 }
 
-size_t layout_bytes(const Analysis& a) { return layout(a).total; }
+// A plan whose visibilities make too many groups for n of its segments (Gaussian
+// layers take narrower ones) tries the first, a delta grid's, alone, then goes without.
+int fewer_groups(const Analysis& a, int n) {
+  return n > 1 && a.gsegs[0].kind == SL1M_PIX_DELTA ? 1 : 0;
+}
+
+size_t plan_total(const Analysis& a) {
+  size_t bytes = layout(a, a.wg_n).total;
+  for (int n = a.wg_n; n > 0;) {
+    n = fewer_groups(a, n);
+    bytes = std::max(bytes, layout(a, n).total);
+  }
+  return bytes;
+}
 
 inline hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
@@ -815,7 +831,7 @@ sl1m_status plan_bytes(const sl1m_problem* problem, bool groups, size_t* bytes) 
     Analysis a;
     sl1m_status s = analyze(problem, a, groups);
     if (s) return s;
-    *bytes = layout(a).total;
+    *bytes = plan_total(a);
     return SL1M_OK;
   } catch (const std::bad_alloc&) {
     return set_error(SL1M_ENOMEM, "host allocation failed");
@@ -854,9 +870,8 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
     Analysis a;
     sl1m_status s = analyze(pr, a, groups);
     if (s) return s;
-    const Layout L = layout(a);
     if (!workspace) return set_error(SL1M_EINVAL, "workspace is NULL");
-    if (workspace_bytes < L.total)
+    if (workspace_bytes < plan_total(a))
       return set_error(SL1M_ENOMEM, "workspace smaller than sl1m_plan_workspace_bytes()");
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0)
       return set_error(SL1M_EINVAL, "workspace must be 256-byte aligned");
@@ -864,13 +879,20 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
     int device = 0;
     SL1M_HIP(hipGetDevice(&device), "get device");
     WgGroups wgg;
-    if (a.wg) {  // the visibilities by |w|; too many groups: the grid evaluation
+    if (a.wg_n) {  // the visibilities by |w|
       std::vector<double> w(a.n_vis);
       SL1M_HIP(hipMemcpyAsync(w.data(), pr->w, a.n_vis * sizeof(double), hipMemcpyDeviceToHost, st),
                "read w");
       SL1M_HIP(hipStreamSynchronize(st), "read w");
-      a.wg = wg_build_groups(w, a.wgp.eta_max, a.wg_cap, wgg);
+      while (a.wg_n) {
+        wgg = WgGroups();
+        float width = 0.0f;
+        for (int i = 0; i < a.wg_n; ++i) width = std::max(width, a.wgp.segs[i].width);
+        if (wg_build_groups(w, width, a.wg_cap, wgg)) break;
+        a.wg_n = fewer_groups(a, a.wg_n);
+      }
     }
+    const Layout L = layout(a, a.wg_n);
     sl1m_plan* p = new sl1m_plan();
     p->device = device;
     p->n_pix = a.n_pix;
@@ -972,19 +994,21 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       p->d_grid_fchunks = reinterpret_cast<GridChunk*>(w + L.grid_fc);
       p->d_grid_pblocks = reinterpret_cast<GridPairBlock*>(w + L.grid_pb);
       p->d_grid_segs = reinterpret_cast<GridSeg*>(w + L.grid_segs);
-      p->d_grid_gblocks = reinterpret_cast<int2*>(w + L.grid_gb);
-      p->grid_gblocks = static_cast<int>(a.grid_gb.size());
+      // Gaussian adjoint blocks of the segments outside the groups
+      int first = 0;
+      while (first < static_cast<int>(a.grid_gb.size()) && a.grid_gb[first].x < a.wg_n) ++first;
+      p->d_grid_gblocks = reinterpret_cast<int2*>(w + L.grid_gb) + first;
+      p->grid_gblocks = static_cast<int>(a.grid_gb.size()) - first;
       p->grid_prec = reinterpret_cast<GridPairRec*>(w + L.grid_prec);
       p->grid_precm = a.grid_multi ? reinterpret_cast<float*>(w + L.grid_precm) : nullptr;
     }
 
-    if (a.wg) {
-      p->wg = true;
-      p->wg_seg = a.wg_seg;
-      p->wg_macros = static_cast<int>(a.wgp.macros.size());
+    if (a.wg_n) {
+      p->wg_n = a.wg_n;
+      p->wg_segs.assign(a.wgp.segs.begin(), a.wgp.segs.begin() + a.wg_n);
+      for (const WgSeg& s2 : p->wg_segs) p->wg_macros += s2.macros;
       p->wg_groups = static_cast<int>(wgg.w0.size());
-      p->wg_cells = static_cast<int64_t>(a.wgp.nu.size());
-      p->wg_chunks = wg_chunks(p->wg_macros, p->wg_groups);
+      p->wg_recg = reinterpret_cast<WgVisG*>(w + L.wg_recg);
       p->wg_mac = reinterpret_cast<WgMacro*>(w + L.wg_mac);
       p->wg_la = reinterpret_cast<double*>(w + L.wg_la);
       p->wg_mb = reinterpret_cast<double*>(w + L.wg_mb);
@@ -1033,7 +1057,7 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
     auto up = [&](void* dst, const void* src, size_t bytes) {
       if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st);
     };
-    if (a.wg) {
+    if (a.wg_n) {
       const WgPlan& t = a.wgp;
       up(p->wg_mac, t.macros.data(), sizeof(WgMacro) * t.macros.size());
       up(p->wg_la, t.la.data(), 8 * t.la.size());
@@ -1055,7 +1079,7 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       up(p->d_grid_fchunks, a.grid_fc.data(), sizeof(GridChunk) * a.grid_fc.size());
       up(p->d_grid_pblocks, a.grid_pb.data(), sizeof(GridPairBlock) * a.grid_pb.size());
       up(p->d_grid_segs, a.gsegs.data(), sizeof(GridSeg) * a.gsegs.size());
-      up(p->d_grid_gblocks, a.grid_gb.data(), sizeof(int2) * a.grid_gb.size());
+      up(w + L.grid_gb, a.grid_gb.data(), sizeof(int2) * a.grid_gb.size());
     }
     if (e == hipSuccess) e = launch_fill(p->flag, 1, sizeof(int), st);
     if (e == hipSuccess)

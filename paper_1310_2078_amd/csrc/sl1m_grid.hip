@@ -264,8 +264,8 @@ hipError_t launch_grid_forward(sl1m_plan* p, const void* xp, hipStream_t st) {
   const float* scale = static_cast<const float*>(p->pscale);
   float2* part = static_cast<float2*>(fwd_rows1(p));
   for (const GridSeg& g : p->grid_segs) {
-    if (p->wg && &g == &p->grid_segs[p->wg_seg]) {
-      const hipError_t e = launch_wg_forward(p, xp, st);
+    if (&g - p->grid_segs.data() < p->wg_n) {
+      const hipError_t e = launch_wg_forward(p, g, xp, st);
       if (e != hipSuccess) return e;
       continue;
     }
@@ -344,8 +344,8 @@ hipError_t launch_grid_adjoint(sl1m_plan* p, hipStream_t st) {
   float* part = static_cast<float*>(p->apart);
   const float2* rres = static_cast<const float2*>(p->rres);
   for (const GridSeg& g : p->grid_segs) {
-    if (p->wg && &g == &p->grid_segs[p->wg_seg]) {
-      const hipError_t e = launch_wg_adjoint(p, st);
+    if (&g - p->grid_segs.data() < p->wg_n) {
+      const hipError_t e = launch_wg_adjoint(p, g, st);
       if (e != hipSuccess) return e;
       continue;
     }
@@ -378,7 +378,7 @@ hipError_t launch_grid_adjoint(sl1m_plan* p, hipStream_t st) {
       if (e != hipSuccess) return e;
     }
   }
-  // every Gaussian grid segment in one launch (residual records of layer L,
+  // every Gaussian grid segment outside the groups in one launch (records of layer L,
   // single right-hand side: slot 1 + L)
   if (p->grid_gblocks > 0) {
     hipError_t e = timed(p, T_GRID_ADJ_GAUSS, st, [&] {

@@ -179,6 +179,8 @@ struct GridSeg {
 
 namespace sl1m {
 struct WgMacro;  // sl1m_wgroup.h
+struct WgVisG;
+struct WgSeg;
 // timing kinds (sl1m_timing): 0 forward, 1 adjoint, 2 FISTA update, then the
 // grid kernels by launch: 3 delta forward, 4 delta adjoint, 5 Gaussian
 // forward (one launch per layer), 6 Gaussian adjoint (all layers)
@@ -257,12 +259,12 @@ struct sl1m_plan {
   int grid_gblocks = 0;
   sl1m::Chunk* d_chunks1 = nullptr;         // fd1 | fg1 | pd1 | pg1
 
-  // group evaluation of the delta grid segment (sl1m_wgroup.h): its tables and
-  // the visibility groups
-  bool wg = false;
-  int wg_seg = 0;                 // index into grid_segs
-  int wg_macros = 0, wg_groups = 0, wg_chunks = 1;
-  int64_t wg_cells = 0;
+  // group evaluation of the first wg_n grid segments (sl1m_wgroup.h): their
+  // tables and the visibility groups
+  int wg_n = 0;
+  int wg_macros = 0, wg_groups = 0;
+  std::vector<sl1m::WgSeg> wg_segs;
+  sl1m::WgVisG* wg_recg = nullptr;  // [layer][slot]
   sl1m::WgMacro* wg_mac = nullptr;
   double *wg_la = nullptr, *wg_mb = nullptr, *wg_nu = nullptr;
   float* wg_eta = nullptr;
@@ -359,6 +361,8 @@ hipError_t launch_gather(sl1m_plan* p, const void* x, void* xp, int nr, hipStrea
 hipError_t launch_forward(sl1m_plan* p, const void* xp, int nr, hipStream_t st);
 // Partial rows a forward with nr right-hand sides writes (grid or direct split).
 int forward_rows(const sl1m_plan* p, int nr);
+// grid partial rows of the segments that the group evaluation takes
+int wg_skipped_rows(const sl1m_plan* p);
 hipError_t launch_forward_reduce(sl1m_plan* p, const void* data, void* out, bool adj_records,
                                  int nr, hipStream_t st);
 hipError_t launch_adjoint_prep(sl1m_plan* p, const void* r, int nr, hipStream_t st);

@@ -824,10 +824,16 @@ int forward_rows(const sl1m_plan* p, int nr) {
   return p->n_fchunks;
 }
 
+int wg_skipped_rows(const sl1m_plan* p) {
+  int n = 0;
+  for (int i = 0; i < p->wg_n; ++i) n += p->grid_segs[i].nfc;
+  return n;
+}
+
 void* fwd_rows1(const sl1m_plan* p) {
-  if (!p->wg) return p->fpart;
+  if (p->wg_n == 0) return p->fpart;
   const int64_t skip = static_cast<int64_t>(p->wg_macros) * p->wg_groups * kWgVis -
-                       static_cast<int64_t>(p->grid_segs[p->wg_seg].nfc) * p->n_vis;
+                       static_cast<int64_t>(wg_skipped_rows(p)) * p->n_vis;
   return static_cast<float2*>(p->fpart) + skip;
 }
 
@@ -835,7 +841,7 @@ template <typename R>
 static hipError_t fwd_reduce_t(sl1m_plan* p, const void* data, void* out, bool recs, int nr,
                                hipStream_t st) {
   if (p->n_vis == 0) return hipSuccess;
-  if (nr == 1 && p->wg && !mfma_forward_call(p, nr))
+  if (nr == 1 && p->wg_n > 0 && !mfma_forward_call(p, nr))
     return launch_wg_forward_reduce(p, data, out, recs, st);
   hipLaunchKernelGGL((k_fwd_reduce<R>), dim3(grid1(p->n_vis)), dim3(kBlock), 0, st,
                      static_cast<const C2<R>*>(p->fpart), forward_rows(p, nr), p->n_vis, nr,
@@ -853,7 +859,7 @@ hipError_t launch_forward_reduce(sl1m_plan* p, const void* data, void* out, bool
 template <typename R>
 static hipError_t adj_prep_t(sl1m_plan* p, const void* r, int nr, hipStream_t st) {
   if (p->n_vis == 0) return hipSuccess;
-  if (nr == 1 && p->wg && !mfma_adjoint_call(p, nr)) return launch_wg_adjoint_prep(p, r, st);
+  if (nr == 1 && p->wg_n > 0 && !mfma_adjoint_call(p, nr)) return launch_wg_adjoint_prep(p, r, st);
   hipLaunchKernelGGL((k_adj_prep<R>), dim3(grid1(p->n_vis)), dim3(kBlock), 0, st,
                      static_cast<const C2<R>*>(r), p->n_vis, nr, static_cast<const R*>(p->vgain),
                      static_cast<C2<R>*>(p->rres), static_cast<const R*>(p->layerDs),
@@ -910,9 +916,10 @@ hipError_t launch_adjoint(sl1m_plan* p, int nr, hipStream_t st) {
 
 // Pixels whose adjoint sum is whole in row 0 of the partials.
 static int2 wg_pixels(const sl1m_plan* p, int nr) {
-  if (!p->wg || nr != 1 || mfma_adjoint_call(p, nr)) return make_int2(0, 0);
-  const Segment& s = p->segs[p->grid_segs[p->wg_seg].seg];
-  return make_int2(static_cast<int>(s.start), static_cast<int>(s.start + s.count));
+  if (p->wg_n == 0 || nr != 1 || mfma_adjoint_call(p, nr)) return make_int2(0, 0);
+  const Segment& a = p->segs[p->grid_segs[0].seg];
+  const Segment& b = p->segs[p->grid_segs[p->wg_n - 1].seg];
+  return make_int2(static_cast<int>(a.start), static_cast<int>(b.start + b.count));
 }
 
 template <typename R>

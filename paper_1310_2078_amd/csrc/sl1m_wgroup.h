@@ -1,4 +1,4 @@
-// Group evaluation of delta grid segments on the matrix cores (gfx950, float32
+// Group evaluation of grid segments on the matrix cores (gfx950, float32
 // plans, one right-hand side): tables and launchers.
 //
 // The grid evaluation (sl1m_grid.h) factorises an entry into A_k(l) B_k(m) C_k(nu).
@@ -13,6 +13,10 @@
 // cores take.  Inside a tile nu(a,b) = nuT + eta(a,b): the factor of nuT is
 // exact per visibility, that of eta a short series, whose argument 2 pi dw eta
 // the cut of the groups keeps below kWgX radians.
+//
+// Gaussian layers (the completed-square form of sl1m_grid.h): gamma = exp(2 pi i
+// (C r^2 - w kappa)) leaves exp(-2 pi i w kappa) alone to the groups, C l^2 and C m^2
+// going to the factors of l and m, which are complex pairs a+-, b+- with their tapers.
 //
 // The operands are float32 values split into two float16 (value = hi + lo to
 // 2^-22 of it), each product as hi hi + hi lo + lo hi with float32 sums.
@@ -36,6 +40,8 @@ constexpr float kWgXN = 1.2e-3f;
 constexpr float kWgXM = 2.5e-3f;
 constexpr float kWgXW = 1.5e-2f;
 constexpr float kWgX = 5.0e-2f;
+// Gaussian segments: no series below kWgXZ, one order below kWgXN, at most kWgXW.
+constexpr float kWgXZ = 5.0e-7f;
 
 // Up to four tiles (one per wavefront) of neighbouring rows over the same columns.
 struct WgMacro {
@@ -44,18 +50,34 @@ struct WgMacro {
   int32_t cell_off;            // first cell of the first tile (kWgCells per tile)
   float eta_max, nu_t[4];      // largest |eta|; each tile's nuT
   float xs;                    // 2 pi s, s the power of two that the macro's eta are divided by
+  float m_lo, m_hi;            // column positions' range; each tile's row positions' range
+  float l_lo[4], l_hi[4];
 };
 
-// Host-built tables of one delta grid segment.  Tile cells are numbered
+// What a Gaussian layer holds per slot: entry = D (1 + i s) exp(2 pi i (A l + B m + C r^2
+// - w kappa + e0)) 2^(c1 ((u - w l)^2 + (v - w m)^2)), all of the folded coordinates.
+struct alignas(16) WgVisG {
+  double A, B, C;
+  float u, v, w, c1;
+  float e0, D, Ds, pad;
+};
+
+// Where a segment's macros and cells lie in the tables.
+struct WgSeg {
+  int32_t mac0, macros;
+  int64_t cell0, cells;
+  float width;                 // largest eta over its series limit
+};
+
+// Host-built tables of grid segments, one after the other.  Tile cells are numbered
 // column * kWgRows + row.
 struct WgPlan {
+  std::vector<WgSeg> segs;
   std::vector<WgMacro> macros;
   std::vector<double> la, mb;      // row / column positions of the macros
-  std::vector<double> nu;          // per tile cell
+  std::vector<double> nu;          // per tile cell: nu (delta) or kappa
   std::vector<float> eta;          // per tile cell, divided by the macro's s (below 1)
   std::vector<int32_t> slot;       // [4 per tile cell] permuted pixel or -1
-  float eta_max = 0.0f;
-  int64_t padded = 0;              // cells evaluated, padding included
 };
 
 // Visibility groups: `order` holds per slot (kWgVis per group) 2 k + (1 where
@@ -67,9 +89,12 @@ struct WgGroups {
   std::vector<int32_t> count;      // visibilities of the group
 };
 
-void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c3,
+// cells evaluated for a segment, padding included
+int64_t wg_padded(const GridSeg& g);
+// appends a segment; `c`: nu or kappa per grid cell
+void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c,
                     const int32_t* slot, WgPlan& out);
-bool wg_build_groups(const std::vector<double>& w, float eta_max, int64_t max_groups,
+bool wg_build_groups(const std::vector<double>& w, float width, int64_t max_groups,
                      WgGroups& out);
 // groups a plan reserves room for
 int64_t wg_group_cap(int64_t n_vis);
@@ -78,13 +103,13 @@ int wg_chunks(int macros, int groups);
 int wg_chunk_cap(int macros);
 
 hipError_t launch_wg_setup(sl1m_plan* p, hipStream_t st);
-hipError_t launch_wg_forward(sl1m_plan* p, const void* xp, hipStream_t st);
+hipError_t launch_wg_forward(sl1m_plan* p, const GridSeg& g, const void* xp, hipStream_t st);
 // the forward reduction (launch_forward_reduce) of a plan with groups, one side
 hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, bool adj_records,
                                     hipStream_t st);
 // adjoint records of a plan with groups, one side (launch_adjoint_prep)
 hipError_t launch_wg_adjoint_prep(sl1m_plan* p, const void* r, hipStream_t st);
 // the segment's gradient sums into row 0 of the adjoint partials (its only row)
-hipError_t launch_wg_adjoint(sl1m_plan* p, hipStream_t st);
+hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st);
 
 }  // namespace sl1m

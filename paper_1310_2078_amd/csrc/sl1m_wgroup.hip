@@ -1,4 +1,4 @@
-// Group evaluation of delta grid segments (sl1m_wgroup.h): host tables, kernels
+// Group evaluation of grid segments (sl1m_wgroup.h): host tables, kernels
 // and launchers.
 #include <algorithm>
 #include <cmath>
@@ -34,11 +34,19 @@ int wg_chunks(int macros, int groups) {
   return std::max(1, std::min(groups, wg_chunk_cap(macros)));
 }
 
+int64_t wg_padded(const GridSeg& g) {
+  return static_cast<int64_t>((g.na + kWgRows - 1) / kWgRows * kWgRows) * ((g.nb + 15) / 16 * 16);
+}
+
 // Row sets of kWgRows |l| values and column sets of up to kWgSteps steps of 16
 // |m| values, both spread evenly over the macros.
-void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c3,
+void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c,
                     const int32_t* slot, WgPlan& out) {
   const int na = g.na, nb = g.nb;
+  WgSeg seg{};
+  seg.mac0 = static_cast<int32_t>(out.macros.size());
+  seg.cell0 = static_cast<int64_t>(out.nu.size());
+  double seg_eta = 0.0;
   const int rsets = (na + kWgRows - 1) / kWgRows, rmac = (rsets + 3) / 4;
   const int steps = (nb + 15) / 16, cmac = (steps + kWgSteps - 1) / kWgSteps;
   for (int ri = 0; ri < rmac; ++ri)
@@ -59,18 +67,22 @@ void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const 
         const int ib = 16 * s0 + i;
         out.mb.push_back(ib < 16 * s1 && ib < nb ? mb[ib] : 0.0);
       }
+      m.m_lo = static_cast<float>(mb[16 * s0]);
+      m.m_hi = static_cast<float>(mb[std::min(16 * s1, nb) - 1]);
       double eta_max = 0.0;
       const size_t first = out.nu.size();
       for (int w = 0; w < m.sets; ++w) {
         const int a0 = kWgRows * (r0 + w), a1 = std::min(a0 + kWgRows, na);
         const int b0 = 16 * s0, b1 = std::min(16 * s1, nb);
+        m.l_lo[w] = static_cast<float>(la[a0]);
+        m.l_hi[w] = static_cast<float>(la[a1 - 1]);
         auto cell = [&](int ia, int ib) {
           return (static_cast<int64_t>(ib / kGridNB) * na + ia) * kGridNB + ib % kGridNB;
         };
         double lo = 1e300, hi = -1e300;
         for (int ib = b0; ib < b1; ++ib)
           for (int ia = a0; ia < a1; ++ia) {
-            const double v = c3[cell(ia, ib)];
+            const double v = c[cell(ia, ib)];
             lo = std::min(lo, v);
             hi = std::max(hi, v);
           }
@@ -85,12 +97,11 @@ void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const 
           for (int ia = a0; ia < a1; ++ia) {
             const int64_t q = cell(ia, ib);
             const size_t o = n0 + static_cast<size_t>(ib - b0) * kWgRows + (ia - a0);
-            out.nu[o] = c3[q];
-            out.eta[o] = static_cast<float>(c3[q] - nt);
-            eta_max = std::max(eta_max, std::fabs(c3[q] - nt));
+            out.nu[o] = c[q];
+            out.eta[o] = static_cast<float>(c[q] - nt);
+            eta_max = std::max(eta_max, std::fabs(c[q] - nt));
             for (int s = 0; s < 4; ++s) out.slot[4 * o + s] = slot[4 * q + s];
           }
-        out.padded += kWgRows * 16 * m.steps;
       }
       // eta / s in [-1, 1] and x s (at most 2 kWgX) both lie in float16's range
       int ex = 0;
@@ -99,12 +110,17 @@ void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const 
       for (size_t o = first; o < out.eta.size(); ++o) out.eta[o] /= static_cast<float>(s);
       m.xs = static_cast<float>(6.283185307179586 * s);
       m.eta_max = static_cast<float>(eta_max);
-      out.eta_max = std::max(out.eta_max, m.eta_max);
+      seg_eta = std::max(seg_eta, eta_max);
       out.macros.push_back(m);
     }
+  const float limit = g.kind == SL1M_PIX_DELTA ? kWgX : kWgXW;
+  seg.width = static_cast<float>(seg_eta) / limit;
+  seg.macros = static_cast<int32_t>(out.macros.size()) - seg.mac0;
+  seg.cells = static_cast<int64_t>(out.nu.size()) - seg.cell0;
+  out.segs.push_back(seg);
 }
 
-bool wg_build_groups(const std::vector<double>& w, float eta_max, int64_t max_groups,
+bool wg_build_groups(const std::vector<double>& w, float width, int64_t max_groups,
                      WgGroups& out) {
   const int64_t n = static_cast<int64_t>(w.size());
   double wm = 0.0;
@@ -130,7 +146,7 @@ bool wg_build_groups(const std::vector<double>& w, float eta_max, int64_t max_gr
     for (int64_t i = 0; i < n; ++i) b[cnt[(key[a[i]] >> sh) & 1023u]++] = a[i];
     a.swap(b);
   }
-  const double hmax = eta_max > 0.0f ? kWgX / (6.283185307179586 * eta_max) : 1e300;
+  const double hmax = width > 0.0f ? 1.0 / (6.283185307179586 * width) : 1e300;
   for (int64_t i = 0; i < n;) {
     double lo = std::fabs(w[a[i]]), hi = lo;
     int64_t j = i + 1;
@@ -206,6 +222,24 @@ __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
+}
+
+// Sums over the quads; lane L ends with visibility L.
+__device__ __forceinline__ void quad_sum(const float (&vr)[4], const float (&vi)[4], int lane,
+                                         float& sr, float& si) {
+  const bool hi = (lane & 32) != 0, md = (lane & 16) != 0;
+  float ar[2], ai[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const float kr = hi ? vr[t + 2] : vr[t], ki = hi ? vi[t + 2] : vi[t];
+    const float or_ = hi ? vr[t] : vr[t + 2], oi = hi ? vi[t] : vi[t + 2];
+    ar[t] = kr + __shfl_xor(or_, 32, 64);
+    ai[t] = ki + __shfl_xor(oi, 32, 64);
+  }
+  const float kr = md ? ar[1] : ar[0], ki = md ? ai[1] : ai[0];
+  const float or_ = md ? ar[0] : ar[1], oi = md ? ai[0] : ai[1];
+  sr = kr + __shfl_xor(or_, 16, 64);
+  si = ki + __shfl_xor(oi, 16, 64);
 }
 
 // One step (16 columns) of one kind pair (re, im): the tile rows' values pr, pi
@@ -344,14 +378,14 @@ struct FwdLds {
 // Forward: block (groups x, x + gridDim.x, ..; macro y); row y of the partial sums holds the
 // macro's sum per slot.
 __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
-    const WgMacro* __restrict__ macros, const float* __restrict__ xp,
+    const WgMacro* __restrict__ macros, int mac0, const float* __restrict__ xp,
     const float* __restrict__ pscale, const int4* __restrict__ slot, const double* __restrict__ nu,
     const float* __restrict__ eta, const double* __restrict__ la, const double* __restrict__ mb,
     const double* __restrict__ su, const double* __restrict__ sv, const float* __restrict__ sdw,
     const double* __restrict__ w0s, const float* __restrict__ hs, const int32_t* __restrict__ cnt,
     int n_groups, float2* __restrict__ rows) {
   __shared__ FwdLds lds;
-  const int mac = blockIdx.y;
+  const int mac = mac0 + static_cast<int>(blockIdx.y);
   const ConstPtr<WgMacro> cm = as_const(macros) + mac;
   const int sets = cm->sets, steps = cm->steps;
   const float eta_max = cm->eta_max, xs = cm->xs;
@@ -497,19 +531,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
           vi[t] = fmaf(as, d.si[t][i], vi[t]);
         }
       }
-      // sum over the quads; lane L ends with visibility L
-      const bool hi = (lane & 32) != 0, md = (lane & 16) != 0;
-      float ar[2], ai[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const float kr = hi ? vr[t + 2] : vr[t], ki = hi ? vi[t + 2] : vi[t];
-        const float or_ = hi ? vr[t] : vr[t + 2], oi = hi ? vi[t] : vi[t + 2];
-        ar[t] = kr + __shfl_xor(or_, 32, 64);
-        ai[t] = ki + __shfl_xor(oi, 32, 64);
-      }
-      const float kr = md ? ar[1] : ar[0], ki = md ? ai[1] : ai[0];
-      const float or_ = md ? ar[0] : ar[1], oi = md ? ai[0] : ai[1];
-      const float sr = kr + __shfl_xor(or_, 16, 64), si = ki + __shfl_xor(oi, 16, 64);
+      float sr, si;
+      quad_sum(vr, vi, lane, sr, si);
       const float th = dw * nu_t;
       const float ct = __builtin_amdgcn_cosf(th), st = __builtin_amdgcn_sinf(th);
       re = sc * fmaf(ct, sr, st * si);
@@ -560,7 +583,7 @@ __global__ void k_wg_fwd_reduce(const float2* __restrict__ part, int n_macros, i
   if (t >= n_slots) return;
   const int32_t o = order[t];
   if (o < 0) {
-    if (rres) res[t] = make_float2(0.0f, 0.0f);
+    if (res) res[t] = make_float2(0.0f, 0.0f);
     return;
   }
   const int64_t k = o >> 1;
@@ -579,8 +602,8 @@ __global__ void k_wg_fwd_reduce(const float2* __restrict__ part, int n_macros, i
     im -= data[k].y;
   }
   if (out) out[k] = make_float2(re, im);
-  if (rres) {
-    write_res<float>(rres, layerDs, n_layers, n_vis, 1, k, 0, gr, gi, re, im);
+  if (rres) write_res<float>(rres, layerDs, n_layers, n_vis, 1, k, 0, gr, gi, re, im);
+  if (res) {
     const float ci = gr * im - gi * re;
     res[t] = make_float2(gr * re + gi * im, o & 1 ? -ci : ci);
   }
@@ -760,13 +783,13 @@ __device__ __forceinline__ void adj_group(const float (&pc)[2][8], const float (
 // Adjoint: block (groups x, x + gridDim.x, ..; macro y); part[x][cell] = (G1, G2,
 // G3, G4) of its groups.
 __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
-    const WgMacro* __restrict__ macros, const float2* __restrict__ res,
+    const WgMacro* __restrict__ macros, int mac0, const float2* __restrict__ res,
     const double* __restrict__ nu, const float* __restrict__ eta, const double* __restrict__ la,
     const double* __restrict__ mb, const double* __restrict__ su, const double* __restrict__ sv,
     const float* __restrict__ sdw, const double* __restrict__ w0s, const float* __restrict__ hs,
-    int n_groups, int64_t cells, float4* __restrict__ part) {
+    int n_groups, int64_t cbase, int64_t cells, float4* __restrict__ part) {
   __shared__ AdjLds lds;
-  const ConstPtr<WgMacro> cm = as_const(macros) + blockIdx.y;
+  const ConstPtr<WgMacro> cm = as_const(macros) + mac0 + blockIdx.y;
   const int sets = cm->sets, steps = cm->steps;
   const float eta_max = cm->eta_max, xs = cm->xs;
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
@@ -897,12 +920,658 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
   for (int c = 0; c < kWgSteps; ++c)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      part[blockIdx.x * cells + cell0 + (16 * c + r16) * kWgRows + quad * 4 + i] =
+      part[blockIdx.x * cells + cell0 - cbase + (16 * c + r16) * kWgRows + quad * 4 + i] =
           make_float4(g[0][c][i], g[1][c][i], g[2][c][i], g[3][c][i]);
 }
 
+// ---------------------------------------------------------------------------
+// Gaussian layers (completed-square form, sl1m_grid.h).  An entry is
+//   D (1 + i s) exp(2 pi i (e0 - w kappa)) a_sign(|l|) b_sign(|m|),
+//   a+- = T(u -+ w|l|) exp(2 pi i (+- A|l| + C l^2)), b+- the same of v, |m|, B,
+// where C l^2 + C m^2 carries the phase's r^2 term; kappa alone (n - 1 + r^2 / 2, a
+// fourth-order term) is left to the groups, in the tiles of the delta segments.
+// Both factors are complex, so the products are twice as long.  Tapers are formed
+// against the largest of the macro's columns and (adjoint) of the tile's rows per
+// visibility, so that the float16 operands keep their precision where a whole
+// baseline's taper is small.  Bound by the vector instructions around the products
+// (C_0 and its splits, the rows' and columns' phasors and tapers), as for delta
+// pixels.  512 x 512 pixels, 409,600 visibilities: forward 5.5 ms, adjoint 6.5 ms;
+// the grid evaluation of the same layer took 13.2 and 14.9.  300 x 300 truncated,
+// 100,003: 0.47 / 0.54 ms against 1.33 / 1.53.
+// ---------------------------------------------------------------------------
+
+// log2 of the largest taper over +-[lo, hi] at baseline coordinate d
+__device__ __forceinline__ float taper_top(float c1, float d, float w, float lo, float hi) {
+  const float a = fmaf(-w, lo, d), b = fmaf(-w, hi, d), e = fmaf(w, lo, d), f = fmaf(w, hi, d);
+  const float p = a * b <= 0.0f ? 0.0f : fminf(fabsf(a), fabsf(b));
+  const float q = e * f <= 0.0f ? 0.0f : fminf(fabsf(e), fabsf(f));
+  const float m = fminf(p, q);
+  return c1 * (m * m);
+}
+
+// up 2^(c1 d^2 - top), at most up (padded positions may lie above the top).  Columns
+// stand kGUp high: tapers down to 2^-28 of the largest are normal float16.  (The factor
+// in the exponent would cost the exponent four bits.)
+constexpr float kGUp = 0x1.0p14f, kGDown = 0x1.0p-14f;
+__device__ __forceinline__ float taper(float c1, float d, float top, float up) {
+  return up * __builtin_amdgcn_exp2f(fminf(fmaf(c1, d * d, -top), 0.0f));
+}
+
+struct alignas(16) FwdGLds {
+  uint4 col[kWgCols / 2 * 4 * 64];  // [two columns][B1 hi, lo, B2 hi, lo][visibility]
+  double la[4 * kWgRows], mb[kWgCols], A[kWgVis], C[kWgVis];
+  float4 uw[kWgVis];                // u, w, c1, x
+  float2 red[4][kWgVis];
+};
+
+// gamma x of one step of 8 columns for the two row signs: this lane's row, two
+// columns of two signs, (re, im) each.
+__device__ __forceinline__ void gauss_rows(double w0, const double (&kap)[2], const float4 (&x)[2],
+                                           float (&pp)[8], float (&pm)[8]) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    float cc, cs;
+    phasor_fine(fma(w0, kap[j], kMagicFine), cc, cs);
+    pp[4 * j] = cc * x[j].x;
+    pp[4 * j + 1] = -cs * x[j].x;
+    pp[4 * j + 2] = cc * x[j].z;
+    pp[4 * j + 3] = -cs * x[j].z;
+    pm[4 * j] = cc * x[j].y;
+    pm[4 * j + 1] = -cs * x[j].y;
+    pm[4 * j + 2] = cc * x[j].w;
+    pm[4 * j + 3] = -cs * x[j].w;
+  }
+}
+
+__device__ __forceinline__ Op8 times_eta(const Op8& p, const float (&eta)[2]) {
+  Op8 r;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const _Float16 e = static_cast<_Float16>(eta[j / 2]);
+    r.v[j] = p.v[j] * h2_t{e, e};
+  }
+  return r;
+}
+
+// D (re, im; two row signs): sums over the tile's columns, SER 1 with the first
+// order -i x eta.
+struct GAcc {
+  f4_t d[4][4];  // [+ re, + im, - re, - im][visibility tile]
+};
+
+template <int SER>
+__device__ __forceinline__ void fwd_gauss_tile(int steps, double w0,
+                                               const double (&kap)[2 * kWgSteps][2],
+                                               const float4 (&x)[2 * kWgSteps][2],
+                                               const float (&eta)[2 * kWgSteps][2],
+                                               const uint4* __restrict__ col,
+                                               const float (&xv)[4], int nt, GAcc& a) {
+#pragma unroll
+  for (int ks = 0; ks < 2 * kWgSteps; ++ks) {
+    if (ks >= 2 * steps) continue;
+    float pp[8], pm[8];
+    gauss_rows(w0, kap[ks], x[ks], pp, pm);
+    Op8 ph, pl, pe, mh, ml, me;
+    split8(pp, ph, pl);
+    split8(pm, mh, ml);
+    if constexpr (SER > 0) {
+      pe = times_eta(ph, eta[ks]);
+      me = times_eta(mh, eta[ks]);
+    }
+    const uint4* q = col + ks * 4 * 4 * 64;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (t >= nt) continue;
+      const h8_t b1h = as_h8(q[16 * t]), b1l = as_h8(q[64 + 16 * t]);
+      const h8_t b2h = as_h8(q[128 + 16 * t]), b2l = as_h8(q[192 + 16 * t]);
+      a.d[0][t] = mma(ph.vec(), b1h, a.d[0][t]);
+      a.d[1][t] = mma(ph.vec(), b2h, a.d[1][t]);
+      a.d[2][t] = mma(mh.vec(), b1h, a.d[2][t]);
+      a.d[3][t] = mma(mh.vec(), b2h, a.d[3][t]);
+      a.d[0][t] = mma(ph.vec(), b1l, a.d[0][t]);
+      a.d[1][t] = mma(ph.vec(), b2l, a.d[1][t]);
+      a.d[2][t] = mma(mh.vec(), b1l, a.d[2][t]);
+      a.d[3][t] = mma(mh.vec(), b2l, a.d[3][t]);
+      a.d[0][t] = mma(pl.vec(), b1h, a.d[0][t]);
+      a.d[1][t] = mma(pl.vec(), b2h, a.d[1][t]);
+      a.d[2][t] = mma(ml.vec(), b1h, a.d[2][t]);
+      a.d[3][t] = mma(ml.vec(), b2h, a.d[3][t]);
+      if constexpr (SER > 0) {
+        const _Float16 xf = static_cast<_Float16>(xv[t]);
+        const h8_t x2 = b2h * xf, x1 = b1h * -xf;
+        a.d[0][t] = mma(pe.vec(), x2, a.d[0][t]);
+        a.d[1][t] = mma(pe.vec(), x1, a.d[1][t]);
+        a.d[2][t] = mma(me.vec(), x2, a.d[2][t]);
+        a.d[3][t] = mma(me.vec(), x1, a.d[3][t]);
+      }
+    }
+  }
+}
+
+// The same for arguments up to kWgXW: first order split like the zeroth into sums of
+// its own, second order in one product.  One row sign and two visibility tiles at a
+// time (the rows are formed again for each): all at once spill 126 registers.
+__device__ __forceinline__ void fwd_gauss_wide(int steps, double w0,
+                                               const double (&kap)[2 * kWgSteps][2],
+                                               const float4 (&x)[2 * kWgSteps][2],
+                                               const float (&eta)[2 * kWgSteps][2],
+                                               const uint4* __restrict__ col,
+                                               const float (&xv)[4], int nt, GAcc& a) {
+#pragma unroll
+  for (int th = 0; th < 4; th += 2) {
+    if (th >= nt) continue;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      f4_t d1[2][2];
+      asm volatile("" : "+v"(w0));  // the rows are not kept from one pass to the next
+#pragma unroll
+      for (int o = 0; o < 2; ++o) d1[o][0] = d1[o][1] = f4_t{0, 0, 0, 0};
+#pragma unroll
+      for (int ks = 0; ks < 2 * kWgSteps; ++ks) {
+        if (ks >= 2 * steps) continue;
+        float pp[2][8], pe[8];
+        gauss_rows(w0, kap[ks], x[ks], pp[0], pp[1]);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) pe[j] = eta[ks][j / 4] * pp[s][j];
+        Op8 ph, pl, eh, el;
+        split8(pp[s], ph, pl);
+        split8(pe, eh, el);
+        const Op8 e2 = times_eta(eh, eta[ks]);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const uint4* q = col + ks * 4 * 4 * 64 + 16 * (th + t);
+          const _Float16 xf = static_cast<_Float16>(xv[th + t]);
+          const _Float16 hf = static_cast<_Float16>(-0.5f * xv[th + t]);
+#pragma unroll
+          for (int o = 0; o < 2; ++o) {  // re, im
+            const h8_t bh = as_h8(q[128 * o]), bl = as_h8(q[128 * o + 64]);
+            f4_t& z = a.d[2 * s + o][th + t];
+            z = mma(ph.vec(), bh, z);
+            z = mma(ph.vec(), bl, z);
+            z = mma(pl.vec(), bh, z);
+            z = mma(e2.vec(), bh * xf * hf, z);
+            d1[o][t] = mma(eh.vec(), bh, d1[o][t]);
+            d1[o][t] = mma(eh.vec(), bl, d1[o][t]);
+            d1[o][t] = mma(el.vec(), bh, d1[o][t]);
+          }
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          f4_t& zr = a.d[2 * s][th + t];
+          f4_t& zi = a.d[2 * s + 1][th + t];
+          zr[i] = fmaf(xv[th + t], d1[1][t][i], zr[i]);
+          zi[i] = fmaf(-xv[th + t], d1[0][t][i], zi[i]);
+        }
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
+    const WgMacro* __restrict__ macros, int mac0, const float* __restrict__ xp,
+    const float* __restrict__ pscale, const int4* __restrict__ slot, const double* __restrict__ kap,
+    const float* __restrict__ eta, const double* __restrict__ la, const double* __restrict__ mb,
+    const WgVisG* __restrict__ rec, const float* __restrict__ sdw, const double* __restrict__ w0s,
+    const float* __restrict__ hs, const int32_t* __restrict__ cnt, int n_groups,
+    float2* __restrict__ rows) {
+  __shared__ FwdGLds lds;
+  const int mac = mac0 + static_cast<int>(blockIdx.y);
+  const ConstPtr<WgMacro> cm = as_const(macros) + mac;
+  const int sets = cm->sets, steps = cm->steps;
+  const float eta_max = cm->eta_max, xs = cm->xs, m_lo = cm->m_lo, m_hi = cm->m_hi;
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool active = wv < sets;
+  const float kap_t = cm->nu_t[wv];
+  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
+  if (tid < 4 * kWgRows) lds.la[tid] = la[cm->a_off + tid];
+  if (tid < kWgCols) lds.mb[tid] = mb[cm->b_off + tid];
+  // amplitudes of this lane's row and its two columns of every 8, times the power
+  // of two that brings the tile's largest into [2^13, 2^14)
+  double kp[2 * kWgSteps][2];
+  float4 x[2 * kWgSteps][2];
+  float et[2 * kWgSteps][2];
+  float mx = 0.0f;
+#pragma unroll
+  for (int s = 0; s < 2 * kWgSteps; ++s)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int64_t o = cell0 + (8 * s + 2 * quad + j) * kWgRows + r16;
+      kp[s][j] = kap[o];
+      et[s][j] = eta[o];
+      const int4 q = slot[o];
+      const float x0 = q.x >= 0 ? xp[q.x] * pscale[q.x] : 0.0f;
+      const float x1 = q.y >= 0 ? xp[q.y] * pscale[q.y] : 0.0f;
+      const float x2 = q.z >= 0 ? xp[q.z] * pscale[q.z] : 0.0f;
+      const float x3 = q.w >= 0 ? xp[q.w] * pscale[q.w] : 0.0f;
+      const float m = fmaxf(fmaxf(fabsf(x0), fabsf(x1)), fmaxf(fabsf(x2), fabsf(x3)));
+      const float sum = (x0 + x1) + (x2 + x3);
+      mx = fmaxf(mx, sum != sum ? __builtin_inff() : m);  // fmaxf drops a NaN
+      x[s][j] = make_float4(x0, x1, x2, x3);
+    }
+  const float c = op_scale(wave_max(mx)), sc = 1.0f / c;
+#pragma unroll
+  for (int s = 0; s < 2 * kWgSteps; ++s)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      x[s][j].x *= c;
+      x[s][j].y *= c;
+      x[s][j].z *= c;
+      x[s][j].w *= c;
+    }
+  const int g0 = static_cast<int>(blockIdx.x), gs = static_cast<int>(gridDim.x);
+  const ConstPtr<double> cw0 = as_const(w0s);
+  const ConstPtr<float> chs = as_const(hs);
+  const ConstPtr<int32_t> ccnt = as_const(cnt);
+  WgVisG rn = {};
+  double w0n = 0.0;
+  float dwn = 0.0f, hn = 0.0f;
+  int cn = 0;
+  auto load = [&](int g) {
+    rn = rec[g * kWgVis + lane];
+    dwn = sdw[g * kWgVis + lane];
+    w0n = cw0[g];
+    hn = chs[g];
+    cn = ccnt[g];
+  };
+  if (g0 < n_groups) load(g0);
+  __syncthreads();
+  for (int g = g0; g < n_groups; g += gs) {
+    const WgVisG r = rn;
+    const float dw = dwn;
+    const double w0 = w0n;
+    const float xm = kTwoPi * hn * eta_max;
+    const int ser = xm <= kWgXZ ? 0 : xm <= kWgXN ? 1 : 2;
+    const int nt = (cn + 15) >> 4;
+    if (wv == 0) {
+      lds.A[lane] = r.A;
+      lds.C[lane] = r.C;
+      lds.uw[lane] = make_float4(r.u, r.w, r.c1, xs * dw);
+    }
+    load(g + gs < n_groups ? g + gs : g);
+    const float top = taper_top(r.c1, r.v, r.w, m_lo, m_hi);
+    for (int un = wv; un < 8 * steps; un += 4) {
+      uint4 o[4];
+      uint32_t* const po = reinterpret_cast<uint32_t*>(o);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const double m = lds.mb[un * 2 + j];
+        const float mr = static_cast<float>(m);
+        float cb, sb;
+        phasor(fma(r.B, m, fma(r.C, m * m, kMagic)), cb, sb);
+        const float tp = taper(r.c1, fmaf(-r.w, mr, r.v), top, kGUp);
+        const float tm = taper(r.c1, fmaf(r.w, mr, r.v), top, kGUp);
+        // b+ = tp (cb, sb); b- with the conjugate linear phase: its C m^2 part keeps
+        // its sign, so the phasor of -B m + C m^2 is formed on its own
+        float cm_, sm_;
+        phasor(fma(-r.B, m, fma(r.C, m * m, kMagic)), cm_, sm_);
+        h2_t hp, lp, hm, lm;
+        split2(tp * cb, tp * sb, hp, lp);
+        split2(tm * cm_, tm * sm_, hm, lm);
+        // B1 = (re, -im), B2 = (im, re) of b+ and b-
+        po[2 * j] = as_u32(h2_t{hp[0], -hp[1]});
+        po[2 * j + 1] = as_u32(h2_t{hm[0], -hm[1]});
+        po[4 + 2 * j] = as_u32(h2_t{lp[0], -lp[1]});
+        po[4 + 2 * j + 1] = as_u32(h2_t{lm[0], -lm[1]});
+        po[8 + 2 * j] = as_u32(hp.yx);
+        po[8 + 2 * j + 1] = as_u32(hm.yx);
+        po[12 + 2 * j] = as_u32(lp.yx);
+        po[12 + 2 * j + 1] = as_u32(lm.yx);
+      }
+      uint4* dst = lds.col + un * 4 * 64 + lane;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) dst[q * 64] = o[q];
+    }
+    __syncthreads();
+    float re = 0.0f, im = 0.0f;
+    if (active) {
+      GAcc d;
+#pragma unroll
+      for (int o = 0; o < 4; ++o)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) d.d[o][t] = f4_t{0, 0, 0, 0};
+      float xv[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) xv[t] = lds.uw[16 * t + r16].w;
+      const uint4* col = lds.col + quad * 4 * 64 + r16;
+      if (ser == 0)
+        fwd_gauss_tile<0>(steps, w0, kp, x, et, col, xv, nt, d);
+      else if (ser == 1)
+        fwd_gauss_tile<1>(steps, w0, kp, x, et, col, xv, nt, d);
+      else
+        fwd_gauss_wide(steps, w0, kp, x, et, col, xv, nt, d);
+      float vr[4], vi[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        vr[t] = vi[t] = 0.0f;
+        if (t >= nt) continue;
+        const double A = lds.A[16 * t + r16], C = lds.C[16 * t + r16];
+        const float4 uw = lds.uw[16 * t + r16];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const double l = lds.la[wv * kWgRows + quad * 4 + i];
+          const float lr = static_cast<float>(l);
+          float cp, sp, cn_, sn_;
+          const double q2 = fma(C, l * l, kMagic);
+          phasor(fma(A, l, q2), cp, sp);
+          phasor(fma(-A, l, q2), cn_, sn_);
+          const float du = fmaf(-uw.y, lr, uw.x), dv = fmaf(uw.y, lr, uw.x);
+          const float tp = pow2(uw.z * (du * du)), tm = pow2(uw.z * (dv * dv));
+          const float apr = tp * cp, api = tp * sp, amr = tm * cn_, ami = tm * sn_;
+          vr[t] = fmaf(apr, d.d[0][t][i], fmaf(-api, d.d[1][t][i], vr[t]));
+          vi[t] = fmaf(apr, d.d[1][t][i], fmaf(api, d.d[0][t][i], vi[t]));
+          vr[t] = fmaf(amr, d.d[2][t][i], fmaf(-ami, d.d[3][t][i], vr[t]));
+          vi[t] = fmaf(amr, d.d[3][t][i], fmaf(ami, d.d[2][t][i], vi[t]));
+        }
+      }
+      float sr, si;
+      quad_sum(vr, vi, lane, sr, si);
+      // visibility `lane`: D (1 + i s), e0, the tile's kappa, the columns' top
+      const float th = fmaf(-dw, kap_t, r.e0);
+      const float ct = __builtin_amdgcn_cosf(th), st = __builtin_amdgcn_sinf(th);
+      const float k = sc * kGDown * pow2(top);
+      const float fr = k * fmaf(r.D, ct, -r.Ds * st), fi = k * fmaf(r.D, st, r.Ds * ct);
+      re = fmaf(fr, sr, -fi * si);
+      im = fmaf(fr, si, fi * sr);
+    }
+    lds.red[wv][lane] = make_float2(re, im);
+    __syncthreads();
+    if (tid < kWgVis) {
+      const float2 a = lds.red[0][tid], b = lds.red[1][tid], c2 = lds.red[2][tid],
+                   d = lds.red[3][tid];
+      rows[(static_cast<int64_t>(mac) * n_groups + g) * kWgVis + tid] =
+          make_float2((a.x + b.x) + (c2.x + d.x), (a.y + b.y) + (c2.y + d.y));
+    }
+  }
+}
+
+constexpr int kGPitch = 68;  // uint32 (visibilities) per column of an operand, padded
+
+struct alignas(16) AdjGLds {
+  uint32_t col[2][4][kWgCols][kGPitch];  // [b+, b-][B1 hi, lo, B2 hi, lo][column][visibility]
+  double la[4 * kWgRows], mb[kWgCols], A[kWgVis], C[kWgVis];
+  float4 uw[kWgVis];                     // u, w, c1, x
+  float2 rho[4][kWgVis];
+  float top[4][kWgVis];
+  uint32_t x[kWgVis];                    // (x, x) in float16
+};
+
+struct GOp {  // row operand of 16 visibilities: (re, im) each; hi, lo, and x times them
+  Op8 h, l, eh, el;
+};
+
+// G of one sign pair += Re conj(C_0) (T + i eta T1 - eta^2 T2), SER as in the
+// forward; `b`: this lane's column operand, `x` its visibilities' x.
+template <int SER>
+__device__ __forceinline__ void adj_gauss_kind(const GOp (&a)[4], const uint4* __restrict__ b,
+                                               const uint4* __restrict__ x,
+                                               const float (&cc)[kWgSteps][4],
+                                               const float (&cs)[kWgSteps][4],
+                                               const float (&eta)[kWgSteps][4], int steps,
+                                               float (&g)[kWgSteps][4]) {
+  constexpr int kPart = kWgCols * kGPitch / 4, kTile = 16 * kGPitch / 4;
+  f4_t t[4][kWgSteps], h[2][kWgSteps];
+#pragma unroll
+  for (int c = 0; c < kWgSteps; ++c) {
+#pragma unroll
+    for (int o = 0; o < 4; ++o) t[o][c] = f4_t{0, 0, 0, 0};
+    h[0][c] = h[1][c] = f4_t{0, 0, 0, 0};
+    if (c >= steps) continue;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint4* q = b + c * kTile + 4 * k;
+      const h8_t b1h = as_h8(q[0]), b2h = as_h8(q[2 * kPart]);
+      const h8_t b1l = as_h8(q[kPart]), b2l = as_h8(q[3 * kPart]);
+      t[0][c] = mma(a[k].h.vec(), b1h, t[0][c]);
+      t[1][c] = mma(a[k].h.vec(), b2h, t[1][c]);
+      if constexpr (SER > 0) {
+        t[2][c] = mma(a[k].eh.vec(), b1h, t[2][c]);
+        t[3][c] = mma(a[k].eh.vec(), b2h, t[3][c]);
+      }
+      t[0][c] = mma(a[k].h.vec(), b1l, t[0][c]);
+      t[1][c] = mma(a[k].h.vec(), b2l, t[1][c]);
+      if constexpr (SER > 1) {
+        t[2][c] = mma(a[k].eh.vec(), b1l, t[2][c]);
+        t[3][c] = mma(a[k].eh.vec(), b2l, t[3][c]);
+      }
+      t[0][c] = mma(a[k].l.vec(), b1h, t[0][c]);
+      t[1][c] = mma(a[k].l.vec(), b2h, t[1][c]);
+      if constexpr (SER > 1) {
+        t[2][c] = mma(a[k].el.vec(), b1h, t[2][c]);
+        t[3][c] = mma(a[k].el.vec(), b2h, t[3][c]);
+        const h8_t s = a[k].eh.vec() * (as_h8(x[4 * k]) * static_cast<_Float16>(0.5f));
+        h[0][c] = mma(s, b1h, h[0][c]);
+        h[1][c] = mma(s, b2h, h[1][c]);
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < kWgSteps; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float e = eta[c][i];
+      float zr = t[0][c][i], zi = t[1][c][i];
+      if constexpr (SER > 0) {
+        zr = fmaf(-e, t[3][c][i], zr);
+        zi = fmaf(e, t[2][c][i], zi);
+      }
+      if constexpr (SER > 1) {
+        zr = fmaf(-e * e, h[0][c][i], zr);
+        zi = fmaf(-e * e, h[1][c][i], zi);
+      }
+      g[c][i] = fmaf(cc[c][i], zr, g[c][i]);
+      g[c][i] = fmaf(-cs[c][i], zi, g[c][i]);
+      asm volatile("" : "+v"(g[c][i]));  // formed here (adj_fold)
+    }
+}
+
+struct GRow {  // this lane's row and the group's visibilities (LDS)
+  float lr;
+  double l, l2;
+  const float4* uw;
+  const double *A, *C;
+  const float2* rho;
+  const float* top;
+};
+
+template <int SER>
+__device__ __forceinline__ void adj_gauss_group(const GRow& r, int quad,
+                                                const uint4* __restrict__ b,
+                                                const uint4* __restrict__ x,
+                                                const float (&cc)[kWgSteps][4],
+                                                const float (&cs)[kWgSteps][4],
+                                                const float (&eta)[kWgSteps][4], int steps,
+                                                float (&g)[4][kWgSteps][4]) {
+  constexpr int kSign = 4 * kWgCols * kGPitch / 4;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {  // row signs
+    GOp a[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const h8_t xk = as_h8(x[4 * k]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int v = 16 * k + 4 * quad + j;
+        const float4 uw = r.uw[v];
+        const double A = s ? -r.A[v] : r.A[v];
+        float ca, sa;
+        phasor(fma(A, r.l, fma(r.C[v], r.l2, kMagic)), ca, sa);
+        const float t = taper(uw.z, fmaf(s ? uw.y : -uw.y, r.lr, uw.x), r.top[v], 1.0f);
+        ca *= t;
+        sa *= t;
+        const float2 z = r.rho[v];
+        const float yr = fmaf(ca, z.x, sa * z.y), yi = fmaf(ca, z.y, -sa * z.x);
+        split2(yr, yi, a[k].h.v[j], a[k].l.v[j]);
+        if constexpr (SER > 1) split2(uw.w * yr, uw.w * yi, a[k].eh.v[j], a[k].el.v[j]);
+      }
+      if constexpr (SER == 1) a[k].eh = __builtin_bit_cast(Op8, a[k].h.vec() * xk);
+    }
+    adj_gauss_kind<SER>(a, b, x, cc, cs, eta, steps, g[s]);
+    adj_gauss_kind<SER>(a, b + kSign, x, cc, cs, eta, steps, g[2 + s]);
+  }
+}
+
+// part[x][cell] = the four sign slots' sums
+__global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
+    const WgMacro* __restrict__ macros, int mac0, const float2* __restrict__ res,
+    const double* __restrict__ kap, const float* __restrict__ eta, const double* __restrict__ la,
+    const double* __restrict__ mb, const WgVisG* __restrict__ rec, const float* __restrict__ sdw,
+    const double* __restrict__ w0s, const float* __restrict__ hs, int n_groups, int64_t cbase,
+    int64_t cells, float4* __restrict__ part) {
+  __shared__ AdjGLds lds;
+  const ConstPtr<WgMacro> cm = as_const(macros) + mac0 + blockIdx.y;
+  const int sets = cm->sets, steps = cm->steps;
+  const float eta_max = cm->eta_max, xs = cm->xs, m_lo = cm->m_lo, m_hi = cm->m_hi;
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool active = wv < sets;
+  const float kap_t = cm->nu_t[wv], l_lo = cm->l_lo[wv], l_hi = cm->l_hi[wv];
+  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
+  if (tid < 4 * kWgRows) lds.la[tid] = la[cm->a_off + tid];
+  if (tid < kWgCols) lds.mb[tid] = mb[cm->b_off + tid];
+  double kp[kWgSteps][4];
+  float et[kWgSteps][4], g[4][kWgSteps][4];
+#pragma unroll
+  for (int c = 0; c < kWgSteps; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t q = cell0 + (16 * c + r16) * kWgRows + quad * 4 + i;
+      kp[c][i] = kap[q];
+      et[c][i] = eta[q];
+#pragma unroll
+      for (int o = 0; o < 4; ++o) g[o][c][i] = 0.0f;
+    }
+  const int g0 = static_cast<int>(blockIdx.x), gs = static_cast<int>(gridDim.x);
+  const ConstPtr<double> cw0 = as_const(w0s);
+  const ConstPtr<float> chs = as_const(hs);
+  WgVisG rn = {};
+  float2 zn = make_float2(0.0f, 0.0f);
+  double w0n = 0.0;
+  float dwn = 0.0f, hn = 0.0f;
+  auto load = [&](int gi) {
+    rn = rec[gi * kWgVis + lane];
+    zn = res[gi * kWgVis + lane];
+    dwn = sdw[gi * kWgVis + lane];
+    w0n = cw0[gi];
+    hn = chs[gi];
+  };
+  if (g0 < n_groups) load(g0);
+  __syncthreads();
+  for (int gi = g0; gi < n_groups; gi += gs) {
+    const WgVisG r = rn;
+    const double w0 = w0n;
+    const float xm = kTwoPi * hn * eta_max;
+    const int ser = xm <= kWgXZ ? 0 : xm <= kWgXN ? 1 : 2;
+    // residual times conj of the visibility's factors, with both tops
+    const float top = taper_top(r.c1, r.v, r.w, m_lo, m_hi);
+    const float ltop = taper_top(r.c1, r.u, r.w, l_lo, l_hi);
+    const float th = fmaf(-dwn, kap_t, r.e0);
+    const float k = pow2(top + ltop);
+    const float c0 = __builtin_amdgcn_cosf(th), s0 = __builtin_amdgcn_sinf(th);
+    const float ct = k * fmaf(r.D, c0, -r.Ds * s0), st = k * fmaf(r.D, s0, r.Ds * c0);
+    const float rr = fmaf(ct, zn.x, st * zn.y), ri = fmaf(ct, zn.y, -st * zn.x);
+    const float am = fmaxf(fabsf(rr), fabsf(ri));
+    const float sc = op_scale(2.0f * wave_max(rr != rr || ri != ri ? __builtin_inff() : am));
+    lds.rho[wv][lane] = make_float2(rr * sc, ri * sc);
+    lds.top[wv][lane] = ltop;
+    const float inv = kGDown / sc;
+    if (wv == 0) {
+      lds.A[lane] = r.A;
+      lds.C[lane] = r.C;
+      const float x = xs * dwn;
+      lds.uw[lane] = make_float4(r.u, r.w, r.c1, x);
+      lds.x[lane] = as_u32(__builtin_convertvector((f2_t{x, x}), h2_t));
+    }
+    load(gi + gs < n_groups ? gi + gs : gi);
+    for (int c = wv; c < 16 * steps; c += 4) {
+      const double m = lds.mb[c];
+      const float mr = static_cast<float>(m);
+      const double q2 = fma(r.C, m * m, kMagic);
+      float cp, sp, cn, sn;
+      phasor(fma(r.B, m, q2), cp, sp);
+      phasor(fma(-r.B, m, q2), cn, sn);
+      const float tp = taper(r.c1, fmaf(-r.w, mr, r.v), top, kGUp);
+      const float tm = taper(r.c1, fmaf(r.w, mr, r.v), top, kGUp);
+      h2_t hi, lo;
+      // conj(b): B1 = (re, im), B2 = (-im, re)
+      split2(tp * cp, tp * sp, hi, lo);
+      lds.col[0][0][c][lane] = as_u32(hi);
+      lds.col[0][1][c][lane] = as_u32(lo);
+      lds.col[0][2][c][lane] = as_u32(h2_t{-hi[1], hi[0]});
+      lds.col[0][3][c][lane] = as_u32(h2_t{-lo[1], lo[0]});
+      split2(tm * cn, tm * sn, hi, lo);
+      lds.col[1][0][c][lane] = as_u32(hi);
+      lds.col[1][1][c][lane] = as_u32(lo);
+      lds.col[1][2][c][lane] = as_u32(h2_t{-hi[1], hi[0]});
+      lds.col[1][3][c][lane] = as_u32(h2_t{-lo[1], lo[0]});
+    }
+    __syncthreads();
+    if (active) {
+      float cc[kWgSteps][4], cs[kWgSteps][4];
+#pragma unroll
+      for (int c = 0; c < kWgSteps; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          phasor_fine(fma(w0, kp[c][i], kMagicFine), cc[c][i], cs[c][i]);
+          cc[c][i] *= inv;
+          cs[c][i] *= inv;
+        }
+      const double l = lds.la[wv * kWgRows + r16], l2 = l * l;
+      const float lr = static_cast<float>(l);
+      const uint4* x = reinterpret_cast<const uint4*>(&lds.x[4 * quad]);
+      const uint4* b = reinterpret_cast<const uint4*>(&lds.col[0][0][r16][4 * quad]);
+      const GRow row{lr, l, l2, lds.uw, lds.A, lds.C, lds.rho[wv], lds.top[wv]};
+      if (ser == 0)
+        adj_gauss_group<0>(row, quad, b, x, cc, cs, et, steps, g);
+      else if (ser == 1)
+        adj_gauss_group<1>(row, quad, b, x, cc, cs, et, steps, g);
+      else
+        adj_gauss_group<2>(row, quad, b, x, cc, cs, et, steps, g);
+    }
+    __syncthreads();
+  }
+  if (!active) return;
+#pragma unroll
+  for (int c = 0; c < kWgSteps; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      part[blockIdx.x * cells + cell0 - cbase + (16 * c + r16) * kWgRows + quad * 4 + i] =
+          make_float4(g[0][c][i], g[1][c][i], g[2][c][i], g[3][c][i]);
+}
+
+// Per-slot constants of a Gaussian layer (coordinates negated where w < 0).
+__global__ void k_wg_slots_gauss(const int32_t* __restrict__ order, const double* __restrict__ vu,
+                                 const double* __restrict__ vv, const double* __restrict__ vw,
+                                 double sigma, int64_t n, WgVisG* __restrict__ rec) {
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  WgVisG r = {};
+  const int32_t o = order[t];
+  if (o >= 0) {
+    const int32_t k = o >> 1;
+    const double sg = o & 1 ? -1.0 : 1.0;
+    const double u = sg * vu[k], v = sg * vv[k], w = sg * vw[k];
+    const double s2 = sigma * sigma, s = w * s2, D = 1.0 / (1.0 + s * s);
+    r.A = -D * u;
+    r.B = -D * v;
+    r.C = 0.5 * D * w;
+    r.u = static_cast<float>(u);
+    r.v = static_cast<float>(v);
+    r.w = static_cast<float>(w);
+    r.c1 = static_cast<float>(-M_PI * s2 * D * 1.4426950408889634);
+    const double e = -0.5 * D * w * s2 * s2 * (u * u + v * v);
+    r.e0 = static_cast<float>(e - rint(e));
+    r.D = static_cast<float>(D);
+    r.Ds = static_cast<float>(D * s);
+  }
+  rec[t] = r;
+}
+
 // Chunk sums of every cell, combined into its sign slots (row 0 of the adjoint
-// partials).
+// partials); GAUSS: they are the slots' sums themselves.
+template <bool GAUSS>
 __global__ __launch_bounds__(kBlock) void k_wg_adj_reduce(const float4* __restrict__ part,
                                                           int n_chunks, int64_t cells,
                                                           const int4* __restrict__ slot,
@@ -929,6 +1598,13 @@ __global__ __launch_bounds__(kBlock) void k_wg_adj_reduce(const float4* __restri
   const float g2 = (a[0].y + a[1].y) + (a[2].y + a[3].y);
   const float g3 = (a[0].z + a[1].z) + (a[2].z + a[3].z);
   const float g4 = (a[0].w + a[1].w) + (a[2].w + a[3].w);
+  if constexpr (GAUSS) {
+    if (s.x >= 0) out[s.x] = g1;
+    if (s.y >= 0) out[s.y] = g2;
+    if (s.z >= 0) out[s.z] = g3;
+    if (s.w >= 0) out[s.w] = g4;
+    return;
+  }
   if (s.x >= 0) out[s.x] = g1 - g2 - g3 - g4;
   if (s.y >= 0) out[s.y] = g1 + g2 - g3 + g4;
   if (s.z >= 0) out[s.z] = g1 + g2 + g3 - g4;
@@ -948,7 +1624,7 @@ __global__ void k_wg_adj_prep(const float2* __restrict__ r, const int32_t* __res
     const int64_t k = o >> 1;
     const float gr = gain ? gain[2 * k] : 1.0f, gi = gain ? gain[2 * k + 1] : 0.0f;
     const float2 v = r[k];
-    write_res<float>(rres, layerDs, n_layers, n_vis, 1, k, 0, gr, gi, v.x, v.y);
+    if (rres) write_res<float>(rres, layerDs, n_layers, n_vis, 1, k, 0, gr, gi, v.x, v.y);
     const float ci = gr * v.y - gi * v.x;
     z = make_float2(gr * v.x + gi * v.y, o & 1 ? -ci : ci);
   }
@@ -962,36 +1638,59 @@ inline unsigned blocks1(int64_t n) { return static_cast<unsigned>((n + kBlock - 
 
 hipError_t launch_wg_setup(sl1m_plan* p, hipStream_t st) {
   const int64_t n = static_cast<int64_t>(p->wg_groups) * kWgVis;
-  if (!p->wg || n == 0) return hipSuccess;
+  if (p->wg_n == 0 || n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_wg_slots, dim3(blocks1(n)), dim3(kBlock), 0, st, p->wg_order, p->wg_w0,
                      p->vu, p->vv, p->vw, n, p->wg_su, p->wg_sv, p->wg_dw);
+  for (int i = 0; i < p->wg_n; ++i) {
+    const GridSeg& g = p->grid_segs[i];
+    if (g.kind != SL1M_PIX_DELTA)
+      hipLaunchKernelGGL(k_wg_slots_gauss, dim3(blocks1(n)), dim3(kBlock), 0, st, p->wg_order,
+                         p->vu, p->vv, p->vw, p->layer_sigma[g.layer], n,
+                         p->wg_recg + g.layer * n);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_wg_forward(sl1m_plan* p, const void* xp, hipStream_t st) {
-  return timed(p, T_GRID_FWD_DELTA, st, [&] {
-    hipLaunchKernelGGL(k_wg_fwd,
-                       dim3(static_cast<unsigned>(p->wg_chunks), static_cast<unsigned>(p->wg_macros)),
-                       dim3(kBlock), 0, st, p->wg_mac, static_cast<const float*>(xp),
-                       static_cast<const float*>(p->pscale),
-                       reinterpret_cast<const int4*>(p->wg_slot), p->wg_nu, p->wg_eta, p->wg_la,
-                       p->wg_mb, p->wg_su, p->wg_sv, p->wg_dw, p->wg_w0, p->wg_h, p->wg_count,
-                       p->wg_groups, static_cast<float2*>(p->fpart));
+hipError_t launch_wg_forward(sl1m_plan* p, const GridSeg& g, const void* xp, hipStream_t st) {
+  const WgSeg& s = p->wg_segs[&g - p->grid_segs.data()];
+  const dim3 grid(static_cast<unsigned>(wg_chunks(s.macros, p->wg_groups)),
+                  static_cast<unsigned>(s.macros));
+  const float* x = static_cast<const float*>(xp);
+  const float* scale = static_cast<const float*>(p->pscale);
+  const int4* slot = reinterpret_cast<const int4*>(p->wg_slot);
+  float2* rows = static_cast<float2*>(p->fpart);
+  if (g.kind == SL1M_PIX_DELTA)
+    return timed(p, T_GRID_FWD_DELTA, st, [&] {
+      hipLaunchKernelGGL(k_wg_fwd, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, x, scale, slot,
+                         p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb, p->wg_su, p->wg_sv, p->wg_dw,
+                         p->wg_w0, p->wg_h, p->wg_count, p->wg_groups, rows);
+      return hipGetLastError();
+    });
+  return timed(p, T_GRID_FWD_GAUSS, st, [&] {
+    hipLaunchKernelGGL(k_wg_fwd_gauss, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, x, scale,
+                       slot, p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb,
+                       p->wg_recg + static_cast<int64_t>(g.layer) * p->wg_groups * kWgVis,
+                       p->wg_dw, p->wg_w0, p->wg_h, p->wg_count, p->wg_groups, rows);
     return hipGetLastError();
   });
+}
+
+// Residual records by visibility are for the segments outside the groups.
+static float2* rres_of(const sl1m_plan* p) {
+  return p->wg_n < static_cast<int>(p->segs.size()) ? static_cast<float2*>(p->rres) : nullptr;
 }
 
 hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, bool recs,
                                     hipStream_t st) {
   const int64_t slots = static_cast<int64_t>(p->wg_groups) * kWgVis;
-  const int nfc = p->grid_segs[p->wg_seg].nfc;
-  const float2* rows = static_cast<const float2*>(fwd_rows1(p)) + nfc * p->n_vis;
+  const int skip = wg_skipped_rows(p);
+  const float2* rows = static_cast<const float2*>(fwd_rows1(p)) + skip * p->n_vis;
   hipLaunchKernelGGL(k_wg_fwd_reduce, dim3(blocks1(slots)), dim3(kBlock), 0, st,
                      static_cast<const float2*>(p->fpart), p->wg_macros, slots, p->wg_order, rows,
-                     forward_rows(p, 1) - nfc, p->n_vis, static_cast<const float*>(p->vgain),
+                     forward_rows(p, 1) - skip, p->n_vis, static_cast<const float*>(p->vgain),
                      static_cast<const float2*>(data), static_cast<float2*>(out),
-                     recs ? static_cast<float2*>(p->rres) : nullptr,
-                     static_cast<const float*>(p->layerDs), p->n_layers, p->wg_res);
+                     recs ? rres_of(p) : nullptr, static_cast<const float*>(p->layerDs),
+                     p->n_layers, recs ? p->wg_res : nullptr);
   return hipGetLastError();
 }
 
@@ -999,25 +1698,37 @@ hipError_t launch_wg_adjoint_prep(sl1m_plan* p, const void* r, hipStream_t st) {
   const int64_t slots = static_cast<int64_t>(p->wg_groups) * kWgVis;
   hipLaunchKernelGGL(k_wg_adj_prep, dim3(blocks1(slots)), dim3(kBlock), 0, st,
                      static_cast<const float2*>(r), p->wg_order, slots, p->n_vis,
-                     static_cast<const float*>(p->vgain), p->wg_res,
-                     static_cast<float2*>(p->rres), static_cast<const float*>(p->layerDs),
-                     p->n_layers);
+                     static_cast<const float*>(p->vgain), p->wg_res, rres_of(p),
+                     static_cast<const float*>(p->layerDs), p->n_layers);
   return hipGetLastError();
 }
 
-hipError_t launch_wg_adjoint(sl1m_plan* p, hipStream_t st) {
-  hipError_t e = timed(p, T_GRID_ADJ_DELTA, st, [&] {
-    hipLaunchKernelGGL(k_wg_adj,
-                       dim3(static_cast<unsigned>(p->wg_chunks), static_cast<unsigned>(p->wg_macros)),
-                       dim3(kBlock), 0, st, p->wg_mac, p->wg_res, p->wg_nu, p->wg_eta, p->wg_la,
-                       p->wg_mb, p->wg_su, p->wg_sv, p->wg_dw, p->wg_w0, p->wg_h, p->wg_groups,
-                       p->wg_cells, p->wg_part);
+hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st) {
+  const WgSeg& s = p->wg_segs[&g - p->grid_segs.data()];
+  const int chunks = wg_chunks(s.macros, p->wg_groups);
+  const dim3 grid(static_cast<unsigned>(chunks), static_cast<unsigned>(s.macros));
+  const int4* slot = reinterpret_cast<const int4*>(p->wg_slot) + s.cell0;
+  const bool delta = g.kind == SL1M_PIX_DELTA;
+  hipError_t e = timed(p, delta ? T_GRID_ADJ_DELTA : T_GRID_ADJ_GAUSS, st, [&] {
+    if (delta)
+      hipLaunchKernelGGL(k_wg_adj, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, p->wg_res,
+                         p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb, p->wg_su, p->wg_sv, p->wg_dw,
+                         p->wg_w0, p->wg_h, p->wg_groups, s.cell0, s.cells, p->wg_part);
+    else
+      hipLaunchKernelGGL(k_wg_adj_gauss, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, p->wg_res,
+                         p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb,
+                         p->wg_recg + static_cast<int64_t>(g.layer) * p->wg_groups * kWgVis,
+                         p->wg_dw, p->wg_w0, p->wg_h, p->wg_groups, s.cell0, s.cells, p->wg_part);
     return hipGetLastError();
   });
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_wg_adj_reduce, dim3(blocks1(p->wg_cells)), dim3(kBlock), 0, st, p->wg_part,
-                     p->wg_chunks, p->wg_cells, reinterpret_cast<const int4*>(p->wg_slot),
-                     static_cast<float*>(p->apart));
+  float* out = static_cast<float*>(p->apart);
+  if (delta)
+    hipLaunchKernelGGL(k_wg_adj_reduce<false>, dim3(blocks1(s.cells)), dim3(kBlock), 0, st,
+                       p->wg_part, chunks, s.cells, slot, out);
+  else
+    hipLaunchKernelGGL(k_wg_adj_reduce<true>, dim3(blocks1(s.cells)), dim3(kBlock), 0, st,
+                       p->wg_part, chunks, s.cells, slot, out);
   return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""Group evaluation of delta grids (visibilities in groups of nearly one w, the sums on
+"""Group evaluation of grids (visibilities in groups of nearly one w, the sums on
 the matrix cores): operators against the FP64 oracle at the FP32 operator tolerance and
 the element-wise bound (tests/elementwise.py), at the sizes where its tiles (16 |l|
 values by 32 |m| values, four tiles to a block), its groups (64 visibilities, tiles of
@@ -100,3 +100,60 @@ def test_scales_zeros_and_non_finite():
     r[7] = np.nan
     assert not np.isfinite(plan.forward(x).cpu().numpy()).any()
     assert not np.isfinite(plan.adjoint(r).cpu().numpy()).any()
+
+
+# name: |l| x |m| pixels, spacing, sigma (spacings), kind, visibilities, w spread, with a
+# delta grid of twice the resolution
+GAUSS = {
+    "no_series": (40, 40, 1e-3, 2.0, W.PIX_GAUSS_WIDE, 1000, 5.0, False),
+    "paraxial_odd": (33, 35, 2e-3, 1.0, W.PIX_GAUSS_PARAXIAL, 65, 20.0, False),
+    "one_order": (64, 130, 4e-3, 1.0, W.PIX_GAUSS_WIDE, 2047, 12.0, False),
+    "wide": (48, 48, 1.2e-2, 0.5, W.PIX_GAUSS_WIDE, 2500, 40.0, False),
+    "layer_and_delta": (34, 40, 8e-3, 1.0, W.PIX_GAUSS_WIDE, 3001, 60.0, True),
+    "steep_taper": (40, 40, 5e-3, 3.0, W.PIX_GAUSS_WIDE, 1500, 60.0, False),
+}
+
+
+def _gauss_case(name):
+    nl, nm, d, sig, kind, nv, ws, delta = GAUSS[name]
+    seed = 70 + sorted(GAUSS).index(name)
+    wl = W.small_random(seed, 10, nv, uv_radius=300.0, w_sigma=ws, with_gains=True)
+    l, m = _grid(nl, nm, d)
+    wl.sigma, wl.kind = np.full(l.size, sig * d), np.full(l.size, kind, np.uint8)
+    if delta:
+        l2, m2 = _grid(2 * nl, 2 * nm, d / 2)
+        wl.sigma = np.concatenate([np.zeros(l2.size), wl.sigma])
+        wl.kind = np.concatenate([np.zeros(l2.size, np.uint8), wl.kind])
+        l, m = np.concatenate([l2, l]), np.concatenate([m2, m])
+    wl.l, wl.m, wl.x_true = l, m, None
+    rng = np.random.default_rng(seed)
+    return wl, rng.standard_normal(l.size), (rng.standard_normal(nv)
+                                             + 1j * rng.standard_normal(nv))
+
+
+@pytest.mark.parametrize("name", list(GAUSS))
+def test_group_gaussians(name):
+    print(f"[case] gaussian groups {name}", flush=True)
+    wl, x, r = _gauss_case(name)
+    p = O.Problem.from_workload(wl)
+    Vo, go = O.forward(p, x), O.adjoint(p, r)
+    plan = sl1m.Plan.from_workload(wl)
+    V, g = plan.forward(x).cpu().numpy(), plan.adjoint(r).cpu().numpy()
+    wf = E.worst_ratio(V, Vo, E.abs_forward_rows(p, x), wl.n_pix)
+    wa = E.worst_ratio(g, go, E.abs_adjoint_cols(p, r), wl.n_vis)
+    print(f"    forward {rel(V, Vo):.3e} adjoint {rel(g, go):.3e} element-wise {wf:.3e} {wa:.3e}",
+          flush=True)
+    assert rel(V, Vo) <= TOL and rel(g, go) <= TOL
+    assert wf <= 1.0 and wa <= 1.0
+    # one pixel, far from the largest taper of its tile: its entries alone
+    j = wl.n_pix - 1
+    e = np.zeros(wl.n_pix)
+    e[j] = 1.0
+    V1, Vo1 = plan.forward(e).cpu().numpy(), O.forward(p, e)
+    assert rel(V1, Vo1) <= TOL
+    # the same bits again; a NaN reaches every output
+    assert np.array_equal(plan.forward(x).cpu().numpy(), V)
+    assert np.array_equal(plan.adjoint(r).cpu().numpy(), g)
+    x[-1], r[-1] = np.nan, np.nan
+    assert not np.isfinite(plan.forward(x).cpu().numpy()).any()
+    assert not np.isfinite(plan.adjoint(r).cpu().numpy()[wl.kind != 0]).any()
