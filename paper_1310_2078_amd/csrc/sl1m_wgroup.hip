@@ -5,6 +5,7 @@
 
 #include "sl1m_device.h"
 #include "sl1m_wgroup.h"
+#include "sl1m_wgroup_dev.h"
 
 namespace sl1m {
 
@@ -176,53 +177,7 @@ namespace {
 
 using namespace dev;
 
-typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
-typedef float f2_t __attribute__((ext_vector_type(2)));
-typedef float f4_t __attribute__((ext_vector_type(4)));
-
-constexpr float kTwoPi = 6.28318530717958648f;
 constexpr int kParts = 5;  // column operand: hi, lo, x hi, x lo, x^2 / 2 (x = 2 pi s dw)
-
-// exp(2 pi i a b) with the phase kept to 2^-24 turn (phasor: 2^-23) from FP64
-// kMagicFine = kMagic / 2 on: two more instructions, for C_0, whose phase every
-// entry of a group shares.
-constexpr double kMagicFine = 0.5 * kMagic;
-__device__ __forceinline__ void phasor_fine(double t, float& c, float& s) {
-  const int32_t f = static_cast<int32_t>(static_cast<uint32_t>(__double2loint(t)) << 8);
-  const float p = static_cast<float>(f) * 0x1.0p-32f;
-  s = __builtin_amdgcn_sinf(p);
-  c = __builtin_amdgcn_cosf(p);
-}
-
-// value = hi + lo in float16 (hi rounded to nearest, lo the rounded rest)
-__device__ __forceinline__ void split2(float p, float q, h2_t& hi, h2_t& lo) {
-  hi = __builtin_convertvector((f2_t{p, q}), h2_t);
-  lo = __builtin_convertvector(
-      (f2_t{p - static_cast<float>(hi[0]), q - static_cast<float>(hi[1])}), h2_t);
-}
-
-struct Op8 {
-  h2_t v[4];
-  __device__ __forceinline__ h8_t vec() const { return __builtin_bit_cast(h8_t, *this); }
-};
-
-__device__ __forceinline__ void split8(const float (&p)[8], Op8& hi, Op8& lo) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) split2(p[2 * j], p[2 * j + 1], hi.v[j], lo.v[j]);
-}
-
-__device__ __forceinline__ f4_t mma(h8_t a, h8_t b, f4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ h8_t as_h8(uint4 v) { return __builtin_bit_cast(h8_t, v); }
-__device__ __forceinline__ uint32_t as_u32(h2_t v) { return __builtin_bit_cast(uint32_t, v); }
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
 
 // Sums over the quads; lane L ends with visibility L.
 __device__ __forceinline__ void quad_sum(const float (&vr)[4], const float (&vi)[4], int lane,
@@ -940,23 +895,6 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
 // 100,003: 0.47 / 0.54 ms against 1.33 / 1.53.
 // ---------------------------------------------------------------------------
 
-// log2 of the largest taper over +-[lo, hi] at baseline coordinate d
-__device__ __forceinline__ float taper_top(float c1, float d, float w, float lo, float hi) {
-  const float a = fmaf(-w, lo, d), b = fmaf(-w, hi, d), e = fmaf(w, lo, d), f = fmaf(w, hi, d);
-  const float p = a * b <= 0.0f ? 0.0f : fminf(fabsf(a), fabsf(b));
-  const float q = e * f <= 0.0f ? 0.0f : fminf(fabsf(e), fabsf(f));
-  const float m = fminf(p, q);
-  return c1 * (m * m);
-}
-
-// up 2^(c1 d^2 - top), at most up (padded positions may lie above the top).  Columns
-// stand kGUp high: tapers down to 2^-28 of the largest are normal float16.  (The factor
-// in the exponent would cost the exponent four bits.)
-constexpr float kGUp = 0x1.0p14f, kGDown = 0x1.0p-14f;
-__device__ __forceinline__ float taper(float c1, float d, float top, float up) {
-  return up * __builtin_amdgcn_exp2f(fminf(fmaf(c1, d * d, -top), 0.0f));
-}
-
 struct alignas(16) FwdGLds {
   uint4 col[kWgCols / 2 * 4 * 64];  // [two columns][B1 hi, lo, B2 hi, lo][visibility]
   double la[4 * kWgRows], mb[kWgCols], A[kWgVis], C[kWgVis];
@@ -1570,34 +1508,51 @@ __global__ void k_wg_slots_gauss(const int32_t* __restrict__ order, const double
 }
 
 // Chunk sums of every cell, combined into its sign slots (row 0 of the adjoint
-// partials); GAUSS: they are the slots' sums themselves.
+// partials); GAUSS: they are the slots' sums themselves.  A block takes 16 cells, 16
+// threads each every 16th chunk: small segments have few cells and many chunks (one
+// thread a cell: 32 x 32 x 2,000 9.8 us, now 3.5; 64 x 64 pixels in 795 chunks 156 us, now
+// 6; the adjoint of 256 x 256 pixels with three layers x 50,000 718, now 433).
+constexpr int kRedCells = 16, kRedSlices = kBlock / kRedCells;
 template <bool GAUSS>
 __global__ __launch_bounds__(kBlock) void k_wg_adj_reduce(const float4* __restrict__ part,
                                                           int n_chunks, int64_t cells,
                                                           const int4* __restrict__ slot,
                                                           float* __restrict__ out) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  if (q >= cells) return;
+  __shared__ float4 sh[kRedSlices][kRedCells];
+  const int tid = static_cast<int>(threadIdx.x), ci = tid % kRedCells, sl = tid / kRedCells;
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * kRedCells + ci;  // cells: a multiple of 16
+  float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b = a;
+  for (int c = sl; c < n_chunks; c += 2 * kRedSlices) {
+    const float4 v = part[c * cells + q];
+    a.x += v.x;
+    a.y += v.y;
+    a.z += v.z;
+    a.w += v.w;
+    if (c + kRedSlices < n_chunks) {
+      const float4 w = part[(c + kRedSlices) * cells + q];
+      b.x += w.x;
+      b.y += w.y;
+      b.z += w.z;
+      b.w += w.w;
+    }
+  }
+  sh[sl][ci] = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+  __syncthreads();
+  // threads of a cell: component sl % 4, slices sl / 4, sl / 4 + 4, ..
+  const float* f = &sh[0][0].x;
+  float v = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v += f[((sl / 4 + 4 * i) * kRedCells + ci) * 4 + sl % 4];
+  __syncthreads();
+  float* w = &sh[0][0].x;
+  w[(sl / 4 * kRedCells + ci) * 4 + sl % 4] = v;
+  __syncthreads();
+  if (sl != 0) return;
   const int4 s = slot[q];
-  if (s.x < 0 && s.y < 0 && s.z < 0 && s.w < 0) return;
-  // four running sums: shorter chains of float32 roundings, four loads in flight
-  float4 a[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) a[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  for (int c = 0; c < n_chunks; c += 4)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (c + i < n_chunks) {
-        const float4 v = part[(c + i) * cells + q];
-        a[i].x += v.x;
-        a[i].y += v.y;
-        a[i].z += v.z;
-        a[i].w += v.w;
-      }
-  const float g1 = (a[0].x + a[1].x) + (a[2].x + a[3].x);
-  const float g2 = (a[0].y + a[1].y) + (a[2].y + a[3].y);
-  const float g3 = (a[0].z + a[1].z) + (a[2].z + a[3].z);
-  const float g4 = (a[0].w + a[1].w) + (a[2].w + a[3].w);
+  const float g1 = (sh[0][ci].x + sh[1][ci].x) + (sh[2][ci].x + sh[3][ci].x);
+  const float g2 = (sh[0][ci].y + sh[1][ci].y) + (sh[2][ci].y + sh[3][ci].y);
+  const float g3 = (sh[0][ci].z + sh[1][ci].z) + (sh[2][ci].z + sh[3][ci].z);
+  const float g4 = (sh[0][ci].w + sh[1][ci].w) + (sh[2][ci].w + sh[3][ci].w);
   if constexpr (GAUSS) {
     if (s.x >= 0) out[s.x] = g1;
     if (s.y >= 0) out[s.y] = g2;
@@ -1631,6 +1586,8 @@ __global__ void k_wg_adj_prep(const float2* __restrict__ r, const int32_t* __res
   res[t] = z;
 }
 
+
+static_assert(kWgCells % kRedCells == 0, "whole blocks of cells");
 
 inline unsigned blocks1(int64_t n) { return static_cast<unsigned>((n + kBlock - 1) / kBlock); }
 
@@ -1723,11 +1680,12 @@ hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st) {
   });
   if (e != hipSuccess) return e;
   float* out = static_cast<float*>(p->apart);
+  const dim3 rb(static_cast<unsigned>(s.cells / kRedCells));
   if (delta)
-    hipLaunchKernelGGL(k_wg_adj_reduce<false>, dim3(blocks1(s.cells)), dim3(kBlock), 0, st,
+    hipLaunchKernelGGL(k_wg_adj_reduce<false>, rb, dim3(kBlock), 0, st,
                        p->wg_part, chunks, s.cells, slot, out);
   else
-    hipLaunchKernelGGL(k_wg_adj_reduce<true>, dim3(blocks1(s.cells)), dim3(kBlock), 0, st,
+    hipLaunchKernelGGL(k_wg_adj_reduce<true>, rb, dim3(kBlock), 0, st,
                        p->wg_part, chunks, s.cells, slot, out);
   return hipGetLastError();
 }

@@ -1,0 +1,76 @@
+// Device helpers of the group evaluation (sl1m_wgroup.h): float16 operands split from
+// float32, phasors, tapers.
+#pragma once
+
+#include "sl1m_device.h"
+#include "sl1m_wgroup.h"
+
+namespace sl1m {
+namespace dev {
+
+typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
+typedef float f2_t __attribute__((ext_vector_type(2)));
+typedef float f4_t __attribute__((ext_vector_type(4)));
+
+constexpr float kTwoPi = 6.28318530717958648f;
+
+// exp(2 pi i a b) with the phase kept to 2^-24 turn (phasor: 2^-23) from FP64
+// kMagicFine = kMagic / 2 on: two more instructions, for C_0, whose phase every
+// entry of a group shares.
+constexpr double kMagicFine = 0.5 * kMagic;
+__device__ __forceinline__ void phasor_fine(double t, float& c, float& s) {
+  const int32_t f = static_cast<int32_t>(static_cast<uint32_t>(__double2loint(t)) << 8);
+  const float p = static_cast<float>(f) * 0x1.0p-32f;
+  s = __builtin_amdgcn_sinf(p);
+  c = __builtin_amdgcn_cosf(p);
+}
+
+// value = hi + lo in float16 (hi rounded to nearest, lo the rounded rest)
+__device__ __forceinline__ void split2(float p, float q, h2_t& hi, h2_t& lo) {
+  hi = __builtin_convertvector((f2_t{p, q}), h2_t);
+  lo = __builtin_convertvector(
+      (f2_t{p - static_cast<float>(hi[0]), q - static_cast<float>(hi[1])}), h2_t);
+}
+
+struct Op8 {
+  h2_t v[4];
+  __device__ __forceinline__ h8_t vec() const { return __builtin_bit_cast(h8_t, *this); }
+};
+
+__device__ __forceinline__ void split8(const float (&p)[8], Op8& hi, Op8& lo) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) split2(p[2 * j], p[2 * j + 1], hi.v[j], lo.v[j]);
+}
+
+__device__ __forceinline__ f4_t mma(h8_t a, h8_t b, f4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ h8_t as_h8(uint4 v) { return __builtin_bit_cast(h8_t, v); }
+__device__ __forceinline__ uint32_t as_u32(h2_t v) { return __builtin_bit_cast(uint32_t, v); }
+
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  return v;
+}
+
+// log2 of the largest taper over +-[lo, hi] at baseline coordinate d
+__device__ __forceinline__ float taper_top(float c1, float d, float w, float lo, float hi) {
+  const float a = fmaf(-w, lo, d), b = fmaf(-w, hi, d), e = fmaf(w, lo, d), f = fmaf(w, hi, d);
+  const float p = a * b <= 0.0f ? 0.0f : fminf(fabsf(a), fabsf(b));
+  const float q = e * f <= 0.0f ? 0.0f : fminf(fabsf(e), fabsf(f));
+  const float m = fminf(p, q);
+  return c1 * (m * m);
+}
+
+// up 2^(c1 d^2 - top), at most up (padded positions may lie above the top).  Columns
+// stand kGUp high: tapers down to 2^-28 of the largest are normal float16.  (The factor
+// in the exponent would cost the exponent four bits.)
+constexpr float kGUp = 0x1.0p14f, kGDown = 0x1.0p-14f;
+__device__ __forceinline__ float taper(float c1, float d, float top, float up) {
+  return up * __builtin_amdgcn_exp2f(fminf(fmaf(c1, d * d, -top), 0.0f));
+}
+
+}  // namespace dev
+}  // namespace sl1m
