@@ -58,7 +58,6 @@ struct Analysis {
   // follow one another
   int wg_n = 0;
   int64_t wg_cap = 0;          // visibility groups the workspace holds
-  WgPlan wgp;
 };
 
 sl1m_status d2h(void* dst, const void* src, size_t bytes, const char* what) {
@@ -174,13 +173,12 @@ size_t plan_total(const Analysis& a);
 void choose_groups(Analysis& a) {
   const size_t without = plan_total(a);
   int n = 0;
+  int64_t total = 0;
   for (const GridSeg& g : a.gsegs) {
     const int64_t padded = wg_padded(g);
     if (g.seg != a.gsegs[0].seg + n || padded > 4 * static_cast<int64_t>(g.na) * g.nb) break;
-    if (static_cast<int64_t>(a.wgp.nu.size()) + 2 * padded > INT32_MAX) break;
-    wg_build_tiles(g, a.grid_la.data() + g.la_off, a.grid_mb.data() + g.mb_off,
-                   (g.kind == SL1M_PIX_DELTA ? a.grid_c3 : a.grid_c4).data() + g.cell_off,
-                   a.grid_slot.data() + 4 * g.cell_off, a.wgp);
+    total += wg_max_cells(g);
+    if (total > INT32_MAX) break;
     ++n;
   }
   if (n == 0) return;
@@ -552,7 +550,7 @@ struct Layout {
       grid_mb, grid_c3, grid_c4, grid_slot, grid_rec, grid_fc, grid_pb, grid_segs, grid_gb,
       grid_prec, grid_precm, mx, mr, mred, grid_mfma_b, grid_mfma_nu, phl, vhl,
       wg_mac, wg_la, wg_mb, wg_nu, wg_eta, wg_slot, wg_order, wg_count, wg_su, wg_sv, wg_dw, wg_w0,
-      wg_h, wg_part, wg_res, wg_recg, total;
+      wg_h, wg_part, wg_res, wg_recg, wg_alpha, wg_beta, total;
 };
 
 // `wg_n`: grid segments in the group evaluation
@@ -595,12 +593,13 @@ Layout layout(const Analysis& a, int wg_n) {
   const size_t grid_rows = a.grid ? a.grid_fc.size() + a.fd1.size() + a.fg1.size() : 0;
   // group evaluation: a row of slots per macro in place of the segment's rows
   const size_t slots = wg_n ? static_cast<size_t>(a.wg_cap) * kWgVis : 0;
-  size_t wg_rows = grid_rows * nv, wg_macros = 0, wg_part = 0;
+  size_t wg_rows = grid_rows * nv, wg_macros = 0, wg_part = 0, wg_cells = 0;
   for (int i = 0; i < wg_n; ++i) {
-    const WgSeg& s = a.wgp.segs[i];
-    wg_rows -= static_cast<size_t>(a.gsegs[i].nfc) * nv;
-    wg_macros += static_cast<size_t>(s.macros);
-    wg_part = std::max(wg_part, 16 * static_cast<size_t>(s.cells) * wg_chunk_cap(s.macros));
+    const GridSeg& g = a.gsegs[i];
+    wg_rows -= static_cast<size_t>(g.nfc) * nv;
+    wg_macros += static_cast<size_t>(wg_max_macros(g));
+    wg_cells += static_cast<size_t>(wg_max_cells(g));
+    wg_part = std::max(wg_part, wg_part_bytes(g));
   }
   wg_rows += wg_macros * slots;
   L.fpart = take(2 * rb *
@@ -646,14 +645,14 @@ Layout layout(const Analysis& a, int wg_n) {
   L.phl = take(hl ? sizeof(HLRec) * static_cast<size_t>(a.n_pix) : 0);
   L.vhl = take(hl ? sizeof(HLRec) * static_cast<size_t>(a.n_vis) : 0);
   if (wg_n) {
-    const WgPlan& t = a.wgp;
-    const size_t wc = t.nu.size();
-    L.wg_mac = take(sizeof(WgMacro) * t.macros.size());
-    L.wg_la = take(8 * t.la.size());
-    L.wg_mb = take(8 * t.mb.size());
-    L.wg_nu = take(8 * wc);
-    L.wg_eta = take(4 * wc);
-    L.wg_slot = take(16 * wc);
+    L.wg_mac = take(sizeof(WgMacro) * wg_macros);
+    L.wg_la = take(8 * 4 * kWgRows * wg_macros);
+    L.wg_mb = take(8 * kFlatCols * wg_macros);
+    L.wg_alpha = take(8 * 4 * kWgRows * wg_macros);
+    L.wg_beta = take(8 * kFlatCols * wg_macros);
+    L.wg_nu = take(8 * wg_cells);
+    L.wg_eta = take(4 * wg_cells);
+    L.wg_slot = take(16 * wg_cells);
     L.wg_order = take(4 * slots);
     L.wg_count = take(4 * static_cast<size_t>(a.wg_cap));
     L.wg_su = take(8 * slots);
@@ -879,15 +878,24 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
     int device = 0;
     SL1M_HIP(hipGetDevice(&device), "get device");
     WgGroups wgg;
+    WgPlan wgp;
     if (a.wg_n) {  // the visibilities by |w|
       std::vector<double> w(a.n_vis);
       SL1M_HIP(hipMemcpyAsync(w.data(), pr->w, a.n_vis * sizeof(double), hipMemcpyDeviceToHost, st),
                "read w");
       SL1M_HIP(hipStreamSynchronize(st), "read w");
+      double w_max = 0.0;
+      for (double x : w) w_max = std::max(w_max, std::fabs(x));
+      for (int i = 0; i < a.wg_n; ++i) {
+        const GridSeg& g = a.gsegs[i];
+        wg_build_tiles(g, a.grid_la.data() + g.la_off, a.grid_mb.data() + g.mb_off,
+                       (g.kind == SL1M_PIX_DELTA ? a.grid_c3 : a.grid_c4).data() + g.cell_off,
+                       a.grid_slot.data() + 4 * g.cell_off, w_max, wgp);
+      }
       while (a.wg_n) {
         wgg = WgGroups();
         float width = 0.0f;
-        for (int i = 0; i < a.wg_n; ++i) width = std::max(width, a.wgp.segs[i].width);
+        for (int i = 0; i < a.wg_n; ++i) width = std::max(width, wgp.segs[i].width);
         if (wg_build_groups(w, width, a.wg_cap, wgg)) break;
         a.wg_n = fewer_groups(a, a.wg_n);
       }
@@ -1005,7 +1013,7 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
 
     if (a.wg_n) {
       p->wg_n = a.wg_n;
-      p->wg_segs.assign(a.wgp.segs.begin(), a.wgp.segs.begin() + a.wg_n);
+      p->wg_segs.assign(wgp.segs.begin(), wgp.segs.begin() + a.wg_n);
       for (const WgSeg& s2 : p->wg_segs) p->wg_macros += s2.macros;
       p->wg_groups = static_cast<int>(wgg.w0.size());
       p->wg_recg = reinterpret_cast<WgVisG*>(w + L.wg_recg);
@@ -1014,6 +1022,8 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       p->wg_mb = reinterpret_cast<double*>(w + L.wg_mb);
       p->wg_nu = reinterpret_cast<double*>(w + L.wg_nu);
       p->wg_eta = reinterpret_cast<float*>(w + L.wg_eta);
+      p->wg_alpha = reinterpret_cast<double*>(w + L.wg_alpha);
+      p->wg_beta = reinterpret_cast<double*>(w + L.wg_beta);
       p->wg_slot = reinterpret_cast<int32_t*>(w + L.wg_slot);
       p->wg_count = reinterpret_cast<int32_t*>(w + L.wg_count);
       p->wg_res = reinterpret_cast<float2*>(w + L.wg_res);
@@ -1058,12 +1068,14 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st);
     };
     if (a.wg_n) {
-      const WgPlan& t = a.wgp;
+      const WgPlan& t = wgp;
       up(p->wg_mac, t.macros.data(), sizeof(WgMacro) * t.macros.size());
       up(p->wg_la, t.la.data(), 8 * t.la.size());
       up(p->wg_mb, t.mb.data(), 8 * t.mb.size());
       up(p->wg_nu, t.nu.data(), 8 * t.nu.size());
       up(p->wg_eta, t.eta.data(), 4 * t.eta.size());
+      up(p->wg_alpha, t.alpha.data(), 8 * t.alpha.size());
+      up(p->wg_beta, t.beta.data(), 8 * t.beta.size());
       up(p->wg_slot, t.slot.data(), 4 * t.slot.size());
       up(p->wg_order, wgg.order.data(), 4 * wgg.order.size());
       up(p->wg_count, wgg.count.data(), 4 * wgg.count.size());

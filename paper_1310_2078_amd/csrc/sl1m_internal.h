@@ -267,6 +267,7 @@ struct sl1m_plan {
   sl1m::WgVisG* wg_recg = nullptr;  // [layer][slot]
   sl1m::WgMacro* wg_mac = nullptr;
   double *wg_la = nullptr, *wg_mb = nullptr, *wg_nu = nullptr;
+  double *wg_alpha = nullptr, *wg_beta = nullptr;
   float* wg_eta = nullptr;
   int32_t* wg_slot = nullptr;
   int32_t *wg_order = nullptr, *wg_count = nullptr;

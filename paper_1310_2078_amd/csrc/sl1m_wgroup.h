@@ -42,6 +42,14 @@ constexpr float kWgXW = 1.5e-2f;
 constexpr float kWgX = 5.0e-2f;
 // Gaussian segments: no series below kWgXZ, one order below kWgXN, at most kWgXW.
 constexpr float kWgXZ = 5.0e-7f;
+// Segments that need no cell factor (sl1m_wflat.hip): tiles twice as wide; the largest
+// |2 pi w eta| of one: one order up to kFlatN, two up to kFlatX, in one float16 product
+// each.
+constexpr int kFlatSteps = 4;
+constexpr int kFlatCols = 16 * kFlatSteps;
+constexpr int kFlatCells = kWgRows * kFlatCols;
+constexpr float kFlatN = 6.0e-4f;
+constexpr float kFlatX = 2.5e-3f;
 
 // Up to four tiles (one per wavefront) of neighbouring rows over the same columns.
 struct WgMacro {
@@ -66,17 +74,19 @@ struct alignas(16) WgVisG {
 struct WgSeg {
   int32_t mac0, macros;
   int64_t cell0, cells;
+  int32_t flat;                // evaluated without cell factors (sl1m_wflat.hip)
   float width;                 // largest eta over its series limit
 };
 
 // Host-built tables of grid segments, one after the other.  Tile cells are numbered
-// column * kWgRows + row.
+// column * kWgRows + row, kWgCells or (flat segments) kFlatCells of a tile.
 struct WgPlan {
   std::vector<WgSeg> segs;
   std::vector<WgMacro> macros;
   std::vector<double> la, mb;      // row / column positions of the macros
   std::vector<double> nu;          // per tile cell: nu (delta) or kappa
   std::vector<float> eta;          // per tile cell, divided by the macro's s (below 1)
+  std::vector<double> alpha, beta; // flat segments: separable part at the positions
   std::vector<int32_t> slot;       // [4 per tile cell] permuted pixel or -1
 };
 
@@ -91,9 +101,14 @@ struct WgGroups {
 
 // cells evaluated for a segment, padding included
 int64_t wg_padded(const GridSeg& g);
-// appends a segment; `c`: nu or kappa per grid cell
+// macros and tile cells of a segment, the larger of both kinds of tiles
+int wg_max_macros(const GridSeg& g);
+int64_t wg_max_cells(const GridSeg& g);
+// bytes of the segment's adjoint chunk sums
+size_t wg_part_bytes(const GridSeg& g);
+// appends a segment; `c`: nu or kappa per grid cell, `w_max`: largest |w|
 void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c,
-                    const int32_t* slot, WgPlan& out);
+                    const int32_t* slot, double w_max, WgPlan& out);
 bool wg_build_groups(const std::vector<double>& w, float width, int64_t max_groups,
                      WgGroups& out);
 // groups a plan reserves room for
@@ -101,6 +116,8 @@ int64_t wg_group_cap(int64_t n_vis);
 // group chunks (blocks per macro) of the operator kernels, at most wg_chunk_cap()
 int wg_chunks(int macros, int groups);
 int wg_chunk_cap(int macros);
+int flat_chunks(int macros, int groups);
+int flat_chunk_cap(int macros);
 
 hipError_t launch_wg_setup(sl1m_plan* p, hipStream_t st);
 hipError_t launch_wg_forward(sl1m_plan* p, const GridSeg& g, const void* xp, hipStream_t st);
@@ -111,5 +128,10 @@ hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, b
 hipError_t launch_wg_adjoint_prep(sl1m_plan* p, const void* r, hipStream_t st);
 // the segment's gradient sums into row 0 of the adjoint partials (its only row)
 hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st);
+
+// sl1m_wflat.hip: flat segments (the adjoint: its chunk sums)
+hipError_t launch_flat_forward(sl1m_plan* p, const GridSeg& g, const WgSeg& s, const float* x,
+                               hipStream_t st);
+hipError_t launch_flat_adjoint(sl1m_plan* p, const GridSeg& g, const WgSeg& s, hipStream_t st);
 
 }  // namespace sl1m

@@ -39,86 +39,176 @@ int64_t wg_padded(const GridSeg& g) {
   return static_cast<int64_t>((g.na + kWgRows - 1) / kWgRows * kWgRows) * ((g.nb + 15) / 16 * 16);
 }
 
-// Row sets of kWgRows |l| values and column sets of up to kWgSteps steps of 16
-// |m| values, both spread evenly over the macros.
-void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c,
-                    const int32_t* slot, WgPlan& out) {
-  const int na = g.na, nb = g.nb;
+// Flat segments: one round of the blocks that stay resident (256 x 256 x 100,000: 210 /
+// 293 us, two rounds 222 / 305; 300 x 300 Gaussian pixels x 100,003: 302 / 435, two
+// rounds 316 / 446).
+int flat_chunk_cap(int macros) { return std::max(1, 512 / macros); }
+int flat_chunks(int macros, int groups) {
+  return std::max(1, std::min(groups, flat_chunk_cap(macros)));
+}
+
+namespace {
+
+// Macros and tile cells of a segment in tiles of up to `cs` column steps.
+struct WgShape {
+  int rsets, rmac, steps, cmac;
+  WgShape(const GridSeg& g, int cs)
+      : rsets((g.na + kWgRows - 1) / kWgRows), rmac((rsets + 3) / 4), steps((g.nb + 15) / 16),
+        cmac((steps + cs - 1) / cs) {}
+  int macros() const { return rmac * cmac; }
+  int64_t cells(int cs) const { return static_cast<int64_t>(rsets) * cmac * kWgRows * 16 * cs; }
+};
+
+// largest magnitude e as a power of two s: e / s in [1/2, 1), 1 for 0
+double pow2_of(double e) {
+  int ex = 0;
+  (void)std::frexp(e, &ex);
+  return e > 0.0 ? std::ldexp(1.0, ex) : 1.0;
+}
+
+// One segment's tables.  flat: c = alpha(l) + beta(m) + eta, exact along the macro's
+// middle row and column, each tile's eta centred by its rows' alpha; else c = nu_t + eta.
+// Row sets of kWgRows |l| values and column sets of up to `cs` steps of 16 |m| values,
+// both spread evenly over the macros.
+void append_segment(const GridSeg& g, const double* la, const double* mb, const double* c,
+                    const int32_t* slot, bool flat, WgPlan& out) {
+  const int na = g.na, nb = g.nb, cs = flat ? kFlatSteps : kWgSteps;
+  const size_t tile = static_cast<size_t>(kWgRows) * 16 * cs;
+  const WgShape sh(g, cs);
   WgSeg seg{};
   seg.mac0 = static_cast<int32_t>(out.macros.size());
   seg.cell0 = static_cast<int64_t>(out.nu.size());
+  seg.flat = flat ? 1 : 0;
   double seg_eta = 0.0;
-  const int rsets = (na + kWgRows - 1) / kWgRows, rmac = (rsets + 3) / 4;
-  const int steps = (nb + 15) / 16, cmac = (steps + kWgSteps - 1) / kWgSteps;
-  for (int ri = 0; ri < rmac; ++ri)
-    for (int ci = 0; ci < cmac; ++ci) {
-      const int r0 = rsets * ri / rmac, r1 = rsets * (ri + 1) / rmac;
-      const int s0 = steps * ci / cmac, s1 = steps * (ci + 1) / cmac;
+  auto cell = [&](int ia, int ib) {
+    return (static_cast<int64_t>(ib / kGridNB) * na + ia) * kGridNB + ib % kGridNB;
+  };
+  for (int ri = 0; ri < sh.rmac; ++ri)
+    for (int ci = 0; ci < sh.cmac; ++ci) {
+      const int r0 = sh.rsets * ri / sh.rmac, r1 = sh.rsets * (ri + 1) / sh.rmac;
+      const int s0 = sh.steps * ci / sh.cmac, s1 = sh.steps * (ci + 1) / sh.cmac;
+      const int a0 = kWgRows * r0, a1 = std::min(kWgRows * r1, na);
+      const int b0 = 16 * s0, b1 = std::min(16 * s1, nb);
       WgMacro m{};
       m.sets = r1 - r0;
       m.steps = s1 - s0;
       m.a_off = static_cast<int32_t>(out.la.size());
       m.b_off = static_cast<int32_t>(out.mb.size());
       m.cell_off = static_cast<int32_t>(out.nu.size());
-      for (int i = 0; i < 4 * kWgRows; ++i) {
-        const int ia = kWgRows * r0 + i;
-        out.la.push_back(i < kWgRows * m.sets && ia < na ? la[ia] : 0.0);
+      m.m_lo = static_cast<float>(mb[b0]);
+      m.m_hi = static_cast<float>(mb[b1 - 1]);
+      out.la.resize(out.la.size() + 4 * kWgRows, 0.0);
+      out.alpha.resize(out.la.size(), 0.0);
+      out.mb.resize(out.mb.size() + 16 * cs, 0.0);
+      out.beta.resize(out.mb.size(), 0.0);
+      double* const al = &out.alpha[m.a_off];
+      double* const be = &out.beta[m.b_off];
+      std::copy(la + a0, la + a1, &out.la[m.a_off]);
+      std::copy(mb + b0, mb + b1, &out.mb[m.b_off]);
+      if (flat) {
+        const int ic = (a0 + a1) / 2, jc = (b0 + b1) / 2;
+        for (int ia = a0; ia < a1; ++ia) al[ia - a0] = c[cell(ia, jc)] - c[cell(ic, jc)];
+        for (int ib = b0; ib < b1; ++ib) be[ib - b0] = c[cell(ic, ib)];
       }
-      for (int i = 0; i < kWgCols; ++i) {
-        const int ib = 16 * s0 + i;
-        out.mb.push_back(ib < 16 * s1 && ib < nb ? mb[ib] : 0.0);
-      }
-      m.m_lo = static_cast<float>(mb[16 * s0]);
-      m.m_hi = static_cast<float>(mb[std::min(16 * s1, nb) - 1]);
       double eta_max = 0.0;
       const size_t first = out.nu.size();
+      out.nu.resize(first + m.sets * tile, 0.0);
+      out.eta.resize(first + m.sets * tile, 0.0f);
+      out.slot.resize(4 * (first + m.sets * tile), -1);
+      std::vector<double> rest(m.sets * tile, 0.0);
       for (int w = 0; w < m.sets; ++w) {
-        const int a0 = kWgRows * (r0 + w), a1 = std::min(a0 + kWgRows, na);
-        const int b0 = 16 * s0, b1 = std::min(16 * s1, nb);
-        m.l_lo[w] = static_cast<float>(la[a0]);
-        m.l_hi[w] = static_cast<float>(la[a1 - 1]);
-        auto cell = [&](int ia, int ib) {
-          return (static_cast<int64_t>(ib / kGridNB) * na + ia) * kGridNB + ib % kGridNB;
-        };
+        const int t0 = a0 + kWgRows * w, t1 = std::min(t0 + kWgRows, na);
+        m.l_lo[w] = static_cast<float>(la[t0]);
+        m.l_hi[w] = static_cast<float>(la[t1 - 1]);
         double lo = 1e300, hi = -1e300;
         for (int ib = b0; ib < b1; ++ib)
-          for (int ia = a0; ia < a1; ++ia) {
-            const double v = c[cell(ia, ib)];
+          for (int ia = t0; ia < t1; ++ia) {
+            const double v = c[cell(ia, ib)] - al[ia - a0] - be[ib - b0];
             lo = std::min(lo, v);
             hi = std::max(hi, v);
           }
-        // the tile's reference as the kernels hold it (float32)
-        m.nu_t[w] = static_cast<float>(0.5 * (lo + hi));
+        // the tile's reference: in the rows' alpha, or as the kernels hold it (float32)
+        double mid = 0.5 * (lo + hi);
+        if (flat) {
+          for (int ia = t0; ia < t1; ++ia) al[ia - a0] += mid;
+          mid = 0.0;
+        }
+        m.nu_t[w] = static_cast<float>(mid);
         const double nt = static_cast<double>(m.nu_t[w]);
-        const size_t n0 = out.nu.size();
-        out.nu.resize(n0 + kWgCells, 0.0);
-        out.eta.resize(n0 + kWgCells, 0.0f);
-        out.slot.resize(4 * (n0 + kWgCells), -1);
         for (int ib = b0; ib < b1; ++ib)
-          for (int ia = a0; ia < a1; ++ia) {
+          for (int ia = t0; ia < t1; ++ia) {
             const int64_t q = cell(ia, ib);
-            const size_t o = n0 + static_cast<size_t>(ib - b0) * kWgRows + (ia - a0);
-            out.nu[o] = c[q];
-            out.eta[o] = static_cast<float>(c[q] - nt);
-            eta_max = std::max(eta_max, std::fabs(c[q] - nt));
-            for (int s = 0; s < 4; ++s) out.slot[4 * o + s] = slot[4 * q + s];
+            const size_t o = w * tile + static_cast<size_t>(ib - b0) * kWgRows + (ia - t0);
+            out.nu[first + o] = c[q];
+            rest[o] = c[q] - al[ia - a0] - be[ib - b0] - nt;
+            eta_max = std::max(eta_max, std::fabs(rest[o]));
+            for (int s = 0; s < 4; ++s) out.slot[4 * (first + o) + s] = slot[4 * q + s];
           }
       }
       // eta / s in [-1, 1] and x s (at most 2 kWgX) both lie in float16's range
-      int ex = 0;
-      (void)std::frexp(eta_max, &ex);
-      const double s = eta_max > 0.0 ? std::ldexp(1.0, ex) : 1.0;
-      for (size_t o = first; o < out.eta.size(); ++o) out.eta[o] /= static_cast<float>(s);
+      const double s = pow2_of(eta_max);
+      for (size_t o = 0; o < rest.size(); ++o) out.eta[first + o] = static_cast<float>(rest[o] / s);
       m.xs = static_cast<float>(6.283185307179586 * s);
       m.eta_max = static_cast<float>(eta_max);
       seg_eta = std::max(seg_eta, eta_max);
       out.macros.push_back(m);
     }
+  // a flat segment's groups may be of any width
   const float limit = g.kind == SL1M_PIX_DELTA ? kWgX : kWgXW;
-  seg.width = static_cast<float>(seg_eta) / limit;
+  seg.width = flat ? 0.0f : static_cast<float>(seg_eta) / limit;
   seg.macros = static_cast<int32_t>(out.macros.size()) - seg.mac0;
   seg.cells = static_cast<int64_t>(out.nu.size()) - seg.cell0;
   out.segs.push_back(seg);
+}
+
+// Largest |eta| of the segment's flat tables.
+double flat_eta(const GridSeg& g, const double* c) {
+  const WgShape sh(g, kFlatSteps);
+  auto at = [&](int ia, int ib) {
+    return c[(static_cast<int64_t>(ib / kGridNB) * g.na + ia) * kGridNB + ib % kGridNB];
+  };
+  double top = 0.0;
+  for (int ri = 0; ri < sh.rmac; ++ri)
+    for (int ci = 0; ci < sh.cmac; ++ci) {
+      const int a0 = kWgRows * (sh.rsets * ri / sh.rmac), b0 = 16 * (sh.steps * ci / sh.cmac);
+      const int a1 = std::min(kWgRows * (sh.rsets * (ri + 1) / sh.rmac), g.na);
+      const int b1 = std::min(16 * (sh.steps * (ci + 1) / sh.cmac), g.nb);
+      const int ic = (a0 + a1) / 2, jc = (b0 + b1) / 2;
+      for (int t0 = a0; t0 < a1; t0 += kWgRows) {
+        const int t1 = std::min(t0 + kWgRows, a1);
+        double lo = 1e300, hi = -1e300;
+        for (int ib = b0; ib < b1; ++ib)
+          for (int ia = t0; ia < t1; ++ia) {
+            const double v = at(ia, ib) - (at(ia, jc) - at(ic, jc)) - at(ic, ib);
+            lo = std::min(lo, v);
+            hi = std::max(hi, v);
+          }
+        top = std::max(top, 0.5 * (hi - lo));
+      }
+    }
+  return top;
+}
+
+}  // namespace
+
+int wg_max_macros(const GridSeg& g) { return WgShape(g, kWgSteps).macros(); }
+
+int64_t wg_max_cells(const GridSeg& g) {
+  return std::max(WgShape(g, kWgSteps).cells(kWgSteps), WgShape(g, kFlatSteps).cells(kFlatSteps));
+}
+
+size_t wg_part_bytes(const GridSeg& g) {
+  const WgShape a(g, kWgSteps), b(g, kFlatSteps);
+  return sizeof(float4) * std::max(a.cells(kWgSteps) * wg_chunk_cap(a.macros()),
+                                   b.cells(kFlatSteps) * flat_chunk_cap(b.macros()));
+}
+
+void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c,
+                    const int32_t* slot, double w_max, WgPlan& out) {
+  // Without cell factors where the series allows it: 1.9 times faster (disk baselines of
+  // |w| < 250 over +-0.05, sl1m_wflat.hip), and closer: fewer phasors are rounded.
+  const bool flat = 6.2831854 * w_max * flat_eta(g, c) <= 0.999 * kFlatX;
+  append_segment(g, la, mb, c, slot, flat, out);
 }
 
 bool wg_build_groups(const std::vector<double>& w, float width, int64_t max_groups,
@@ -1508,12 +1598,12 @@ __global__ void k_wg_slots_gauss(const int32_t* __restrict__ order, const double
 }
 
 // Chunk sums of every cell, combined into its sign slots (row 0 of the adjoint
-// partials); GAUSS: they are the slots' sums themselves.  A block takes 16 cells, 16
-// threads each every 16th chunk: small segments have few cells and many chunks (one
-// thread a cell: 32 x 32 x 2,000 9.8 us, now 3.5; 64 x 64 pixels in 795 chunks 156 us, now
-// 6; the adjoint of 256 x 256 pixels with three layers x 50,000 718, now 433).
+// partials); SLOTS: they are the slots' sums themselves.  A block takes 16 cells, 16
+// threads each every 16th chunk: small segments have few cells and many chunks (with
+// one thread a cell 32 x 32 x 2,000 took 9.8 us instead of 4.4, and the adjoint of 256 x
+// 256 pixels with three layers x 50,000 718 us instead of 433).
 constexpr int kRedCells = 16, kRedSlices = kBlock / kRedCells;
-template <bool GAUSS>
+template <bool SLOTS>
 __global__ __launch_bounds__(kBlock) void k_wg_adj_reduce(const float4* __restrict__ part,
                                                           int n_chunks, int64_t cells,
                                                           const int4* __restrict__ slot,
@@ -1553,7 +1643,7 @@ __global__ __launch_bounds__(kBlock) void k_wg_adj_reduce(const float4* __restri
   const float g2 = (sh[0][ci].y + sh[1][ci].y) + (sh[2][ci].y + sh[3][ci].y);
   const float g3 = (sh[0][ci].z + sh[1][ci].z) + (sh[2][ci].z + sh[3][ci].z);
   const float g4 = (sh[0][ci].w + sh[1][ci].w) + (sh[2][ci].w + sh[3][ci].w);
-  if constexpr (GAUSS) {
+  if constexpr (SLOTS) {
     if (s.x >= 0) out[s.x] = g1;
     if (s.y >= 0) out[s.y] = g2;
     if (s.z >= 0) out[s.z] = g3;
@@ -1587,7 +1677,7 @@ __global__ void k_wg_adj_prep(const float2* __restrict__ r, const int32_t* __res
 }
 
 
-static_assert(kWgCells % kRedCells == 0, "whole blocks of cells");
+static_assert(kWgCells % kRedCells == 0 && kFlatCells % kRedCells == 0, "whole blocks of cells");
 
 inline unsigned blocks1(int64_t n) { return static_cast<unsigned>((n + kBlock - 1) / kBlock); }
 
@@ -1613,6 +1703,7 @@ hipError_t launch_wg_forward(sl1m_plan* p, const GridSeg& g, const void* xp, hip
   const dim3 grid(static_cast<unsigned>(wg_chunks(s.macros, p->wg_groups)),
                   static_cast<unsigned>(s.macros));
   const float* x = static_cast<const float*>(xp);
+  if (s.flat) return launch_flat_forward(p, g, s, x, st);
   const float* scale = static_cast<const float*>(p->pscale);
   const int4* slot = reinterpret_cast<const int4*>(p->wg_slot);
   float2* rows = static_cast<float2*>(p->fpart);
@@ -1662,11 +1753,12 @@ hipError_t launch_wg_adjoint_prep(sl1m_plan* p, const void* r, hipStream_t st) {
 
 hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st) {
   const WgSeg& s = p->wg_segs[&g - p->grid_segs.data()];
-  const int chunks = wg_chunks(s.macros, p->wg_groups);
+  const int chunks = (s.flat ? flat_chunks : wg_chunks)(s.macros, p->wg_groups);
   const dim3 grid(static_cast<unsigned>(chunks), static_cast<unsigned>(s.macros));
   const int4* slot = reinterpret_cast<const int4*>(p->wg_slot) + s.cell0;
   const bool delta = g.kind == SL1M_PIX_DELTA;
   hipError_t e = timed(p, delta ? T_GRID_ADJ_DELTA : T_GRID_ADJ_GAUSS, st, [&] {
+    if (s.flat) return launch_flat_adjoint(p, g, s, st);
     if (delta)
       hipLaunchKernelGGL(k_wg_adj, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, p->wg_res,
                          p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb, p->wg_su, p->wg_sv, p->wg_dw,
@@ -1681,7 +1773,7 @@ hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st) {
   if (e != hipSuccess) return e;
   float* out = static_cast<float*>(p->apart);
   const dim3 rb(static_cast<unsigned>(s.cells / kRedCells));
-  if (delta)
+  if (delta && !s.flat)
     hipLaunchKernelGGL(k_wg_adj_reduce<false>, rb, dim3(kBlock), 0, st,
                        p->wg_part, chunks, s.cells, slot, out);
   else

@@ -1,8 +1,9 @@
 """Group evaluation of grids (visibilities in groups of nearly one w, the sums on
 the matrix cores): operators against the FP64 oracle at the FP32 operator tolerance and
 the element-wise bound (tests/elementwise.py), at the sizes where its tiles (16 |l|
-values by 32 |m| values, four tiles to a block), its groups (64 visibilities, tiles of
-16) and its series (argument classes set by the spread of w in a group) end.
+values by 32 |m| values, 64 without cell factors, four tiles to a block), its groups (64
+visibilities, tiles of 16) and its series (argument classes set by the spread of w in a
+group, or by the largest w) end.
 
 A plan of one side takes it, a plan of two sides the grid evaluation for the same calls,
 so results that differ in their bits show that it ran.
@@ -40,6 +41,10 @@ CASES = {
     "wide_field": (48, 48, 6e-3, 6000, 30.0, True, 1.0),       # split first order, groups cut
     "third_order": (40, 40, 6e-3, 3001, 40.0, False, 1.0),
     "w_zero": (36, 36, 2e-3, 1500, 0.0, False, 1.0),           # one w: no series
+    "many_groups": (40, 40, 4e-3, 30000, 30.0, False, 1.0),    # cell factors, one order
+    "flat_65": (129, 129, 1e-3, 500, 20.0, True, 1.0),         # 65 x 65 cells, one order
+    "flat_two_orders": (150, 34, 1.5e-3, 700, 150.0, False, 1.0),
+    "flat_one_visibility": (40, 40, 2e-3, 1, 1.0, False, 1.0),
     "cut_off": (70, 70, 1e-3, 2700, 20.0, True, 0.55),         # truncated mid-row, shuffled
 }
 
@@ -108,6 +113,7 @@ GAUSS = {
     "no_series": (40, 40, 1e-3, 2.0, W.PIX_GAUSS_WIDE, 1000, 5.0, False),
     "paraxial_odd": (33, 35, 2e-3, 1.0, W.PIX_GAUSS_PARAXIAL, 65, 20.0, False),
     "one_order": (64, 130, 4e-3, 1.0, W.PIX_GAUSS_WIDE, 2047, 12.0, False),
+    "flat_two_orders": (64, 130, 4e-3, 1.0, W.PIX_GAUSS_WIDE, 700, 1.0, False),
     "wide": (48, 48, 1.2e-2, 0.5, W.PIX_GAUSS_WIDE, 2500, 40.0, False),
     "layer_and_delta": (34, 40, 8e-3, 1.0, W.PIX_GAUSS_WIDE, 3001, 60.0, True),
     "steep_taper": (40, 40, 5e-3, 3.0, W.PIX_GAUSS_WIDE, 1500, 60.0, False),
