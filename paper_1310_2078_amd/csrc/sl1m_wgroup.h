@@ -15,8 +15,9 @@
 // the cut of the groups keeps below kWgX radians.
 //
 // Gaussian layers (the completed-square form of sl1m_grid.h): gamma = exp(2 pi i
-// (C r^2 - w kappa)) leaves exp(-2 pi i w kappa) alone to the groups, C l^2 and C m^2
-// going to the factors of l and m, which are complex pairs a+-, b+- with their tapers.
+// (C r^2 - w kappa)) leaves the part of exp(-2 pi i w kappa) that does not separate alone
+// to the groups; the rest goes to the factors of l and m, which are complex pairs a+-,
+// b+- with their tapers.
 //
 // The operands are float32 values split into two float16 (value = hi + lo to
 // 2^-22 of it), each product as hi hi + hi lo + lo hi with float32 sums.
@@ -40,7 +41,7 @@ constexpr float kWgXN = 1.2e-3f;
 constexpr float kWgXM = 2.5e-3f;
 constexpr float kWgXW = 1.5e-2f;
 constexpr float kWgX = 5.0e-2f;
-// Gaussian segments: no series below kWgXZ, one order below kWgXN, at most kWgXW.
+// Gaussian segments: no series up to kWgXZ, one order up to kWgXN.
 constexpr float kWgXZ = 5.0e-7f;
 // Segments that need no cell factor (sl1m_wflat.hip): tiles twice as wide; the largest
 // |2 pi w eta| of one: one order up to kFlatN, two up to kFlatX, in one float16 product
@@ -84,9 +85,9 @@ struct WgPlan {
   std::vector<WgSeg> segs;
   std::vector<WgMacro> macros;
   std::vector<double> la, mb;      // row / column positions of the macros
-  std::vector<double> nu;          // per tile cell: nu (delta) or kappa
+  std::vector<double> nu;          // per tile cell: nu, or eta where alpha and beta serve
   std::vector<float> eta;          // per tile cell, divided by the macro's s (below 1)
-  std::vector<double> alpha, beta; // flat segments: separable part at the positions
+  std::vector<double> alpha, beta; // separable part at the positions (0: none)
   std::vector<int32_t> slot;       // [4 per tile cell] permuted pixel or -1
 };
 

@@ -66,13 +66,16 @@ double pow2_of(double e) {
   return e > 0.0 ? std::ldexp(1.0, ex) : 1.0;
 }
 
-// One segment's tables.  flat: c = alpha(l) + beta(m) + eta, exact along the macro's
-// middle row and column, each tile's eta centred by its rows' alpha; else c = nu_t + eta.
+// One segment's tables.  Flat segments and Gaussian ones: c = alpha(l) + beta(m) + eta,
+// exact along the macro's middle row and column, each tile's eta centred by its rows'
+// alpha (and nu holds eta); other delta segments, whose real factors of l and m have no
+// place for alpha and beta: c = nu_t + eta.
 // Row sets of kWgRows |l| values and column sets of up to `cs` steps of 16 |m| values,
 // both spread evenly over the macros.
 void append_segment(const GridSeg& g, const double* la, const double* mb, const double* c,
                     const int32_t* slot, bool flat, WgPlan& out) {
   const int na = g.na, nb = g.nb, cs = flat ? kFlatSteps : kWgSteps;
+  const bool parts = flat || g.kind != SL1M_PIX_DELTA;
   const size_t tile = static_cast<size_t>(kWgRows) * 16 * cs;
   const WgShape sh(g, cs);
   WgSeg seg{};
@@ -105,7 +108,7 @@ void append_segment(const GridSeg& g, const double* la, const double* mb, const 
       double* const be = &out.beta[m.b_off];
       std::copy(la + a0, la + a1, &out.la[m.a_off]);
       std::copy(mb + b0, mb + b1, &out.mb[m.b_off]);
-      if (flat) {
+      if (parts) {
         const int ic = (a0 + a1) / 2, jc = (b0 + b1) / 2;
         for (int ia = a0; ia < a1; ++ia) al[ia - a0] = c[cell(ia, jc)] - c[cell(ic, jc)];
         for (int ib = b0; ib < b1; ++ib) be[ib - b0] = c[cell(ic, ib)];
@@ -129,7 +132,7 @@ void append_segment(const GridSeg& g, const double* la, const double* mb, const 
           }
         // the tile's reference: in the rows' alpha, or as the kernels hold it (float32)
         double mid = 0.5 * (lo + hi);
-        if (flat) {
+        if (parts) {
           for (int ia = t0; ia < t1; ++ia) al[ia - a0] += mid;
           mid = 0.0;
         }
@@ -139,8 +142,8 @@ void append_segment(const GridSeg& g, const double* la, const double* mb, const 
           for (int ia = t0; ia < t1; ++ia) {
             const int64_t q = cell(ia, ib);
             const size_t o = w * tile + static_cast<size_t>(ib - b0) * kWgRows + (ia - t0);
-            out.nu[first + o] = c[q];
             rest[o] = c[q] - al[ia - a0] - be[ib - b0] - nt;
+            out.nu[first + o] = parts ? rest[o] : c[q];
             eta_max = std::max(eta_max, std::fabs(rest[o]));
             for (int s = 0; s < 4; ++s) out.slot[4 * (first + o) + s] = slot[4 * q + s];
           }
@@ -154,7 +157,7 @@ void append_segment(const GridSeg& g, const double* la, const double* mb, const 
       out.macros.push_back(m);
     }
   // a flat segment's groups may be of any width
-  const float limit = g.kind == SL1M_PIX_DELTA ? kWgX : kWgXW;
+  const float limit = g.kind == SL1M_PIX_DELTA ? kWgX : kWgXN;
   seg.width = flat ? 0.0f : static_cast<float>(seg_eta) / limit;
   seg.macros = static_cast<int32_t>(out.macros.size()) - seg.mac0;
   seg.cells = static_cast<int64_t>(out.nu.size()) - seg.cell0;
@@ -973,8 +976,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
 // Gaussian layers (completed-square form, sl1m_grid.h).  An entry is
 //   D (1 + i s) exp(2 pi i (e0 - w kappa)) a_sign(|l|) b_sign(|m|),
 //   a+- = T(u -+ w|l|) exp(2 pi i (+- A|l| + C l^2)), b+- the same of v, |m|, B,
-// where C l^2 + C m^2 carries the phase's r^2 term; kappa alone (n - 1 + r^2 / 2, a
-// fourth-order term) is left to the groups, in the tiles of the delta segments.
+// where C l^2 + C m^2 carries the phase's r^2 term; kappa (n - 1 + r^2 / 2) is alpha(l)
+// + beta(m) + eta (append_segment), exp(-2 pi i w alpha) and exp(-2 pi i w beta) join
+// the factors, and eta alone is left to the groups, whose series needs one order only
+// (with kappa itself the coarse layers needed a second order and a split first one).
 // Both factors are complex, so the products are twice as long.  Tapers are formed
 // against the largest of the macro's columns and (adjoint) of the tile's rows per
 // visibility, so that the float16 operands keep their precision where a whole
@@ -987,7 +992,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
 
 struct alignas(16) FwdGLds {
   uint4 col[kWgCols / 2 * 4 * 64];  // [two columns][B1 hi, lo, B2 hi, lo][visibility]
-  double la[4 * kWgRows], mb[kWgCols], A[kWgVis], C[kWgVis];
+  double la[4 * kWgRows], al[4 * kWgRows], mb[kWgCols], be[kWgCols];
+  double A[kWgVis], C[kWgVis], w[kWgVis];
   float4 uw[kWgVis];                // u, w, c1, x
   float2 red[4][kWgVis];
 };
@@ -1076,71 +1082,11 @@ __device__ __forceinline__ void fwd_gauss_tile(int steps, double w0,
   }
 }
 
-// The same for arguments up to kWgXW: first order split like the zeroth into sums of
-// its own, second order in one product.  One row sign and two visibility tiles at a
-// time (the rows are formed again for each): all at once spill 126 registers.
-__device__ __forceinline__ void fwd_gauss_wide(int steps, double w0,
-                                               const double (&kap)[2 * kWgSteps][2],
-                                               const float4 (&x)[2 * kWgSteps][2],
-                                               const float (&eta)[2 * kWgSteps][2],
-                                               const uint4* __restrict__ col,
-                                               const float (&xv)[4], int nt, GAcc& a) {
-#pragma unroll
-  for (int th = 0; th < 4; th += 2) {
-    if (th >= nt) continue;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      f4_t d1[2][2];
-      asm volatile("" : "+v"(w0));  // the rows are not kept from one pass to the next
-#pragma unroll
-      for (int o = 0; o < 2; ++o) d1[o][0] = d1[o][1] = f4_t{0, 0, 0, 0};
-#pragma unroll
-      for (int ks = 0; ks < 2 * kWgSteps; ++ks) {
-        if (ks >= 2 * steps) continue;
-        float pp[2][8], pe[8];
-        gauss_rows(w0, kap[ks], x[ks], pp[0], pp[1]);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) pe[j] = eta[ks][j / 4] * pp[s][j];
-        Op8 ph, pl, eh, el;
-        split8(pp[s], ph, pl);
-        split8(pe, eh, el);
-        const Op8 e2 = times_eta(eh, eta[ks]);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const uint4* q = col + ks * 4 * 4 * 64 + 16 * (th + t);
-          const _Float16 xf = static_cast<_Float16>(xv[th + t]);
-          const _Float16 hf = static_cast<_Float16>(-0.5f * xv[th + t]);
-#pragma unroll
-          for (int o = 0; o < 2; ++o) {  // re, im
-            const h8_t bh = as_h8(q[128 * o]), bl = as_h8(q[128 * o + 64]);
-            f4_t& z = a.d[2 * s + o][th + t];
-            z = mma(ph.vec(), bh, z);
-            z = mma(ph.vec(), bl, z);
-            z = mma(pl.vec(), bh, z);
-            z = mma(e2.vec(), bh * xf * hf, z);
-            d1[o][t] = mma(eh.vec(), bh, d1[o][t]);
-            d1[o][t] = mma(eh.vec(), bl, d1[o][t]);
-            d1[o][t] = mma(el.vec(), bh, d1[o][t]);
-          }
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          f4_t& zr = a.d[2 * s][th + t];
-          f4_t& zi = a.d[2 * s + 1][th + t];
-          zr[i] = fmaf(xv[th + t], d1[1][t][i], zr[i]);
-          zi[i] = fmaf(-xv[th + t], d1[0][t][i], zi[i]);
-        }
-    }
-  }
-}
-
 __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
     const WgMacro* __restrict__ macros, int mac0, const float* __restrict__ xp,
     const float* __restrict__ pscale, const int4* __restrict__ slot, const double* __restrict__ kap,
     const float* __restrict__ eta, const double* __restrict__ la, const double* __restrict__ mb,
+    const double* __restrict__ alpha, const double* __restrict__ beta,
     const WgVisG* __restrict__ rec, const float* __restrict__ sdw, const double* __restrict__ w0s,
     const float* __restrict__ hs, const int32_t* __restrict__ cnt, int n_groups,
     float2* __restrict__ rows) {
@@ -1152,10 +1098,15 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool active = wv < sets;
-  const float kap_t = cm->nu_t[wv];
   const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
-  if (tid < 4 * kWgRows) lds.la[tid] = la[cm->a_off + tid];
-  if (tid < kWgCols) lds.mb[tid] = mb[cm->b_off + tid];
+  if (tid < 4 * kWgRows) {
+    lds.la[tid] = la[cm->a_off + tid];
+    lds.al[tid] = alpha[cm->a_off + tid];
+  }
+  if (tid < kWgCols) {
+    lds.mb[tid] = mb[cm->b_off + tid];
+    lds.be[tid] = beta[cm->b_off + tid];
+  }
   // amplitudes of this lane's row and its two columns of every 8, times the power
   // of two that brings the tile's largest into [2^13, 2^14)
   double kp[2 * kWgSteps][2];
@@ -1210,12 +1161,13 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
     const WgVisG r = rn;
     const float dw = dwn;
     const double w0 = w0n;
-    const float xm = kTwoPi * hn * eta_max;
-    const int ser = xm <= kWgXZ ? 0 : xm <= kWgXN ? 1 : 2;
+    const bool one = kTwoPi * hn * eta_max > kWgXZ;  // an order of the series
     const int nt = (cn + 15) >> 4;
+    const double w = w0 + static_cast<double>(dw);
     if (wv == 0) {
       lds.A[lane] = r.A;
       lds.C[lane] = r.C;
+      lds.w[lane] = w;
       lds.uw[lane] = make_float4(r.u, r.w, r.c1, xs * dw);
     }
     load(g + gs < n_groups ? g + gs : g);
@@ -1227,14 +1179,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
       for (int j = 0; j < 2; ++j) {
         const double m = lds.mb[un * 2 + j];
         const float mr = static_cast<float>(m);
-        float cb, sb;
-        phasor(fma(r.B, m, fma(r.C, m * m, kMagic)), cb, sb);
+        const double q = fma(r.C, m * m, -w * lds.be[un * 2 + j]);
+        float cb, sb, cm_, sm_;
+        phasor(fma(r.B, m, q) + kMagic, cb, sb);
+        phasor(fma(-r.B, m, q) + kMagic, cm_, sm_);
         const float tp = taper(r.c1, fmaf(-r.w, mr, r.v), top, kGUp);
         const float tm = taper(r.c1, fmaf(r.w, mr, r.v), top, kGUp);
-        // b+ = tp (cb, sb); b- with the conjugate linear phase: its C m^2 part keeps
-        // its sign, so the phasor of -B m + C m^2 is formed on its own
-        float cm_, sm_;
-        phasor(fma(-r.B, m, fma(r.C, m * m, kMagic)), cm_, sm_);
         h2_t hp, lp, hm, lm;
         split2(tp * cb, tp * sb, hp, lp);
         split2(tm * cm_, tm * sm_, hm, lm);
@@ -1264,27 +1214,25 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
 #pragma unroll
       for (int t = 0; t < 4; ++t) xv[t] = lds.uw[16 * t + r16].w;
       const uint4* col = lds.col + quad * 4 * 64 + r16;
-      if (ser == 0)
-        fwd_gauss_tile<0>(steps, w0, kp, x, et, col, xv, nt, d);
-      else if (ser == 1)
+      if (one)
         fwd_gauss_tile<1>(steps, w0, kp, x, et, col, xv, nt, d);
       else
-        fwd_gauss_wide(steps, w0, kp, x, et, col, xv, nt, d);
+        fwd_gauss_tile<0>(steps, w0, kp, x, et, col, xv, nt, d);
       float vr[4], vi[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         vr[t] = vi[t] = 0.0f;
         if (t >= nt) continue;
-        const double A = lds.A[16 * t + r16], C = lds.C[16 * t + r16];
+        const double A = lds.A[16 * t + r16], C = lds.C[16 * t + r16], W = lds.w[16 * t + r16];
         const float4 uw = lds.uw[16 * t + r16];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const double l = lds.la[wv * kWgRows + quad * 4 + i];
           const float lr = static_cast<float>(l);
           float cp, sp, cn_, sn_;
-          const double q2 = fma(C, l * l, kMagic);
-          phasor(fma(A, l, q2), cp, sp);
-          phasor(fma(-A, l, q2), cn_, sn_);
+          const double q = fma(C, l * l, -W * lds.al[wv * kWgRows + quad * 4 + i]);
+          phasor(fma(A, l, q) + kMagic, cp, sp);
+          phasor(fma(-A, l, q) + kMagic, cn_, sn_);
           const float du = fmaf(-uw.y, lr, uw.x), dv = fmaf(uw.y, lr, uw.x);
           const float tp = pow2(uw.z * (du * du)), tm = pow2(uw.z * (dv * dv));
           const float apr = tp * cp, api = tp * sp, amr = tm * cn_, ami = tm * sn_;
@@ -1296,9 +1244,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
       }
       float sr, si;
       quad_sum(vr, vi, lane, sr, si);
-      // visibility `lane`: D (1 + i s), e0, the tile's kappa, the columns' top
-      const float th = fmaf(-dw, kap_t, r.e0);
-      const float ct = __builtin_amdgcn_cosf(th), st = __builtin_amdgcn_sinf(th);
+      // visibility `lane`: D (1 + i s), e0, the columns' top
+      const float ct = __builtin_amdgcn_cosf(r.e0), st = __builtin_amdgcn_sinf(r.e0);
       const float k = sc * kGDown * pow2(top);
       const float fr = k * fmaf(r.D, ct, -r.Ds * st), fi = k * fmaf(r.D, st, r.Ds * ct);
       re = fmaf(fr, sr, -fi * si);
@@ -1319,33 +1266,32 @@ constexpr int kGPitch = 68;  // uint32 (visibilities) per column of an operand, 
 
 struct alignas(16) AdjGLds {
   uint32_t col[2][4][kWgCols][kGPitch];  // [b+, b-][B1 hi, lo, B2 hi, lo][column][visibility]
-  double la[4 * kWgRows], mb[kWgCols], A[kWgVis], C[kWgVis];
+  double la[4 * kWgRows], al[4 * kWgRows], mb[kWgCols], be[kWgCols];
+  double A[kWgVis], C[kWgVis], w[kWgVis];
   float4 uw[kWgVis];                     // u, w, c1, x
   float2 rho[4][kWgVis];
   float top[4][kWgVis];
   uint32_t x[kWgVis];                    // (x, x) in float16
 };
 
-struct GOp {  // row operand of 16 visibilities: (re, im) each; hi, lo, and x times them
-  Op8 h, l, eh, el;
+struct GOp {  // row operand of 16 visibilities: (re, im) each; hi, lo, and x times hi
+  Op8 h, l, e;
 };
 
-// G of one sign pair += Re conj(C_0) (T + i eta T1 - eta^2 T2), SER as in the
-// forward; `b`: this lane's column operand, `x` its visibilities' x.
+// G of one sign pair += Re conj(C_0) (T + i eta T1), T1 with SER 1; `b`: this lane's
+// column operand.
 template <int SER>
 __device__ __forceinline__ void adj_gauss_kind(const GOp (&a)[4], const uint4* __restrict__ b,
-                                               const uint4* __restrict__ x,
                                                const float (&cc)[kWgSteps][4],
                                                const float (&cs)[kWgSteps][4],
                                                const float (&eta)[kWgSteps][4], int steps,
                                                float (&g)[kWgSteps][4]) {
   constexpr int kPart = kWgCols * kGPitch / 4, kTile = 16 * kGPitch / 4;
-  f4_t t[4][kWgSteps], h[2][kWgSteps];
+  f4_t t[4][kWgSteps];
 #pragma unroll
   for (int c = 0; c < kWgSteps; ++c) {
 #pragma unroll
     for (int o = 0; o < 4; ++o) t[o][c] = f4_t{0, 0, 0, 0};
-    h[0][c] = h[1][c] = f4_t{0, 0, 0, 0};
     if (c >= steps) continue;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -1355,24 +1301,13 @@ __device__ __forceinline__ void adj_gauss_kind(const GOp (&a)[4], const uint4* _
       t[0][c] = mma(a[k].h.vec(), b1h, t[0][c]);
       t[1][c] = mma(a[k].h.vec(), b2h, t[1][c]);
       if constexpr (SER > 0) {
-        t[2][c] = mma(a[k].eh.vec(), b1h, t[2][c]);
-        t[3][c] = mma(a[k].eh.vec(), b2h, t[3][c]);
+        t[2][c] = mma(a[k].e.vec(), b1h, t[2][c]);
+        t[3][c] = mma(a[k].e.vec(), b2h, t[3][c]);
       }
       t[0][c] = mma(a[k].h.vec(), b1l, t[0][c]);
       t[1][c] = mma(a[k].h.vec(), b2l, t[1][c]);
-      if constexpr (SER > 1) {
-        t[2][c] = mma(a[k].eh.vec(), b1l, t[2][c]);
-        t[3][c] = mma(a[k].eh.vec(), b2l, t[3][c]);
-      }
       t[0][c] = mma(a[k].l.vec(), b1h, t[0][c]);
       t[1][c] = mma(a[k].l.vec(), b2h, t[1][c]);
-      if constexpr (SER > 1) {
-        t[2][c] = mma(a[k].el.vec(), b1h, t[2][c]);
-        t[3][c] = mma(a[k].el.vec(), b2h, t[3][c]);
-        const h8_t s = a[k].eh.vec() * (as_h8(x[4 * k]) * static_cast<_Float16>(0.5f));
-        h[0][c] = mma(s, b1h, h[0][c]);
-        h[1][c] = mma(s, b2h, h[1][c]);
-      }
     }
   }
 #pragma unroll
@@ -1385,10 +1320,6 @@ __device__ __forceinline__ void adj_gauss_kind(const GOp (&a)[4], const uint4* _
         zr = fmaf(-e, t[3][c][i], zr);
         zi = fmaf(e, t[2][c][i], zi);
       }
-      if constexpr (SER > 1) {
-        zr = fmaf(-e * e, h[0][c][i], zr);
-        zi = fmaf(-e * e, h[1][c][i], zi);
-      }
       g[c][i] = fmaf(cc[c][i], zr, g[c][i]);
       g[c][i] = fmaf(-cs[c][i], zi, g[c][i]);
       asm volatile("" : "+v"(g[c][i]));  // formed here (adj_fold)
@@ -1397,9 +1328,9 @@ __device__ __forceinline__ void adj_gauss_kind(const GOp (&a)[4], const uint4* _
 
 struct GRow {  // this lane's row and the group's visibilities (LDS)
   float lr;
-  double l, l2;
+  double l, l2, al;
   const float4* uw;
-  const double *A, *C;
+  const double *A, *C, *w;
   const float2* rho;
   const float* top;
 };
@@ -1425,19 +1356,18 @@ __device__ __forceinline__ void adj_gauss_group(const GRow& r, int quad,
         const float4 uw = r.uw[v];
         const double A = s ? -r.A[v] : r.A[v];
         float ca, sa;
-        phasor(fma(A, r.l, fma(r.C[v], r.l2, kMagic)), ca, sa);
+        phasor(fma(A, r.l, fma(r.C[v], r.l2, -r.w[v] * r.al)) + kMagic, ca, sa);
         const float t = taper(uw.z, fmaf(s ? uw.y : -uw.y, r.lr, uw.x), r.top[v], 1.0f);
         ca *= t;
         sa *= t;
         const float2 z = r.rho[v];
         const float yr = fmaf(ca, z.x, sa * z.y), yi = fmaf(ca, z.y, -sa * z.x);
         split2(yr, yi, a[k].h.v[j], a[k].l.v[j]);
-        if constexpr (SER > 1) split2(uw.w * yr, uw.w * yi, a[k].eh.v[j], a[k].el.v[j]);
       }
-      if constexpr (SER == 1) a[k].eh = __builtin_bit_cast(Op8, a[k].h.vec() * xk);
+      if constexpr (SER > 0) a[k].e = __builtin_bit_cast(Op8, a[k].h.vec() * xk);
     }
-    adj_gauss_kind<SER>(a, b, x, cc, cs, eta, steps, g[s]);
-    adj_gauss_kind<SER>(a, b + kSign, x, cc, cs, eta, steps, g[2 + s]);
+    adj_gauss_kind<SER>(a, b, cc, cs, eta, steps, g[s]);
+    adj_gauss_kind<SER>(a, b + kSign, cc, cs, eta, steps, g[2 + s]);
   }
 }
 
@@ -1445,7 +1375,8 @@ __device__ __forceinline__ void adj_gauss_group(const GRow& r, int quad,
 __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
     const WgMacro* __restrict__ macros, int mac0, const float2* __restrict__ res,
     const double* __restrict__ kap, const float* __restrict__ eta, const double* __restrict__ la,
-    const double* __restrict__ mb, const WgVisG* __restrict__ rec, const float* __restrict__ sdw,
+    const double* __restrict__ mb, const double* __restrict__ alpha,
+    const double* __restrict__ beta, const WgVisG* __restrict__ rec, const float* __restrict__ sdw,
     const double* __restrict__ w0s, const float* __restrict__ hs, int n_groups, int64_t cbase,
     int64_t cells, float4* __restrict__ part) {
   __shared__ AdjGLds lds;
@@ -1455,10 +1386,16 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool active = wv < sets;
-  const float kap_t = cm->nu_t[wv], l_lo = cm->l_lo[wv], l_hi = cm->l_hi[wv];
+  const float l_lo = cm->l_lo[wv], l_hi = cm->l_hi[wv];
   const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
-  if (tid < 4 * kWgRows) lds.la[tid] = la[cm->a_off + tid];
-  if (tid < kWgCols) lds.mb[tid] = mb[cm->b_off + tid];
+  if (tid < 4 * kWgRows) {
+    lds.la[tid] = la[cm->a_off + tid];
+    lds.al[tid] = alpha[cm->a_off + tid];
+  }
+  if (tid < kWgCols) {
+    lds.mb[tid] = mb[cm->b_off + tid];
+    lds.be[tid] = beta[cm->b_off + tid];
+  }
   double kp[kWgSteps][4];
   float et[kWgSteps][4], g[4][kWgSteps][4];
 #pragma unroll
@@ -1490,14 +1427,13 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
   for (int gi = g0; gi < n_groups; gi += gs) {
     const WgVisG r = rn;
     const double w0 = w0n;
-    const float xm = kTwoPi * hn * eta_max;
-    const int ser = xm <= kWgXZ ? 0 : xm <= kWgXN ? 1 : 2;
+    const bool one = kTwoPi * hn * eta_max > kWgXZ;  // an order of the series
     // residual times conj of the visibility's factors, with both tops
     const float top = taper_top(r.c1, r.v, r.w, m_lo, m_hi);
     const float ltop = taper_top(r.c1, r.u, r.w, l_lo, l_hi);
-    const float th = fmaf(-dwn, kap_t, r.e0);
+    const double w = w0 + static_cast<double>(dwn);
     const float k = pow2(top + ltop);
-    const float c0 = __builtin_amdgcn_cosf(th), s0 = __builtin_amdgcn_sinf(th);
+    const float c0 = __builtin_amdgcn_cosf(r.e0), s0 = __builtin_amdgcn_sinf(r.e0);
     const float ct = k * fmaf(r.D, c0, -r.Ds * s0), st = k * fmaf(r.D, s0, r.Ds * c0);
     const float rr = fmaf(ct, zn.x, st * zn.y), ri = fmaf(ct, zn.y, -st * zn.x);
     const float am = fmaxf(fabsf(rr), fabsf(ri));
@@ -1508,6 +1444,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
     if (wv == 0) {
       lds.A[lane] = r.A;
       lds.C[lane] = r.C;
+      lds.w[lane] = w;
       const float x = xs * dwn;
       lds.uw[lane] = make_float4(r.u, r.w, r.c1, x);
       lds.x[lane] = as_u32(__builtin_convertvector((f2_t{x, x}), h2_t));
@@ -1516,10 +1453,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
     for (int c = wv; c < 16 * steps; c += 4) {
       const double m = lds.mb[c];
       const float mr = static_cast<float>(m);
-      const double q2 = fma(r.C, m * m, kMagic);
+      const double q = fma(r.C, m * m, -w * lds.be[c]);
       float cp, sp, cn, sn;
-      phasor(fma(r.B, m, q2), cp, sp);
-      phasor(fma(-r.B, m, q2), cn, sn);
+      phasor(fma(r.B, m, q) + kMagic, cp, sp);
+      phasor(fma(-r.B, m, q) + kMagic, cn, sn);
       const float tp = taper(r.c1, fmaf(-r.w, mr, r.v), top, kGUp);
       const float tm = taper(r.c1, fmaf(r.w, mr, r.v), top, kGUp);
       h2_t hi, lo;
@@ -1550,13 +1487,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
       const float lr = static_cast<float>(l);
       const uint4* x = reinterpret_cast<const uint4*>(&lds.x[4 * quad]);
       const uint4* b = reinterpret_cast<const uint4*>(&lds.col[0][0][r16][4 * quad]);
-      const GRow row{lr, l, l2, lds.uw, lds.A, lds.C, lds.rho[wv], lds.top[wv]};
-      if (ser == 0)
-        adj_gauss_group<0>(row, quad, b, x, cc, cs, et, steps, g);
-      else if (ser == 1)
+      const GRow row{lr,    l,     l2,    lds.al[wv * kWgRows + r16], lds.uw, lds.A, lds.C,
+                     lds.w, lds.rho[wv], lds.top[wv]};
+      if (one)
         adj_gauss_group<1>(row, quad, b, x, cc, cs, et, steps, g);
       else
-        adj_gauss_group<2>(row, quad, b, x, cc, cs, et, steps, g);
+        adj_gauss_group<0>(row, quad, b, x, cc, cs, et, steps, g);
     }
     __syncthreads();
   }
@@ -1716,7 +1652,7 @@ hipError_t launch_wg_forward(sl1m_plan* p, const GridSeg& g, const void* xp, hip
     });
   return timed(p, T_GRID_FWD_GAUSS, st, [&] {
     hipLaunchKernelGGL(k_wg_fwd_gauss, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, x, scale,
-                       slot, p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb,
+                       slot, p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb, p->wg_alpha, p->wg_beta,
                        p->wg_recg + static_cast<int64_t>(g.layer) * p->wg_groups * kWgVis,
                        p->wg_dw, p->wg_w0, p->wg_h, p->wg_count, p->wg_groups, rows);
     return hipGetLastError();
@@ -1765,7 +1701,7 @@ hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st) {
                          p->wg_w0, p->wg_h, p->wg_groups, s.cell0, s.cells, p->wg_part);
     else
       hipLaunchKernelGGL(k_wg_adj_gauss, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, p->wg_res,
-                         p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb,
+                         p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb, p->wg_alpha, p->wg_beta,
                          p->wg_recg + static_cast<int64_t>(g.layer) * p->wg_groups * kWgVis,
                          p->wg_dw, p->wg_w0, p->wg_h, p->wg_groups, s.cell0, s.cells, p->wg_part);
     return hipGetLastError();
