@@ -52,9 +52,19 @@ namespace {
 // Macros and tile cells of a segment in tiles of up to `cs` column steps.
 struct WgShape {
   int rsets, rmac, steps, cmac;
+  bool lone;
   WgShape(const GridSeg& g, int cs)
       : rsets((g.na + kWgRows - 1) / kWgRows), rmac((rsets + 3) / 4), steps((g.nb + 15) / 16),
-        cmac((steps + cs - 1) / cs) {}
+        cmac((steps + cs - 1) / cs), lone(cs == kWgSteps && rsets % 4 == 1 && rsets <= 9) {}
+  // Evenly over the macros, but one set over (2^k pixels a side: 2^(k-1) + 1 |l| values)
+  // has the last macro for itself, whose wavefronts share it, where that is much of the
+  // grid: five sets 0.55 against 0.69 ms (128 x 128 Gaussian pixels x 409,600, forward),
+  // nine sets 376 against 395 us (256 x 256 x 97,536); at 33 sets what the four form
+  // each for themselves costs more (10.1 against 9.8 ms).  Flat segments form less and
+  // are evaluated faster without (256 x 256 x 100,000: 210 against 217 us).
+  int first_set(int ri) const {
+    return lone ? std::min(4 * ri, rsets) : rsets * ri / rmac;
+  }
   int macros() const { return rmac * cmac; }
   int64_t cells(int cs) const { return static_cast<int64_t>(rsets) * cmac * kWgRows * 16 * cs; }
 };
@@ -71,7 +81,7 @@ double pow2_of(double e) {
 // alpha (and nu holds eta); other delta segments, whose real factors of l and m have no
 // place for alpha and beta: c = nu_t + eta.
 // Row sets of kWgRows |l| values and column sets of up to `cs` steps of 16 |m| values,
-// both spread evenly over the macros.
+// spread over the macros.
 void append_segment(const GridSeg& g, const double* la, const double* mb, const double* c,
                     const int32_t* slot, bool flat, WgPlan& out) {
   const int na = g.na, nb = g.nb, cs = flat ? kFlatSteps : kWgSteps;
@@ -88,7 +98,7 @@ void append_segment(const GridSeg& g, const double* la, const double* mb, const 
   };
   for (int ri = 0; ri < sh.rmac; ++ri)
     for (int ci = 0; ci < sh.cmac; ++ci) {
-      const int r0 = sh.rsets * ri / sh.rmac, r1 = sh.rsets * (ri + 1) / sh.rmac;
+      const int r0 = sh.first_set(ri), r1 = sh.first_set(ri + 1);
       const int s0 = sh.steps * ci / sh.cmac, s1 = sh.steps * (ci + 1) / sh.cmac;
       const int a0 = kWgRows * r0, a1 = std::min(kWgRows * r1, na);
       const int b0 = 16 * s0, b1 = std::min(16 * s1, nb);
@@ -173,8 +183,8 @@ double flat_eta(const GridSeg& g, const double* c) {
   double top = 0.0;
   for (int ri = 0; ri < sh.rmac; ++ri)
     for (int ci = 0; ci < sh.cmac; ++ci) {
-      const int a0 = kWgRows * (sh.rsets * ri / sh.rmac), b0 = 16 * (sh.steps * ci / sh.cmac);
-      const int a1 = std::min(kWgRows * (sh.rsets * (ri + 1) / sh.rmac), g.na);
+      const int a0 = kWgRows * sh.first_set(ri), b0 = 16 * (sh.steps * ci / sh.cmac);
+      const int a1 = std::min(kWgRows * sh.first_set(ri + 1), g.na);
       const int b1 = std::min(16 * (sh.steps * (ci + 1) / sh.cmac), g.nb);
       const int ic = (a0 + a1) / 2, jc = (b0 + b1) / 2;
       for (int t0 = a0; t0 < a1; t0 += kWgRows) {
@@ -297,7 +307,7 @@ __device__ __forceinline__ void quad_sum(const float (&vr)[4], const float (&vi)
 template <int SER, bool FULL>
 __device__ __forceinline__ void kind_pair(const float (&pr)[8], const float (&pi)[8],
                                           const float (&eta)[4], const uint4* __restrict__ col,
-                                          const float (&hx)[4], int nt, f4_t (&dre)[4],
+                                          const float (&hx)[4], int t0, int t1, f4_t (&dre)[4],
                                           f4_t (&dim)[4]) {
   Op8 rh, rl, ih, il, erh, erl, eih, eil;
   split8(pr, rh, rl);
@@ -346,7 +356,7 @@ __device__ __forceinline__ void kind_pair(const float (&pr)[8], const float (&pi
   }
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    if (!FULL && t >= nt) continue;
+    if (!FULL && (t < t0 || t >= t1)) continue;
     const h8_t bh = as_h8(col[16 * t]), bl = as_h8(col[64 + 16 * t]), ch = as_h8(col[128 + 16 * t]);
     dre[t] = mma(rh.vec(), bh, dre[t]);
     dim[t] = mma(ih.vec(), bh, dim[t]);
@@ -385,8 +395,8 @@ template <int SER, bool FULL>
 __device__ __forceinline__ void fwd_tile(int steps, double w0, const double* __restrict__ nu,
                                          const float4 (&e)[kWgSteps][4],
                                          const float (&eta)[kWgSteps][4],
-                                         const uint4* __restrict__ col, const float (&hx)[4], int nt,
-                                         FwdAcc& d) {
+                                         const uint4* __restrict__ col, const float (&hx)[4], int t0,
+                                         int t1, FwdAcc& d) {
 #pragma unroll
   for (int s = 0; s < kWgSteps; ++s) {
     if (!FULL && s >= steps) continue;
@@ -403,7 +413,7 @@ __device__ __forceinline__ void fwd_tile(int steps, double w0, const double* __r
       pi[2 * j] = -cs[j] * e[s][j].x;
       pi[2 * j + 1] = -cc[j] * e[s][j].z;
     }
-    kind_pair<SER, FULL>(pr, pi, eta[s], c, hx, nt, d.cr, d.ci);
+    kind_pair<SER, FULL>(pr, pi, eta[s], c, hx, t0, t1, d.cr, d.ci);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       pr[2 * j] = -cs[j] * e[s][j].w;
@@ -411,7 +421,7 @@ __device__ __forceinline__ void fwd_tile(int steps, double w0, const double* __r
       pi[2 * j] = -cc[j] * e[s][j].w;
       pi[2 * j + 1] = -cs[j] * e[s][j].y;
     }
-    kind_pair<SER, FULL>(pr, pi, eta[s], c, hx, nt, d.sr, d.si);
+    kind_pair<SER, FULL>(pr, pi, eta[s], c, hx, t0, t1, d.sr, d.si);
   }
 }
 
@@ -439,9 +449,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
   const float eta_max = cm->eta_max, xs = cm->xs;
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool active = wv < sets;
-  const float nu_t = cm->nu_t[wv];
-  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
+  const WavePart wp = wave_part(sets, wv);
+  const bool active = wp.active;
+  const float nu_t = cm->nu_t[wp.set];
+  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(wp.set) * kWgCells;
   if (tid < 4 * kWgRows) lds.la[tid] = la[cm->a_off + tid];
   if (tid < kWgCols) lds.mb[tid] = mb[cm->b_off + tid];
   const int64_t lane0 = cell0 + quad * 4 * kWgRows + r16;  // this lane's row, first column
@@ -551,28 +562,29 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
       for (int t = 0; t < 4; ++t) hx[t] = lds.hx[16 * t + r16];
       const uint4* col = lds.col + quad * kParts * 64 + r16;
       const double* nuw = &lds.nu[wv][quad * 4 * kWgRows + r16];
-      const bool full = steps == kWgSteps && nt == 4;
+      const int t0 = wp.lo, t1 = nt < wp.hi ? nt : wp.hi;
+      const bool full = steps == kWgSteps && t1 - t0 == 4;
       if (full && ser == 0)
-        fwd_tile<0, true>(steps, w0, nuw, e, et, col, hx, nt, d);
+        fwd_tile<0, true>(steps, w0, nuw, e, et, col, hx, t0, t1, d);
       else if (ser == 0)
-        fwd_tile<0, false>(steps, w0, nuw, e, et, col, hx, nt, d);
+        fwd_tile<0, false>(steps, w0, nuw, e, et, col, hx, t0, t1, d);
       else if (ser == 1)
-        fwd_tile<1, false>(steps, w0, nuw, e, et, col, hx, nt, d);
+        fwd_tile<1, false>(steps, w0, nuw, e, et, col, hx, t0, t1, d);
       else if (ser == 2)
-        fwd_tile<2, false>(steps, w0, nuw, e, et, col, hx, nt, d);
+        fwd_tile<2, false>(steps, w0, nuw, e, et, col, hx, t0, t1, d);
       else
-        fwd_tile<3, false>(steps, w0, nuw, e, et, col, hx, nt, d);
+        fwd_tile<3, false>(steps, w0, nuw, e, et, col, hx, t0, t1, d);
       // lane: visibility 16 t + r16, rows 4 quad + i
       float vr[4], vi[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         vr[t] = vi[t] = 0.0f;
-        if (t >= nt) continue;
+        if (t < t0 || t >= t1) continue;
         const double u = lds.u[16 * t + r16];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           float ac, as;
-          phasor(fma(u, lds.la[wv * kWgRows + quad * 4 + i], kMagic), ac, as);
+          phasor(fma(u, lds.la[wp.set * kWgRows + quad * 4 + i], kMagic), ac, as);
           vr[t] = fmaf(ac, d.cr[t][i], vr[t]);
           vi[t] = fmaf(ac, d.ci[t][i], vi[t]);
           vr[t] = fmaf(as, d.sr[t][i], vr[t]);
@@ -816,16 +828,16 @@ __device__ __forceinline__ void adj_group(const float (&pc)[2][8], const float (
                                           const uint4* __restrict__ b, const uint4* __restrict__ hx,
                                           const float (&cc)[kWgSteps][4],
                                           const float (&cs)[kWgSteps][4],
-                                          const float* __restrict__ eta, int steps,
+                                          const float* __restrict__ eta, int steps, int mask,
                                           float (&g)[4][kWgSteps][4]) {
   constexpr int kType = kWgCols * kAdjPitch / 4;
   AdjOp a[2];
-  adj_rows(pc, rho, a);
-  adj_kind<SER, FULL, false>(a, b, hx, cc, cs, eta, steps, g[0]);
-  adj_kind<SER, FULL, true>(a, b + kType, hx, cc, cs, eta, steps, g[2]);
-  adj_rows(ps, rho, a);
-  adj_kind<SER, FULL, false>(a, b + kType, hx, cc, cs, eta, steps, g[1]);
-  adj_kind<SER, FULL, true>(a, b, hx, cc, cs, eta, steps, g[3]);
+  if (mask & 5) adj_rows(pc, rho, a);
+  if (mask & 1) adj_kind<SER, FULL, false>(a, b, hx, cc, cs, eta, steps, g[0]);
+  if (mask & 4) adj_kind<SER, FULL, true>(a, b + kType, hx, cc, cs, eta, steps, g[2]);
+  if (mask & 10) adj_rows(ps, rho, a);
+  if (mask & 2) adj_kind<SER, FULL, false>(a, b + kType, hx, cc, cs, eta, steps, g[1]);
+  if (mask & 8) adj_kind<SER, FULL, true>(a, b, hx, cc, cs, eta, steps, g[3]);
 }
 
 // Adjoint: block (groups x, x + gridDim.x, ..; macro y); part[x][cell] = (G1, G2,
@@ -842,9 +854,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
   const float eta_max = cm->eta_max, xs = cm->xs;
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool active = wv < sets;
-  const float nu_t = cm->nu_t[wv];
-  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
+  const WavePart wp = wave_part(sets, wv);
+  const bool active = wp.active;
+  const float nu_t = cm->nu_t[wp.set];
+  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(wp.set) * kWgCells;
   if (tid < 4 * kWgRows) lds.la[tid] = la[cm->a_off + tid];
   if (tid < kWgCols) lds.mb[tid] = mb[cm->b_off + tid];
   // this lane's cells: column 16 c + r16, rows 4 quad + i
@@ -932,7 +945,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
     __syncthreads();
     if (active) {
       float pc[2][8], ps[2][8];
-      const double l = lds.la[wv * kWgRows + r16];
+      const double l = lds.la[wp.set * kWgRows + r16];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -951,15 +964,20 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
       const uint4* hx = reinterpret_cast<const uint4*>(&lds.hx[4 * quad]);
       const float2* rho = &lds.rho[wv][8 * quad];
       if (ser == 0 && steps == kWgSteps)
-        adj_group<0, true>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+        adj_group<0, true>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, wp.mask,
+                          g);
       else if (ser == 0)
-        adj_group<0, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+        adj_group<0, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, wp.mask,
+                          g);
       else if (ser == 1)
-        adj_group<1, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+        adj_group<1, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, wp.mask,
+                          g);
       else if (ser == 2)
-        adj_group<2, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+        adj_group<2, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, wp.mask,
+                          g);
       else
-        adj_group<3, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, g);
+        adj_group<3, false>(pc, ps, rho, b, hx, cc, cs, &lds.eta[wv][0][lane], steps, wp.mask,
+                          g);
     }
     __syncthreads();
   }
@@ -968,8 +986,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
   for (int c = 0; c < kWgSteps; ++c)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      part[blockIdx.x * cells + cell0 - cbase + (16 * c + r16) * kWgRows + quad * 4 + i] =
-          make_float4(g[0][c][i], g[1][c][i], g[2][c][i], g[3][c][i]);
+      store_slots(part + blockIdx.x * cells + cell0 - cbase + (16 * c + r16) * kWgRows +
+                      quad * 4 + i,
+                  wp.mask, make_float4(g[0][c][i], g[1][c][i], g[2][c][i], g[3][c][i]));
 }
 
 // ---------------------------------------------------------------------------
@@ -1039,7 +1058,7 @@ __device__ __forceinline__ void fwd_gauss_tile(int steps, double w0,
                                                const float4 (&x)[2 * kWgSteps][2],
                                                const float (&eta)[2 * kWgSteps][2],
                                                const uint4* __restrict__ col,
-                                               const float (&xv)[4], int nt, GAcc& a) {
+                                               const float (&xv)[4], int t0, int t1, GAcc& a) {
 #pragma unroll
   for (int ks = 0; ks < 2 * kWgSteps; ++ks) {
     if (ks >= 2 * steps) continue;
@@ -1055,7 +1074,7 @@ __device__ __forceinline__ void fwd_gauss_tile(int steps, double w0,
     const uint4* q = col + ks * 4 * 4 * 64;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      if (t >= nt) continue;
+      if (t < t0 || t >= t1) continue;
       const h8_t b1h = as_h8(q[16 * t]), b1l = as_h8(q[64 + 16 * t]);
       const h8_t b2h = as_h8(q[128 + 16 * t]), b2l = as_h8(q[192 + 16 * t]);
       a.d[0][t] = mma(ph.vec(), b1h, a.d[0][t]);
@@ -1097,8 +1116,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
   const float eta_max = cm->eta_max, xs = cm->xs, m_lo = cm->m_lo, m_hi = cm->m_hi;
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool active = wv < sets;
-  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
+  const WavePart wp = wave_part(sets, wv);
+  const bool active = wp.active;
+  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(wp.set) * kWgCells;
   if (tid < 4 * kWgRows) {
     lds.la[tid] = la[cm->a_off + tid];
     lds.al[tid] = alpha[cm->a_off + tid];
@@ -1205,6 +1225,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
     __syncthreads();
     float re = 0.0f, im = 0.0f;
     if (active) {
+      const int t0 = wp.lo, t1 = nt < wp.hi ? nt : wp.hi;
       GAcc d;
 #pragma unroll
       for (int o = 0; o < 4; ++o)
@@ -1215,22 +1236,22 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
       for (int t = 0; t < 4; ++t) xv[t] = lds.uw[16 * t + r16].w;
       const uint4* col = lds.col + quad * 4 * 64 + r16;
       if (one)
-        fwd_gauss_tile<1>(steps, w0, kp, x, et, col, xv, nt, d);
+        fwd_gauss_tile<1>(steps, w0, kp, x, et, col, xv, t0, t1, d);
       else
-        fwd_gauss_tile<0>(steps, w0, kp, x, et, col, xv, nt, d);
+        fwd_gauss_tile<0>(steps, w0, kp, x, et, col, xv, t0, t1, d);
       float vr[4], vi[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         vr[t] = vi[t] = 0.0f;
-        if (t >= nt) continue;
+        if (t < t0 || t >= t1) continue;
         const double A = lds.A[16 * t + r16], C = lds.C[16 * t + r16], W = lds.w[16 * t + r16];
         const float4 uw = lds.uw[16 * t + r16];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const double l = lds.la[wv * kWgRows + quad * 4 + i];
+          const double l = lds.la[wp.set * kWgRows + quad * 4 + i];
           const float lr = static_cast<float>(l);
           float cp, sp, cn_, sn_;
-          const double q = fma(C, l * l, -W * lds.al[wv * kWgRows + quad * 4 + i]);
+          const double q = fma(C, l * l, -W * lds.al[wp.set * kWgRows + quad * 4 + i]);
           phasor(fma(A, l, q) + kMagic, cp, sp);
           phasor(fma(-A, l, q) + kMagic, cn_, sn_);
           const float du = fmaf(-uw.y, lr, uw.x), dv = fmaf(uw.y, lr, uw.x);
@@ -1342,10 +1363,11 @@ __device__ __forceinline__ void adj_gauss_group(const GRow& r, int quad,
                                                 const float (&cc)[kWgSteps][4],
                                                 const float (&cs)[kWgSteps][4],
                                                 const float (&eta)[kWgSteps][4], int steps,
-                                                float (&g)[4][kWgSteps][4]) {
+                                                int mask, float (&g)[4][kWgSteps][4]) {
   constexpr int kSign = 4 * kWgCols * kGPitch / 4;
 #pragma unroll
   for (int s = 0; s < 2; ++s) {  // row signs
+    if (!(mask & (5 << s))) continue;
     GOp a[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -1366,8 +1388,8 @@ __device__ __forceinline__ void adj_gauss_group(const GRow& r, int quad,
       }
       if constexpr (SER > 0) a[k].e = __builtin_bit_cast(Op8, a[k].h.vec() * xk);
     }
-    adj_gauss_kind<SER>(a, b, cc, cs, eta, steps, g[s]);
-    adj_gauss_kind<SER>(a, b + kSign, cc, cs, eta, steps, g[2 + s]);
+    if (mask & (1 << s)) adj_gauss_kind<SER>(a, b, cc, cs, eta, steps, g[s]);
+    if (mask & (4 << s)) adj_gauss_kind<SER>(a, b + kSign, cc, cs, eta, steps, g[2 + s]);
   }
 }
 
@@ -1385,9 +1407,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
   const float eta_max = cm->eta_max, xs = cm->xs, m_lo = cm->m_lo, m_hi = cm->m_hi;
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool active = wv < sets;
-  const float l_lo = cm->l_lo[wv], l_hi = cm->l_hi[wv];
-  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kWgCells;
+  const WavePart wp = wave_part(sets, wv);
+  const bool active = wp.active;
+  const float l_lo = cm->l_lo[wp.set], l_hi = cm->l_hi[wp.set];
+  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(wp.set) * kWgCells;
   if (tid < 4 * kWgRows) {
     lds.la[tid] = la[cm->a_off + tid];
     lds.al[tid] = alpha[cm->a_off + tid];
@@ -1483,16 +1506,16 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
           cc[c][i] *= inv;
           cs[c][i] *= inv;
         }
-      const double l = lds.la[wv * kWgRows + r16], l2 = l * l;
+      const double l = lds.la[wp.set * kWgRows + r16], l2 = l * l;
       const float lr = static_cast<float>(l);
       const uint4* x = reinterpret_cast<const uint4*>(&lds.x[4 * quad]);
       const uint4* b = reinterpret_cast<const uint4*>(&lds.col[0][0][r16][4 * quad]);
-      const GRow row{lr,    l,     l2,    lds.al[wv * kWgRows + r16], lds.uw, lds.A, lds.C,
+      const GRow row{lr,    l,     l2,    lds.al[wp.set * kWgRows + r16], lds.uw, lds.A, lds.C,
                      lds.w, lds.rho[wv], lds.top[wv]};
       if (one)
-        adj_gauss_group<1>(row, quad, b, x, cc, cs, et, steps, g);
+        adj_gauss_group<1>(row, quad, b, x, cc, cs, et, steps, wp.mask, g);
       else
-        adj_gauss_group<0>(row, quad, b, x, cc, cs, et, steps, g);
+        adj_gauss_group<0>(row, quad, b, x, cc, cs, et, steps, wp.mask, g);
     }
     __syncthreads();
   }
@@ -1501,8 +1524,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
   for (int c = 0; c < kWgSteps; ++c)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      part[blockIdx.x * cells + cell0 - cbase + (16 * c + r16) * kWgRows + quad * 4 + i] =
-          make_float4(g[0][c][i], g[1][c][i], g[2][c][i], g[3][c][i]);
+      store_slots(part + blockIdx.x * cells + cell0 - cbase + (16 * c + r16) * kWgRows +
+                      quad * 4 + i,
+                  wp.mask, make_float4(g[0][c][i], g[1][c][i], g[2][c][i], g[3][c][i]));
 }
 
 // Per-slot constants of a Gaussian layer (coordinates negated where w < 0).

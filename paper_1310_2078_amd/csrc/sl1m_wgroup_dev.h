@@ -55,6 +55,30 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// What a wavefront of a macro does: one of its row sets; with one set alone, a quarter of
+// its visibility tiles (forward) or sign slots (adjoint).
+struct WavePart {
+  int set, lo, hi;  // visibility tiles [lo, hi)
+  int mask;         // slots
+  bool active;
+};
+__device__ __forceinline__ WavePart wave_part(int sets, int wv) {
+  if (sets == 1) return {0, wv, wv + 1, 1 << wv, true};
+  return {wv < sets ? wv : 0, 0, 4, 15, wv < sets};
+}
+
+__device__ __forceinline__ void store_slots(float4* __restrict__ o, int mask, float4 v) {
+  if (mask == 15) {
+    *o = v;
+    return;
+  }
+  float* const f = &o->x;
+  if (mask & 1) f[0] = v.x;
+  if (mask & 2) f[1] = v.y;
+  if (mask & 4) f[2] = v.z;
+  if (mask & 8) f[3] = v.w;
+}
+
 // log2 of the largest taper over +-[lo, hi] at baseline coordinate d
 __device__ __forceinline__ float taper_top(float c1, float d, float w, float lo, float hi) {
   const float a = fmaf(-w, lo, d), b = fmaf(-w, hi, d), e = fmaf(w, lo, d), f = fmaf(w, hi, d);
