@@ -550,7 +550,7 @@ struct Layout {
       grid_mb, grid_c3, grid_c4, grid_slot, grid_rec, grid_fc, grid_pb, grid_segs, grid_gb,
       grid_prec, grid_precm, mx, mr, mred, grid_mfma_b, grid_mfma_nu, phl, vhl,
       wg_mac, wg_la, wg_mb, wg_nu, wg_eta, wg_slot, wg_order, wg_count, wg_su, wg_sv, wg_dw, wg_w0,
-      wg_h, wg_part, wg_res, wg_recg, wg_alpha, wg_beta, total;
+      wg_h, wg_part, wg_res, wg_recg, wg_alpha, wg_beta, wg_map, total;
 };
 
 // `wg_n`: grid segments in the group evaluation
@@ -660,6 +660,7 @@ Layout layout(const Analysis& a, int wg_n) {
     L.wg_dw = take(4 * slots);
     L.wg_w0 = take(8 * static_cast<size_t>(a.wg_cap));
     L.wg_res = take(8 * slots);
+    L.wg_map = take(wg_alias && wg_n == 1 && wg_flat_macros(a.gsegs[0]) == 1 ? 4 * np : 0);
     L.wg_recg = take(sizeof(WgVisG) * slots * a.layer_sigma.size());
     if (!wg_alias) L.wg_part = take(wg_part);
     L.wg_h = take(4 * static_cast<size_t>(a.wg_cap));
@@ -707,6 +708,11 @@ sl1m_status read_red(sl1m_plan* p, double* host, int n, hipStream_t st) {
 // combined into `out` (caller order) minus `data` if given.
 sl1m_status apply_forward(sl1m_plan* p, const void* xp, const void* data, void* out, bool recs,
                           hipStream_t st, int nr = 1) {
+  if (nr == 1 && wg_single(p)) {
+    SL1M_HIP(timed(p, T_FWD, st, [&] { return launch_flat_single(p, xp, data, out, recs, st); }),
+             "forward kernel");
+    return SL1M_OK;
+  }
   SL1M_HIP(timed(p, T_FWD, st, [&] { return launch_forward(p, xp, nr, st); }), "forward kernel");
   SL1M_HIP(launch_forward_reduce(p, data, out, recs, nr, st), "forward reduce");
   return SL1M_OK;
@@ -788,6 +794,8 @@ sl1m_status power_iteration(sl1m_plan* p, int32_t iters, uint64_t seed, const vo
   if (s) return s;
   if (!(h[1] > 0.0)) return set_error(SL1M_EINVAL, "power iteration start vector is zero");
   SL1M_HIP(launch_scale(p, p->xperm, p->n_pix, 1.0 / std::sqrt(h[1]), st), "normalise");
+  // the norms stay on the device: one wait at the end instead of one a step.  A step
+  // without a norm (M x = 0, or not a number) leaves zeros, or the same, to those after it.
   double rq = 0.0;
   for (int32_t it = 0; it < iters; ++it) {
     s = apply_forward(p, p->xperm, nullptr, p->res, true, st);
@@ -795,12 +803,12 @@ sl1m_status power_iteration(sl1m_plan* p, int32_t iters, uint64_t seed, const vo
     SL1M_HIP(timed(p, T_ADJ, st, [&] { return launch_adjoint(p, 1, st); }), "adjoint kernel");
     SL1M_HIP(launch_adjoint_reduce(p, p->img, false, 1, st), "adjoint reduce");
     SL1M_HIP(launch_dot_norm(p, p->xperm, p->img, st), "rayleigh");
+    if (it + 1 < iters) SL1M_HIP(launch_normalise(p, p->img, p->xperm, st), "normalise");
+  }
+  if (iters > 0) {
     s = read_red(p, h, 2, st);
     if (s) return s;
     rq = h[0];
-    if (!(h[1] > 0.0)) break;
-    SL1M_HIP(launch_copy_real(p, p->img, p->xperm, p->n_pix, st), "copy");
-    SL1M_HIP(launch_scale(p, p->xperm, p->n_pix, 1.0 / std::sqrt(h[1]), st), "normalise");
   }
   *rq_out = rq;
   return SL1M_OK;
@@ -1017,6 +1025,7 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       for (const WgSeg& s2 : p->wg_segs) p->wg_macros += s2.macros;
       p->wg_groups = static_cast<int>(wgg.w0.size());
       p->wg_recg = reinterpret_cast<WgVisG*>(w + L.wg_recg);
+      p->wg_map = reinterpret_cast<int32_t*>(w + L.wg_map);
       p->wg_mac = reinterpret_cast<WgMacro*>(w + L.wg_mac);
       p->wg_la = reinterpret_cast<double*>(w + L.wg_la);
       p->wg_mb = reinterpret_cast<double*>(w + L.wg_mb);
@@ -1047,6 +1056,7 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       for (int64_t j = 0; j < a.n_pix; ++j) perm[j] = static_cast<int32_t>(j);
     }
     std::vector<Chunk> chunks;
+    std::vector<int32_t> wg_map;
     chunks.insert(chunks.end(), a.fd.begin(), a.fd.end());
     chunks.insert(chunks.end(), a.fg.begin(), a.fg.end());
     chunks.insert(chunks.end(), a.pd.begin(), a.pd.end());
@@ -1077,6 +1087,12 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       up(p->wg_alpha, t.alpha.data(), 8 * t.alpha.size());
       up(p->wg_beta, t.beta.data(), 8 * t.beta.size());
       up(p->wg_slot, t.slot.data(), 4 * t.slot.size());
+      if (wg_single(p)) {
+        wg_map.resize(a.n_pix);
+        for (size_t i = 0; i < t.slot.size(); ++i)
+          if (t.slot[i] >= 0) wg_map[t.slot[i]] = static_cast<int32_t>(i);
+        up(p->wg_map, wg_map.data(), 4 * wg_map.size());
+      }
       up(p->wg_order, wgg.order.data(), 4 * wgg.order.size());
       up(p->wg_count, wgg.count.data(), 4 * wgg.count.size());
       up(p->wg_w0, wgg.w0.data(), 8 * wgg.w0.size());
@@ -1532,8 +1548,9 @@ static sl1m_status solve_impl(sl1m_plan* p, const void* vis, const void* x0,
     }
     info->L = L;
     const bool resume = state && state->t >= 1.0;
-    const double scal_h[5] = {resume ? state->t : 1.0, 1.0 / L, prm->lambda / L, prm->lambda,
-                              0.0};
+    // [6]: the update's block counter
+    const double scal_h[7] = {resume ? state->t : 1.0, 1.0 / L, prm->lambda / L, prm->lambda,
+                              0.0, 0.0, 0.0};
     SL1M_HIP(hipMemcpyAsync(p->scal, scal_h, sizeof(scal_h), hipMemcpyHostToDevice, st),
              "solver scalars");
     if (resume) {

@@ -265,6 +265,7 @@ struct sl1m_plan {
   int wg_macros = 0, wg_groups = 0;
   std::vector<sl1m::WgSeg> wg_segs;
   sl1m::WgVisG* wg_recg = nullptr;  // [layer][slot]
+  int32_t* wg_map = nullptr;        // one flat macro (wg_single): pixel -> 4 tile cell + slot
   sl1m::WgMacro* wg_mac = nullptr;
   double *wg_la = nullptr, *wg_mb = nullptr, *wg_nu = nullptr;
   double *wg_alpha = nullptr, *wg_beta = nullptr;
@@ -364,6 +365,10 @@ hipError_t launch_forward(sl1m_plan* p, const void* xp, int nr, hipStream_t st);
 int forward_rows(const sl1m_plan* p, int nr);
 // grid partial rows of the segments that the group evaluation takes
 int wg_skipped_rows(const sl1m_plan* p);
+// a plan of one flat macro: its forward writes the visibilities (no rows to add), the
+// consumers of its adjoint add the chunk sums
+bool wg_single(const sl1m_plan* p);
+int wg_single_chunks(const sl1m_plan* p);
 hipError_t launch_forward_reduce(sl1m_plan* p, const void* data, void* out, bool adj_records,
                                  int nr, hipStream_t st);
 hipError_t launch_adjoint_prep(sl1m_plan* p, const void* r, int nr, hipStream_t st);
@@ -374,6 +379,8 @@ hipError_t launch_adjoint_reduce(sl1m_plan* p, void* g_out, bool unpermute, int 
 hipError_t launch_fista_update(sl1m_plan* p, hipStream_t st);
 hipError_t launch_fill(void* dst, size_t n_elems, size_t elem_bytes, hipStream_t st);
 hipError_t launch_splitmix_start(sl1m_plan* p, uint64_t seed, void* dst, hipStream_t st);
+// dst = src / |src|, |src|^2 as launch_dot_norm left it on the device
+hipError_t launch_normalise(sl1m_plan* p, const void* src, void* dst, hipStream_t st);
 hipError_t launch_scale(sl1m_plan* p, void* x, int64_t n, double a, hipStream_t st);
 hipError_t launch_unpermute(sl1m_plan* p, const void* src, void* dst, hipStream_t st);
 hipError_t launch_copy_real(sl1m_plan* p, const void* src, void* dst, int64_t n, hipStream_t st);

@@ -152,16 +152,27 @@ __global__ void k_fwd_reduce(const C2<R>* __restrict__ part, int n_rows, int64_t
 // thread of the block must call it (it synchronises the block).
 constexpr int kRowPix = 64;
 static_assert(kBlock == 4 * kRowPix, "row_sum uses four wavefronts of kRowPix lanes");
-// Pixels [one.x, one.y) have their whole sum in row 0 (group evaluation).
+// Where the sums of a pixel are: element map[j] (j without a map) of rows of `stride`;
+// pixels [one.x, one.y) have their whole sum in row 0 (group evaluation).
 template <typename R>
-__device__ __forceinline__ R row_sum(const R* __restrict__ part, int n_rows, int64_t n_pix, int r,
-                                     int64_t j, int2 one, R (*sh)[kRowPix]) {
+struct AdjRows {
+  const R* part;
+  int n_rows;
+  int64_t stride;
+  const int32_t* map;
+  int2 one;
+};
+template <typename R>
+__device__ __forceinline__ R row_sum(const AdjRows<R>& a, int64_t n_pix, int r, int64_t j,
+                                     R (*sh)[kRowPix]) {
   const int wv = threadIdx.x / kRowPix, ln = threadIdx.x % kRowPix;
   R g = R(0);
-  const int rows = j >= one.x && j < one.y ? 1 : n_rows;
-  if (j < n_pix && wv < rows)
-    strided_sum<R>(part + static_cast<int64_t>(r * n_rows + wv) * n_pix + j, (rows - wv + 3) / 4,
-                   4 * n_pix, g);
+  const int rows = j >= a.one.x && j < a.one.y ? 1 : a.n_rows;
+  if (j < n_pix && wv < rows) {
+    const int64_t q = a.map ? a.map[j] : j;
+    strided_sum<R>(a.part + static_cast<int64_t>(r * a.n_rows + wv) * a.stride + q,
+                   (rows - wv + 3) / 4, 4 * a.stride, g);
+  }
   sh[wv][ln] = g;
   __syncthreads();
   const R t = wv == 0 ? (sh[0][ln] + sh[1][ln]) + (sh[2][ln] + sh[3][ln]) : R(0);
@@ -172,15 +183,14 @@ __device__ __forceinline__ R row_sum(const R* __restrict__ part, int n_rows, int
 // g[r][perm[j]] (or g[r][j]) = scale_j * sum_c part[r][c][j]; blocks of
 // kBlock threads cover kRowPix pixels.
 template <typename R>
-__global__ __launch_bounds__(kBlock) void k_adj_reduce(const R* __restrict__ part, int n_rows,
-                                                       int64_t n_pix, int nr, int2 one,
-                                                       const R* __restrict__ scale,
+__global__ __launch_bounds__(kBlock) void k_adj_reduce(AdjRows<R> rows, int64_t n_pix,
+                                                       int nr, const R* __restrict__ scale,
                                                        const int32_t* __restrict__ perm,
                                                        R* __restrict__ out) {
   __shared__ R sh[4][kRowPix];
   const int64_t j = static_cast<int64_t>(blockIdx.x) * kRowPix + threadIdx.x % kRowPix;
   for (int r = 0; r < nr; ++r) {
-    const R g = row_sum<R>(part, n_rows, n_pix, r, j, one, sh);
+    const R g = row_sum<R>(rows, n_pix, r, j, sh);
     if (threadIdx.x < kRowPix && j < n_pix) out[r * n_pix + (perm ? perm[j] : j)] = g * scale[j];
   }
 }
@@ -190,19 +200,19 @@ __global__ __launch_bounds__(kBlock) void k_adj_reduce(const R* __restrict__ par
 // with g = scale_j * sum_c part[c][j] and beta = (t_k - 1) / t_{k+1}.  The
 // scalars live on the device (scal[0] = t_k, scal[1] = 1/L, scal[2] = lambda/L)
 // so the iteration's launches are identical every time and can be replayed
-// from a captured graph; k_tstep advances t afterwards.
+// from a captured graph; t advances afterwards: k_tstep, or with a ticket (an
+// atomic counter that returns to 0) the last block, which saves its launch.
 // A non-finite z (overflow of a diverging iteration) would be mapped to 0 by
 // the threshold; it is recorded in *flag instead so the solve can report it.
 template <typename R>
-__global__ __launch_bounds__(kBlock) void k_fista(const R* __restrict__ part, int n_rows,
-                                                  int64_t n_pix, int2 one,
+__global__ __launch_bounds__(kBlock) void k_fista(AdjRows<R> rows, int64_t n_pix,
                                                   const R* __restrict__ scale,
                                                   R* __restrict__ y, R* __restrict__ img,
-                                                  const double* __restrict__ scal,
+                                                  double* scal, unsigned* ticket,
                                                   int* __restrict__ flag) {
   __shared__ R sh[4][kRowPix];
   const int64_t j = static_cast<int64_t>(blockIdx.x) * kRowPix + threadIdx.x % kRowPix;
-  R g = row_sum<R>(part, n_rows, n_pix, 0, j, one, sh);
+  R g = row_sum<R>(rows, n_pix, 0, j, sh);
   if (threadIdx.x >= kRowPix || j >= n_pix) return;
   const double t = scal[0];
   const double tn = 0.5 * (1.0 + sqrt(1.0 + 4.0 * t * t));
@@ -215,20 +225,24 @@ __global__ __launch_bounds__(kBlock) void k_fista(const R* __restrict__ part, in
   const R io = img[j];
   y[j] = in + beta * (in - io);
   img[j] = in;
+  // few blocks: the last to come here steps t (every block has read it)
+  if (ticket && threadIdx.x == 0) {
+    __threadfence();
+    if (atomicInc(ticket, gridDim.x - 1) == gridDim.x - 1) scal[0] = tn;
+  }
 }
 
 // MFISTA (the monotone variant of Beck & Teboulle the paper names): the
 // proximal step z_k = T^{lambda/L}(y_k - g / L) into z, g as for k_fista.
 template <typename R>
-__global__ __launch_bounds__(kBlock) void k_prox(const R* __restrict__ part, int n_rows,
-                                                 int64_t n_pix, int2 one,
+__global__ __launch_bounds__(kBlock) void k_prox(AdjRows<R> rows, int64_t n_pix,
                                                  const R* __restrict__ scale,
                                                  const R* __restrict__ y, R* __restrict__ z,
                                                  const double* __restrict__ scal,
                                                  int* __restrict__ flag) {
   __shared__ R sh[4][kRowPix];
   const int64_t j = static_cast<int64_t>(blockIdx.x) * kRowPix + threadIdx.x % kRowPix;
-  R g = row_sum<R>(part, n_rows, n_pix, 0, j, one, sh);
+  R g = row_sum<R>(rows, n_pix, 0, j, sh);
   if (threadIdx.x >= kRowPix || j >= n_pix) return;
   const R inv_L = static_cast<R>(scal[1]), thr = static_cast<R>(scal[2]);
   g *= scale[j];
@@ -440,6 +454,16 @@ __global__ void k_copy(const R* __restrict__ src, int64_t n, R* __restrict__ dst
 __global__ void k_fill_u32(uint32_t* __restrict__ dst, int64_t n) {
   const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (j < n) dst[j] = 0u;
+}
+
+// dst = src / |src|, norm[0] = |src|^2 (all zeros where that is not positive)
+template <typename R>
+__global__ void k_normalise(const R* __restrict__ src, int64_t n, const double* __restrict__ norm,
+                            R* __restrict__ dst) {
+  const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const double h = norm[0];
+  const R a = static_cast<R>(h > 0.0 ? 1.0 / sqrt(h) : 0.0);
+  if (j < n) dst[j] = src[j] * a;
 }
 
 template <typename R>
@@ -914,20 +938,31 @@ hipError_t launch_adjoint(sl1m_plan* p, int nr, hipStream_t st) {
   return SL1M_DISPATCH_R(p, adjoint_t, p, nr, st);
 }
 
-// Pixels whose adjoint sum is whole in row 0 of the partials.
-static int2 wg_pixels(const sl1m_plan* p, int nr) {
-  if (p->wg_n == 0 || nr != 1 || mfma_adjoint_call(p, nr)) return make_int2(0, 0);
-  const Segment& a = p->segs[p->grid_segs[0].seg];
-  const Segment& b = p->segs[p->grid_segs[p->wg_n - 1].seg];
-  return make_int2(static_cast<int>(a.start), static_cast<int>(b.start + b.count));
+// Where the adjoint's partial sums are.
+template <typename R>
+static AdjRows<R> adj_rows(const sl1m_plan* p, int nr) {
+  AdjRows<R> a{static_cast<const R*>(p->apart), p->n_achunks, p->n_pix, nullptr, make_int2(0, 0)};
+  if (p->wg_n == 0 || nr != 1 || mfma_adjoint_call(p, nr)) return a;
+  if constexpr (std::is_same<R, float>::value) {
+    if (wg_single(p)) {
+      a.part = &p->wg_part->x;
+      a.n_rows = wg_single_chunks(p);
+      a.stride = 4 * p->wg_segs[0].cells;
+      a.map = p->wg_map;
+      return a;
+    }
+  }
+  const Segment& f = p->segs[p->grid_segs[0].seg];
+  const Segment& l = p->segs[p->grid_segs[p->wg_n - 1].seg];
+  a.one = make_int2(static_cast<int>(f.start), static_cast<int>(l.start + l.count));
+  return a;
 }
 
 template <typename R>
 static hipError_t adj_reduce_t(sl1m_plan* p, void* g, bool unpermute, int nr, hipStream_t st) {
   if (p->n_pix == 0) return hipSuccess;
   hipLaunchKernelGGL((k_adj_reduce<R>), dim3(grid1(p->n_pix, kRowPix)), dim3(kBlock), 0, st,
-                     static_cast<const R*>(p->apart), p->n_achunks, p->n_pix, nr, wg_pixels(p, nr),
-                     static_cast<const R*>(p->pscale), unpermute ? p->perm : nullptr,
+                     adj_rows<R>(p, nr), p->n_pix, nr, static_cast<const R*>(p->pscale), unpermute ? p->perm : nullptr,
                      static_cast<R*>(g));
   return hipGetLastError();
 }
@@ -937,12 +972,16 @@ hipError_t launch_adjoint_reduce(sl1m_plan* p, void* g, bool unpermute, int nr, 
 
 template <typename R>
 static hipError_t fista_t(sl1m_plan* p, hipStream_t st) {
+  // k_tstep is 3.3 us of a 32 x 32 x 2,000 iteration's 32; the blocks' atomics meet at one
+  // address, so many blocks keep it
+  const unsigned blocks = grid1(p->n_pix, kRowPix);
+  unsigned* const ticket =
+      p->n_pix > 0 && blocks <= 256 ? reinterpret_cast<unsigned*>(p->scal + 6) : nullptr;
   if (p->n_pix > 0)
-    hipLaunchKernelGGL((k_fista<R>), dim3(grid1(p->n_pix, kRowPix)), dim3(kBlock), 0, st,
-                       static_cast<const R*>(p->apart), p->n_achunks, p->n_pix, wg_pixels(p, 1),
-                       static_cast<const R*>(p->pscale), static_cast<R*>(p->xperm),
-                       static_cast<R*>(p->img), p->scal, p->flag);
-  hipLaunchKernelGGL(k_tstep, dim3(1), dim3(64), 0, st, p->scal);
+    hipLaunchKernelGGL((k_fista<R>), dim3(blocks), dim3(kBlock), 0, st, adj_rows<R>(p, 1),
+                       p->n_pix, static_cast<const R*>(p->pscale), static_cast<R*>(p->xperm),
+                       static_cast<R*>(p->img), p->scal, ticket, p->flag);
+  if (!ticket) hipLaunchKernelGGL(k_tstep, dim3(1), dim3(64), 0, st, p->scal);
   return hipGetLastError();
 }
 hipError_t launch_fista_update(sl1m_plan* p, hipStream_t st) {
@@ -953,8 +992,8 @@ template <typename R>
 static hipError_t prox_t(sl1m_plan* p, hipStream_t st) {
   if (p->n_pix > 0)
     hipLaunchKernelGGL((k_prox<R>), dim3(grid1(p->n_pix, kRowPix)), dim3(kBlock), 0, st,
-                       static_cast<const R*>(p->apart), p->n_achunks, p->n_pix, wg_pixels(p, 1),
-                       static_cast<const R*>(p->pscale), static_cast<const R*>(p->xperm),
+                       adj_rows<R>(p, 1), p->n_pix, static_cast<const R*>(p->pscale),
+                       static_cast<const R*>(p->xperm),
                        static_cast<R*>(p->zbuf), p->scal, p->flag);
   return hipGetLastError();
 }
@@ -1006,6 +1045,17 @@ static hipError_t scale_t(sl1m_plan*, void* x, int64_t n, double a, hipStream_t 
                      static_cast<R>(a));
   return hipGetLastError();
 }
+template <typename R>
+static hipError_t normalise_t(sl1m_plan* p, const void* src, void* dst, hipStream_t st) {
+  if (p->n_pix == 0) return hipSuccess;
+  hipLaunchKernelGGL((k_normalise<R>), dim3(grid1(p->n_pix)), dim3(kBlock), 0, st,
+                     static_cast<const R*>(src), p->n_pix, p->red_out + 1, static_cast<R*>(dst));
+  return hipGetLastError();
+}
+hipError_t launch_normalise(sl1m_plan* p, const void* src, void* dst, hipStream_t st) {
+  return SL1M_DISPATCH_R(p, normalise_t, p, src, dst, st);
+}
+
 hipError_t launch_scale(sl1m_plan* p, void* x, int64_t n, double a, hipStream_t st) {
   return SL1M_DISPATCH_R(p, scale_t, p, x, n, a, st);
 }

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_fwd(
     const float* __restrict__ pscale, const int4* __restrict__ slot,
     const float* __restrict__ eta, const double* __restrict__ la, const double* __restrict__ mb,
     const double* __restrict__ alpha, const double* __restrict__ beta, FlatIn<GAUSS> in,
-    int n_groups, float2* __restrict__ rows) {
+    int n_groups, WgOut fin, float2* __restrict__ rows) {
   __shared__ FlatFwdLds<GAUSS> lds;
   const int mac = mac0 + static_cast<int>(blockIdx.y);
   const ConstPtr<WgMacro> cm = as_const(macros) + mac;
@@ -339,8 +339,19 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_fwd(
     if (tid < kWgVis) {
       const float2 p = lds.red[0][tid], q = lds.red[1][tid], u = lds.red[2][tid],
                    v = lds.red[3][tid];
-      rows[(static_cast<int64_t>(mac) * n_groups + g) * kWgVis + tid] =
-          make_float2((p.x + q.x) + (u.x + v.x), (p.y + q.y) + (u.y + v.y));
+      float2 sum = make_float2((p.x + q.x) + (u.x + v.x), (p.y + q.y) + (u.y + v.y));
+      const int64_t slot_g = static_cast<int64_t>(g) * kWgVis + tid;
+      if (fin.order) {  // the plan's only macro: nothing to add up
+        const int32_t o = fin.order[slot_g];
+        if (o & 1) sum.y = -sum.y;
+        float gr, gi;
+        if (o >= 0)
+          (void)wg_finish(fin, slot_g, o, sum, gr, gi);
+        else if (fin.res)
+          fin.res[slot_g] = make_float2(0.0f, 0.0f);
+      } else {
+        rows[static_cast<int64_t>(mac) * n_groups * kWgVis + slot_g] = sum;
+      }
     }
   }
 }
@@ -581,21 +592,35 @@ static FlatIn<GAUSS> flat_in(const sl1m_plan* p, const GridSeg& g) {
 
 template <bool GAUSS>
 static hipError_t flat_forward_t(sl1m_plan* p, const GridSeg& g, const WgSeg& s, const float* x,
-                                 hipStream_t st) {
+                                 const WgOut& fin, hipStream_t st) {
   const dim3 grid(static_cast<unsigned>(flat_chunks(s.macros, p->wg_groups)),
                   static_cast<unsigned>(s.macros));
   hipLaunchKernelGGL(k_flat_fwd<GAUSS>, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, x,
                      static_cast<const float*>(p->pscale),
                      reinterpret_cast<const int4*>(p->wg_slot), p->wg_eta, p->wg_la, p->wg_mb,
-                     p->wg_alpha, p->wg_beta, flat_in<GAUSS>(p, g), p->wg_groups,
+                     p->wg_alpha, p->wg_beta, flat_in<GAUSS>(p, g), p->wg_groups, fin,
                      static_cast<float2*>(p->fpart));
   return hipGetLastError();
 }
 
 hipError_t launch_flat_forward(sl1m_plan* p, const GridSeg& g, const WgSeg& s, const float* x,
                                   hipStream_t st) {
-  return g.kind == SL1M_PIX_DELTA ? flat_forward_t<false>(p, g, s, x, st)
-                                  : flat_forward_t<true>(p, g, s, x, st);
+  const WgOut none{};
+  return g.kind == SL1M_PIX_DELTA ? flat_forward_t<false>(p, g, s, x, none, st)
+                                  : flat_forward_t<true>(p, g, s, x, none, st);
+}
+
+hipError_t launch_flat_single(sl1m_plan* p, const void* x, const void* data, void* out, bool recs,
+                              hipStream_t st) {
+  const GridSeg& g = p->grid_segs[0];
+  const bool delta = g.kind == SL1M_PIX_DELTA;
+  const WgOut fin{p->wg_order, static_cast<const float*>(p->vgain), static_cast<const float2*>(data),
+                  static_cast<float2*>(out), recs ? p->wg_res : nullptr};
+  const float* xf = static_cast<const float*>(x);
+  return timed(p, delta ? T_GRID_FWD_DELTA : T_GRID_FWD_GAUSS, st, [&] {
+    return delta ? flat_forward_t<false>(p, g, p->wg_segs[0], xf, fin, st)
+                 : flat_forward_t<true>(p, g, p->wg_segs[0], xf, fin, st);
+  });
 }
 
 template <bool GAUSS>

@@ -105,6 +105,7 @@ int64_t wg_padded(const GridSeg& g);
 // macros and tile cells of a segment, the larger of both kinds of tiles
 int wg_max_macros(const GridSeg& g);
 int64_t wg_max_cells(const GridSeg& g);
+int wg_flat_macros(const GridSeg& g);
 // bytes of the segment's adjoint chunk sums
 size_t wg_part_bytes(const GridSeg& g);
 // appends a segment; `c`: nu or kappa per grid cell, `w_max`: largest |w|
@@ -133,6 +134,9 @@ hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st);
 // sl1m_wflat.hip: flat segments (the adjoint: its chunk sums)
 hipError_t launch_flat_forward(sl1m_plan* p, const GridSeg& g, const WgSeg& s, const float* x,
                                hipStream_t st);
+// wg_single: forward and reduction at once
+hipError_t launch_flat_single(sl1m_plan* p, const void* x, const void* data, void* out,
+                              bool adj_records, hipStream_t st);
 hipError_t launch_flat_adjoint(sl1m_plan* p, const GridSeg& g, const WgSeg& s, hipStream_t st);
 
 }  // namespace sl1m

@@ -204,6 +204,8 @@ double flat_eta(const GridSeg& g, const double* c) {
 
 }  // namespace
 
+int wg_flat_macros(const GridSeg& g) { return WgShape(g, kFlatSteps).macros(); }
+
 int wg_max_macros(const GridSeg& g) { return WgShape(g, kWgSteps).macros(); }
 
 int64_t wg_max_cells(const GridSeg& g) {
@@ -633,17 +635,14 @@ __global__ void k_wg_slots(const int32_t* __restrict__ order, const double* __re
 // segments' rows (indexed by visibility); gain, data and adjoint records as
 // k_fwd_reduce.
 __global__ void k_wg_fwd_reduce(const float2* __restrict__ part, int n_macros, int64_t n_slots,
-                                const int32_t* __restrict__ order,
                                 const float2* __restrict__ rows, int n_rows, int64_t n_vis,
-                                const float* __restrict__ gain, const float2* __restrict__ data,
-                                float2* __restrict__ out, float2* __restrict__ rres,
-                                const float* __restrict__ layerDs, int n_layers,
-                                float2* __restrict__ res) {
+                                WgOut w, float2* __restrict__ rres,
+                                const float* __restrict__ layerDs, int n_layers) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (t >= n_slots) return;
-  const int32_t o = order[t];
+  const int32_t o = w.order[t];
   if (o < 0) {
-    if (res) res[t] = make_float2(0.0f, 0.0f);
+    if (w.res) w.res[t] = make_float2(0.0f, 0.0f);
     return;
   }
   const int64_t k = o >> 1;
@@ -651,22 +650,9 @@ __global__ void k_wg_fwd_reduce(const float2* __restrict__ part, int n_macros, i
   strided_sum<float2>(part + t, n_macros, n_slots, acc);
   if (o & 1) acc.y = -acc.y;
   strided_sum<float2>(rows + k, n_rows, n_vis, acc);
-  const float gr = gain ? gain[2 * k] : 1.0f, gi = gain ? gain[2 * k + 1] : 0.0f;
-  float re = acc.x, im = acc.y;
-  if (gain) {
-    re = gr * acc.x - gi * acc.y;
-    im = gr * acc.y + gi * acc.x;
-  }
-  if (data) {
-    re -= data[k].x;
-    im -= data[k].y;
-  }
-  if (out) out[k] = make_float2(re, im);
-  if (rres) write_res<float>(rres, layerDs, n_layers, n_vis, 1, k, 0, gr, gi, re, im);
-  if (res) {
-    const float ci = gr * im - gi * re;
-    res[t] = make_float2(gr * re + gi * im, o & 1 ? -ci : ci);
-  }
+  float gr, gi;
+  const float2 v = wg_finish(w, t, o, acc, gr, gi);
+  if (rres) write_res<float>(rres, layerDs, n_layers, n_vis, 1, k, 0, gr, gi, v.x, v.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -1693,14 +1679,19 @@ hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, b
   const int64_t slots = static_cast<int64_t>(p->wg_groups) * kWgVis;
   const int skip = wg_skipped_rows(p);
   const float2* rows = static_cast<const float2*>(fwd_rows1(p)) + skip * p->n_vis;
+  const WgOut w{p->wg_order, static_cast<const float*>(p->vgain), static_cast<const float2*>(data),
+                static_cast<float2*>(out), recs ? p->wg_res : nullptr};
   hipLaunchKernelGGL(k_wg_fwd_reduce, dim3(blocks1(slots)), dim3(kBlock), 0, st,
-                     static_cast<const float2*>(p->fpart), p->wg_macros, slots, p->wg_order, rows,
-                     forward_rows(p, 1) - skip, p->n_vis, static_cast<const float*>(p->vgain),
-                     static_cast<const float2*>(data), static_cast<float2*>(out),
-                     recs ? rres_of(p) : nullptr, static_cast<const float*>(p->layerDs),
-                     p->n_layers, recs ? p->wg_res : nullptr);
+                     static_cast<const float2*>(p->fpart), p->wg_macros, slots, rows,
+                     forward_rows(p, 1) - skip, p->n_vis, w, recs ? rres_of(p) : nullptr,
+                     static_cast<const float*>(p->layerDs), p->n_layers);
   return hipGetLastError();
 }
+
+bool wg_single(const sl1m_plan* p) {
+  return p->wg_n == 1 && p->segs.size() == 1 && p->wg_segs[0].flat && p->wg_segs[0].macros == 1;
+}
+int wg_single_chunks(const sl1m_plan* p) { return flat_chunks(1, p->wg_groups); }
 
 hipError_t launch_wg_adjoint_prep(sl1m_plan* p, const void* r, hipStream_t st) {
   const int64_t slots = static_cast<int64_t>(p->wg_groups) * kWgVis;
@@ -1730,7 +1721,7 @@ hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st) {
                          p->wg_dw, p->wg_w0, p->wg_h, p->wg_groups, s.cell0, s.cells, p->wg_part);
     return hipGetLastError();
   });
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || wg_single(p)) return e;
   float* out = static_cast<float*>(p->apart);
   const dim3 rb(static_cast<unsigned>(s.cells / kRedCells));
   if (delta && !s.flat)

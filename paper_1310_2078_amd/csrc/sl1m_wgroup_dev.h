@@ -79,6 +79,39 @@ __device__ __forceinline__ void store_slots(float4* __restrict__ o, int mask, fl
   if (mask & 8) f[3] = v.w;
 }
 
+// What becomes of a slot's sum: times the gain, less the data (those given), into `out`
+// and, times the conjugate gain, into the adjoint record `res`.
+struct WgOut {
+  const int32_t* order;
+  const float* gain;
+  const float2* data;
+  float2* out;
+  float2* res;
+};
+// slot t of visibility o / 2 (order), `acc` as for the caller's coordinates; returns the
+// result, gain in gr, gi
+__device__ __forceinline__ float2 wg_finish(const WgOut& w, int64_t t, int32_t o, float2 acc,
+                                            float& gr, float& gi) {
+  const int64_t k = o >> 1;
+  gr = w.gain ? w.gain[2 * k] : 1.0f;
+  gi = w.gain ? w.gain[2 * k + 1] : 0.0f;
+  float re = acc.x, im = acc.y;
+  if (w.gain) {
+    re = gr * acc.x - gi * acc.y;
+    im = gr * acc.y + gi * acc.x;
+  }
+  if (w.data) {
+    re -= w.data[k].x;
+    im -= w.data[k].y;
+  }
+  if (w.out) w.out[k] = make_float2(re, im);
+  if (w.res) {
+    const float ci = gr * im - gi * re;
+    w.res[t] = make_float2(gr * re + gi * im, o & 1 ? -ci : ci);
+  }
+  return make_float2(re, im);
+}
+
 // log2 of the largest taper over +-[lo, hi] at baseline coordinate d
 __device__ __forceinline__ float taper_top(float c1, float d, float w, float lo, float hi) {
   const float a = fmaf(-w, lo, d), b = fmaf(-w, hi, d), e = fmaf(w, lo, d), f = fmaf(w, hi, d);
