@@ -164,13 +164,30 @@ bool analyze_grid(Analysis& a, int si, const std::vector<double>& L, const std::
 
 size_t plan_total(const Analysis& a);
 
+// The first n grid segments hold every pixel.
+bool all_pixels(const Analysis& a, int n) {
+  int64_t c = 0;
+  for (int i = 0; i < n; ++i) c += a.segs[a.gsegs[i].seg].count;
+  return n > 0 && c == a.n_pix;
+}
+
 // Group evaluation of the grid segments (plans of one side: the grid
 // evaluation shares its phasors among several, and a side on its own then gives
 // the same bits as among others): each segment's tiles, unless they hold more
 // than four times its cells with padding.  A plan that fits the no-allocation
 // scratch without the group tables but not with them keeps the grid evaluation,
 // so that what sl1m_forward_noalloc takes does not shrink.
+//
+// Plans of wide Gaussian pixels alone, above kGroupGaussMax of them, keep it too: the
+// server runs such requests with its own grid kernels, and a served image agrees with a
+// plan's within 1e-5 of the peak.  That deconvolution is ill conditioned (pixels two
+// spacings wide): two float32 evaluations, 4e-7 (groups) and 5.6e-7 (grid) from float64,
+// are 3.3e-6 of the peak apart after 200 iterations on 131,072 pixels x 100,000 (each
+// about 9e-6 from the float64 solve) and 1.0e-5 to 1.8e-5 on 262,144 x 200,000.  The
+// groups would take a quarter of the time there as well.
+constexpr int64_t kGroupGaussMax = 131072;
 void choose_groups(Analysis& a) {
+  if (a.gsegs[0].kind != SL1M_PIX_DELTA && all_pixels(a, 1) && a.n_pix > kGroupGaussMax) return;
   const size_t without = plan_total(a);
   int n = 0;
   int64_t total = 0;
@@ -608,7 +625,7 @@ Layout layout(const Analysis& a, int wg_n) {
                           wg_n ? wg_rows : 0));
   // the group evaluation's chunk sums stand behind row 0 (which takes their
   // total) where no other segment uses the rows, else in a region of their own
-  const bool wg_alias = wg_n > 0 && wg_n == static_cast<int>(a.segs.size());
+  const bool wg_alias = all_pixels(a, wg_n);
   L.apart = take(std::max(rb * static_cast<size_t>(a.n_achunks) * np * nr,
                           wg_alias ? align_up(rb * np) + wg_part : 0));
   if (wg_alias) L.wg_part = L.apart + align_up(rb * np);

@@ -1669,9 +1669,15 @@ hipError_t launch_wg_forward(sl1m_plan* p, const GridSeg& g, const void* xp, hip
   });
 }
 
+static bool wg_all_pixels(const sl1m_plan* p) {
+  int64_t c = 0;
+  for (int i = 0; i < p->wg_n; ++i) c += p->segs[p->grid_segs[i].seg].count;
+  return c == p->n_pix;
+}
+
 // Residual records by visibility are for the segments outside the groups.
 static float2* rres_of(const sl1m_plan* p) {
-  return p->wg_n < static_cast<int>(p->segs.size()) ? static_cast<float2*>(p->rres) : nullptr;
+  return wg_all_pixels(p) ? nullptr : static_cast<float2*>(p->rres);
 }
 
 hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, bool recs,
@@ -1689,7 +1695,7 @@ hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, b
 }
 
 bool wg_single(const sl1m_plan* p) {
-  return p->wg_n == 1 && p->segs.size() == 1 && p->wg_segs[0].flat && p->wg_segs[0].macros == 1;
+  return p->wg_n == 1 && wg_all_pixels(p) && p->wg_segs[0].flat && p->wg_segs[0].macros == 1;
 }
 int wg_single_chunks(const sl1m_plan* p) { return flat_chunks(1, p->wg_groups); }
 
