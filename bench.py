@@ -15,10 +15,10 @@ objective's forward (counted: evals = (2 steps + 1) N_p N_v).
 Reported beside it, in the same JSON line:
 * the full L1 solve of the workload (30 power-iteration steps for L, 100
   FISTA iterations, objective), timed once: `l1_solve_time_s`;
-* per-kernel durations of the grid evaluation (HIP events recorded by the
+* per-kernel durations of the operators (HIP events recorded by the
   library around each launch, on the launch stream) and the dominant
-  kernel's roofline: its executed FLOPs against the FP32 vector peak, and
-  its issue-slot model priced at the issue rates measured on this GPU;
+  kernel's roofline: its executed matrix FLOPs against the dense float16
+  matrix peak;
 * the served-latency part of the metric: config 5's stream of 256 requests
   (Poisson arrivals at 4/s, 200 FISTA iterations each), batched by the
   library's continuous-batching server and one at a time, p50/p99/mean
@@ -47,23 +47,17 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_FP32_TFLOPS = 157.3            # MI355X FP32 vector peak (published)
+PEAK_F16_MATRIX_TFLOPS = 2500.0     # MI355X dense float16 matrix peak (published)
 FLOP_PER_EVAL_DELTA = 14            # phase 3 FMA, reduction 2, sin+cos 2, accumulate 2 FMA
 FLOP_PER_EVAL_GAUSS_WIDE = 26       # + taper 9, amplitude 1, kappa FMA 2
-# The same counting rules (FMA = 2, sin, cos, exp2 = 1) applied to what the
-# grid kernels execute: a mirrored pair of delta cells (8 entries) costs one
-# FP64 phase FMA, one sin/cos pair and about 20 FP32 operations, 36 FLOP; a
-# single delta cell (4 entries) 24; a Gaussian cell (4 entries) one sin/cos
-# pair, two exp2 and about 26 FP32 operations, at most 32.
+# The group kernels' figure is their float16 matrix products: 8 real products
+# per delta cell (4 entries) and 16 per Gaussian cell, each as three split
+# products and one of the series' first order (more where the series needs it).
 EXEC_FLOP_PER_EVAL = {
-    "k_grid_fwd_delta_pairs": 4.5,
-    "k_grid_adj_delta_square": 4.5,
-    "k_grid_fwd_delta": 6.0,
-    "k_grid_adj_delta": 6.0,
-    "k_grid_fwd_gauss_pairs": 8.0,
-    "k_grid_adj_gauss_multi": 8.0,
-    "k_fwd_delta<float,4>": 14.0,
-    "k_adj_delta<float,4>": 14.0,
+    "k_wg_fwd": 16.0,
+    "k_wg_adj": 16.0,
+    "k_wg_fwd_gauss": 32.0,
+    "k_wg_adj_gauss": 32.0,
 }
 
 
@@ -93,6 +87,11 @@ def kernel_source_hash(kernel: str) -> str:
             return fh.read()
 
     base = kernel.split("<")[0]
+    if kernel.startswith("k_wg"):   # the group kernels share their file's device functions
+        h = hashlib.sha256()
+        for f in ("sl1m_wgroup.hip", "sl1m_wgroup_dev.h", "sl1m_wgroup.h", "sl1m_device.h"):
+            h.update(read(f).encode())
+        return h.hexdigest()[:16]
     grid = kernel.startswith("k_grid")
     parts = [_function_text(read("sl1m_grid.hip" if grid else "sl1m_kernels.hip"), base)]
     if grid:
@@ -104,33 +103,6 @@ def kernel_source_hash(kernel: str) -> str:
     for t in parts:
         h.update(t.encode())
     return h.hexdigest()[:16]
-
-
-# Inner-loop instruction mix of the grid kernels (counted in their gfx950
-# assembly): entries per wavefront unit of work, then FP32-rate (FP32
-# arithmetic, bit operations, integer), FP64, sin/cos and exp2 wave64
-# instructions per unit.  Units: the pair adjoints' a wavefront and a
-# visibility (64 lanes x 32 entries); the delta pair forward's a wavefront
-# and a (pair record, visibility) (64 lanes x 8 entries, with the per-|l|
-# phasors spread over the 8 records); the Gaussian pair forward's a wavefront
-# and an |l| value (64 lanes x 8 pair records x 8 entries); the direct
-# kernels' a wavefront and an entry.
-SLOT_MIX = {
-    "k_grid_adj_delta_square": (2048, 72, 6, 12, 0),
-    "k_grid_fwd_delta_pairs": (512, 21.25, 1.25, 2.5, 0),
-    "k_grid_adj_gauss_multi": (2048, 158, 10, 12, 4),
-    "k_grid_fwd_gauss_pairs": (4096, 319, 18, 20, 4),
-    "k_adj_delta<float,4>": (64, 3, 3, 2, 0),
-    "k_fwd_delta<float,4>": (64, 3, 3, 2, 0),
-}
-
-
-def slot_model_s(name, evals, rates, cus):
-    """Issue-slot time of `evals` entries of kernel `name` at the measured
-    per-CU issue rates."""
-    per_unit, n32, n64, ntr, nexp = SLOT_MIX[name]
-    return (evals / per_unit) / cus * (n32 / rates["fp32_fma"] + n64 / rates["fp64_fma"]
-                                       + ntr / rates["sin_cos"] + nexp / rates["exp"])
 
 
 HBM_PEAK_BPS = 8.0e12  # MI355X HBM3E, published
@@ -198,12 +170,9 @@ def ingest_counters(fetch_csv, write_csv, bench_log=None):
         scale = CALIB_BYTES / (sum(big) / len(big))
         for key, pat in (("k_fwd_delta<float,4>", "k_fwd_delta<float, 4, false, 1>"),
                          ("k_adj_delta<float,4>", "k_adj_delta<float, 4, false, 1>"),
-                         ("k_grid_fwd_delta_pairs", "k_grid_fwd_delta_pairs"),
-                         ("k_grid_adj_delta_square", "k_grid_adj_delta_square"),
-                         ("k_grid_fwd_delta", "k_grid_fwd_delta("),
-                         ("k_grid_adj_delta", "k_grid_adj_delta("),
-                         ("k_grid_fwd_gauss_pairs", "k_grid_fwd_gauss_pairs"),
-                         ("k_grid_adj_gauss_multi", "k_grid_adj_gauss_multi")):
+                         ("k_wg_fwd", "k_wg_fwd("), ("k_wg_adj", "k_wg_adj("),
+                         ("k_wg_fwd_gauss", "k_wg_fwd_gauss("),
+                         ("k_wg_adj_gauss", "k_wg_adj_gauss(")):
             vals = [v for n, v in rows if pat in n]
             if vals:
                 rec = out.setdefault(key, {"source_hash": kernel_source_hash(key)})
@@ -489,17 +458,14 @@ def config4_data(wl4, plan, dev):
 
 
 def dominant_kernel(pinfo, tim, n_delta, n_gauss, n_vis, n_layers):
-    """The grid kernel with the longest average launch in the timed region:
-    (name, average ms, evals per launch)."""
-    pairs = bool(pinfo["grid_pairs"])
+    """The operator kernel with the longest average launch in the timed region:
+    (name, average ms, evals per launch).  Plans of one right-hand side on these
+    grids take the group evaluation (one launch per Gaussian layer)."""
     cands = [
-        ("k_grid_fwd_delta_pairs" if pairs else "k_grid_fwd_delta", "grid_fwd_delta",
-         n_delta * n_vis),
-        ("k_grid_adj_delta_square" if pairs else "k_grid_adj_delta", "grid_adj_delta",
-         n_delta * n_vis),
-        ("k_grid_adj_gauss_multi", "grid_adj_gauss", n_gauss * n_vis),
-        # one launch per layer: evals per launch on average
-        ("k_grid_fwd_gauss_pairs", "grid_fwd_gauss", n_gauss * n_vis / max(n_layers, 1)),
+        ("k_wg_fwd", "grid_fwd_delta", n_delta * n_vis),
+        ("k_wg_adj", "grid_adj_delta", n_delta * n_vis),
+        ("k_wg_adj_gauss", "grid_adj_gauss", n_gauss * n_vis / max(n_layers, 1)),
+        ("k_wg_fwd_gauss", "grid_fwd_gauss", n_gauss * n_vis / max(n_layers, 1)),
     ]
     best = None
     for name, key, ev in cands:
@@ -569,40 +535,33 @@ def headline(args, dev):
     dom_name, dom_ms, dom_evals = dominant_kernel(pinfo, tim, n_delta, n_gauss, n_vis, n_layers)
     exec_flop = EXEC_FLOP_PER_EVAL[dom_name]
     achieved = exec_flop * dom_evals / (dom_ms * 1e-3) / 1e12
-    canonical = (FLOP_PER_EVAL_DELTA if "delta" in dom_name else FLOP_PER_EVAL_GAUSS_WIDE)
+    canonical = (FLOP_PER_EVAL_GAUSS_WIDE if "gauss" in dom_name else FLOP_PER_EVAL_DELTA)
     # executed FLOPs of one iteration (both operators) over the time of a step
-    exec_step = 2 * n_vis * (n_delta * EXEC_FLOP_PER_EVAL["k_grid_adj_delta_square"]
-                             + n_gauss * EXEC_FLOP_PER_EVAL["k_grid_adj_gauss_multi"])
+    exec_step = 2 * n_vis * (n_delta * EXEC_FLOP_PER_EVAL["k_wg_adj"]
+                             + n_gauss * EXEC_FLOP_PER_EVAL["k_wg_adj_gauss"])
     canon_step = 2 * n_vis * (n_delta * FLOP_PER_EVAL_DELTA + n_gauss * FLOP_PER_EVAL_GAUSS_WIDE)
     step_s = elapsed / args.steps
     roof = {
         "bound": "alu",
         "kernel": dom_name,
         "achieved": achieved,
-        "peak": PEAK_FP32_TFLOPS,
+        "peak": PEAK_F16_MATRIX_TFLOPS,
         "unit": "TFLOP/s",
-        "frac": achieved / PEAK_FP32_TFLOPS,
+        "frac": achieved / PEAK_F16_MATRIX_TFLOPS,
         "traffic": load_traffic(dom_name, plan_shape),
         "kernel_avg_ms": dom_ms,
         "evals_per_launch": dom_evals,
         "executed_flop_per_eval": exec_flop,
-        "accounting": "achieved/frac: the FLOPs the kernel executes (FMA = 2; sin, cos, exp2 = "
-                      "1; the grid factorisation shares one sincos among 4 or 8 entries) over "
-                      "its average launch duration (HIP events on the launch stream); "
-                      "effective_*: the direct evaluation's count per entry at the same rate",
+        "accounting": "achieved/frac: the float16 matrix FLOPs the kernel executes at least "
+                      "(three split products and one order of the series per real product of "
+                      "a cell's factors) over its average launch duration (HIP events on the "
+                      "launch stream), against the dense float16 matrix peak; the vector "
+                      "instructions that form its operands take more issue time than these "
+                      "(profiles/group_kernels_config2_counters.md); effective_*: the direct "
+                      "evaluation's FP32 count per entry at the same rate",
         "effective_flop_per_eval": canonical,
         "effective_tflops": canonical * dom_evals / (dom_ms * 1e-3) / 1e12,
     }
-    rates = sl1m.issue_rates(dev)
-    cus = torch.cuda.get_device_properties(dev).multi_processor_count
-    if dom_name in SLOT_MIX:
-        per_unit, n32, n64, ntr, nexp = SLOT_MIX[dom_name]
-        t_model = slot_model_s(dom_name, dom_evals, rates, cus)
-        roof["slots"] = {
-            "unit": "wave64 instructions per s per CU", "rates": rates, "cus": cus,
-            "mix_per_unit": {"entries": per_unit, "fp32_rate": n32, "fp64": n64, "sin_cos": ntr,
-                             "exp": nexp},
-            "model_ms": t_model * 1e3, "frac": t_model * 1e3 / dom_ms}
     out = {
         "metric": "pixel x visibility evals/s (forward + adjoint) of the L1 solve on config 4; "
                   "L1 solve time; p50/p99 served latency (config 5)",
@@ -615,7 +574,7 @@ def headline(args, dev):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32 (f64 phase)",
+        "dtype": "f32 (f64 phase; matrix products as split f16 pairs with f32 sums)",
         "data": "synthetic",
         "config": {
             "workload": "config4: 1024^2 wide-field delta grid over +-0.35 plus wide-field "
@@ -643,7 +602,7 @@ def headline(args, dev):
             "grid_fwd_delta_avg_ms": avg["grid_fwd_delta"],
             "grid_adj_delta_avg_ms": avg["grid_adj_delta"],
             "grid_fwd_gauss_avg_ms_per_layer": avg["grid_fwd_gauss"],
-            "grid_adj_gauss_avg_ms": avg["grid_adj_gauss"],
+            "grid_adj_gauss_avg_ms_per_layer": avg["grid_adj_gauss"],
             # the update's algorithmic bytes: read the gradient (adjoint
             # output), scale, y and I, write y and I -- 20 B per pixel
             "fista_update_hbm_gbs": 20.0 * n_pix / (avg["fista"] * 1e-3) / 1e9
@@ -656,16 +615,6 @@ def headline(args, dev):
         },
         "roofline": roof,
     }
-    # every grid kernel against its issue-slot model (per launch)
-    pairs = bool(pinfo["grid_pairs"])
-    slot = {}
-    for name, key, ev in (("k_grid_fwd_delta_pairs", "grid_fwd_delta", n_delta * n_vis),
-                          ("k_grid_adj_delta_square", "grid_adj_delta", n_delta * n_vis),
-                          ("k_grid_adj_gauss_multi", "grid_adj_gauss", n_gauss * n_vis),
-                          ("k_grid_fwd_gauss_pairs", "grid_fwd_gauss", n_gauss * n_vis / n_layers)):
-        if pairs and avg.get(key) and name in SLOT_MIX:
-            slot[name] = slot_model_s(name, ev, rates, cus) * 1e3 / avg[key]
-    out["kernels"]["slot_frac"] = slot
     ctx = {"wl": wl4, "plan": plan, "data": V, "extended_data": V_ext,
            "evals_per_s": evals / elapsed}
     return out, ctx
@@ -700,15 +649,11 @@ def config2_secondary(dev, steps=20):
            "grid_adj_delta_avg_ms": avg["grid_adj_delta"],
            "grid_fwd_delta_avg_ms": avg["grid_fwd_delta"],
            "plan": {k: pinfo[k] for k in PLAN_KEYS}}
-    name = "k_grid_adj_delta_square"
-    if avg["grid_adj_delta"] and name in SLOT_MIX:
-        rates = sl1m.issue_rates(dev)
-        cus = torch.cuda.get_device_properties(dev).multi_processor_count
-        t_model = slot_model_s(name, wl.n_pix * wl.n_vis, rates, cus)
-        out["adjoint_slot_frac"] = t_model * 1e3 / avg["grid_adj_delta"]
+    name = "k_wg_adj"
+    if avg["grid_adj_delta"]:
         out["adjoint_executed_frac"] = (EXEC_FLOP_PER_EVAL[name] * wl.n_pix * wl.n_vis
                                         / (avg["grid_adj_delta"] * 1e-3) / 1e12
-                                        / PEAK_FP32_TFLOPS)
+                                        / PEAK_F16_MATRIX_TFLOPS)
         out["adjoint_traffic"] = load_traffic(name, out["plan"])
     return plan, wl, out
 

@@ -179,7 +179,10 @@ typedef enum {
  *            its distinct |l| and |m| values (padded to a multiple of 8 |m|
  *            values), times four signs, holds at most 2.5 times as many
  *            positions as it has pixels.  SL1M_GRID_REQUIRE needs at least
- *            one qualifying segment.
+ *            one qualifying segment.  Plans with max_rhs 0 or 1 evaluate their
+ *            qualifying segments in groups of visibilities of nearly one |w|
+ *            on the matrix cores where that is faster (float32 operands as
+ *            float16 pairs, float32 sums); sl1m_plan_create reads w for it.
  */
 typedef struct {
   int64_t n_pix;
@@ -420,11 +423,12 @@ sl1m_status sl1m_dirty_image(sl1m_plan* plan, const void* vis, void* img_out, vo
  * events and reports, per kind, the number of timed launches and the sum of
  * their durations in milliseconds.  Kinds: 0 = forward operator kernels,
  * 1 = adjoint operator kernels, 2 = FISTA vector update; and single launches
- * of the grid evaluation inside kinds 0 and 1: 3 = delta forward
- * (k_grid_fwd_delta_pairs or k_grid_fwd_delta), 4 = delta adjoint
- * (k_grid_adj_delta_square or k_grid_adj_delta), 5 = Gaussian forward (one
- * launch per layer), 6 = Gaussian adjoint (every layer in one launch);
- * 7 is unused.
+ * of the grid and group evaluations inside kinds 0 and 1: 3 = delta forward
+ * (k_wg_fwd or k_flat_fwd; k_grid_fwd_delta_pairs or k_grid_fwd_delta), 4 =
+ * delta adjoint (k_wg_adj or k_flat_adj; k_grid_adj_delta_square or
+ * k_grid_adj_delta), 5 = Gaussian forward (one launch per layer), 6 =
+ * Gaussian adjoint (one launch per layer; every layer outside the group
+ * evaluation in one launch); 7 is unused.
  *
  * Host trace ranges: sl1m_plan_create, sl1m_tune, the power iteration, every
  * solve ("sl1m solve"), sl1m_server_step and each plan build of the server's
