@@ -192,8 +192,13 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_fwd(
   const float eta_max = cm->eta_max, xs = cm->xs, m_lo = cm->m_lo, m_hi = cm->m_hi;
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, quad = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool active = wv < sets;
-  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? wv : 0) * kFlatCells;
+  // one or two row sets: the wavefronts share a set's visibility tiles (the operands are
+  // loaded once, so nothing is formed twice)
+  const int set = sets == 1 ? 0 : sets == 2 ? wv >> 1 : wv;
+  const int t_lo = sets == 1 ? wv : sets == 2 ? 2 * (wv & 1) : 0;
+  const int t_hi = sets == 1 ? wv + 1 : sets == 2 ? t_lo + 2 : 4;
+  const bool active = set < sets;
+  const int64_t cell0 = cm->cell_off + static_cast<int64_t>(active ? set : 0) * kFlatCells;
   FlatVis rn = in.load(g0, lane, xs);
   int sn = in.ser(g0, eta_max), cn = as_const(in.cnt)[g0];
   if (tid < 4 * kWgRows) {
@@ -283,7 +288,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_fwd(
     if (active) {
       float sr = 0.0f, si = 0.0f;
 #pragma unroll 1
-      for (int t = 0; t < nt; ++t) {
+      for (int t = t_lo; t < (nt < t_hi ? nt : t_hi); ++t) {
         const int v = 16 * t + r16;
         const uint4* col = lds.col + quad * 4 * 64 + v;
         f4_t d[4];
@@ -297,7 +302,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_fwd(
         float vr = 0.0f, vi = 0.0f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int row = wv * kWgRows + quad * 4 + i;
+          const int row = set * kWgRows + quad * 4 + i;
           const double l = lds.la[row];
           float pc, ps, mc, ms;
           flat_phasors<GAUSS>(A, C, w, l, lds.al[row], pc, ps, mc, ms);
