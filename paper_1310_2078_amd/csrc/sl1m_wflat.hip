@@ -489,7 +489,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_adj(
     sn = in.ser(g0, eta_max);
   }
   __syncthreads();
-  const float sc = op_scale(2.0f * fmaxf(fmaxf(lds.mx[0], lds.mx[1]), fmaxf(lds.mx[2], lds.mx[3])));
+  const float sc =
+      0.5f * op_scale(fmaxf(fmaxf(lds.mx[0], lds.mx[1]), fmaxf(lds.mx[2], lds.mx[3])));
   for (int g = g0; g < n_groups; g += gs) {
     const FlatVis r = rn;
     const int ser = sn;

@@ -237,7 +237,7 @@ bool wg_build_groups(const std::vector<double>& w, float width, int64_t max_grou
   if (wm >= 0x1.0p27) return false;  // phases below 2^27 turns (|nu| < 1): kMagicFine
   // order by |w| in 2^20 bins (two stable counting passes of 10 bits); equal bins
   // keep the caller's order
-  const double scale = wm > 0.0 ? 1048575.0 / wm : 0.0;
+  const double scale = wm > 1e-290 ? 1048575.0 / wm : 0.0;
   std::vector<uint32_t> key(n);
   std::vector<int32_t> a(n), b(n);
   for (int64_t k = 0; k < n; ++k) {
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
       e[s][j] = make_float4(sum, (x1 + x2) - (x0 + x3), (x0 + x1) - (x2 + x3),
                             (x0 - x1) + (x2 - x3));
     }
-  const float c = op_scale(4.0f * wave_max(mx)), sc = 1.0f / c;
+  const float c = 0.25f * op_scale(wave_max(mx)), sc = 1.0f / c;  // 4 mx may overflow
 #pragma unroll
   for (int s = 0; s < kWgSteps; ++s)
 #pragma unroll
@@ -1452,7 +1452,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
     const float ct = k * fmaf(r.D, c0, -r.Ds * s0), st = k * fmaf(r.D, s0, r.Ds * c0);
     const float rr = fmaf(ct, zn.x, st * zn.y), ri = fmaf(ct, zn.y, -st * zn.x);
     const float am = fmaxf(fabsf(rr), fabsf(ri));
-    const float sc = op_scale(2.0f * wave_max(rr != rr || ri != ri ? __builtin_inff() : am));
+    const float sc = 0.5f * op_scale(wave_max(rr != rr || ri != ri ? __builtin_inff() : am));
     lds.rho[wv][lane] = make_float2(rr * sc, ri * sc);
     lds.top[wv][lane] = ltop;
     const float inv = kGDown / sc;

@@ -107,6 +107,20 @@ def test_scales_zeros_and_non_finite():
     assert not np.isfinite(plan.adjoint(r).cpu().numpy()).any()
 
 
+@pytest.mark.parametrize("name", ["many_groups", "odd_17_tiles"])
+def test_amplitudes_near_the_largest_float(name):
+    """One pixel or one visibility of 2^120 (exact: powers of two) and of 2^126."""
+    wl, x, r = _case(name)
+    plan = sl1m.Plan.from_workload(wl)
+    x, r = 0 * x, 0 * r
+    x[7], r[9] = 1.0, 1.0
+    for f, v in ((plan.forward, x), (plan.adjoint, r)):
+        a, b = f(v).cpu().numpy(), f(v * 2.0 ** 120).cpu().numpy()
+        assert np.array_equal(b, a * np.float32(2.0 ** 120))
+        c = f(v * 2.0 ** 126).cpu().numpy()
+        assert np.isfinite(c).all() and rel(c / np.float32(2.0 ** 126), a) <= TOL
+
+
 # name: |l| x |m| pixels, spacing, sigma (spacings), kind, visibilities, w spread, with a
 # delta grid of twice the resolution
 GAUSS = {
