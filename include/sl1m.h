@@ -282,7 +282,9 @@ typedef struct {
                                segment a square delta grid); 0: direct        */
   int32_t grid_mfma;        /* matrix-core plan whose forward runs on the grid
                                evaluation (all pixels one square delta grid) */
-  int32_t reserved[2];
+  int32_t grid_groups;      /* grid segments (the first ones) that single-RHS calls
+                               evaluate in groups of visibilities on the matrix cores */
+  int32_t grid_flat;        /* bit i: segment i of these without cell factors  */
 } sl1m_plan_info;
 
 sl1m_status sl1m_plan_query(const sl1m_plan* plan, sl1m_plan_info* info);

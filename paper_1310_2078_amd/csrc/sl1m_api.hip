@@ -698,16 +698,10 @@ Layout layout(const Analysis& a, int wg_n) {
   return L;
 }
 
-// A plan whose visibilities make too many groups for n of its segments (Gaussian
-// layers take narrower ones) tries the first, a delta grid's, alone, then goes without.
-int fewer_groups(const Analysis& a, int n) {
-  return n > 1 && a.gsegs[0].kind == SL1M_PIX_DELTA ? 1 : 0;
-}
-
 size_t plan_total(const Analysis& a) {
   size_t bytes = layout(a, a.wg_n).total;
   for (int n = a.wg_n; n > 0;) {
-    n = fewer_groups(a, n);
+    n = wg_fewer(a.gsegs[0], n);
     bytes = std::max(bytes, layout(a, n).total);
   }
   return bytes;
@@ -921,21 +915,9 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       SL1M_HIP(hipMemcpyAsync(w.data(), pr->w, a.n_vis * sizeof(double), hipMemcpyDeviceToHost, st),
                "read w");
       SL1M_HIP(hipStreamSynchronize(st), "read w");
-      double w_max = 0.0;
-      for (double x : w) w_max = std::max(w_max, std::fabs(x));
-      for (int i = 0; i < a.wg_n; ++i) {
-        const GridSeg& g = a.gsegs[i];
-        wg_build_tiles(g, a.grid_la.data() + g.la_off, a.grid_mb.data() + g.mb_off,
-                       (g.kind == SL1M_PIX_DELTA ? a.grid_c3 : a.grid_c4).data() + g.cell_off,
-                       a.grid_slot.data() + 4 * g.cell_off, w_max, wgp);
-      }
-      while (a.wg_n) {
-        wgg = WgGroups();
-        float width = 0.0f;
-        for (int i = 0; i < a.wg_n; ++i) width = std::max(width, wgp.segs[i].width);
-        if (wg_build_groups(w, width, a.wg_cap, wgg)) break;
-        a.wg_n = fewer_groups(a, a.wg_n);
-      }
+      const WgGrids grids{a.grid_la.data(), a.grid_mb.data(), a.grid_c3.data(), a.grid_c4.data(),
+                          a.grid_slot.data()};
+      a.wg_n = wg_build(a.gsegs.data(), a.wg_n, grids, w, a.wg_cap, wgp, wgg);
     }
     const Layout L = layout(a, a.wg_n);
     sl1m_plan* p = new sl1m_plan();
@@ -1050,7 +1032,7 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
 
     if (a.wg_n) {
       p->wg_n = a.wg_n;
-      p->wg_segs.assign(wgp.segs.begin(), wgp.segs.begin() + a.wg_n);
+      p->wg_segs = wgp.segs;
       for (const WgSeg& s2 : p->wg_segs) p->wg_macros += s2.macros;
       p->wg_groups = static_cast<int>(wgg.w0.size());
       p->wg_recg = reinterpret_cast<WgVisG*>(w + L.wg_recg);
@@ -1108,24 +1090,32 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
     };
     if (a.wg_n) {
       const WgPlan& t = wgp;
-      up(p->wg_mac, t.macros.data(), sizeof(WgMacro) * t.macros.size());
-      up(p->wg_la, t.la.data(), 8 * t.la.size());
-      up(p->wg_mb, t.mb.data(), 8 * t.mb.size());
-      up(p->wg_nu, t.nu.data(), 8 * t.nu.size());
-      up(p->wg_eta, t.eta.data(), 4 * t.eta.size());
-      up(p->wg_alpha, t.alpha.data(), 8 * t.alpha.size());
-      up(p->wg_beta, t.beta.data(), 8 * t.beta.size());
-      up(p->wg_slot, t.slot.data(), 4 * t.slot.size());
+      // a table never leaves its region [at, end)
+      auto put = [&](size_t at, size_t end, const auto& v) {
+        const size_t bytes = sizeof(v[0]) * v.size();
+        if (bytes > end - at)
+          e = hipErrorInvalidValue;
+        else
+          up(w + at, v.data(), bytes);
+      };
+      put(L.wg_mac, L.wg_la, t.macros);
+      put(L.wg_la, L.wg_mb, t.la);
+      put(L.wg_mb, L.wg_alpha, t.mb);
+      put(L.wg_alpha, L.wg_beta, t.alpha);
+      put(L.wg_beta, L.wg_nu, t.beta);
+      put(L.wg_nu, L.wg_eta, t.nu);
+      put(L.wg_eta, L.wg_slot, t.eta);
+      put(L.wg_slot, L.wg_order, t.slot);
       if (wg_single(p)) {
         wg_map.resize(a.n_pix);
         for (size_t i = 0; i < t.slot.size(); ++i)
           if (t.slot[i] >= 0) wg_map[t.slot[i]] = static_cast<int32_t>(i);
-        up(p->wg_map, wg_map.data(), 4 * wg_map.size());
+        put(L.wg_map, L.wg_recg, wg_map);
       }
-      up(p->wg_order, wgg.order.data(), 4 * wgg.order.size());
-      up(p->wg_count, wgg.count.data(), 4 * wgg.count.size());
-      up(p->wg_w0, wgg.w0.data(), 8 * wgg.w0.size());
-      up(p->wg_h, wgg.h.data(), 4 * wgg.h.size());
+      put(L.wg_order, L.wg_count, wgg.order);
+      put(L.wg_count, L.wg_su, wgg.count);
+      put(L.wg_w0, L.wg_res, wgg.w0);
+      put(L.wg_h, L.total, wgg.h);
     }
     if (a.grid) {
       up(p->grid_la, a.grid_la.data(), 8 * a.grid_la.size());
@@ -1423,6 +1413,8 @@ sl1m_status sl1m_plan_query(const sl1m_plan* p, sl1m_plan_info* info) {
   for (const GridSeg& g : p->grid_segs) r.grid_pairs += g.square ? 1 : 0;
   r.grid_multi = p->grid_multi;
   r.grid_mfma = p->grid_mfma ? 1 : 0;
+  r.grid_groups = p->wg_n;
+  for (int i = 0; i < p->wg_n; ++i) r.grid_flat |= p->wg_segs[i].flat << i;
   *info = r;
   return SL1M_OK;
 }

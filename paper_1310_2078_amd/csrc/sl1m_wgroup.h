@@ -113,6 +113,18 @@ void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const 
                     const int32_t* slot, double w_max, WgPlan& out);
 bool wg_build_groups(const std::vector<double>& w, float width, int64_t max_groups,
                      WgGroups& out);
+// The grid tables that the segments' offsets (GridSeg) point into.
+struct WgGrids {
+  const double *la, *mb, *nu, *kappa;
+  const int32_t* slot;
+};
+// The tables of the first n segments and the groups of the visibilities; those of fewer
+// segments (wg_fewer) where their width makes more than max_groups.  Returns how many.
+int wg_build(const GridSeg* segs, int n, const WgGrids& in, const std::vector<double>& w,
+             int64_t max_groups, WgPlan& plan, WgGroups& groups);
+// A plan whose visibilities make too many groups for n of its segments (Gaussian layers
+// take narrower ones) tries the first, a delta grid's, alone, then goes without.
+int wg_fewer(const GridSeg& first, int n);
 // groups a plan reserves room for
 int64_t wg_group_cap(int64_t n_vis);
 // group chunks (blocks per macro) of the operator kernels, at most wg_chunk_cap()

@@ -1,6 +1,4 @@
-// Group evaluation of grid segments (sl1m_wgroup.h): host tables, kernels
-// and launchers.
-#include <algorithm>
+// Group evaluation of grid segments (sl1m_wgroup.h): kernels and launchers.
 #include <cmath>
 
 #include "sl1m_device.h"
@@ -8,271 +6,6 @@
 #include "sl1m_wgroup_dev.h"
 
 namespace sl1m {
-
-// ---------------------------------------------------------------------------
-// host tables
-// ---------------------------------------------------------------------------
-
-// Groups that hold few visibilities (sparse w, a wide field: the cut at kWgX ends
-// them early) still cost C_0 and the float16 splits of every cell.  Measured on
-// 256 x 256 pixels over +-0.3: 97,536 visibilities (1.19 times the full groups)
-// take 0.66 of the grid evaluation's time, 20,000 (2.28 times) 0.98 of it forward
-// and 1.17 adjoint; the line is drawn between.
-int64_t wg_group_cap(int64_t n_vis) {
-  const int64_t full = (n_vis + kWgVis - 1) / kWgVis;
-  return full + full * 3 / 4 + 2;
-}
-
-// Blocks: two of 256 threads stay resident per compute unit (512 in all).  Two
-// rounds of them for small grids (each block loads its tiles' cells first, and
-// the adjoint's chunk sums grow with the count), four for large ones, whose
-// macros differ more in work (256 x 256 x 97,536: 397 / 428 us at two rounds,
-// 395 / 424 at four, 402 / 442 at eight; 100,003 x 151 x 150 pixels 89 / 102 us
-// at two, 89 / 107 at three; 1024 x 1024 x 409,600: 28.4 / 31.5 ms at two, 27.3 /
-// 29.9 at four).
-int wg_chunk_cap(int macros) { return std::max(1, (macros <= 32 ? 1024 : 2048) / macros); }
-int wg_chunks(int macros, int groups) {
-  return std::max(1, std::min(groups, wg_chunk_cap(macros)));
-}
-
-int64_t wg_padded(const GridSeg& g) {
-  return static_cast<int64_t>((g.na + kWgRows - 1) / kWgRows * kWgRows) * ((g.nb + 15) / 16 * 16);
-}
-
-// Flat segments: one round of the blocks that stay resident (256 x 256 x 100,000: 210 /
-// 293 us, two rounds 222 / 305; 300 x 300 Gaussian pixels x 100,003: 302 / 435, two
-// rounds 316 / 446).
-int flat_chunk_cap(int macros) { return std::max(1, 512 / macros); }
-int flat_chunks(int macros, int groups) {
-  return std::max(1, std::min(groups, flat_chunk_cap(macros)));
-}
-
-namespace {
-
-// Macros and tile cells of a segment in tiles of up to `cs` column steps.
-struct WgShape {
-  int rsets, rmac, steps, cmac;
-  bool lone;
-  WgShape(const GridSeg& g, int cs)
-      : rsets((g.na + kWgRows - 1) / kWgRows), rmac((rsets + 3) / 4), steps((g.nb + 15) / 16),
-        cmac((steps + cs - 1) / cs), lone(cs == kWgSteps && rsets % 4 == 1 && rsets <= 9) {}
-  // Evenly over the macros, but one set over (2^k pixels a side: 2^(k-1) + 1 |l| values)
-  // has the last macro for itself, whose wavefronts share it, where that is much of the
-  // grid: five sets 0.55 against 0.69 ms (128 x 128 Gaussian pixels x 409,600, forward),
-  // nine sets 376 against 395 us (256 x 256 x 97,536); at 33 sets what the four form
-  // each for themselves costs more (10.1 against 9.8 ms).  Flat segments form less and
-  // are evaluated faster without (256 x 256 x 100,000: 210 against 217 us).
-  int first_set(int ri) const {
-    return lone ? std::min(4 * ri, rsets) : rsets * ri / rmac;
-  }
-  int macros() const { return rmac * cmac; }
-  int64_t cells(int cs) const { return static_cast<int64_t>(rsets) * cmac * kWgRows * 16 * cs; }
-};
-
-// largest magnitude e as a power of two s: e / s in [1/2, 1), 1 for 0
-double pow2_of(double e) {
-  int ex = 0;
-  (void)std::frexp(e, &ex);
-  return e > 0.0 ? std::ldexp(1.0, ex) : 1.0;
-}
-
-// One segment's tables.  Flat segments and Gaussian ones: c = alpha(l) + beta(m) + eta,
-// exact along the macro's middle row and column, each tile's eta centred by its rows'
-// alpha (and nu holds eta); other delta segments, whose real factors of l and m have no
-// place for alpha and beta: c = nu_t + eta.
-// Row sets of kWgRows |l| values and column sets of up to `cs` steps of 16 |m| values,
-// spread over the macros.
-void append_segment(const GridSeg& g, const double* la, const double* mb, const double* c,
-                    const int32_t* slot, bool flat, WgPlan& out) {
-  const int na = g.na, nb = g.nb, cs = flat ? kFlatSteps : kWgSteps;
-  const bool parts = flat || g.kind != SL1M_PIX_DELTA;
-  const size_t tile = static_cast<size_t>(kWgRows) * 16 * cs;
-  const WgShape sh(g, cs);
-  WgSeg seg{};
-  seg.mac0 = static_cast<int32_t>(out.macros.size());
-  seg.cell0 = static_cast<int64_t>(out.nu.size());
-  seg.flat = flat ? 1 : 0;
-  double seg_eta = 0.0;
-  auto cell = [&](int ia, int ib) {
-    return (static_cast<int64_t>(ib / kGridNB) * na + ia) * kGridNB + ib % kGridNB;
-  };
-  for (int ri = 0; ri < sh.rmac; ++ri)
-    for (int ci = 0; ci < sh.cmac; ++ci) {
-      const int r0 = sh.first_set(ri), r1 = sh.first_set(ri + 1);
-      const int s0 = sh.steps * ci / sh.cmac, s1 = sh.steps * (ci + 1) / sh.cmac;
-      const int a0 = kWgRows * r0, a1 = std::min(kWgRows * r1, na);
-      const int b0 = 16 * s0, b1 = std::min(16 * s1, nb);
-      WgMacro m{};
-      m.sets = r1 - r0;
-      m.steps = s1 - s0;
-      m.a_off = static_cast<int32_t>(out.la.size());
-      m.b_off = static_cast<int32_t>(out.mb.size());
-      m.cell_off = static_cast<int32_t>(out.nu.size());
-      m.m_lo = static_cast<float>(mb[b0]);
-      m.m_hi = static_cast<float>(mb[b1 - 1]);
-      out.la.resize(out.la.size() + 4 * kWgRows, 0.0);
-      out.alpha.resize(out.la.size(), 0.0);
-      out.mb.resize(out.mb.size() + 16 * cs, 0.0);
-      out.beta.resize(out.mb.size(), 0.0);
-      double* const al = &out.alpha[m.a_off];
-      double* const be = &out.beta[m.b_off];
-      std::copy(la + a0, la + a1, &out.la[m.a_off]);
-      std::copy(mb + b0, mb + b1, &out.mb[m.b_off]);
-      if (parts) {
-        const int ic = (a0 + a1) / 2, jc = (b0 + b1) / 2;
-        for (int ia = a0; ia < a1; ++ia) al[ia - a0] = c[cell(ia, jc)] - c[cell(ic, jc)];
-        for (int ib = b0; ib < b1; ++ib) be[ib - b0] = c[cell(ic, ib)];
-      }
-      double eta_max = 0.0;
-      const size_t first = out.nu.size();
-      out.nu.resize(first + m.sets * tile, 0.0);
-      out.eta.resize(first + m.sets * tile, 0.0f);
-      out.slot.resize(4 * (first + m.sets * tile), -1);
-      std::vector<double> rest(m.sets * tile, 0.0);
-      for (int w = 0; w < m.sets; ++w) {
-        const int t0 = a0 + kWgRows * w, t1 = std::min(t0 + kWgRows, na);
-        m.l_lo[w] = static_cast<float>(la[t0]);
-        m.l_hi[w] = static_cast<float>(la[t1 - 1]);
-        double lo = 1e300, hi = -1e300;
-        for (int ib = b0; ib < b1; ++ib)
-          for (int ia = t0; ia < t1; ++ia) {
-            const double v = c[cell(ia, ib)] - al[ia - a0] - be[ib - b0];
-            lo = std::min(lo, v);
-            hi = std::max(hi, v);
-          }
-        // the tile's reference: in the rows' alpha, or as the kernels hold it (float32)
-        double mid = 0.5 * (lo + hi);
-        if (parts) {
-          for (int ia = t0; ia < t1; ++ia) al[ia - a0] += mid;
-          mid = 0.0;
-        }
-        m.nu_t[w] = static_cast<float>(mid);
-        const double nt = static_cast<double>(m.nu_t[w]);
-        for (int ib = b0; ib < b1; ++ib)
-          for (int ia = t0; ia < t1; ++ia) {
-            const int64_t q = cell(ia, ib);
-            const size_t o = w * tile + static_cast<size_t>(ib - b0) * kWgRows + (ia - t0);
-            rest[o] = c[q] - al[ia - a0] - be[ib - b0] - nt;
-            out.nu[first + o] = parts ? rest[o] : c[q];
-            eta_max = std::max(eta_max, std::fabs(rest[o]));
-            for (int s = 0; s < 4; ++s) out.slot[4 * (first + o) + s] = slot[4 * q + s];
-          }
-      }
-      // eta / s in [-1, 1] and x s (at most 2 kWgX) both lie in float16's range
-      const double s = pow2_of(eta_max);
-      for (size_t o = 0; o < rest.size(); ++o) out.eta[first + o] = static_cast<float>(rest[o] / s);
-      m.xs = static_cast<float>(6.283185307179586 * s);
-      m.eta_max = static_cast<float>(eta_max);
-      seg_eta = std::max(seg_eta, eta_max);
-      out.macros.push_back(m);
-    }
-  // a flat segment's groups may be of any width
-  const float limit = g.kind == SL1M_PIX_DELTA ? kWgX : kWgXN;
-  seg.width = flat ? 0.0f : static_cast<float>(seg_eta) / limit;
-  seg.macros = static_cast<int32_t>(out.macros.size()) - seg.mac0;
-  seg.cells = static_cast<int64_t>(out.nu.size()) - seg.cell0;
-  out.segs.push_back(seg);
-}
-
-// Largest |eta| of the segment's flat tables.
-double flat_eta(const GridSeg& g, const double* c) {
-  const WgShape sh(g, kFlatSteps);
-  auto at = [&](int ia, int ib) {
-    return c[(static_cast<int64_t>(ib / kGridNB) * g.na + ia) * kGridNB + ib % kGridNB];
-  };
-  double top = 0.0;
-  for (int ri = 0; ri < sh.rmac; ++ri)
-    for (int ci = 0; ci < sh.cmac; ++ci) {
-      const int a0 = kWgRows * sh.first_set(ri), b0 = 16 * (sh.steps * ci / sh.cmac);
-      const int a1 = std::min(kWgRows * sh.first_set(ri + 1), g.na);
-      const int b1 = std::min(16 * (sh.steps * (ci + 1) / sh.cmac), g.nb);
-      const int ic = (a0 + a1) / 2, jc = (b0 + b1) / 2;
-      for (int t0 = a0; t0 < a1; t0 += kWgRows) {
-        const int t1 = std::min(t0 + kWgRows, a1);
-        double lo = 1e300, hi = -1e300;
-        for (int ib = b0; ib < b1; ++ib)
-          for (int ia = t0; ia < t1; ++ia) {
-            const double v = at(ia, ib) - (at(ia, jc) - at(ic, jc)) - at(ic, ib);
-            lo = std::min(lo, v);
-            hi = std::max(hi, v);
-          }
-        top = std::max(top, 0.5 * (hi - lo));
-      }
-    }
-  return top;
-}
-
-}  // namespace
-
-int wg_flat_macros(const GridSeg& g) { return WgShape(g, kFlatSteps).macros(); }
-
-int wg_max_macros(const GridSeg& g) { return WgShape(g, kWgSteps).macros(); }
-
-int64_t wg_max_cells(const GridSeg& g) {
-  return std::max(WgShape(g, kWgSteps).cells(kWgSteps), WgShape(g, kFlatSteps).cells(kFlatSteps));
-}
-
-size_t wg_part_bytes(const GridSeg& g) {
-  const WgShape a(g, kWgSteps), b(g, kFlatSteps);
-  return sizeof(float4) * std::max(a.cells(kWgSteps) * wg_chunk_cap(a.macros()),
-                                   b.cells(kFlatSteps) * flat_chunk_cap(b.macros()));
-}
-
-void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c,
-                    const int32_t* slot, double w_max, WgPlan& out) {
-  // Without cell factors where the series allows it: 1.9 times faster (disk baselines of
-  // |w| < 250 over +-0.05, sl1m_wflat.hip), and closer: fewer phasors are rounded.
-  const bool flat = 6.2831854 * w_max * flat_eta(g, c) <= 0.999 * kFlatX;
-  append_segment(g, la, mb, c, slot, flat, out);
-}
-
-bool wg_build_groups(const std::vector<double>& w, float width, int64_t max_groups,
-                     WgGroups& out) {
-  const int64_t n = static_cast<int64_t>(w.size());
-  double wm = 0.0;
-  for (double x : w) {
-    if (!std::isfinite(x)) return false;
-    wm = std::max(wm, std::fabs(x));
-  }
-  if (wm >= 0x1.0p27) return false;  // phases below 2^27 turns (|nu| < 1): kMagicFine
-  // order by |w| in 2^20 bins (two stable counting passes of 10 bits); equal bins
-  // keep the caller's order
-  const double scale = wm > 1e-290 ? 1048575.0 / wm : 0.0;
-  std::vector<uint32_t> key(n);
-  std::vector<int32_t> a(n), b(n);
-  for (int64_t k = 0; k < n; ++k) {
-    key[k] = static_cast<uint32_t>(std::fabs(w[k]) * scale);
-    a[k] = static_cast<int32_t>(k);
-  }
-  for (int pass = 0; pass < 2; ++pass) {
-    int64_t cnt[1025] = {};
-    const int sh = 10 * pass;
-    for (int64_t i = 0; i < n; ++i) ++cnt[((key[a[i]] >> sh) & 1023u) + 1];
-    for (int i = 0; i < 1024; ++i) cnt[i + 1] += cnt[i];
-    for (int64_t i = 0; i < n; ++i) b[cnt[(key[a[i]] >> sh) & 1023u]++] = a[i];
-    a.swap(b);
-  }
-  const double hmax = width > 0.0f ? 1.0 / (6.283185307179586 * width) : 1e300;
-  for (int64_t i = 0; i < n;) {
-    double lo = std::fabs(w[a[i]]), hi = lo;
-    int64_t j = i + 1;
-    for (; j < n && j - i < kWgVis; ++j) {
-      const double x = std::fabs(w[a[j]]);
-      const double l2 = std::min(lo, x), h2 = std::max(hi, x);
-      if (h2 - l2 > 2.0 * hmax) break;
-      lo = l2;
-      hi = h2;
-    }
-    if (static_cast<int64_t>(out.w0.size()) >= max_groups) return false;
-    for (int s = 0; s < kWgVis; ++s)
-      out.order.push_back(i + s < j ? 2 * a[i + s] + (w[a[i + s]] < 0.0 ? 1 : 0) : -1);
-    out.w0.push_back(0.5 * (lo + hi));
-    out.h.push_back(static_cast<float>(0.5 * (hi - lo)));
-    out.count.push_back(static_cast<int32_t>(j - i));
-    i = j;
-  }
-  return true;
-}
 
 // ---------------------------------------------------------------------------
 // kernels

@@ -239,7 +239,7 @@ class PlanInfo(ctypes.Structure):
         ("n_fchunks", ctypes.c_int32), ("n_fchunks_grid", ctypes.c_int32),
         ("n_achunks", ctypes.c_int32), ("grid_pairs", ctypes.c_int32),
         ("grid_multi", ctypes.c_int32), ("grid_mfma", ctypes.c_int32),
-        ("reserved", ctypes.c_int32 * 2),
+        ("grid_groups", ctypes.c_int32), ("grid_flat", ctypes.c_int32),
     ]
 
     def as_dict(self):

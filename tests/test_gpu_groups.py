@@ -177,3 +177,62 @@ def test_group_gaussians(name):
     x[-1], r[-1] = np.nan, np.nan
     assert not np.isfinite(plan.forward(x).cpu().numpy()).any()
     assert not np.isfinite(plan.adjoint(r).cpu().numpy()[wl.kind != 0]).any()
+
+
+# name: delta pixels a side, spacing, pixels a side and spacing of a wide Gaussian layer
+# around them (sigma one spacing), visibilities, w spread; segments in groups, those without
+# cell factors (bits)
+LAYERS = {
+    "both": (40, 5e-3, 96, 0.5 / 96, 6000, 60.0, 2, 0),
+    "both_delta_flat": (40, 2.5e-3, 96, 0.5 / 96, 3000, 6.0, 2, 1),
+    "delta_alone": (40, 5e-3, 96, 0.5 / 96, 3000, 60.0, 1, 0),       # too many groups for both
+    "delta_alone_flat": (40, 2.5e-3, 96, 0.5 / 96, 3000, 100.0, 1, 1),
+}
+
+
+def _layer_case(name):
+    dn, dd, gn, gd, nv, ws = LAYERS[name][:6]
+    seed = 90 + sorted(LAYERS).index(name)
+    wl = W.small_random(seed, 10, nv, uv_radius=200.0, w_sigma=ws, with_gains=True)
+    l, m = _grid(dn, dn, dd)
+    l2, m2 = _grid(gn, gn, gd)
+    wl.l, wl.m, wl.x_true = np.concatenate([l, l2]), np.concatenate([m, m2]), None
+    wl.sigma = np.concatenate([np.zeros(l.size), np.full(l2.size, gd)])
+    wl.kind = np.concatenate([np.zeros(l.size, np.uint8),
+                              np.full(l2.size, W.PIX_GAUSS_WIDE, np.uint8)])
+    rng = np.random.default_rng(seed)
+    return wl, rng.standard_normal(wl.l.size), (rng.standard_normal(nv)
+                                                + 1j * rng.standard_normal(nv))
+
+
+@pytest.mark.parametrize("name", list(LAYERS))
+def test_delta_grid_inside_a_layer(name):
+    """Both segments in groups, or the delta grid alone beside the layer's grid evaluation."""
+    print(f"[case] groups and layers {name}", flush=True)
+    wl, x, r = _layer_case(name)
+    p = O.Problem.from_workload(wl)
+    Vo, go = O.forward(p, x), O.adjoint(p, r)
+    plan = sl1m.Plan.from_workload(wl)
+    info = plan.info()
+    assert (info["grid"], info["grid_groups"], info["grid_flat"]) == (2, *LAYERS[name][6:])
+    V, g = plan.forward(x).cpu().numpy(), plan.adjoint(r).cpu().numpy()
+    wf = E.worst_ratio(V, Vo, E.abs_forward_rows(p, x), wl.n_pix)
+    wa = E.worst_ratio(g, go, E.abs_adjoint_cols(p, r), wl.n_vis)
+    print(f"    forward {rel(V, Vo):.3e} adjoint {rel(g, go):.3e} element-wise {wf:.3e} {wa:.3e}",
+          flush=True)
+    assert rel(V, Vo) <= TOL and wf <= 1.0 and wa <= 1.0
+    for k in (0, W.PIX_GAUSS_WIDE):       # the pixels of either kind on their own
+        assert rel(g[wl.kind == k], go[wl.kind == k]) <= TOL
+    r[-1] = np.nan
+    assert not np.isfinite(plan.adjoint(r).cpu().numpy()).any()
+
+
+@pytest.mark.parametrize("name", list(GAUSS))
+def test_gaussian_cases_evaluation(name):
+    """Which evaluation the Gaussian cases take: all but two whose visibilities make too many
+    groups for any segment take the groups, with cell factors where the series asks for them."""
+    plan = sl1m.Plan.from_workload(_gauss_case(name)[0])
+    info = plan.info()
+    want = {"no_series": (1, 1), "paraxial_odd": (1, 1), "one_order": (1, 0),
+            "flat_two_orders": (1, 1), "steep_taper": (1, 0)}.get(name, (0, 0))
+    assert (info["grid_groups"], info["grid_flat"]) == want
