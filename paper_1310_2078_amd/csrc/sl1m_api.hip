@@ -562,7 +562,8 @@ sl1m_status analyze(const sl1m_problem* pr, Analysis& a, bool groups = true,
       a.n_achunks = static_cast<int>((nv32 + a.kchunk - 1) / a.kchunk);
     }
   }
-  if (groups && a.grid && a.max_rhs == 1) choose_groups(a);
+  // matrix-core plans off the square grid take their own kernels for every call
+  if (groups && a.grid && a.max_rhs == 1 && (!mfma || a.grid_mfma)) choose_groups(a);
   // what fits the no-allocation scratch without the finer chunks still fits it
   if (fine64 && plan_total(a) > SL1M_NOALLOC_SCRATCH_BYTES) {
     Analysis b;

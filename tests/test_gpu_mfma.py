@@ -332,3 +332,41 @@ def test_mfma_empty_inputs(prec):
     assert g.shape == (4, 10) and np.all(g == 0)
     V = plan.forward(np.ones(10)).cpu().numpy()
     assert V.shape == (0,)
+
+
+@pytest.mark.parametrize("prec", ["mfma_f16", "mfma_bf16"])
+def test_mfma_one_side_on_a_grid_of_unequal_sides(prec):
+    """A grid whose |l| and |m| values differ (64 x 48 pixels, 33 x 25 values) runs on the
+    matrix cores for every side count: the residual records of the power iteration and of a
+    solve are those its adjoint reads.  L is a quadratic form in an operator that is within
+    4u of its norm: 8u, and u more for the rounding of the vector.  The solve as
+    test_mfma_solve_config1 (float16)."""
+    say(f"[case] mfma {prec} 64x48 x 2000, one side")
+    rng = np.random.default_rng(51)
+    L, M = np.meshgrid((np.arange(64) - 32) * 1.5e-3, (np.arange(48) - 24) * 1.5e-3)
+    l, m = L.ravel(), M.ravel()
+    n = l.size
+    u, v, w = W.disk_uvw(rng, 2000, 300.0, 5.0)
+    wl = W.Workload("grid64x48", l, m, np.zeros(n), np.zeros(n, np.uint8), u, v, w)
+    plan = sl1m.Plan.from_workload(wl, precision=prec)
+    info = plan.info()
+    assert info["grid"] == 1 and info["grid_mfma"] == 0 and info["grid_groups"] == 0
+    p = O.Problem.from_workload(wl)
+    x = rng.standard_normal(n)
+    _check_forward(prec, p, plan.forward(x).cpu().numpy()[None], x[None])
+    op = O.Operator(p)
+    _, rq = O.power_iteration(op, 30, seed=3)
+    got = plan.estimate_L(30, seed=3)
+    u_t = {"mfma_f16": 2.0 ** -11, "mfma_bf16": 2.0 ** -8}[prec]
+    say(f"    L {got:.6g}, oracle {rq:.6g}: relative error / u {abs(got - rq) / rq / u_t:.3f}")
+    assert abs(got - rq) <= 9 * u_t * rq
+    sky = np.zeros(n)
+    sky[rng.choice(n, 8, replace=False)] = rng.uniform(0.5, 2.0, 8)
+    V = op.forward(sky) + W.complex_noise(rng, 2000, 0.1)
+    lam = 3.0 * 0.1 * np.sqrt(2000.0)
+    ref = O.fista(op, V, 1.01 * rq, lam, 40)
+    img, inf = plan.solve(V, lam, 40, L=1.01 * rq)
+    F = O.objective(op, V, img.cpu().numpy().astype(np.float64), lam)[0]
+    say(f"    F gpu {inf['F']:.8g}, oracle F of the gpu image {F:.8g}, oracle {ref.F:.8g}")
+    if prec == "mfma_f16":
+        assert abs(inf["F"] - ref.F) <= 1e-2 * ref.F and abs(F - ref.F) <= 1e-2 * ref.F
