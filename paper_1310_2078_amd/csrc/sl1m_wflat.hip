@@ -376,7 +376,7 @@ struct alignas(16) FlatAdjLds {
   uint32_t x[kWgVis];                       // (x, x) in float16
   float2 rho[4][kWgVis];
   float top[GAUSS ? 4 : 1][kWgVis];
-  float mx[4];
+  float mx[GAUSS ? 1 : 4];
 };
 
 // One row sign of a group: G (two column signs) += the products' sums, the series in eta
@@ -462,15 +462,26 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_adj(
     lds.mb[tid] = mb[cm->b_off + tid];
     lds.be[tid] = beta[cm->b_off + tid];
   }
-  // one scale for the block's residuals
+  // One scale for the operands of a wavefront's groups: of the residuals (delta pixels,
+  // where the wavefronts share them), or of the residuals times their tapers.  Where every
+  // baseline is tapered a scale of the bare residuals left the operands below float16's
+  // range: relative errors of the gradient of 7e-6 at tapers of 2^-20, 0.05 at 2^-33.  (A
+  // scale per group, folded into the sums, spills: 300 x 300 pixels x 100,003 550 us.)
   float mx = 0.0f;
-  for (int g = g0 + wv * gs; g < n_groups; g += 4 * gs) {
-    const float2 z = res[static_cast<int64_t>(g) * kWgVis + lane];
+  for (int g = GAUSS ? g0 : g0 + wv * gs; g < n_groups; g += GAUSS ? gs : 4 * gs) {
+    float2 z = res[static_cast<int64_t>(g) * kWgVis + lane];
+    if constexpr (GAUSS) {
+      const WgVisG* const q = in.rec + static_cast<int64_t>(g) * kWgVis + lane;
+      const float k = pow2(taper_top(q->c1, q->v, q->w, m_lo, m_hi) +
+                           taper_top(q->c1, q->u, q->w, l_lo, l_hi));
+      z.x *= k;  // |D (1 + i s)| <= 1
+      z.y *= k;
+    }
     const float m = fmaxf(fabsf(z.x), fabsf(z.y));
     mx = fmaxf(mx, z.x != z.x || z.y != z.y ? __builtin_inff() : m);
   }
   mx = wave_max(mx);
-  if (lane == 0) lds.mx[wv] = mx;
+  if (!GAUSS && lane == 0) lds.mx[wv] = mx;
   f4_t gr[4][kFlatSteps];
   h2_t et[kFlatSteps][2];
 #pragma unroll
@@ -489,13 +500,14 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_adj(
     sn = in.ser(g0, eta_max);
   }
   __syncthreads();
-  const float sc =
-      0.5f * op_scale(fmaxf(fmaxf(lds.mx[0], lds.mx[1]), fmaxf(lds.mx[2], lds.mx[3])));
+  if constexpr (!GAUSS)
+    mx = fmaxf(fmaxf(lds.mx[0], lds.mx[1]), fmaxf(lds.mx[2], lds.mx[3]));
+  const float sc = 0.5f * op_scale(mx);
   for (int g = g0; g < n_groups; g += gs) {
     const FlatVis r = rn;
     const int ser = sn;
     const float top = GAUSS ? taper_top(r.c1, r.v, r.wf, m_lo, m_hi) : 0.0f;
-    float2 z = make_float2(sc * zn.x, sc * zn.y);
+    float2 z = zn;
     if constexpr (GAUSS) {
       // times conj D (1 + i s) exp(2 pi i e0), with both tops
       const float ltop = taper_top(r.c1, r.u, r.wf, l_lo, l_hi), k = pow2(top + ltop);
@@ -506,7 +518,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_adj(
       z.y = fmaf(ct, z.y, -st * zr);
       lds.top[GAUSS ? wv : 0][lane] = ltop;
     }
-    lds.rho[wv][lane] = z;
+    lds.rho[wv][lane] = make_float2(sc * z.x, sc * z.y);
     if (wv == 0) {
       lds.A[lane] = r.A;
       lds.w[lane] = r.w;

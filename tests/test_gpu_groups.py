@@ -236,3 +236,31 @@ def test_gaussian_cases_evaluation(name):
     want = {"no_series": (1, 1), "paraxial_odd": (1, 1), "one_order": (1, 0),
             "flat_two_orders": (1, 1), "steep_taper": (1, 0)}.get(name, (0, 0))
     assert (info["grid_groups"], info["grid_flat"]) == want
+
+
+@pytest.mark.parametrize("reach", [0.5, 2.1, 2.4, 2.7, 3.0, 3.3])
+def test_gaussian_baselines_all_tapered(reach):
+    """Every visibility on long baselines (sigma |(u, v)| = reach, tapers of 2^-1 to 2^-49),
+    w = 0: no cell factors.  The adjoint keeps the forward's relative accuracy."""
+    print(f"[case] tapered ring {reach}", flush=True)
+    d, nv = 1.5e-3, 700
+    rng = np.random.default_rng(120)
+    wl = W.small_random(120, 10, nv, with_gains=True)
+    wl.l, wl.m = _grid(40, 70, d)
+    wl.sigma, wl.kind = np.full(wl.l.size, 2.0 * d), np.full(wl.l.size, W.PIX_GAUSS_WIDE, np.uint8)
+    wl.x_true = None
+    phi, rho = rng.uniform(0, 2 * np.pi, nv), reach / (2.0 * d) * rng.uniform(0.98, 1.0, nv)
+    wl.u, wl.v, wl.w = rho * np.cos(phi), rho * np.sin(phi), np.zeros(nv)
+    x = rng.standard_normal(wl.l.size)
+    r = rng.standard_normal(nv) + 1j * rng.standard_normal(nv)
+    p = O.Problem.from_workload(wl)
+    plan = sl1m.Plan.from_workload(wl)
+    info = plan.info()
+    assert (info["grid_groups"], info["grid_flat"]) == (1, 1)
+    Vo, go = O.forward(p, x), O.adjoint(p, r)
+    V, g = plan.forward(x).cpu().numpy(), plan.adjoint(r).cpu().numpy()
+    print(f"    forward {rel(V, Vo):.3e} adjoint {rel(g, go):.3e}", flush=True)
+    assert rel(V, Vo) <= TOL and rel(g, go) <= TOL
+    s = r.astype(np.complex128)
+    dirty = plan.dirty_image(s).cpu().numpy()
+    assert np.isfinite(dirty).all() and dirty.any()
