@@ -579,7 +579,7 @@ struct Layout {
       grid_la,
       grid_mb, grid_c3, grid_c4, grid_slot, grid_rec, grid_fc, grid_pb, grid_segs, grid_gb,
       grid_prec, grid_precm, mx, mr, mred, grid_mfma_b, grid_mfma_nu, phl, vhl,
-      wg_mac, wg_la, wg_mb, wg_nu, wg_eta, wg_slot, wg_order, wg_count, wg_su, wg_sv, wg_dw, wg_w0,
+      wg_mac, wg_la, wg_mb, wg_nu, wg_eta, wg_slot, wg_order, wg_count, wg_su, wg_sv, wg_sw, wg_dw, wg_w0,
       wg_h, wg_part, wg_res, wg_recg, wg_alpha, wg_beta, wg_map, total;
 };
 
@@ -687,6 +687,7 @@ Layout layout(const Analysis& a, int wg_n) {
     L.wg_count = take(4 * static_cast<size_t>(a.wg_cap));
     L.wg_su = take(8 * slots);
     L.wg_sv = take(8 * slots);
+    L.wg_sw = take(8 * slots);
     L.wg_dw = take(4 * slots);
     L.wg_w0 = take(8 * static_cast<size_t>(a.wg_cap));
     L.wg_res = take(8 * slots);
@@ -1052,6 +1053,7 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       p->wg_order = reinterpret_cast<int32_t*>(w + L.wg_order);
       p->wg_su = reinterpret_cast<double*>(w + L.wg_su);
       p->wg_sv = reinterpret_cast<double*>(w + L.wg_sv);
+      p->wg_sw = reinterpret_cast<double*>(w + L.wg_sw);
       p->wg_dw = reinterpret_cast<float*>(w + L.wg_dw);
       p->wg_w0 = reinterpret_cast<double*>(w + L.wg_w0);
       p->wg_h = reinterpret_cast<float*>(w + L.wg_h);

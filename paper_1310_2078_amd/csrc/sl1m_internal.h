@@ -272,7 +272,7 @@ struct sl1m_plan {
   float* wg_eta = nullptr;
   int32_t* wg_slot = nullptr;
   int32_t *wg_order = nullptr, *wg_count = nullptr;
-  double *wg_su = nullptr, *wg_sv = nullptr, *wg_w0 = nullptr;
+  double *wg_su = nullptr, *wg_sv = nullptr, *wg_sw = nullptr, *wg_w0 = nullptr;
   float *wg_dw = nullptr, *wg_h = nullptr;
   float4* wg_part = nullptr;      // adjoint partial sums [chunk][tile cell]
   float2* wg_res = nullptr;       // residual records per slot (conjugated where w < 0)

@@ -39,6 +39,7 @@ struct FlatIn {
   const double* __restrict__ su;
   const double* __restrict__ sv;
   const WgVisG* __restrict__ rec;
+  const double* __restrict__ sw;
   const float* __restrict__ sdw;
   const double* __restrict__ w0s;
   const float* __restrict__ hs;
@@ -47,7 +48,10 @@ struct FlatIn {
   __device__ __forceinline__ FlatVis load(int g, int lane, float xs) const {
     FlatVis r = {};
     const int64_t t = static_cast<int64_t>(g) * kWgVis + lane;
-    r.w = as_const(w0s)[g] + static_cast<double>(sdw[t]);
+    // The groups may be of any width: delta pixels take w itself (w n may be hundreds of
+    // turns over the field, and float32 of w - w0 5e-5 rad off).  For Gaussian pixels what
+    // is left to w, kappa, is below a turn, and the sum needs no second register.
+    r.w = GAUSS ? as_const(w0s)[g] + static_cast<double>(sdw[t]) : sw[t];
     r.x = xs * static_cast<float>(r.w);
     if constexpr (GAUSS) {
       const WgVisG q = rec[t];
@@ -601,6 +605,7 @@ static FlatIn<GAUSS> flat_in(const sl1m_plan* p, const GridSeg& g) {
   in.su = p->wg_su;
   in.sv = p->wg_sv;
   in.rec = GAUSS ? p->wg_recg + static_cast<int64_t>(g.layer) * p->wg_groups * kWgVis : nullptr;
+  in.sw = p->wg_sw;
   in.sdw = p->wg_dw;
   in.w0s = p->wg_w0;
   in.hs = p->wg_h;

@@ -349,16 +349,20 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
   }
 }
 
-// Per-slot coordinates: the visibility's, negated where w < 0; w - w0.
+// Per-slot coordinates: the visibility's, negated where w < 0; w - w0 (padding: the group's
+// w0, 0).
 __global__ void k_wg_slots(const int32_t* __restrict__ order, const double* __restrict__ w0s,
                            const double* __restrict__ vu, const double* __restrict__ vv,
                            const double* __restrict__ vw, int64_t n, double* __restrict__ su,
-                           double* __restrict__ sv, float* __restrict__ sdw) {
+                           double* __restrict__ sv, double* __restrict__ sw,
+                           float* __restrict__ sdw) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (t >= n) return;
   const int32_t o = order[t];
+  const double w0 = w0s[t / kWgVis];
   if (o < 0) {
     su[t] = sv[t] = 0.0;
+    sw[t] = w0;
     sdw[t] = 0.0f;
     return;
   }
@@ -366,7 +370,8 @@ __global__ void k_wg_slots(const int32_t* __restrict__ order, const double* __re
   const double sg = o & 1 ? -1.0 : 1.0;
   su[t] = sg * vu[k];
   sv[t] = sg * vv[k];
-  sdw[t] = static_cast<float>(sg * vw[k] - w0s[t / kWgVis]);
+  sw[t] = sg * vw[k];
+  sdw[t] = static_cast<float>(sw[t] - w0);
 }
 
 // Slot t's visibility: the macros' rows, conjugated where w < 0, and the other
@@ -1372,7 +1377,7 @@ hipError_t launch_wg_setup(sl1m_plan* p, hipStream_t st) {
   const int64_t n = static_cast<int64_t>(p->wg_groups) * kWgVis;
   if (p->wg_n == 0 || n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_wg_slots, dim3(blocks1(n)), dim3(kBlock), 0, st, p->wg_order, p->wg_w0,
-                     p->vu, p->vv, p->vw, n, p->wg_su, p->wg_sv, p->wg_dw);
+                     p->vu, p->vv, p->vw, n, p->wg_su, p->wg_sv, p->wg_sw, p->wg_dw);
   for (int i = 0; i < p->wg_n; ++i) {
     const GridSeg& g = p->grid_segs[i];
     if (g.kind != SL1M_PIX_DELTA)

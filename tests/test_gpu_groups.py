@@ -264,3 +264,27 @@ def test_gaussian_baselines_all_tapered(reach):
     s = r.astype(np.complex128)
     dirty = plan.dirty_image(s).cpu().numpy()
     assert np.isfinite(dirty).all() and dirty.any()
+
+
+def test_spread_w_without_cell_factors():
+    """A narrow field with one group of visibilities of widely spread w (hundreds of turns of
+    w n over the field): entries of single pixels within the element-wise bound's entry error,
+    which takes the phase as float64 until it is reduced."""
+    n, nv = 256, 64
+    d = 0.012 / n
+    wl = W.small_random(130, 10, nv, uv_radius=3000.0)
+    wl.l, wl.m = _grid(n, n, d)
+    wl.sigma, wl.kind, wl.x_true = np.zeros(n * n), np.zeros(n * n, np.uint8), None
+    wl.w = np.random.default_rng(130).uniform(-1e7, 1e7, nv)
+    plan = sl1m.Plan.from_workload(wl)
+    info = plan.info()
+    assert (info["grid_groups"], info["grid_flat"]) == (1, 1)
+    p = O.Problem.from_workload(wl)
+    worst = 0.0
+    for j in (0, n - 1, n * (n - 1), n * n - 1, n * (n // 2)):
+        e = np.zeros(n * n)
+        e[j] = 1.0
+        V, Vo = plan.forward(e).cpu().numpy(), O.forward(p, e)
+        worst = max(worst, float(np.max(np.abs(V - Vo) / np.abs(Vo))))
+    print(f"    largest entry error {worst:.3e}", flush=True)
+    assert worst <= E.E_ENTRY["fp32"]
