@@ -173,8 +173,7 @@ bool all_pixels(const Analysis& a, int n) {
 
 // Group evaluation of the grid segments (plans of one side: the grid
 // evaluation shares its phasors among several, and a side on its own then gives
-// the same bits as among others): each segment's tiles, unless they hold more
-// than four times its cells with padding.  A plan that fits the no-allocation
+// the same bits as among others), as far as wg_segments allows.  A plan that fits the no-allocation
 // scratch without the group tables but not with them keeps the grid evaluation,
 // so that what sl1m_forward_noalloc takes does not shrink.
 //
@@ -189,15 +188,7 @@ constexpr int64_t kGroupGaussMax = 131072;
 void choose_groups(Analysis& a) {
   if (a.gsegs[0].kind != SL1M_PIX_DELTA && all_pixels(a, 1) && a.n_pix > kGroupGaussMax) return;
   const size_t without = plan_total(a);
-  int n = 0;
-  int64_t total = 0;
-  for (const GridSeg& g : a.gsegs) {
-    const int64_t padded = wg_padded(g);
-    if (g.seg != a.gsegs[0].seg + n || padded > 4 * static_cast<int64_t>(g.na) * g.nb) break;
-    total += wg_max_cells(g);
-    if (total > INT32_MAX) break;
-    ++n;
-  }
+  const int n = wg_segments(a.gsegs.data(), static_cast<int>(a.gsegs.size()), a.n_vis);
   if (n == 0) return;
   a.wg_cap = wg_group_cap(a.n_vis);
   a.wg_n = n;

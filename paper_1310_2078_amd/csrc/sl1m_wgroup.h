@@ -100,8 +100,11 @@ struct WgGroups {
   std::vector<int32_t> count;      // visibilities of the group
 };
 
-// cells evaluated for a segment, padding included
-int64_t wg_padded(const GridSeg& g);
+// How many of a plan's grid segments, from the first on, groups of n_vis visibilities take:
+// consecutive segments whose tiles hold at most four times their cells with padding.  The
+// tables number cells, slots (2 k + sign) and the launches' macros in 32 bits or fewer:
+// none from 2^30 visibilities on, no more than 2^31 - 1 cells and 65,535 macros.
+int wg_segments(const GridSeg* segs, int n_segs, int64_t n_vis);
 // macros and tile cells of a segment, the larger of both kinds of tiles
 int wg_max_macros(const GridSeg& g);
 int64_t wg_max_cells(const GridSeg& g);

@@ -29,10 +29,6 @@ int wg_chunks(int macros, int groups) {
   return std::max(1, std::min(groups, wg_chunk_cap(macros)));
 }
 
-int64_t wg_padded(const GridSeg& g) {
-  return static_cast<int64_t>((g.na + kWgRows - 1) / kWgRows * kWgRows) * ((g.nb + 15) / 16 * 16);
-}
-
 // Flat segments: one round of the blocks that stay resident (256 x 256 x 100,000: 210 /
 // 293 us, two rounds 222 / 305; 300 x 300 Gaussian pixels x 100,003: 302 / 435, two
 // rounds 316 / 446).
@@ -204,6 +200,21 @@ int wg_max_macros(const GridSeg& g) { return WgShape(g, kWgSteps).macros(); }
 
 int64_t wg_max_cells(const GridSeg& g) {
   return std::max(WgShape(g, kWgSteps).cells(kWgSteps), WgShape(g, kFlatSteps).cells(kFlatSteps));
+}
+
+int wg_segments(const GridSeg* segs, int n_segs, int64_t n_vis) {
+  if (n_vis >= int64_t{1} << 30) return 0;
+  int64_t cells = 0, macros = 0;
+  int n = 0;
+  for (; n < n_segs; ++n) {
+    const GridSeg& g = segs[n];
+    const int64_t sets = (g.na + kWgRows - 1) / kWgRows, steps = (g.nb + 15) / 16;
+    if (g.seg != segs[0].seg + n || 16 * kWgRows * sets * steps > int64_t{4} * g.na * g.nb) break;
+    cells += wg_max_cells(g);
+    macros += wg_max_macros(g);
+    if (cells > INT32_MAX || macros > 65535) break;
+  }
+  return n;
 }
 
 size_t wg_part_bytes(const GridSeg& g) {

@@ -55,7 +55,40 @@ static void add_segment(Grids& t, int kind, int nl, int nm, double d) {
   t.segs.push_back(g);
 }
 
+// The limits of wg_segments: 32-bit slots, launch sizes, padding.
+static void segment_checks() {
+  auto seg = [](int na, int nb) {
+    GridSeg g{};
+    g.na = na;
+    g.nb = nb;
+    return g;
+  };
+  const int64_t most = (int64_t{1} << 30) - 1;
+  const GridSeg small = seg(17, 17);
+  CHECK(wg_segments(&small, 1, 1) == 1 && wg_segments(&small, 1, most) == 1);
+  CHECK(wg_segments(&small, 1, most + 1) == 0 && wg_segments(&small, 1, INT32_MAX) == 0);
+  // the slots of the most groups a plan of that many visibilities may have
+  CHECK(wg_group_cap(most) * kWgVis <= INT32_MAX && 2 * (most - 1) + 1 <= INT32_MAX);
+  // macros: 4 row sets x 32 columns each
+  const GridSeg fits = seg(64, 32 * 65535), more = seg(64, 32 * 65535 + 1);
+  CHECK(wg_segments(&fits, 1, 1000) == 1 && wg_segments(&more, 1, 1000) == 0);
+  // a segment past the limit ends the run, and so does one that does not follow
+  GridSeg three[3] = {small, more, small};
+  three[1].seg = 1;
+  three[2].seg = 2;
+  CHECK(wg_segments(three, 3, 1000) == 1);
+  three[1] = small;
+  three[1].seg = 2;
+  CHECK(wg_segments(three, 2, 1000) == 1);
+  three[1].seg = 1;
+  CHECK(wg_segments(three, 3, 1000) == 3);
+  // padding: four columns of 16 fill a quarter, three do not
+  const GridSeg four = seg(512, 4), three_c = seg(512, 3);
+  CHECK(wg_segments(&four, 1, 1000) == 1 && wg_segments(&three_c, 1, 1000) == 0);
+}
+
 int main() {
+  segment_checks();
   int n = 0;
   CHECK(std::scanf("%d", &n) == 1);
   Grids t;
