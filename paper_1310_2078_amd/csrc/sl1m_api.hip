@@ -58,6 +58,7 @@ struct Analysis {
   // follow one another
   int wg_n = 0;
   int64_t wg_cap = 0;          // visibility groups the workspace holds
+  int wg_mrows = 0;            // and the most rows of forward sums (one per macro)
 };
 
 sl1m_status d2h(void* dst, const void* src, size_t bytes, const char* what) {
@@ -164,6 +165,12 @@ bool analyze_grid(Analysis& a, int si, const std::vector<double>& L, const std::
 
 size_t plan_total(const Analysis& a);
 
+int wg_macros(const Analysis& a, int n) {
+  int macros = 0;
+  for (int i = 0; i < n; ++i) macros += wg_max_macros(a.gsegs[i]);
+  return macros;
+}
+
 // The first n grid segments hold every pixel.
 bool all_pixels(const Analysis& a, int n) {
   int64_t c = 0;
@@ -185,6 +192,7 @@ bool all_pixels(const Analysis& a, int n) {
 // about 9e-6 from the float64 solve) and 1.0e-5 to 1.8e-5 on 262,144 x 200,000.  The
 // groups would take a quarter of the time there as well.
 constexpr int64_t kGroupGaussMax = 131072;
+constexpr size_t kGroupRoom = size_t{4} << 30, kGroupMost = size_t{64} << 30;
 void choose_groups(Analysis& a) {
   if (a.gsegs[0].kind != SL1M_PIX_DELTA && all_pixels(a, 1) && a.n_pix > kGroupGaussMax) return;
   const size_t without = plan_total(a);
@@ -192,6 +200,25 @@ void choose_groups(Analysis& a) {
   if (n == 0) return;
   a.wg_cap = wg_group_cap(a.n_vis);
   a.wg_n = n;
+  // A row of slots per macro outgrows the card on large problems (2048 x 2048 pixels x 40
+  // million visibilities: 321 GB, 67 without groups).  So the groups may take a plan up to
+  // kGroupRoom or a quarter more than it is without them, but past kGroupMost no further
+  // than it is without: what fits a card still does.  Rows that do not fit are added up in
+  // passes over the macros.
+  const size_t room =
+      std::max({without, kGroupRoom, std::min(without + without / 4, kGroupMost)});
+  for (; a.wg_n; a.wg_n = wg_fewer(a.gsegs[0], a.wg_n)) {
+    auto fits = [&](int rows) {
+      a.wg_mrows = rows;
+      return plan_total(a) <= room;
+    };
+    int lo = 1, hi = wg_macros(a, a.wg_n);  // the most rows that fit
+    if (fits(hi)) break;
+    if (!fits(lo)) continue;
+    while (hi - lo > 1) (fits((lo + hi) / 2) ? lo : hi) = (lo + hi) / 2;
+    a.wg_mrows = lo;
+    break;
+  }
   if (without <= SL1M_NOALLOC_SCRATCH_BYTES && plan_total(a) > SL1M_NOALLOC_SCRATCH_BYTES)
     a.wg_n = 0;
 }
@@ -571,7 +598,7 @@ struct Layout {
       grid_mb, grid_c3, grid_c4, grid_slot, grid_rec, grid_fc, grid_pb, grid_segs, grid_gb,
       grid_prec, grid_precm, mx, mr, mred, grid_mfma_b, grid_mfma_nu, phl, vhl,
       wg_mac, wg_la, wg_mb, wg_nu, wg_eta, wg_slot, wg_order, wg_count, wg_su, wg_sv, wg_sw, wg_dw, wg_w0,
-      wg_h, wg_part, wg_res, wg_recg, wg_alpha, wg_beta, wg_map, total;
+      wg_h, wg_part, wg_res, wg_recg, wg_alpha, wg_beta, wg_map, wg_sums, total;
 };
 
 // `wg_n`: grid segments in the group evaluation
@@ -612,17 +639,18 @@ Layout layout(const Analysis& a, int wg_n) {
   L.chunks = take(sizeof(Chunk) * (nfc + npt + a.fd1.size() + a.fg1.size() + a.pd1.size() +
                                    a.pg1.size()));
   const size_t grid_rows = a.grid ? a.grid_fc.size() + a.fd1.size() + a.fg1.size() : 0;
-  // group evaluation: a row of slots per macro in place of the segment's rows
+  // group evaluation: rows of slots (macros) in place of the segments' rows
   const size_t slots = wg_n ? static_cast<size_t>(a.wg_cap) * kWgVis : 0;
-  size_t wg_rows = grid_rows * nv, wg_macros = 0, wg_part = 0, wg_cells = 0;
+  size_t wg_rows = grid_rows * nv, wg_part = 0, wg_cells = 0;
   for (int i = 0; i < wg_n; ++i) {
     const GridSeg& g = a.gsegs[i];
     wg_rows -= static_cast<size_t>(g.nfc) * nv;
-    wg_macros += static_cast<size_t>(wg_max_macros(g));
     wg_cells += static_cast<size_t>(wg_max_cells(g));
-    wg_part = std::max(wg_part, wg_part_bytes(g));
+    wg_part = std::max(wg_part, wg_part_bytes(g, a.wg_cap));
   }
-  wg_rows += wg_macros * slots;
+  const size_t macros = static_cast<size_t>(wg_macros(a, wg_n));
+  L.wg_sums = std::min<size_t>(macros, a.wg_mrows) * slots;
+  wg_rows += L.wg_sums;
   L.fpart = take(2 * rb *
                  std::max(std::max({nfc * nr, grid_rows * std::max<size_t>(1, a.grid_multi),
                                     static_cast<size_t>(a.n_mfchunks) * nr}) * nv,
@@ -666,11 +694,11 @@ Layout layout(const Analysis& a, int wg_n) {
   L.phl = take(hl ? sizeof(HLRec) * static_cast<size_t>(a.n_pix) : 0);
   L.vhl = take(hl ? sizeof(HLRec) * static_cast<size_t>(a.n_vis) : 0);
   if (wg_n) {
-    L.wg_mac = take(sizeof(WgMacro) * wg_macros);
-    L.wg_la = take(8 * 4 * kWgRows * wg_macros);
-    L.wg_mb = take(8 * kFlatCols * wg_macros);
-    L.wg_alpha = take(8 * 4 * kWgRows * wg_macros);
-    L.wg_beta = take(8 * kFlatCols * wg_macros);
+    L.wg_mac = take(sizeof(WgMacro) * macros);
+    L.wg_la = take(8 * 4 * kWgRows * macros);
+    L.wg_mb = take(8 * kFlatCols * macros);
+    L.wg_alpha = take(8 * 4 * kWgRows * macros);
+    L.wg_beta = take(8 * kFlatCols * macros);
     L.wg_nu = take(8 * wg_cells);
     L.wg_eta = take(4 * wg_cells);
     L.wg_slot = take(16 * wg_cells);
@@ -1028,6 +1056,8 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       p->wg_segs = wgp.segs;
       for (const WgSeg& s2 : p->wg_segs) p->wg_macros += s2.macros;
       p->wg_groups = static_cast<int>(wgg.w0.size());
+      p->wg_mrows = static_cast<int>(std::min<size_t>(
+          p->wg_macros, L.wg_sums / (static_cast<size_t>(p->wg_groups) * kWgVis)));
       p->wg_recg = reinterpret_cast<WgVisG*>(w + L.wg_recg);
       p->wg_map = reinterpret_cast<int32_t*>(w + L.wg_map);
       p->wg_mac = reinterpret_cast<WgMacro*>(w + L.wg_mac);

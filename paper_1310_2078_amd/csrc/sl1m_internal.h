@@ -263,6 +263,7 @@ struct sl1m_plan {
   // tables and the visibility groups
   int wg_n = 0;
   int wg_macros = 0, wg_groups = 0;
+  int wg_mrows = 0;               // macro rows of the forward: macros m, m + wg_mrows, .. share one
   std::vector<sl1m::WgSeg> wg_segs;
   sl1m::WgVisG* wg_recg = nullptr;  // [layer][slot]
   int32_t* wg_map = nullptr;        // one flat macro (wg_single): pixel -> 4 tile cell + slot

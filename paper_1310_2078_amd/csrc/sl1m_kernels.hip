@@ -856,7 +856,7 @@ int wg_skipped_rows(const sl1m_plan* p) {
 
 void* fwd_rows1(const sl1m_plan* p) {
   if (p->wg_n == 0) return p->fpart;
-  const int64_t skip = static_cast<int64_t>(p->wg_macros) * p->wg_groups * kWgVis -
+  const int64_t skip = static_cast<int64_t>(p->wg_mrows) * p->wg_groups * kWgVis -
                        static_cast<int64_t>(wg_skipped_rows(p)) * p->n_vis;
   return static_cast<float2*>(p->fpart) + skip;
 }

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_fwd(
     const float* __restrict__ pscale, const int4* __restrict__ slot,
     const float* __restrict__ eta, const double* __restrict__ la, const double* __restrict__ mb,
     const double* __restrict__ alpha, const double* __restrict__ beta, FlatIn<GAUSS> in,
-    int n_groups, WgOut fin, float2* __restrict__ rows) {
+    int n_groups, WgOut fin, bool add, float2* __restrict__ rows) {
   __shared__ FlatFwdLds<GAUSS> lds;
   const int mac = mac0 + static_cast<int>(blockIdx.y);
   const ConstPtr<WgMacro> cm = as_const(macros) + mac;
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_fwd(
         else if (fin.res)
           fin.res[slot_g] = make_float2(0.0f, 0.0f);
       } else {
-        rows[static_cast<int64_t>(mac) * n_groups * kWgVis + slot_g] = sum;
+        store_row(rows, static_cast<int64_t>(blockIdx.y) * n_groups * kWgVis + slot_g, add, sum);
       }
     }
   }
@@ -616,14 +616,16 @@ static FlatIn<GAUSS> flat_in(const sl1m_plan* p, const GridSeg& g) {
 template <bool GAUSS>
 static hipError_t flat_forward_t(sl1m_plan* p, const GridSeg& g, const WgSeg& s, const float* x,
                                  const WgOut& fin, hipStream_t st) {
-  const dim3 grid(static_cast<unsigned>(flat_chunks(s.macros, p->wg_groups)),
-                  static_cast<unsigned>(s.macros));
-  hipLaunchKernelGGL(k_flat_fwd<GAUSS>, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, x,
-                     static_cast<const float*>(p->pscale),
-                     reinterpret_cast<const int4*>(p->wg_slot), p->wg_eta, p->wg_la, p->wg_mb,
-                     p->wg_alpha, p->wg_beta, flat_in<GAUSS>(p, g), p->wg_groups, fin,
-                     static_cast<float2*>(p->fpart));
-  return hipGetLastError();
+  return wg_passes(p, s, [&](int mac0, int macros, float2* rows, bool add) {
+    const dim3 grid(static_cast<unsigned>(flat_chunks(macros, p->wg_groups)),
+                    static_cast<unsigned>(macros));
+    hipLaunchKernelGGL(k_flat_fwd<GAUSS>, grid, dim3(kBlock), 0, st, p->wg_mac, mac0, x,
+                       static_cast<const float*>(p->pscale),
+                       reinterpret_cast<const int4*>(p->wg_slot), p->wg_eta, p->wg_la, p->wg_mb,
+                       p->wg_alpha, p->wg_beta, flat_in<GAUSS>(p, g), p->wg_groups, fin, add,
+                       rows);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_flat_forward(sl1m_plan* p, const GridSeg& g, const WgSeg& s, const float* x,

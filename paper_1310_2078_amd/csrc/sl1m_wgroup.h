@@ -23,6 +23,8 @@
 // 2^-22 of it), each product as hi hi + hi lo + lo hi with float32 sums.
 #pragma once
 
+#include <algorithm>
+
 #include "sl1m_internal.h"
 
 namespace sl1m {
@@ -109,8 +111,8 @@ int wg_segments(const GridSeg* segs, int n_segs, int64_t n_vis);
 int wg_max_macros(const GridSeg& g);
 int64_t wg_max_cells(const GridSeg& g);
 int wg_flat_macros(const GridSeg& g);
-// bytes of the segment's adjoint chunk sums
-size_t wg_part_bytes(const GridSeg& g);
+// bytes of the segment's adjoint chunk sums, of at most max_groups groups
+size_t wg_part_bytes(const GridSeg& g, int64_t max_groups);
 // appends a segment; `c`: nu or kappa per grid cell, `w_max`: largest |w|
 void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c,
                     const int32_t* slot, double w_max, WgPlan& out);
@@ -145,6 +147,21 @@ hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, b
 hipError_t launch_wg_adjoint_prep(sl1m_plan* p, const void* r, hipStream_t st);
 // the segment's gradient sums into row 0 of the adjoint partials (its only row)
 hipError_t launch_wg_adjoint(sl1m_plan* p, const GridSeg& g, hipStream_t st);
+
+// A segment's forward in passes over its macros: `launch`(first macro, macros, their rows of
+// sums [macro][group][visibility], whether an earlier pass has left sums there).
+template <typename F>
+hipError_t wg_passes(const sl1m_plan* p, const WgSeg& s, F&& launch) {
+  hipError_t e = hipSuccess;
+  for (int m = s.mac0, end = s.mac0 + s.macros; m < end && e == hipSuccess;) {
+    const int row = m % p->wg_mrows, n = std::min(end - m, p->wg_mrows - row);
+    float2* const rows = static_cast<float2*>(p->fpart) +
+                         static_cast<int64_t>(row) * p->wg_groups * kWgVis;
+    e = launch(m, n, rows, m >= p->wg_mrows);
+    m += n;
+  }
+  return e;
+}
 
 // sl1m_wflat.hip: flat segments (the adjoint: its chunk sums)
 hipError_t launch_flat_forward(sl1m_plan* p, const GridSeg& g, const WgSeg& s, const float* x,

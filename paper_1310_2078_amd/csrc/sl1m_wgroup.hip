@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
     const float* __restrict__ eta, const double* __restrict__ la, const double* __restrict__ mb,
     const double* __restrict__ su, const double* __restrict__ sv, const float* __restrict__ sdw,
     const double* __restrict__ w0s, const float* __restrict__ hs, const int32_t* __restrict__ cnt,
-    int n_groups, float2* __restrict__ rows) {
+    int n_groups, bool add, float2* __restrict__ rows) {
   __shared__ FwdLds lds;
   const int mac = mac0 + static_cast<int>(blockIdx.y);
   const ConstPtr<WgMacro> cm = as_const(macros) + mac;
@@ -343,8 +343,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
     if (tid < kWgVis) {
       const float2 a = lds.red[0][tid], b = lds.red[1][tid], c2 = lds.red[2][tid],
                    d = lds.red[3][tid];
-      rows[(static_cast<int64_t>(mac) * n_groups + g) * kWgVis + tid] =
-          make_float2((a.x + b.x) + (c2.x + d.x), (a.y + b.y) + (c2.y + d.y));
+      store_row(rows, (static_cast<int64_t>(blockIdx.y) * n_groups + g) * kWgVis + tid, add,
+                make_float2((a.x + b.x) + (c2.x + d.x), (a.y + b.y) + (c2.y + d.y)));
     }
   }
 }
@@ -838,7 +838,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
     const double* __restrict__ alpha, const double* __restrict__ beta,
     const WgVisG* __restrict__ rec, const float* __restrict__ sdw, const double* __restrict__ w0s,
     const float* __restrict__ hs, const int32_t* __restrict__ cnt, int n_groups,
-    float2* __restrict__ rows) {
+    bool add, float2* __restrict__ rows) {
   __shared__ FwdGLds lds;
   const int mac = mac0 + static_cast<int>(blockIdx.y);
   const ConstPtr<WgMacro> cm = as_const(macros) + mac;
@@ -1007,8 +1007,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
     if (tid < kWgVis) {
       const float2 a = lds.red[0][tid], b = lds.red[1][tid], c2 = lds.red[2][tid],
                    d = lds.red[3][tid];
-      rows[(static_cast<int64_t>(mac) * n_groups + g) * kWgVis + tid] =
-          make_float2((a.x + b.x) + (c2.x + d.x), (a.y + b.y) + (c2.y + d.y));
+      store_row(rows, (static_cast<int64_t>(blockIdx.y) * n_groups + g) * kWgVis + tid, add,
+                make_float2((a.x + b.x) + (c2.x + d.x), (a.y + b.y) + (c2.y + d.y)));
     }
   }
 }
@@ -1390,26 +1390,26 @@ hipError_t launch_wg_setup(sl1m_plan* p, hipStream_t st) {
 
 hipError_t launch_wg_forward(sl1m_plan* p, const GridSeg& g, const void* xp, hipStream_t st) {
   const WgSeg& s = p->wg_segs[&g - p->grid_segs.data()];
-  const dim3 grid(static_cast<unsigned>(wg_chunks(s.macros, p->wg_groups)),
-                  static_cast<unsigned>(s.macros));
   const float* x = static_cast<const float*>(xp);
-  if (s.flat) return launch_flat_forward(p, g, s, x, st);
   const float* scale = static_cast<const float*>(p->pscale);
   const int4* slot = reinterpret_cast<const int4*>(p->wg_slot);
-  float2* rows = static_cast<float2*>(p->fpart);
-  if (g.kind == SL1M_PIX_DELTA)
-    return timed(p, T_GRID_FWD_DELTA, st, [&] {
-      hipLaunchKernelGGL(k_wg_fwd, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, x, scale, slot,
-                         p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb, p->wg_su, p->wg_sv, p->wg_dw,
-                         p->wg_w0, p->wg_h, p->wg_count, p->wg_groups, rows);
+  const bool delta = g.kind == SL1M_PIX_DELTA;
+  return timed(p, delta ? T_GRID_FWD_DELTA : T_GRID_FWD_GAUSS, st, [&] {
+    if (s.flat) return launch_flat_forward(p, g, s, x, st);
+    return wg_passes(p, s, [&](int mac0, int macros, float2* rows, bool add) {
+      const dim3 grid(static_cast<unsigned>(wg_chunks(macros, p->wg_groups)),
+                      static_cast<unsigned>(macros));
+      if (delta)
+        hipLaunchKernelGGL(k_wg_fwd, grid, dim3(kBlock), 0, st, p->wg_mac, mac0, x, scale, slot,
+                           p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb, p->wg_su, p->wg_sv, p->wg_dw,
+                           p->wg_w0, p->wg_h, p->wg_count, p->wg_groups, add, rows);
+      else
+        hipLaunchKernelGGL(k_wg_fwd_gauss, grid, dim3(kBlock), 0, st, p->wg_mac, mac0, x, scale,
+                           slot, p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb, p->wg_alpha, p->wg_beta,
+                           p->wg_recg + static_cast<int64_t>(g.layer) * p->wg_groups * kWgVis,
+                           p->wg_dw, p->wg_w0, p->wg_h, p->wg_count, p->wg_groups, add, rows);
       return hipGetLastError();
     });
-  return timed(p, T_GRID_FWD_GAUSS, st, [&] {
-    hipLaunchKernelGGL(k_wg_fwd_gauss, grid, dim3(kBlock), 0, st, p->wg_mac, s.mac0, x, scale,
-                       slot, p->wg_nu, p->wg_eta, p->wg_la, p->wg_mb, p->wg_alpha, p->wg_beta,
-                       p->wg_recg + static_cast<int64_t>(g.layer) * p->wg_groups * kWgVis,
-                       p->wg_dw, p->wg_w0, p->wg_h, p->wg_count, p->wg_groups, rows);
-    return hipGetLastError();
   });
 }
 
@@ -1432,7 +1432,7 @@ hipError_t launch_wg_forward_reduce(sl1m_plan* p, const void* data, void* out, b
   const WgOut w{p->wg_order, static_cast<const float*>(p->vgain), static_cast<const float2*>(data),
                 static_cast<float2*>(out), recs ? p->wg_res : nullptr};
   hipLaunchKernelGGL(k_wg_fwd_reduce, dim3(blocks1(slots)), dim3(kBlock), 0, st,
-                     static_cast<const float2*>(p->fpart), p->wg_macros, slots, rows,
+                     static_cast<const float2*>(p->fpart), p->wg_mrows, slots, rows,
                      forward_rows(p, 1) - skip, p->n_vis, w, recs ? rres_of(p) : nullptr,
                      static_cast<const float*>(p->layerDs), p->n_layers);
   return hipGetLastError();

@@ -79,6 +79,16 @@ __device__ __forceinline__ void store_slots(float4* __restrict__ o, int mask, fl
   if (mask & 8) f[3] = v.w;
 }
 
+// A slot's forward sum of one macro into its row, added where `add`.
+__device__ __forceinline__ void store_row(float2* __restrict__ rows, int64_t at, bool add,
+                                          float2 v) {
+  if (add) {
+    const float2 o = rows[at];
+    v = make_float2(o.x + v.x, o.y + v.y);
+  }
+  rows[at] = v;
+}
+
 // What becomes of a slot's sum: times the gain, less the data (those given), into `out`
 // and, times the conjugate gain, into the adjoint record `res`.
 struct WgOut {

@@ -217,10 +217,11 @@ int wg_segments(const GridSeg* segs, int n_segs, int64_t n_vis) {
   return n;
 }
 
-size_t wg_part_bytes(const GridSeg& g) {
+size_t wg_part_bytes(const GridSeg& g, int64_t max_groups) {
   const WgShape a(g, kWgSteps), b(g, kFlatSteps);
-  return sizeof(float4) * std::max(a.cells(kWgSteps) * wg_chunk_cap(a.macros()),
-                                   b.cells(kFlatSteps) * flat_chunk_cap(b.macros()));
+  const int most = static_cast<int>(max_groups);
+  return sizeof(float4) * std::max(a.cells(kWgSteps) * wg_chunks(a.macros(), most),
+                                   b.cells(kFlatSteps) * flat_chunks(b.macros(), most));
 }
 
 void wg_build_tiles(const GridSeg& g, const double* la, const double* mb, const double* c,

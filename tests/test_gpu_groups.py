@@ -288,3 +288,52 @@ def test_spread_w_without_cell_factors():
         worst = max(worst, float(np.max(np.abs(V - Vo) / np.abs(Vo))))
     print(f"    largest entry error {worst:.3e}", flush=True)
     assert worst <= E.E_ENTRY["fp32"]
+
+
+# name: delta pixels a side, extent, pixels a side of a wide Gaussian layer over them (0: none),
+# visibilities, w spread; segments in groups, those without cell factors
+MANY = {
+    "cell_factors": (1024, 0.3, 0, 3_000_000, 60.0, 1, 0),     # 153 macros: 6.4 GB of rows
+    "delta_and_layer": (768, 0.3, 384, 3_500_000, 60.0, 2, 0),  # 91 + 28 macros: 5.8 GB
+    "flat": (2048, 0.01, 0, 1_200_000, 300.0, 1, 1),           # 289 macros: 4.9 GB
+}
+
+
+@pytest.mark.parametrize("name", list(MANY))
+def test_macros_sharing_rows(name):
+    """More macros than the plan's rows of forward sums: passes that add to them.  The
+    workspace stays below 4 GiB, or a quarter above what it is without groups (no more than
+    that of two sides, which has none); sampled visibilities against the oracle and all of
+    them against the grid evaluation (a plan of two sides)."""
+    n, ext, ng, nv, ws, groups, flat = MANY[name]
+    print(f"[case] shared rows {name}", flush=True)
+    wl = W.small_random(140, 10, nv, uv_radius=400.0, w_sigma=ws)
+    l, m = _grid(n, n, 2 * ext / n)
+    sig = np.zeros(l.size)
+    if ng:
+        l2, m2 = _grid(ng, ng, 2 * ext / ng)
+        l, m = np.concatenate([l, l2]), np.concatenate([m, m2])
+        sig = np.concatenate([sig, np.full(l2.size, 2 * ext / ng)])
+    wl.l, wl.m, wl.sigma, wl.x_true = l, m, sig, None
+    wl.kind = np.where(sig > 0, W.PIX_GAUSS_WIDE, W.PIX_DELTA).astype(np.uint8)
+    x = np.random.default_rng(140).standard_normal(l.size)
+    plan = sl1m.Plan.from_workload(wl)
+    info = plan.info()
+    assert (info["grid_groups"], info["grid_flat"]) == (groups, flat)
+    V = plan.forward(x).cpu().numpy()
+    print(f"    workspace {plan.workspace_bytes / 1e9:.2f} GB", flush=True)
+    ks = np.arange(0, nv, nv // 40)
+    p = O.Problem.from_workload(wl)
+    Vo = sum(O.matrix_block(p, ks, np.arange(b, min(b + 65536, l.size))) @ x[b:b + 65536]
+             for b in range(0, l.size, 65536))
+    assert rel(V[ks], Vo) <= TOL
+    again = plan.forward(x).cpu().numpy()
+    plan.close()
+    assert np.array_equal(again, V)
+    other = sl1m.Plan.from_workload(wl, max_rhs=2)
+    V2 = other.forward(x).cpu().numpy()
+    print(f"    oracle {rel(V[ks], Vo):.3e}, grid evaluation {rel(V, V2):.3e}, its workspace "
+          f"{other.workspace_bytes / 1e9:.2f} GB", flush=True)
+    assert plan.workspace_bytes <= max(4 << 30, 1.25 * other.workspace_bytes)
+    assert rel(V, V2) <= TOL
+    other.close()
