@@ -1246,12 +1246,16 @@ double median(std::vector<float> v) {
   return v.empty() ? 0.0 : v[v.size() / 2];
 }
 
+// Tuning times plans of one side.  Those of a problem of several sides do without groups,
+// which its own plans never use.
+bool tune_groups(const sl1m_problem& problem) { return problem.max_rhs <= 1; }
+
 // Builds the plan of `pr` in the workspace and times `reps` forward and
 // adjoint applications (after one warm-up of each).
-sl1m_status tune_one(const sl1m_problem& pr, void* ws, size_t bytes, int reps, hipStream_t st,
-                     TuneTimes& out) {
+sl1m_status tune_one(const sl1m_problem& pr, bool groups, void* ws, size_t bytes, int reps,
+                     hipStream_t st, TuneTimes& out) {
   sl1m_plan* p = nullptr;
-  if (sl1m_status s = sl1m_plan_create(&pr, ws, bytes, st, &p)) return s;
+  if (sl1m_status s = plan_build(&pr, groups, ws, bytes, st, &p)) return s;
   std::vector<hipEvent_t> ev(2 * (2 * reps + 2), nullptr);
   sl1m_status res = SL1M_OK;
   hipError_t e = hipSuccess;
@@ -1309,7 +1313,7 @@ sl1m_status sl1m_tune_workspace_bytes(const sl1m_problem* problem, size_t* bytes
       p.fwd_vpl = vpl;
       p.adj_ppl = ppl;
       size_t b = 0;
-      if (sl1m_status s = sl1m_plan_workspace_bytes(&p, &b)) return s;
+      if (sl1m_status s = plan_bytes(&p, tune_groups(*problem), &b)) return s;
       mx = std::max(mx, b);
       return SL1M_OK;
     };
@@ -1340,6 +1344,7 @@ sl1m_status sl1m_tune(const sl1m_problem* problem, void* workspace, size_t works
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     sl1m_problem base = *problem;
     base.max_rhs = 1;
+    const bool groups = tune_groups(*problem);
     // does any segment qualify for the grid evaluation?
     bool grid_possible = false;
     {
@@ -1348,7 +1353,7 @@ sl1m_status sl1m_tune(const sl1m_problem* problem, void* workspace, size_t works
       p.grid_mode = SL1M_GRID_AUTO;
       p.tile_blocks = 0;
       p.fwd_vpl = p.adj_ppl = 0;
-      if (sl1m_status s = analyze(&p, a)) return s;
+      if (sl1m_status s = analyze(&p, a, groups)) return s;
       grid_possible = a.grid;
     }
     sl1m_tuning r;
@@ -1377,15 +1382,15 @@ sl1m_status sl1m_tune(const sl1m_problem* problem, void* workspace, size_t works
       TuneTimes t;
       // the first run brings the GPU to its working clock; it is not counted
       // (measured first, the defaults would otherwise look slower)
-      if (sl1m_status s = tune_one(p, workspace, workspace_bytes, reps, st, t)) return s;
-      if (sl1m_status s = tune_one(p, workspace, workspace_bytes, reps, st, t)) return s;
+      if (sl1m_status s = tune_one(p, groups, workspace, workspace_bytes, reps, st, t)) return s;
+      if (sl1m_status s = tune_one(p, groups, workspace, workspace_bytes, reps, st, t)) return s;
       r.default_forward_ms = t.fwd_ms;
       r.default_adjoint_ms = t.adj_ms;
       consider(p, t);
     }
     for (const sl1m_problem& p : tune_stage1(base, grid_possible)) {
       TuneTimes t;
-      if (sl1m_status s = tune_one(p, workspace, workspace_bytes, reps, st, t)) return s;
+      if (sl1m_status s = tune_one(p, groups, workspace, workspace_bytes, reps, st, t)) return s;
       consider(p, t);
     }
     // lane counts of the direct kernels at the best direct split
@@ -1399,7 +1404,7 @@ sl1m_status sl1m_tune(const sl1m_problem* problem, void* workspace, size_t works
           p.fwd_vpl = vpl;
           p.adj_ppl = ppl;
           TuneTimes t;
-          if (sl1m_status s = tune_one(p, workspace, workspace_bytes, reps, st, t)) return s;
+          if (sl1m_status s = tune_one(p, groups, workspace, workspace_bytes, reps, st, t)) return s;
           consider(p, t);
         }
     }

@@ -71,3 +71,22 @@ def test_explicit_lane_counts(vpl, ppl):
     ea = rel(plan.adjoint(r).cpu().numpy(), O.adjoint(p, r))
     say(f"    forward {ef:.3e} adjoint {ea:.3e}")
     assert ef <= 1e-5 and ea <= 1e-5
+
+
+def test_tuning_several_sides_times_their_kernels():
+    """A plan of one side evaluates this grid (16 x 512 values of |l| and |m|) in groups of
+    visibilities, about three times as fast as the grid evaluation that plans of several
+    sides run: tuning times the kernels of the plan it is asked about."""
+    l, m = np.meshgrid((np.arange(31) - 15) * 5e-5, (np.arange(1023) - 511) * 5e-5)
+    wl = W.small_random(33, 10, 100_000, uv_radius=2000.0, w_sigma=300.0)
+    wl.l, wl.m, wl.x_true = l.ravel(), m.ravel(), None
+    wl.sigma, wl.kind = np.zeros(l.size), np.zeros(l.size, np.uint8)
+    ms = []
+    for sides in (1, 2):
+        plan = sl1m.Plan.from_workload(wl, max_rhs=sides)
+        assert plan.info()["grid"] == 1 and plan.info()["grid_groups"] == (sides == 1)
+        t = plan.tune(reps=5)
+        say(f"[case] tune {sides} side(s): {t}")
+        ms.append(t["default_forward_ms"])
+        plan.close()
+    assert ms[1] > 1.5 * ms[0]
