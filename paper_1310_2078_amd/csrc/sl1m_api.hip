@@ -750,15 +750,17 @@ sl1m_status read_red(sl1m_plan* p, double* host, int n, hipStream_t st) {
 
 // V_hat = M x for x already in permuted order in p->xperm (or `xp`); result
 // combined into `out` (caller order) minus `data` if given.
+hipError_t forward_launches(sl1m_plan* p, const void* xp, const void* data, void* out, bool recs,
+                            hipStream_t st, int nr) {
+  if (nr == 1 && wg_single(p))
+    return timed(p, T_FWD, st, [&] { return launch_flat_single(p, xp, data, out, recs, st); });
+  const hipError_t e = timed(p, T_FWD, st, [&] { return launch_forward(p, xp, nr, st); });
+  return e == hipSuccess ? launch_forward_reduce(p, data, out, recs, nr, st) : e;
+}
+
 sl1m_status apply_forward(sl1m_plan* p, const void* xp, const void* data, void* out, bool recs,
                           hipStream_t st, int nr = 1) {
-  if (nr == 1 && wg_single(p)) {
-    SL1M_HIP(timed(p, T_FWD, st, [&] { return launch_flat_single(p, xp, data, out, recs, st); }),
-             "forward kernel");
-    return SL1M_OK;
-  }
-  SL1M_HIP(timed(p, T_FWD, st, [&] { return launch_forward(p, xp, nr, st); }), "forward kernel");
-  SL1M_HIP(launch_forward_reduce(p, data, out, recs, nr, st), "forward reduce");
+  SL1M_HIP(forward_launches(p, xp, data, out, recs, st, nr), "forward kernels");
   return SL1M_OK;
 }
 
@@ -1266,8 +1268,7 @@ sl1m_status tune_one(const sl1m_problem& pr, bool groups, void* ws, size_t bytes
   for (int r = 0; r <= reps && e == hipSuccess; ++r) {
     hipEvent_t* q = &ev[4 * r];
     e = hipEventRecord(q[0], st);
-    if (e == hipSuccess) e = launch_forward(p, p->xperm, 1, st);
-    if (e == hipSuccess) e = launch_forward_reduce(p, nullptr, p->res, true, 1, st);
+    if (e == hipSuccess) e = forward_launches(p, p->xperm, nullptr, p->res, true, st, 1);
     if (e == hipSuccess) e = hipEventRecord(q[1], st);
     if (e == hipSuccess) e = hipEventRecord(q[2], st);
     if (e == hipSuccess) e = launch_adjoint(p, 1, st);
