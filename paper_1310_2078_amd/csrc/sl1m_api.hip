@@ -97,23 +97,24 @@ bool analyze_grid(Analysis& a, int si, const std::vector<double>& L, const std::
     al[t] = std::fabs(L[o]);
     am[t] = std::fabs(M[o]);
   }
-  std::vector<double> ul(al), um(am);
-  std::sort(ul.begin(), ul.end());
-  ul.erase(std::unique(ul.begin(), ul.end()), ul.end());
-  std::sort(um.begin(), um.end());
-  um.erase(std::unique(um.begin(), um.end()), um.end());
-  const int64_t na = static_cast<int64_t>(ul.size()), nb = static_cast<int64_t>(um.size());
+  // 2 x 4 x cells <= 5 nd bounds the values of either axis (|m| by multiples of kGridNB)
+  const char* const sparse = "the pixels fill less than 40% of their grid";
+  std::vector<double> ul, um;
+  std::vector<int32_t> ia_of, ib_of;
+  if (!grid_axis(al.data(), nd, 5 * nd / (8 * kGridNB), ul, ia_of)) return why = sparse, false;
+  const int64_t na = static_cast<int64_t>(ul.size());
   if (na < kGridMinA) return why = "fewer than 16 distinct |l| values", false;
+  if (!grid_axis(am.data(), nd, 5 * nd / (8 * na), um, ib_of)) return why = sparse, false;
+  const int64_t nb = static_cast<int64_t>(um.size());
   const int64_t ng = (nb + kGridNB - 1) / kGridNB;
   const int64_t cells = ng * kGridNB * na;
-  if (2 * 4 * cells > 5 * nd) return why = "the pixels fill less than 40% of their grid", false;
+  if (2 * 4 * cells > 5 * nd) return why = sparse, false;
   if (4 * (a.grid_cells + cells) > INT32_MAX) return why = "grid too large", false;
   std::vector<int32_t> slot(4 * cells, -1);
   for (int64_t t = 0; t < nd; ++t) {
     const int64_t j = sg.start + t;  // permuted index
     const int64_t o = a.perm.empty() ? j : a.perm[j];
-    const int64_t ia = std::lower_bound(ul.begin(), ul.end(), al[t]) - ul.begin();
-    const int64_t ib = std::lower_bound(um.begin(), um.end(), am[t]) - um.begin();
+    const int64_t ia = ia_of[t], ib = ib_of[t];
     const int sgn = (L[o] < 0.0 ? 1 : 0) + (M[o] < 0.0 ? 2 : 0);
     const int64_t q = ((ib / kGridNB) * na + ia) * kGridNB + ib % kGridNB;
     int32_t& sl = slot[4 * q + sgn];
@@ -193,6 +194,7 @@ bool all_pixels(const Analysis& a, int n) {
 // groups would take a quarter of the time there as well.
 constexpr int64_t kGroupGaussMax = 131072;
 constexpr size_t kGroupRoom = size_t{4} << 30, kGroupMost = size_t{64} << 30;
+constexpr size_t kGroupStage = size_t{256} << 10;
 void choose_groups(Analysis& a) {
   if (a.gsegs[0].kind != SL1M_PIX_DELTA && all_pixels(a, 1) && a.n_pix > kGroupGaussMax) return;
   const size_t without = plan_total(a);
@@ -704,16 +706,16 @@ Layout layout(const Analysis& a, int wg_n) {
     L.wg_slot = take(16 * wg_cells);
     L.wg_order = take(4 * slots);
     L.wg_count = take(4 * static_cast<size_t>(a.wg_cap));
+    L.wg_w0 = take(8 * static_cast<size_t>(a.wg_cap));
+    L.wg_h = take(4 * static_cast<size_t>(a.wg_cap));
+    L.wg_map = take(wg_alias && wg_n == 1 && wg_flat_macros(a.gsegs[0]) == 1 ? 4 * np : 0);
     L.wg_su = take(8 * slots);
     L.wg_sv = take(8 * slots);
     L.wg_sw = take(8 * slots);
     L.wg_dw = take(4 * slots);
-    L.wg_w0 = take(8 * static_cast<size_t>(a.wg_cap));
     L.wg_res = take(8 * slots);
-    L.wg_map = take(wg_alias && wg_n == 1 && wg_flat_macros(a.gsegs[0]) == 1 ? 4 * np : 0);
     L.wg_recg = take(sizeof(WgVisG) * slots * a.layer_sigma.size());
     if (!wg_alias) L.wg_part = take(wg_part);
-    L.wg_h = take(4 * static_cast<size_t>(a.wg_cap));
   }
   L.total = off;
   return L;
@@ -1094,6 +1096,7 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
     }
     std::vector<Chunk> chunks;
     std::vector<int32_t> wg_map;
+    std::vector<char> wg_stage;
     chunks.insert(chunks.end(), a.fd.begin(), a.fd.end());
     chunks.insert(chunks.end(), a.fg.begin(), a.fg.end());
     chunks.insert(chunks.end(), a.pd.begin(), a.pd.end());
@@ -1116,34 +1119,49 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
     };
     if (a.wg_n) {
       const WgPlan& t = wgp;
+      // The tables' regions, wg_mac to wg_map, as one copy where they are small (a dozen
+      // copies of their own are 40 us of a 32 x 32 x 2,000 plan's 190).
+      const size_t span = L.wg_su - L.wg_mac;
+      if (span <= kGroupStage) wg_stage.resize(span);
       // a table never leaves its region [at, end)
       auto put = [&](size_t at, size_t end, const auto& v) {
         const size_t bytes = sizeof(v[0]) * v.size();
         if (bytes > end - at)
           e = hipErrorInvalidValue;
-        else
+        else if (wg_stage.empty())
           up(w + at, v.data(), bytes);
+        else if (bytes > 0)
+          std::memcpy(&wg_stage[at - L.wg_mac], v.data(), bytes);
       };
       put(L.wg_mac, L.wg_la, t.macros);
       put(L.wg_la, L.wg_mb, t.la);
       put(L.wg_mb, L.wg_alpha, t.mb);
-      put(L.wg_alpha, L.wg_beta, t.alpha);
-      put(L.wg_beta, L.wg_nu, t.beta);
-      put(L.wg_nu, L.wg_eta, t.nu);
+      // alpha and beta serve flat and Gaussian segments, nu those with cell factors
+      bool parts = false, factors = false;
+      for (int i = 0; i < a.wg_n; ++i) {
+        parts = parts || t.segs[i].flat || a.gsegs[i].kind != SL1M_PIX_DELTA;
+        factors = factors || !t.segs[i].flat;
+      }
+      if (parts) {
+        put(L.wg_alpha, L.wg_beta, t.alpha);
+        put(L.wg_beta, L.wg_nu, t.beta);
+      }
+      if (factors) put(L.wg_nu, L.wg_eta, t.nu);
       put(L.wg_eta, L.wg_slot, t.eta);
       put(L.wg_slot, L.wg_order, t.slot);
       if (wg_single(p)) {
         wg_map.resize(a.n_pix);
         for (size_t i = 0; i < t.slot.size(); ++i)
           if (t.slot[i] >= 0) wg_map[t.slot[i]] = static_cast<int32_t>(i);
-        put(L.wg_map, L.wg_recg, wg_map);
+        put(L.wg_map, L.wg_su, wg_map);
       }
       put(L.wg_order, L.wg_count, wgg.order);
-      put(L.wg_count, L.wg_su, wgg.count);
-      put(L.wg_w0, L.wg_res, wgg.w0);
-      put(L.wg_h, L.total, wgg.h);
+      put(L.wg_count, L.wg_w0, wgg.count);
+      put(L.wg_w0, L.wg_h, wgg.w0);
+      put(L.wg_h, L.wg_map, wgg.h);
+      up(w + L.wg_mac, wg_stage.data(), wg_stage.size());
     }
-    if (a.grid) {
+    if (a.grid && a.wg_n < static_cast<int>(a.gsegs.size())) {  // the grid evaluation's tables
       up(p->grid_la, a.grid_la.data(), 8 * a.grid_la.size());
       up(p->grid_mb, a.grid_mb.data(), 8 * a.grid_mb.size());
       up(p->grid_c3, a.grid_c3.data(), 8 * a.grid_c3.size());

@@ -102,6 +102,10 @@ struct WgGroups {
   std::vector<int32_t> count;      // visibilities of the group
 };
 
+// The distinct values among v[0, n) (finite, not negative) in ascending order and the rank of
+// each; false where there are more than `most`.
+bool grid_axis(const double* v, int64_t n, int64_t most, std::vector<double>& values,
+               std::vector<int32_t>& rank);
 // How many of a plan's grid segments, from the first on, groups of n_vis visibilities take:
 // consecutive segments whose tiles hold at most four times their cells with padding.  The
 // tables number cells, slots (2 k + sign) and the launches' macros in 32 bits or fewer:

@@ -2,10 +2,62 @@
 // of the visibilities.  No device code.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 
 #include "sl1m_wgroup.h"
 
 namespace sl1m {
+
+// A hash of the bits instead of a sort of all values: a grid's axis has few (256 x 256
+// pixels: 129 of 65,536; both axes 0.3 ms instead of 2.9, 16,384 scattered cells end after
+// 1,281).
+bool grid_axis(const double* v, int64_t n, int64_t most, std::vector<double>& values,
+               std::vector<int32_t>& rank) {
+  values.clear();
+  rank.resize(n);
+  int shift = 56;  // table of 2^(64 - shift)
+  std::vector<int32_t> table(256, -1);
+  // a free or its own place of x: from the product's top bits on
+  auto find = [&](double x) -> int32_t& {
+    uint64_t b;
+    std::memcpy(&b, &x, sizeof(b));
+    size_t h = (b ^ b >> 32) * 0x9E3779B97F4A7C15ull >> shift;
+    while (table[h] >= 0 && values[table[h]] != x) h = (h + 1) & (table.size() - 1);
+    return table[h];
+  };
+  double last = -1.0;
+  int32_t id = -1;
+  for (int64_t t = 0; t < n; ++t) {
+    if (v[t] != last) {
+      last = v[t];
+      int32_t& place = find(last);
+      id = place;
+      if (id < 0) {
+        if (static_cast<int64_t>(values.size()) >= most) return false;
+        id = place = static_cast<int32_t>(values.size());
+        values.push_back(last);
+        if (2 * values.size() > table.size()) {
+          shift -= 2;
+          table.assign(4 * table.size(), -1);
+          for (size_t i = 0; i < values.size(); ++i) find(values[i]) = static_cast<int32_t>(i);
+        }
+      }
+    }
+    rank[t] = id;
+  }
+  // first come, then ascending
+  std::vector<int32_t> at(values.size()), to(values.size());
+  for (size_t i = 0; i < at.size(); ++i) at[i] = static_cast<int32_t>(i);
+  std::sort(at.begin(), at.end(), [&](int32_t i, int32_t j) { return values[i] < values[j]; });
+  std::vector<double> sorted(values.size());
+  for (size_t i = 0; i < at.size(); ++i) {
+    sorted[i] = values[at[i]];
+    to[at[i]] = static_cast<int32_t>(i);
+  }
+  values.swap(sorted);
+  for (int32_t& r : rank) r = to[r];
+  return true;
+}
 
 // Groups that hold few visibilities (sparse w, a wide field: the cut at kWgX ends
 // them early) still cost C_0 and the float16 splits of every cell.  Measured on
@@ -241,37 +293,49 @@ bool wg_build_groups(const std::vector<double>& w, float width, int64_t max_grou
     wm = std::max(wm, std::fabs(x));
   }
   if (wm >= 0x1.0p27) return false;  // phases below 2^27 turns (|nu| < 1): kMagicFine
-  // order by |w| in 2^20 bins (two stable counting passes of 10 bits); equal bins
-  // keep the caller's order
+  // order by |w| in 2^20 bins (two stable counting passes of 10 bits over (bin, index)
+  // pairs); equal bins keep the caller's order
   const double scale = wm > 1e-290 ? 1048575.0 / wm : 0.0;
-  std::vector<uint32_t> key(n);
-  std::vector<int32_t> a(n), b(n);
+  std::vector<uint64_t> a(n), b(n);
+  uint32_t at[2][1024] = {};
   for (int64_t k = 0; k < n; ++k) {
-    key[k] = static_cast<uint32_t>(std::fabs(w[k]) * scale);
-    a[k] = static_cast<int32_t>(k);
+    const uint32_t key = static_cast<uint32_t>(std::fabs(w[k]) * scale);
+    a[k] = static_cast<uint64_t>(key) << 32 | static_cast<uint32_t>(k);
+    ++at[0][key & 1023u];
+    ++at[1][key >> 10];
   }
   for (int pass = 0; pass < 2; ++pass) {
-    int64_t cnt[1025] = {};
-    const int sh = 10 * pass;
-    for (int64_t i = 0; i < n; ++i) ++cnt[((key[a[i]] >> sh) & 1023u) + 1];
-    for (int i = 0; i < 1024; ++i) cnt[i + 1] += cnt[i];
-    for (int64_t i = 0; i < n; ++i) b[cnt[(key[a[i]] >> sh) & 1023u]++] = a[i];
+    uint32_t first = 0;
+    for (uint32_t& c : at[pass]) {
+      const uint32_t count = c;
+      c = first;
+      first += count;
+    }
+    const int sh = 32 + 10 * pass;
+    for (int64_t i = 0; i < n; ++i) b[at[pass][(a[i] >> sh) & 1023u]++] = a[i];
     a.swap(b);
   }
   const double hmax = width > 0.0f ? 1.0 / (6.283185307179586 * width) : 1e300;
+  const int64_t least = (n + kWgVis - 1) / kWgVis;
+  out.order.reserve(kWgVis * least);
+  out.w0.reserve(least);
+  out.h.reserve(least);
+  out.count.reserve(least);
   for (int64_t i = 0; i < n;) {
-    double lo = std::fabs(w[a[i]]), hi = lo;
-    int64_t j = i + 1;
-    for (; j < n && j - i < kWgVis; ++j) {
-      const double x = std::fabs(w[a[j]]);
+    if (static_cast<int64_t>(out.w0.size()) >= max_groups) return false;
+    const size_t o = out.order.size();
+    out.order.resize(o + kWgVis, -1);
+    double lo = 1e300, hi = 0.0;
+    int64_t j = i;
+    for (const int64_t end = std::min(n, i + kWgVis); j < end; ++j) {
+      const int32_t k = static_cast<int32_t>(static_cast<uint32_t>(a[j]));
+      const double x = std::fabs(w[k]);
       const double l2 = std::min(lo, x), h2 = std::max(hi, x);
-      if (h2 - l2 > 2.0 * hmax) break;
+      if (j > i && h2 - l2 > 2.0 * hmax) break;
       lo = l2;
       hi = h2;
+      out.order[o + (j - i)] = 2 * k + (w[k] < 0.0 ? 1 : 0);
     }
-    if (static_cast<int64_t>(out.w0.size()) >= max_groups) return false;
-    for (int s = 0; s < kWgVis; ++s)
-      out.order.push_back(i + s < j ? 2 * a[i + s] + (w[a[i + s]] < 0.0 ? 1 : 0) : -1);
     out.w0.push_back(0.5 * (lo + hi));
     out.h.push_back(static_cast<float>(0.5 * (hi - lo)));
     out.count.push_back(static_cast<int32_t>(j - i));

@@ -4,9 +4,11 @@
 // stdin: segments, then per segment kind, |l| x |m| pixels, spacing; visibilities, their w.
 // stdout: the segments kept and the groups; per kept segment whether it is evaluated
 // without cell factors and how many (macro, group) pairs fall into each series class.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <random>
 
 #include "sl1m_wgroup.h"
 
@@ -87,8 +89,28 @@ static void segment_checks() {
   CHECK(wg_segments(&four, 1, 1000) == 1 && wg_segments(&three_c, 1, 1000) == 0);
 }
 
+// grid_axis against a sort, at its limit and past it.
+static void axis_checks() {
+  std::mt19937 rng(3);
+  for (int n : {0, 1, 2, 100, 5000})
+    for (int distinct : {1, 2, 17, 130, 1000, 100000}) {
+      std::vector<double> v(n);
+      for (double& x : v) x = 1e-4 * static_cast<double>(rng() % distinct);
+      if (n > 1) v[n / 2] = 1e-310;  // subnormal
+      std::vector<double> want(v), got;
+      std::sort(want.begin(), want.end());
+      want.erase(std::unique(want.begin(), want.end()), want.end());
+      std::vector<int32_t> rank;
+      const int64_t most = static_cast<int64_t>(want.size());
+      CHECK(grid_axis(v.data(), n, most, got, rank) && got == want);
+      for (int t = 0; t < n; ++t) CHECK(got[rank[t]] == v[t]);
+      if (n > 0) CHECK(!grid_axis(v.data(), n, most - 1, got, rank));
+    }
+}
+
 int main() {
   segment_checks();
+  axis_checks();
   int n = 0;
   CHECK(std::scanf("%d", &n) == 1);
   Grids t;
