@@ -1,7 +1,9 @@
 """Autotuning of launch shapes (sl1m_tune) and explicit lane counts, through
 the C ABI.  A tuned plan computes the same operator (oracle tolerance); the
 tuner's choice is never slower than the default it timed beside it."""
+import ctypes
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -90,3 +92,31 @@ def test_tuning_several_sides_times_their_kernels():
         ms.append(t["default_forward_ms"])
         plan.close()
     assert ms[1] > 1.5 * ms[0]
+
+
+def test_float64_plans_are_analysed_once():
+    """The finer chunks of small float64 plans do not cost large ones a second analysis: the
+    workspace of a float64 problem that is past the no-allocation scratch either way takes
+    about as long to work out as that of the same float32 problem off the grid."""
+    n = 512
+    wl = W.small_random(34, 10, 50_000)
+    l, m, _ = W.grid_pixels(n, 0.2)
+    rng = np.random.default_rng(34)
+    wl.l, wl.m, wl.x_true = l, m, None
+    wl.sigma = np.where(rng.random(l.size) < 0.5, 0.0, 1e-3)
+    wl.kind = np.where(wl.sigma > 0, W.PIX_GAUSS_WIDE, W.PIX_DELTA).astype(np.uint8)
+    best = {}
+    for prec in ("fp32", "fp64"):
+        plan = sl1m.Plan.from_workload(wl, precision=prec, grid="off")
+        assert plan.workspace_bytes > 64 << 20 or prec == "fp32"
+        nbytes = ctypes.c_size_t()
+        times = []
+        for _ in range(15):
+            t = time.perf_counter()
+            assert sl1m.lib().sl1m_plan_workspace_bytes(ctypes.byref(plan._prob),
+                                                        ctypes.byref(nbytes)) == 0
+            times.append(time.perf_counter() - t)
+        best[prec] = min(times)
+        plan.close()
+    say(f"[case] analysis {best}")
+    assert best["fp64"] <= 1.5 * best["fp32"]
