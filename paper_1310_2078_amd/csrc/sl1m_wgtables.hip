@@ -69,14 +69,16 @@ int64_t wg_group_cap(int64_t n_vis) {
   return full + full * 3 / 4 + 2;
 }
 
-// Blocks: two of 256 threads stay resident per compute unit (512 in all).  Two
-// rounds of them for small grids (each block loads its tiles' cells first, and
-// the adjoint's chunk sums grow with the count), four for large ones, whose
-// macros differ more in work (256 x 256 x 97,536: 397 / 428 us at two rounds,
-// 395 / 424 at four, 402 / 442 at eight; 100,003 x 151 x 150 pixels 89 / 102 us
-// at two, 89 / 107 at three; 1024 x 1024 x 409,600: 28.4 / 31.5 ms at two, 27.3 /
-// 29.9 at four).
-int wg_chunk_cap(int macros) { return std::max(1, (macros <= 32 ? 1024 : 2048) / macros); }
+// Blocks: two of 256 threads stay resident per compute unit (512 in all).  One round of
+// them for few macros (each block loads its tiles' cells first, and the adjoint's chunk
+// sums grow with the count), two for small grids, four for large ones, whose macros differ
+// more in work.  Forward / adjoint in us at one, two (and four) rounds: 31 x 127 pixels x
+// 20,000 visibilities (2 macros) 24.5 / 24.4, 27.5 / 29.7 (grid evaluation 24.5 / 41.4);
+// 200 x 200 x 100,000 (8 macros) 152 / 165, 153 / 170; 256 x 256 x 100,000 (15) 268 / 294,
+// 242 / 254; 1024 x 1024 x 409,600: 28.4 / 31.5 ms at two, 27.3 / 29.9 at four.
+int wg_chunk_cap(int macros) {
+  return std::max(1, (macros <= 8 ? 512 : macros <= 32 ? 1024 : 2048) / macros);
+}
 int wg_chunks(int macros, int groups) {
   return std::max(1, std::min(groups, wg_chunk_cap(macros)));
 }
