@@ -380,7 +380,7 @@ struct alignas(16) FlatAdjLds {
   uint32_t x[kWgVis];                       // (x, x) in float16
   float2 rho[4][kWgVis];
   float top[GAUSS ? 4 : 1][kWgVis];
-  float mx[GAUSS ? 1 : 4];
+  float mx[4];
 };
 
 // One row sign of a group: G (two column signs) += the products' sums, the series in eta
@@ -466,18 +466,18 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_adj(
     lds.mb[tid] = mb[cm->b_off + tid];
     lds.be[tid] = beta[cm->b_off + tid];
   }
-  // One scale for the operands of a wavefront's groups: of the residuals (delta pixels,
-  // where the wavefronts share them), or of the residuals times their tapers.  Where every
-  // baseline is tapered a scale of the bare residuals left the operands below float16's
+  // One scale for the operands of the block's groups, of the residuals times their largest
+  // taper (Gaussian; the wavefronts share the pass, over the rows of the whole macro).  Where
+  // every baseline is tapered a scale of the bare residuals left the operands below float16's
   // range: relative errors of the gradient of 7e-6 at tapers of 2^-20, 0.05 at 2^-33.  (A
   // scale per group, folded into the sums, spills: 300 x 300 pixels x 100,003 550 us.)
   float mx = 0.0f;
-  for (int g = GAUSS ? g0 : g0 + wv * gs; g < n_groups; g += GAUSS ? gs : 4 * gs) {
+  for (int g = g0 + wv * gs; g < n_groups; g += 4 * gs) {
     float2 z = res[static_cast<int64_t>(g) * kWgVis + lane];
     if constexpr (GAUSS) {
       const WgVisG* const q = in.rec + static_cast<int64_t>(g) * kWgVis + lane;
       const float k = pow2(taper_top(q->c1, q->v, q->w, m_lo, m_hi) +
-                           taper_top(q->c1, q->u, q->w, l_lo, l_hi));
+                           taper_top(q->c1, q->u, q->w, cm->l_lo[0], cm->l_hi[sets - 1]));
       z.x *= k;  // |D (1 + i s)| <= 1
       z.y *= k;
     }
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_adj(
     mx = fmaxf(mx, z.x != z.x || z.y != z.y ? __builtin_inff() : m);
   }
   mx = wave_max(mx);
-  if (!GAUSS && lane == 0) lds.mx[wv] = mx;
+  if (lane == 0) lds.mx[wv] = mx;
   f4_t gr[4][kFlatSteps];
   h2_t et[kFlatSteps][2];
 #pragma unroll
@@ -504,9 +504,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_adj(
     sn = in.ser(g0, eta_max);
   }
   __syncthreads();
-  if constexpr (!GAUSS)
-    mx = fmaxf(fmaxf(lds.mx[0], lds.mx[1]), fmaxf(lds.mx[2], lds.mx[3]));
-  const float sc = 0.5f * op_scale(mx);
+  const float sc =
+      0.5f * op_scale(fmaxf(fmaxf(lds.mx[0], lds.mx[1]), fmaxf(lds.mx[2], lds.mx[3])));
   for (int g = g0; g < n_groups; g += gs) {
     const FlatVis r = rn;
     const int ser = sn;
