@@ -181,9 +181,7 @@ bool all_pixels(const Analysis& a, int n) {
 
 // Group evaluation of the grid segments (plans of one side: the grid
 // evaluation shares its phasors among several, and a side on its own then gives
-// the same bits as among others), as far as wg_segments allows.  A plan that fits the no-allocation
-// scratch without the group tables but not with them keeps the grid evaluation,
-// so that what sl1m_forward_noalloc takes does not shrink.
+// the same bits as among others), as far as wg_segments and the room allow.
 //
 // Plans of wide Gaussian pixels alone, above kGroupGaussMax of them, keep it too: the
 // server runs such requests with its own grid kernels, and a served image agrees with a
@@ -205,10 +203,13 @@ void choose_groups(Analysis& a) {
   // A row of slots per macro outgrows the card on large problems (2048 x 2048 pixels x 40
   // million visibilities: 321 GB, 67 without groups).  So the groups may take a plan up to
   // kGroupRoom or a quarter more than it is without them, but past kGroupMost no further
-  // than it is without: what fits a card still does.  Rows that do not fit are added up in
-  // passes over the macros.
+  // than it is without: what fits a card still does, and what fits the no-allocation
+  // scratch too.  Rows that do not fit are added up in passes over the macros.
+  const size_t scratch = SL1M_NOALLOC_SCRATCH_BYTES;
   const size_t room =
-      std::max({without, kGroupRoom, std::min(without + without / 4, kGroupMost)});
+      without <= scratch
+          ? scratch
+          : std::max({without, kGroupRoom, std::min(without + without / 4, kGroupMost)});
   for (; a.wg_n; a.wg_n = wg_fewer(a.gsegs[0], a.wg_n)) {
     auto fits = [&](int rows) {
       a.wg_mrows = rows;
@@ -221,8 +222,6 @@ void choose_groups(Analysis& a) {
     a.wg_mrows = lo;
     break;
   }
-  if (without <= SL1M_NOALLOC_SCRATCH_BYTES && plan_total(a) > SL1M_NOALLOC_SCRATCH_BYTES)
-    a.wg_n = 0;
 }
 
 // `groups`: whether the plan may use the group evaluation (the server's plans run
@@ -655,8 +654,9 @@ Layout layout(const Analysis& a, int wg_n) {
   const size_t macros = static_cast<size_t>(wg_macros(a, wg_n));
   L.wg_sums = std::min<size_t>(macros, a.wg_mrows) * slots;
   wg_rows += L.wg_sums;
+  // (plans with groups have one side and never take the direct evaluation's rows)
   L.fpart = take(2 * rb *
-                 std::max(std::max({nfc * nr, grid_rows * std::max<size_t>(1, a.grid_multi),
+                 std::max(std::max({wg_n ? 0 : nfc * nr, grid_rows * std::max<size_t>(1, a.grid_multi),
                                     static_cast<size_t>(a.n_mfchunks) * nr}) * nv,
                           wg_n ? wg_rows : 0));
   // the group evaluation's chunk sums stand behind row 0 (which takes their
@@ -714,7 +714,9 @@ Layout layout(const Analysis& a, int wg_n) {
     L.wg_su = take(8 * slots);
     L.wg_sv = take(8 * slots);
     L.wg_sw = take(8 * slots);
-    L.wg_dw = take(4 * slots);
+    // a delta segment alone reads one of the two
+    const bool one = wg_n == 1 && a.gsegs[0].kind == SL1M_PIX_DELTA;
+    L.wg_dw = one ? L.wg_sw : take(4 * slots);
     L.wg_res = take(8 * slots);
     L.wg_recg = take(sizeof(WgVisG) * slots * a.layer_sigma.size());
     if (!wg_alias) L.wg_part = take(wg_part);
@@ -1062,8 +1064,11 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       p->wg_segs = wgp.segs;
       for (const WgSeg& s2 : p->wg_segs) p->wg_macros += s2.macros;
       p->wg_groups = static_cast<int>(wgg.w0.size());
-      p->wg_mrows = static_cast<int>(std::min<size_t>(
+      // rows for passes of about one size
+      const int fit = static_cast<int>(std::min<size_t>(
           p->wg_macros, L.wg_sums / (static_cast<size_t>(p->wg_groups) * kWgVis)));
+      const int passes = (p->wg_macros + fit - 1) / fit;
+      p->wg_mrows = (p->wg_macros + passes - 1) / passes;
       p->wg_recg = reinterpret_cast<WgVisG*>(w + L.wg_recg);
       p->wg_map = reinterpret_cast<int32_t*>(w + L.wg_map);
       p->wg_mac = reinterpret_cast<WgMacro*>(w + L.wg_mac);
@@ -1080,8 +1085,10 @@ sl1m_status plan_build(const sl1m_problem* pr, bool groups, void* workspace,
       p->wg_order = reinterpret_cast<int32_t*>(w + L.wg_order);
       p->wg_su = reinterpret_cast<double*>(w + L.wg_su);
       p->wg_sv = reinterpret_cast<double*>(w + L.wg_sv);
-      p->wg_sw = reinterpret_cast<double*>(w + L.wg_sw);
-      p->wg_dw = reinterpret_cast<float*>(w + L.wg_dw);
+      // w of flat delta segments, w - w0 of the others
+      const bool flat0 = p->wg_segs[0].flat && a.gsegs[0].kind == SL1M_PIX_DELTA;
+      if (flat0) p->wg_sw = reinterpret_cast<double*>(w + L.wg_sw);
+      if (!flat0 || a.wg_n > 1) p->wg_dw = reinterpret_cast<float*>(w + L.wg_dw);
       p->wg_w0 = reinterpret_cast<double*>(w + L.wg_w0);
       p->wg_h = reinterpret_cast<float*>(w + L.wg_h);
     }

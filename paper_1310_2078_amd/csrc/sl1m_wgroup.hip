@@ -349,8 +349,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
   }
 }
 
-// Per-slot coordinates: the visibility's, negated where w < 0; w - w0 (padding: the group's
-// w0, 0).
+// Per-slot coordinates: the visibility's, negated where w < 0; w and w - w0, as far as they
+// are read (padding: the group's w0, 0).
 __global__ void k_wg_slots(const int32_t* __restrict__ order, const double* __restrict__ w0s,
                            const double* __restrict__ vu, const double* __restrict__ vv,
                            const double* __restrict__ vw, int64_t n, double* __restrict__ su,
@@ -362,16 +362,17 @@ __global__ void k_wg_slots(const int32_t* __restrict__ order, const double* __re
   const double w0 = w0s[t / kWgVis];
   if (o < 0) {
     su[t] = sv[t] = 0.0;
-    sw[t] = w0;
-    sdw[t] = 0.0f;
+    if (sw) sw[t] = w0;
+    if (sdw) sdw[t] = 0.0f;
     return;
   }
   const int32_t k = o >> 1;
   const double sg = o & 1 ? -1.0 : 1.0;
   su[t] = sg * vu[k];
   sv[t] = sg * vv[k];
-  sw[t] = sg * vw[k];
-  sdw[t] = static_cast<float>(sw[t] - w0);
+  const double w = sg * vw[k];
+  if (sw) sw[t] = w;
+  if (sdw) sdw[t] = static_cast<float>(w - w0);
 }
 
 // Slot t's visibility: the macros' rows, conjugated where w < 0, and the other
