@@ -48,17 +48,42 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_F16_MATRIX_TFLOPS = 2500.0     # MI355X dense float16 matrix peak (published)
+PEAK_FP32_TFLOPS = 157.3            # MI355X FP32 vector peak (published)
 FLOP_PER_EVAL_DELTA = 14            # phase 3 FMA, reduction 2, sin+cos 2, accumulate 2 FMA
 FLOP_PER_EVAL_GAUSS_WIDE = 26       # + taper 9, amplitude 1, kappa FMA 2
-# The group kernels' figure is their float16 matrix products: 8 real products
-# per delta cell (4 entries) and 16 per Gaussian cell, each as three split
-# products and one of the series' first order (more where the series needs it).
+# FLOPs per entry that an operator kernel executes at least, and the peak they run against.
+# Group kernels: their float16 matrix products, 8 real products per cell (4 entries) with one
+# real factor, 16 with two complex ones, each as three split products and one of the series'
+# first order (the split triples what the entries need: FLOP_PER_EVAL_*).  Grid kernels, the
+# direct count's rules (FMA = 2, sin, cos, exp2 = 1): a mirrored pair of delta cells 36, a
+# Gaussian cell at most 32.
 EXEC_FLOP_PER_EVAL = {
-    "k_wg_fwd": 16.0,
-    "k_wg_adj": 16.0,
-    "k_wg_fwd_gauss": 32.0,
-    "k_wg_adj_gauss": 32.0,
+    "k_wg_fwd": (16.0, PEAK_F16_MATRIX_TFLOPS),
+    "k_wg_adj": (16.0, PEAK_F16_MATRIX_TFLOPS),
+    "k_wg_fwd_gauss": (32.0, PEAK_F16_MATRIX_TFLOPS),
+    "k_wg_adj_gauss": (32.0, PEAK_F16_MATRIX_TFLOPS),
+    "k_flat_fwd": (16.0, PEAK_F16_MATRIX_TFLOPS),
+    "k_flat_adj": (16.0, PEAK_F16_MATRIX_TFLOPS),
+    "k_grid_fwd_delta_pairs": (4.5, PEAK_FP32_TFLOPS),
+    "k_grid_adj_delta_square": (4.5, PEAK_FP32_TFLOPS),
+    "k_grid_fwd_gauss_pairs": (8.0, PEAK_FP32_TFLOPS),
+    "k_grid_adj_gauss_multi": (8.0, PEAK_FP32_TFLOPS),
 }
+
+
+def operator_kernels(pinfo):
+    """Timing kind -> kernel for a plan of square grids, delta pixels first, as the plan
+    reports what it evaluates in groups and what of that without cell factors."""
+    out = {}
+    for layer, kind, grid in ((0, "delta", ("k_grid_fwd_delta_pairs", "k_grid_adj_delta_square")),
+                              (1, "gauss", ("k_grid_fwd_gauss_pairs", "k_grid_adj_gauss_multi"))):
+        names = grid
+        if layer < pinfo["grid_groups"]:
+            tail = "_gauss" if layer else ""
+            names = (("k_flat_fwd", "k_flat_adj") if pinfo["grid_flat"] >> layer & 1
+                     else ("k_wg_fwd" + tail, "k_wg_adj" + tail))
+        out["grid_fwd_" + kind], out["grid_adj_" + kind] = names
+    return out
 
 
 def _function_text(src: str, name: str) -> str:
@@ -87,9 +112,10 @@ def kernel_source_hash(kernel: str) -> str:
             return fh.read()
 
     base = kernel.split("<")[0]
-    if kernel.startswith("k_wg"):   # the group kernels share their file's device functions
+    if kernel.startswith(("k_wg", "k_flat")):   # these share their file's device functions
         h = hashlib.sha256()
-        for f in ("sl1m_wgroup.hip", "sl1m_wgroup_dev.h", "sl1m_wgroup.h", "sl1m_device.h"):
+        src = "sl1m_wflat.hip" if kernel.startswith("k_flat") else "sl1m_wgroup.hip"
+        for f in (src, "sl1m_wgroup_dev.h", "sl1m_wgroup.h", "sl1m_device.h"):
             h.update(read(f).encode())
         return h.hexdigest()[:16]
     grid = kernel.startswith("k_grid")
@@ -172,7 +198,12 @@ def ingest_counters(fetch_csv, write_csv, bench_log=None):
                          ("k_adj_delta<float,4>", "k_adj_delta<float, 4, false, 1>"),
                          ("k_wg_fwd", "k_wg_fwd("), ("k_wg_adj", "k_wg_adj("),
                          ("k_wg_fwd_gauss", "k_wg_fwd_gauss("),
-                         ("k_wg_adj_gauss", "k_wg_adj_gauss(")):
+                         ("k_wg_adj_gauss", "k_wg_adj_gauss("),
+                         ("k_flat_fwd", "k_flat_fwd<"), ("k_flat_adj", "k_flat_adj<"),
+                         ("k_grid_fwd_delta_pairs", "k_grid_fwd_delta_pairs("),
+                         ("k_grid_adj_delta_square", "k_grid_adj_delta_square("),
+                         ("k_grid_fwd_gauss_pairs", "k_grid_fwd_gauss_pairs("),
+                         ("k_grid_adj_gauss_multi", "k_grid_adj_gauss_multi(")):
             vals = [v for n, v in rows if pat in n]
             if vals:
                 rec = out.setdefault(key, {"source_hash": kernel_source_hash(key)})
@@ -459,13 +490,16 @@ def config4_data(wl4, plan, dev):
 
 def dominant_kernel(pinfo, tim, n_delta, n_gauss, n_vis, n_layers):
     """The operator kernel with the longest average launch in the timed region:
-    (name, average ms, evals per launch).  Plans of one right-hand side on these
-    grids take the group evaluation (one launch per Gaussian layer)."""
+    (name, average ms, evals per launch, timing kind).  Gaussian layers are launched one by one, but for
+    the grid evaluation's adjoint."""
+    names = operator_kernels(pinfo)
+    layer = n_gauss * n_vis / max(n_layers, 1)
     cands = [
-        ("k_wg_fwd", "grid_fwd_delta", n_delta * n_vis),
-        ("k_wg_adj", "grid_adj_delta", n_delta * n_vis),
-        ("k_wg_adj_gauss", "grid_adj_gauss", n_gauss * n_vis / max(n_layers, 1)),
-        ("k_wg_fwd_gauss", "grid_fwd_gauss", n_gauss * n_vis / max(n_layers, 1)),
+        (names["grid_fwd_delta"], "grid_fwd_delta", n_delta * n_vis),
+        (names["grid_adj_delta"], "grid_adj_delta", n_delta * n_vis),
+        (names["grid_adj_gauss"], "grid_adj_gauss",
+         n_gauss * n_vis if names["grid_adj_gauss"] == "k_grid_adj_gauss_multi" else layer),
+        (names["grid_fwd_gauss"], "grid_fwd_gauss", layer),
     ]
     best = None
     for name, key, ev in cands:
@@ -474,7 +508,7 @@ def dominant_kernel(pinfo, tim, n_delta, n_gauss, n_vis, n_layers):
             continue
         avg = ms / n
         if best is None or avg > best[1]:
-            best = (name, avg, ev)
+            best = (name, avg, ev, key)
     return best
 
 
@@ -532,31 +566,35 @@ def headline(args, dev):
     pinfo = plan.info()
     plan_shape = {k: pinfo[k] for k in PLAN_KEYS}
     avg = {k: (ms / n if n else 0.0) for k, (n, ms) in tim.items()}
-    dom_name, dom_ms, dom_evals = dominant_kernel(pinfo, tim, n_delta, n_gauss, n_vis, n_layers)
-    exec_flop = EXEC_FLOP_PER_EVAL[dom_name]
+    dom_name, dom_ms, dom_evals, dom_kind = dominant_kernel(pinfo, tim, n_delta, n_gauss, n_vis,
+                                                            n_layers)
+    names = operator_kernels(pinfo)
+    exec_flop, peak = EXEC_FLOP_PER_EVAL[dom_name]
     achieved = exec_flop * dom_evals / (dom_ms * 1e-3) / 1e12
-    canonical = (FLOP_PER_EVAL_GAUSS_WIDE if "gauss" in dom_name else FLOP_PER_EVAL_DELTA)
+    canonical = (FLOP_PER_EVAL_GAUSS_WIDE if "gauss" in dom_kind else FLOP_PER_EVAL_DELTA)
     # executed FLOPs of one iteration (both operators) over the time of a step
-    exec_step = 2 * n_vis * (n_delta * EXEC_FLOP_PER_EVAL["k_wg_adj"]
-                             + n_gauss * EXEC_FLOP_PER_EVAL["k_wg_adj_gauss"])
+    exec_step = 2 * n_vis * (n_delta * EXEC_FLOP_PER_EVAL[names["grid_adj_delta"]][0]
+                             + n_gauss * EXEC_FLOP_PER_EVAL[names["grid_adj_gauss"]][0])
     canon_step = 2 * n_vis * (n_delta * FLOP_PER_EVAL_DELTA + n_gauss * FLOP_PER_EVAL_GAUSS_WIDE)
     step_s = elapsed / args.steps
     roof = {
         "bound": "alu",
         "kernel": dom_name,
         "achieved": achieved,
-        "peak": PEAK_F16_MATRIX_TFLOPS,
+        "peak": peak,
         "unit": "TFLOP/s",
-        "frac": achieved / PEAK_F16_MATRIX_TFLOPS,
+        "frac": achieved / peak,
         "traffic": load_traffic(dom_name, plan_shape),
         "kernel_avg_ms": dom_ms,
         "evals_per_launch": dom_evals,
         "executed_flop_per_eval": exec_flop,
-        "accounting": "achieved/frac: the float16 matrix FLOPs the kernel executes at least "
-                      "(three split products and one order of the series per real product of "
-                      "a cell's factors) over its average launch duration (HIP events on the "
-                      "launch stream), against the dense float16 matrix peak; the vector "
-                      "instructions that form its operands take more issue time than these "
+        "accounting": "achieved/frac: the FLOPs the kernel executes at least (group kernels: "
+                      "float16 matrix FLOPs, of which three split products and one order of "
+                      "the series stand for each real product of a cell's factors, against the "
+                      "dense float16 matrix peak; grid kernels: vector FLOPs against the FP32 "
+                      "peak) over its average launch duration (HIP events on the launch "
+                      "stream); the vector instructions that form the matrix operands take "
+                      "more issue time than these "
                       "(profiles/group_kernels_config2_counters.md); effective_*: the direct "
                       "evaluation's FP32 count per entry at the same rate",
         "effective_flop_per_eval": canonical,
@@ -585,7 +623,8 @@ def headline(args, dev):
             "n_pix": n_pix,
             "n_vis": n_vis,
             "evals_per_step": 2 * n_pix * n_vis,
-            "evaluation": "grid" if pinfo["grid"] else "direct",
+            "evaluation": "groups" if pinfo["grid_groups"] else
+                          "grid" if pinfo["grid"] else "direct",
             "tuning": tuning,
             "plan": plan_shape,
         },
@@ -609,7 +648,8 @@ def headline(args, dev):
                                     if avg["fista"] else None,
             "fista_update_hbm_frac": 20.0 * n_pix / (avg["fista"] * 1e-3) / HBM_PEAK_BPS
                                      if avg["fista"] else None,
-            "fista_update_rows_read": pinfo["n_achunks"],
+            "fista_update_rows_read": 1 if pinfo["grid_groups"] == 1 + n_layers
+                                      else pinfo["n_achunks"],
             "executed_tflops_per_step": exec_step / step_s / 1e12,
             "effective_tflops_per_step": canon_step / step_s / 1e12,
         },
@@ -649,11 +689,11 @@ def config2_secondary(dev, steps=20):
            "grid_adj_delta_avg_ms": avg["grid_adj_delta"],
            "grid_fwd_delta_avg_ms": avg["grid_fwd_delta"],
            "plan": {k: pinfo[k] for k in PLAN_KEYS}}
-    name = "k_wg_adj"
+    name = operator_kernels(pinfo)["grid_adj_delta"]
     if avg["grid_adj_delta"]:
-        out["adjoint_executed_frac"] = (EXEC_FLOP_PER_EVAL[name] * wl.n_pix * wl.n_vis
-                                        / (avg["grid_adj_delta"] * 1e-3) / 1e12
-                                        / PEAK_F16_MATRIX_TFLOPS)
+        flop, peak = EXEC_FLOP_PER_EVAL[name]
+        out["adjoint_executed_frac"] = (flop * wl.n_pix * wl.n_vis
+                                        / (avg["grid_adj_delta"] * 1e-3) / 1e12 / peak)
         out["adjoint_traffic"] = load_traffic(name, out["plan"])
     return plan, wl, out
 
