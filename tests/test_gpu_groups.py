@@ -337,3 +337,16 @@ def test_macros_sharing_rows(name):
     assert plan.workspace_bytes <= max(4 << 30, 1.25 * other.workspace_bytes)
     assert rel(V, V2) <= TOL
     other.close()
+
+
+@pytest.mark.parametrize("name", ["flat_65", "one_group", "wide_field"])
+def test_timing_counts_one_launch_an_operator(name):
+    """The delta kinds of sl1m_timing, with and without cell factors, one macro or more."""
+    wl, x, r = _case(name)
+    plan = sl1m.Plan.from_workload(wl)
+    plan.timing_begin(16)
+    for _ in range(3):
+        plan.forward(x), plan.adjoint(r)
+    tim = plan.timing_end()
+    for kind in ("forward", "adjoint", "grid_fwd_delta", "grid_adj_delta"):
+        assert tim[kind][0] == 3 and tim[kind][1] > 0.0, (kind, tim)
