@@ -183,6 +183,8 @@ typedef enum {
  *            qualifying segments in groups of visibilities of nearly one |w|
  *            on the matrix cores where that is faster (float32 operands as
  *            float16 pairs, float32 sums); sl1m_plan_create reads w for it.
+ *            Such a plan takes up to 4 GiB, a quarter more workspace than
+ *            without groups, or (past 64 GiB) no more.
  */
 typedef struct {
   int64_t n_pix;
@@ -225,7 +227,8 @@ sl1m_status sl1m_plan_workspace_bytes(const sl1m_problem* problem, size_t* bytes
  * remainder n - 1 + r^2/2, beam factors) and per-visibility gains into the
  * workspace, groups pixels by (kind, sigma) and checks the domain.  The
  * problem's device arrays are read during this call only.  Synchronises
- * `stream` once.  On success *out owns host memory released by
+ * `stream` at its end, and once before to read w where segments may be
+ * evaluated in groups (see grid_mode).  On success *out owns host memory released by
  * sl1m_plan_destroy(). */
 sl1m_status sl1m_plan_create(const sl1m_problem* problem, void* workspace, size_t workspace_bytes,
                              void* stream, sl1m_plan** out);

@@ -189,7 +189,8 @@ bool all_pixels(const Analysis& a, int n) {
 // spacings wide): two float32 evaluations, 4e-7 (groups) and 5.6e-7 (grid) from float64,
 // are 3.3e-6 of the peak apart after 200 iterations on 131,072 pixels x 100,000 (each
 // about 9e-6 from the float64 solve) and 1.0e-5 to 1.8e-5 on 262,144 x 200,000.  The
-// groups would take a quarter of the time there as well.
+// groups would take a quarter of the time there as well.  (A request of several segments
+// runs the server's direct kernels; a plan's grid evaluation never had their bits.)
 constexpr int64_t kGroupGaussMax = 131072;
 constexpr size_t kGroupRoom = size_t{4} << 30, kGroupMost = size_t{64} << 30;
 constexpr size_t kGroupStage = size_t{256} << 10;

@@ -107,8 +107,11 @@ struct WgGroups {
 bool grid_axis(const double* v, int64_t n, int64_t most, std::vector<double>& values,
                std::vector<int32_t>& rank);
 // How many of a plan's grid segments, from the first on, groups of n_vis visibilities take:
-// consecutive segments whose tiles hold at most four times their cells with padding.  The
-// tables number cells, slots (2 k + sign) and the launches' macros in 32 bits or fewer:
+// consecutive segments whose tiles hold at most four times their cells with padding (four
+// |m| values in 16 columns, 1023 x 7 pixels x 20,000 visibilities: forward 32 us, adjoint 57;
+// grid evaluation 59 and 63).  A few thin strips are slower forward alone, two launches'
+// latency against the grid evaluation's one (33 x 127 pixels x 2,000: 22 and 17 us, grid 19
+// and 29).  The tables number cells, slots (2 k + sign) and the launches' macros in 32 bits or fewer:
 // none from 2^30 visibilities on, no more than 2^31 - 1 cells and 65,535 macros.
 int wg_segments(const GridSeg* segs, int n_segs, int64_t n_vis);
 // macros and tile cells of a segment, the larger of both kinds of tiles

@@ -172,7 +172,7 @@ struct FwdLds {
 // macro's sum per slot.  Bound by the vector instructions that form the operands (seven
 // a product: C_0, its float16 splits, the rows' and columns' phasors), at two wavefronts
 // per SIMD: 0.53 of the vector issue slots and 0.30 of the matrix cores' time at 256 x
-// 256 x 97,536, 376 us (grid evaluation 511); 1024 x 1024 x 409,600: 9.8 ms (28.9).
+// 256 x 97,536, 389 us (grid evaluation 511); 1024 x 1024 x 409,600: 10.2 ms (28.9).
 // 16-row tiles of 32 columns: 32 x 32 products leave no registers for the group's 64
 // visibilities (11.6 ms with groups of 32), 48 columns spill.
 __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd(
@@ -572,7 +572,7 @@ __device__ __forceinline__ void adj_group(const float (&pc)[2][8], const float (
 
 // Adjoint: block (groups x, x + gridDim.x, ..; macro y); part[x][cell] = (G1, G2,
 // G3, G4) of its groups.  Bound as the forward (0.57 and 0.33 of the slots): 256 x 256 x
-// 97,536 427 us (grid evaluation 601), 1024 x 1024 x 409,600 11.7 ms (27.4).
+// 97,536 439 us (grid evaluation 601), 1024 x 1024 x 409,600 12.0 ms (27.4).
 __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
     const WgMacro* __restrict__ macros, int mac0, const float2* __restrict__ res,
     const double* __restrict__ nu, const float* __restrict__ eta, const double* __restrict__ la,
@@ -735,7 +735,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj(
 // visibility, so that the float16 operands keep their precision where a whole
 // baseline's taper is small.  Bound by the vector instructions around the products
 // (C_0 and its splits, the rows' and columns' phasors and tapers), as for delta
-// pixels.  512 x 512 pixels, 409,600 visibilities: forward 5.5 ms, adjoint 6.5 ms;
+// pixels.  512 x 512 pixels, 409,600 visibilities: forward 5.3 ms, adjoint 6.5 ms;
 // the grid evaluation of the same layer took 13.2 and 14.9.  300 x 300 truncated,
 // 100,003: 0.47 / 0.54 ms against 1.33 / 1.53.
 // ---------------------------------------------------------------------------
