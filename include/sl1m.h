@@ -183,8 +183,8 @@ typedef enum {
  *            qualifying segments in groups of visibilities of nearly one |w|
  *            on the matrix cores where that is faster (float32 operands as
  *            float16 pairs, float32 sums); sl1m_plan_create reads w for it.
- *            Such a plan takes up to 4 GiB, a quarter more workspace than
- *            without groups, or (past 64 GiB) no more.
+ *            Their workspace is at most 4 GiB or a quarter more than without
+ *            groups, and past 64 GiB no more than without.
  */
 typedef struct {
   int64_t n_pix;

@@ -8,8 +8,11 @@ group, or by the largest w) end.
 A plan of one side takes it, a plan of two sides the grid evaluation for the same calls,
 so results that differ in their bits show that it ran.
 """
+import ctypes
+
 import numpy as np
 import pytest
+import torch
 
 import elementwise as E
 import oracle as O
@@ -350,3 +353,66 @@ def test_timing_counts_one_launch_an_operator(name):
     tim = plan.timing_end()
     for kind in ("forward", "adjoint", "grid_fwd_delta", "grid_adj_delta"):
         assert tim[kind][0] == 3 and tim[kind][1] > 0.0, (kind, tim)
+
+
+# name: |l| x |m| pixels, spacing, visibilities, w spread; without cell factors
+STRIPS = {
+    "one_row_set": (31, 127, 4e-3, 3000, 15.0, 0),         # 16 |l| values: a lone set a macro
+    "one_row_set_flat": (31, 255, 5e-4, 900, 60.0, 1),
+    "two_row_sets": (33, 127, 4e-3, 3000, 15.0, 0),        # 17 values: 15 of 32 rows padded
+    "four_columns": (1023, 7, 4e-4, 700, 60.0, 1),         # 12 of 16 columns padded
+    "four_columns_two_orders": (319, 7, 1.8e-3, 3000, 600.0, 1),
+}
+
+
+@pytest.mark.parametrize("name", list(STRIPS))
+def test_strips(name):
+    nl, nm, d, nv, ws, flat = STRIPS[name]
+    print(f"[case] strip {name}", flush=True)
+    seed = 150 + sorted(STRIPS).index(name)
+    wl = W.small_random(seed, 10, nv, uv_radius=400.0, w_sigma=ws, with_gains=True)
+    wl.l, wl.m = _grid(nl, nm, d)
+    wl.sigma, wl.kind, wl.x_true = np.zeros(wl.l.size), np.zeros(wl.l.size, np.uint8), None
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal(wl.l.size)
+    r = rng.standard_normal(nv) + 1j * rng.standard_normal(nv)
+    p = O.Problem.from_workload(wl)
+    Vo, go = O.forward(p, x), O.adjoint(p, r)
+    plan = sl1m.Plan.from_workload(wl)
+    info = plan.info()
+    V, g = plan.forward(x).cpu().numpy(), plan.adjoint(r).cpu().numpy()
+    wf = E.worst_ratio(V, Vo, E.abs_forward_rows(p, x), wl.n_pix)
+    wa = E.worst_ratio(g, go, E.abs_adjoint_cols(p, r), nv)
+    print(f"    {info['grid_groups']} {info['grid_flat']} forward {rel(V, Vo):.3e} adjoint "
+          f"{rel(g, go):.3e} element-wise {wf:.3e} {wa:.3e}", flush=True)
+    assert (info["grid_groups"], info["grid_flat"]) == (1, flat)
+    assert rel(V, Vo) <= TOL and rel(g, go) <= TOL
+    assert wf <= 1.0 and wa <= 1.0
+
+
+@pytest.mark.parametrize("n,nv,ext", [(40, 2000, 0.05), (40, 20_000, 0.3), (97, 20_000, 0.05),
+                                      (97, 100_000, 0.3)])
+def test_noalloc_is_the_plans_forward(n, nv, ext):
+    """sl1m_forward_noalloc gives the plan's forward bit for bit where the plan evaluates in
+    groups, up to plans that share rows to fit its scratch (the last)."""
+    print(f"[case] noalloc groups {n} {nv} {ext}", flush=True)
+    wl = W.small_random(160, 10, nv, uv_radius=400.0, w_sigma=60.0, with_gains=True)
+    wl.l, wl.m = _grid(n, n, 2 * ext / n)
+    wl.sigma, wl.kind, wl.x_true = np.zeros(n * n), np.zeros(n * n, np.uint8), None
+    x = torch.as_tensor(np.random.default_rng(160).standard_normal(n * n), dtype=torch.float32,
+                        device="cuda")
+    plan = sl1m.Plan.from_workload(wl)
+    assert plan.info()["grid_groups"] == 1 and plan.workspace_bytes <= 64 << 20
+    V = plan.forward(x)
+    lib = sl1m.lib()
+    lib.sl1m_forward_noalloc.argtypes = [ctypes.POINTER(sl1m.Problem)] + 3 * [ctypes.c_void_p]
+    lib.sl1m_forward_noalloc.restype = ctypes.c_int
+    out = torch.full_like(V, float("nan"))
+    for _ in range(2):
+        st = lib.sl1m_forward_noalloc(ctypes.byref(plan._prob), ctypes.c_void_p(x.data_ptr()),
+                                      ctypes.c_void_p(out.data_ptr()),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == sl1m.OK
+        assert torch.equal(torch.view_as_real(out), torch.view_as_real(V))
+    other = sl1m.Plan.from_workload(wl, max_rhs=2)
+    assert rel(V.cpu().numpy(), other.forward(x).cpu().numpy()) <= TOL
