@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_flat_fwd(
       }
       if constexpr (GAUSS) {
         const float ct = __builtin_amdgcn_cosf(r.e0), st = __builtin_amdgcn_sinf(r.e0);
-        const float k = sc * kGDown * pow2(top);
+        const float k = scale_sums(sc * kGDown, sr, si) * pow2(top);
         const float fr = k * fmaf(r.D, ct, -r.Ds * st), fi = k * fmaf(r.D, st, r.Ds * ct);
         re = fmaf(fr, sr, -fi * si);
         im = fmaf(fr, si, fi * sr);

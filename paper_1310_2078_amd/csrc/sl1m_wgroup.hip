@@ -998,7 +998,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_fwd_gauss(
       quad_sum(vr, vi, lane, sr, si);
       // visibility `lane`: D (1 + i s), e0, the columns' top
       const float ct = __builtin_amdgcn_cosf(r.e0), st = __builtin_amdgcn_sinf(r.e0);
-      const float k = sc * kGDown * pow2(top);
+      const float k = scale_sums(sc * kGDown, sr, si) * pow2(top);
       const float fr = k * fmaf(r.D, ct, -r.Ds * st), fi = k * fmaf(r.D, st, r.Ds * ct);
       re = fmaf(fr, sr, -fi * si);
       im = fmaf(fr, si, fi * sr);
@@ -1191,7 +1191,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_wg_adj_gauss(
     const float ct = k * fmaf(r.D, c0, -r.Ds * s0), st = k * fmaf(r.D, s0, r.Ds * c0);
     const float rr = fmaf(ct, zn.x, st * zn.y), ri = fmaf(ct, zn.y, -st * zn.x);
     const float am = fmaxf(fabsf(rr), fabsf(ri));
-    const float sc = 0.5f * op_scale(wave_max(rr != rr || ri != ri ? __builtin_inff() : am));
+    // (at most 2^111: 1 / sc, which the cell factors take on, stays a normal number)
+    const float sc = fminf(
+        0.5f * op_scale(wave_max(rr != rr || ri != ri ? __builtin_inff() : am)), 0x1.0p111f);
     lds.rho[wv][lane] = make_float2(rr * sc, ri * sc);
     lds.top[wv][lane] = ltop;
     const float inv = kGDown / sc;

@@ -131,6 +131,16 @@ __device__ __forceinline__ float taper_top(float c1, float d, float w, float lo,
   return c1 * (m * m);
 }
 
+// Sums (re, im) in units of k, a power of two: what is below one goes to the sums, which are
+// large then (times a small taper it would be subnormal: 1.2e-5 instead of 4.9e-6 at tapers of
+// 2^-113), the rest is returned for the taper (times the sums it could overflow).
+__device__ __forceinline__ float scale_sums(float k, float& re, float& im) {
+  const float s = fminf(k, 1.0f);
+  re *= s;
+  im *= s;
+  return fmaxf(k, 1.0f);
+}
+
 // up 2^(c1 d^2 - top), at most up (padded positions may lie above the top).  Columns
 // stand kGUp high: tapers down to 2^-28 of the largest are normal float16.  (The factor
 // in the exponent would cost the exponent four bits.)

@@ -416,3 +416,43 @@ def test_noalloc_is_the_plans_forward(n, nv, ext):
         assert torch.equal(torch.view_as_real(out), torch.view_as_real(V))
     other = sl1m.Plan.from_workload(wl, max_rhs=2)
     assert rel(V.cpu().numpy(), other.forward(x).cpu().numpy()) <= TOL
+
+
+@pytest.mark.parametrize("w_sigma,d,nv,flat", [(0.0, 1.5e-3, 700, 1), (20.0, 1.5e-3, 700, 1),
+                                               (30.0, 4e-3, 6000, 0)])
+def test_tapers_near_the_smallest_float(w_sigma, d, nv, flat):
+    """Tapers of 2^-113: no further from a float64 plan than the grid evaluation (a plan of two
+    sides), whose float32 exponents have the same rounding, times 1.3 for chance."""
+    rng = np.random.default_rng(170)
+    wl = W.small_random(170, 10, nv, with_gains=True)
+    wl.l, wl.m = _grid(40, 70, d)
+    wl.sigma, wl.kind = np.full(wl.l.size, 2.0 * d), np.full(wl.l.size, W.PIX_GAUSS_WIDE, np.uint8)
+    wl.x_true = None
+    phi, rho = rng.uniform(0, 2 * np.pi, nv), 5.0 / (2.0 * d) * rng.uniform(0.98, 1.0, nv)
+    wl.u, wl.v, wl.w = rho * np.cos(phi), rho * np.sin(phi), w_sigma * rng.standard_normal(nv)
+    x = rng.standard_normal(wl.l.size).astype(np.float32)
+    r = (rng.standard_normal(nv) + 1j * rng.standard_normal(nv)).astype(np.complex64)
+    plan = sl1m.Plan.from_workload(wl)
+    info = plan.info()
+    assert (info["grid_groups"], info["grid_flat"]) == (1, flat)
+    other = sl1m.Plan.from_workload(wl, max_rhs=2, grid="require")
+    exact = sl1m.Plan.from_workload(wl, precision="fp64")
+    for f, v in (("forward", x), ("adjoint", r)):
+        ref = getattr(exact, f)(v).cpu().numpy()
+        e, eg = (rel(getattr(p, f)(v).cpu().numpy(), ref) for p in (plan, other))
+        print(f"    {f} {e:.3e}, grid evaluation {eg:.3e}", flush=True)
+        assert e <= 1.3 * eg
+
+
+@pytest.mark.parametrize("name", ["no_series", "one_order"])
+def test_gaussian_amplitudes_near_the_largest_float(name):
+    """One pixel or one visibility of 2^100 (exact: powers of two) and of 2^126."""
+    wl, x, r = _gauss_case(name)
+    plan = sl1m.Plan.from_workload(wl)
+    x, r = 0 * x, 0 * r
+    x[7], r[9] = 1.0, 1.0
+    for f, v in ((plan.forward, x), (plan.adjoint, r)):
+        a, b = f(v).cpu().numpy(), f(v * 2.0 ** 100).cpu().numpy()
+        assert np.array_equal(b, a * np.float32(2.0 ** 100))
+        c = f(v * 2.0 ** 126).cpu().numpy()
+        assert np.isfinite(c).all() and rel(c / np.float32(2.0 ** 126), a) <= TOL
